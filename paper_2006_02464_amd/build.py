@@ -9,7 +9,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libclockwork_exec.so")
-SOURCES = ["clockwork_exec.hip", "plan.cpp", "kernels_conv.hip", "kernels_conv_dlds.hip", "kernels_resident.hip", "kernels_misc.hip", "worker.hip"]
+SOURCES = ["clockwork_exec.hip", "plan.cpp", "kernels_conv.hip", "kernels_conv_dlds.hip", "kernels_conv_k256.hip", "kernels_resident.hip", "kernels_misc.hip", "worker.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-fno-gpu-rdc",
@@ -22,6 +22,7 @@ FLAGS = [
 # 14 dwords: every user SGPR beside the argument pointer).  The compiler keeps a prologue that loads them the ordinary way for firmware
 # without the feature.
 EXTRA_FLAGS = {"kernels_conv_dlds.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"],
+               "kernels_conv_k256.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"],
                "kernels_misc.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"]}
 
 

@@ -242,13 +242,15 @@ struct SoftmaxArgs {
 // (pixels x channels per workgroup; "wN" = N waves when not 4, each wave then owning 64x64;
 // "k128" = K slices of 128 instead of 64, for Cin % 128 == 0; "gN" = N groups of waves that split
 // every K slice between them and add up at the end; the last four are for large GEMMs: 8 waves of
-// 64x64 or 64x128 each, and 256x128 on 4 waves of 128x64)
+// 64x64 or 64x128 each, and 256x128 on 4 waves of 128x64; "k256": K slices of 256 for long K and
+// few tiles, Cin % 256 == 0)
 enum ConvTile : int32_t {
     T128x128 = 0, T128x64, T64x64, T64x32, T32x64, T32x32, T128x64w2, T64x128w2, T256x64, T128x128w8,
     T128x64k128, T64x64k128, T64x32k128, T32x64k128, T32x32k128,
     T128x64k128g2, T64x64k128g2, T64x64k128g4, T64x32k128g4, T32x64k128g4, T32x32k128g4,
     T32x32k128g8, T128x64g2, T64x64g2, T32x32g4,
-    T256x128w8, T128x256w8, T256x256w8, T256x128, N_CONV_TILES
+    T256x128w8, T128x256w8, T256x256w8, T256x128,
+    T32x32k256g4, T32x32k256g8, T64x32k256g4, T64x32k256g8, T32x64k256g4, T32x64k256g8, T64x64k256g4, N_CONV_TILES
 };
 struct TileDim {
     int bm, bn, threads, bk, kg;
@@ -269,6 +271,8 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
 // The direct-to-LDS kernel for Cin % 64 == 0 and for a first convolution in its stem form
 // (called by launch_conv after its checks); mode = the kernel's addressing mode.
 hipError_t launch_conv_dlds(DType dt, ConvTile tile, int bk, int mode, const ConvArgs &a, hipStream_t s);
+// Its K slices of 256 (kernels_conv_k256.hip; called by launch_conv_dlds).
+hipError_t launch_conv_dlds_k256(DType dt, ConvTile tile, int mode, bool splitk, const ConvArgs &a, hipStream_t s);
 // A convolution (Cin % 64 == 0, Cout 64 or 128) and the 1x1 convolution that consumes it, in one
 // launch (kernels_conv_dlds.hip).  bm = pixels per workgroup (64 or 128).
 hipError_t launch_conv_fused(DType dt, int bm, int kg, const ConvArgs &a, hipStream_t s);

@@ -49,7 +49,7 @@ struct Mfma<bf16> {
 // banks and the key is row%16.
 template <int BK>
 static __device__ __forceinline__ int swz_key(int row) {
-    return BK == 128 ? (row & 15) : BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3);
+    return BK >= 128 ? (row & 15) : BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
 template <int BK>
 static __device__ __forceinline__ int swz(int row, int c) {

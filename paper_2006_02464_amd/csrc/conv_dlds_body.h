@@ -83,7 +83,7 @@ template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, 
 static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const int bid, const int nb_packed) {
     // nb_packed: the convolution's tile count with its tile numbering in the top bits (conv_pack_nb)
     const int nb = conv_nb_tiles(nb_packed), panel = conv_nb_panel(nb_packed);
-    static_assert(BK == 64 || BK == 128, "K slices of 64 or 128");
+    static_assert(BK == 64 || BK == 128 || BK == 256, "K slices of 64, 128 or 256");
     static_assert(KG == 1 || ((BK / 16) % KG == 0 && (!FUSED || KG == 2)), "K groups: whole steps per group");
     static_assert(!FUSED || (!SPLITK && MODE != MODE_STEM && (BN == 64 || BN == 128)), "fused form: whole first layer in one tile");
     constexpr int NT = 64 * WARPS_M * WARPS_N * KG;

@@ -1,0 +1,63 @@
+// Entry point and launch of one convolution on the direct-to-LDS kernel, for the files that instantiate it.
+#pragma once
+#include "conv_dlds_body.h"
+
+namespace cw {
+
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1>
+__global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
+                                                                                 int M, int K, int cout_ldy, int cin_ldx, int nb, int relu,
+                                                                                 const ConvArgs rest) {
+    // The ten leading arguments (14 dwords, all the user SGPRs there are beside the argument
+    // pointer) repeat fields of `rest`: this file is compiled with kernel-argument preloading, so
+    // they are in SGPRs when a wave starts and the first address arithmetic does not wait for a
+    // load of the argument block.  Everything else is read from `rest` when it is needed.
+    // Cout and Cin carry the pixel pitches of y and x in their upper halves, so that the 1x1 form
+    // still needs nothing beyond the preloaded scalars for its addressing.
+    ConvArgs a = rest;
+    a.x = x; a.w = w; a.res = res; a.y = y;
+    a.M = M; a.K = K; a.Cout = cout_ldy & 0xffff; a.Cin = cin_ldx & 0xffff; a.nb = nb; a.relu = relu;
+    a.ld = (int)(((unsigned)cin_ldx >> 16) | ((unsigned)cout_ldy & 0xffff0000u));
+    if constexpr (MODE == MODE_GEMM && !SPLITK && !FUSED) {
+        // batched form: one GEMM per blockIdx.z, operands advanced by the strides in the last argument line
+        if (blockIdx.z != 0) {
+            a.x = static_cast<const char *>(x) + (long long)blockIdx.z * rest.zs_x;
+            a.w = static_cast<const char *>(w) + (long long)blockIdx.z * rest.zs_w;
+            a.y = static_cast<char *>(y) + (long long)blockIdx.z * rest.zs_y;
+        }
+    }
+    conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG>(a, blockIdx.x, nb);
+}
+
+// A tile numbering in 2^p panels needs the channel tiles to divide evenly, and the tile count must
+// leave the bits above kPanelShift free.
+static bool conv_panel_ok(const ConvArgs &a, int bn, unsigned tiles) {
+    if (tiles >= (1u << kPanelShift) || a.panel_log2 < 0 || a.panel_log2 > 3) return false;
+    const int tiles_n = (a.Cout + bn - 1) / bn;
+    return a.panel_log2 == 0 || tiles_n % (1 << a.panel_log2) == 0;
+}
+
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int MODE, bool SPLITK, int KG = 1>
+static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStream_t s) {
+    ConvArgs a = a_in;
+    if (!conv_panel_ok(a, BN, grid.x)) return hipErrorInvalidValue;
+    a.nb = conv_pack_nb((int)grid.x, a.panel_log2);
+    if (!SPLITK && a.ktiles_per_split != a.K / BK) return hipErrorInvalidValue;  // the kernel walks the whole K
+    if (a.nz > 1 && (MODE != MODE_GEMM || SPLITK || a.bias || a.res || grid.z != (unsigned)a.nz)) return hipErrorInvalidValue;
+    if (a.nz <= 1 && grid.z != 1) return hipErrorInvalidValue;
+    constexpr int NS = RingDepth<BM, BN, BK>::value;
+    constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
+    static_assert(NS * stage_bytes <= 160 * 1024, "ring does not fit the LDS");
+    auto kern = conv_dlds_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, false, KG>;
+    // More than 64 KiB of LDS per workgroup has to be requested once per kernel; done on first
+    // use (under LOAD's graph recording or the first plain EXEC), never per launch afterwards.
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
+    if (attr != hipSuccess) return attr;
+    // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
+    // at the end needs its own room)
+    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG - 1) * BM * BN * 4);
+    kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a);
+    return hipGetLastError();
+}
+
+}  // namespace cw

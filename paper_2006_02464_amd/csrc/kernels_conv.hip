@@ -315,6 +315,13 @@ TileDim conv_tile_dim(ConvTile t) {
         case T128x256w8: return {128, 256, 512, 64, 1};
         case T256x256w8: return {256, 256, 512, 64, 1};
         case T256x128: return {256, 128, 256, 64, 1};
+        case T32x32k256g4: return {32, 32, 256, 256, 4};
+        case T32x32k256g8: return {32, 32, 512, 256, 8};
+        case T64x32k256g4: return {64, 32, 512, 256, 4};
+        case T64x32k256g8: return {64, 32, 1024, 256, 8};
+        case T32x64k256g4: return {32, 64, 512, 256, 4};
+        case T32x64k256g8: return {32, 64, 1024, 256, 8};
+        case T64x64k256g4: return {64, 64, 1024, 256, 4};
         default: return {32, 32, 64, 64, 1};
     }
 }
@@ -331,7 +338,10 @@ ConvTile conv_tile_k64(ConvTile t) {
         case T64x32k128: case T64x32k128g4: return T64x32;
         case T32x64k128: case T32x64k128g4: return T32x64;
         case T32x32k128: return T32x32;
-        case T32x32k128g4: case T32x32k128g8: return T32x32g4;
+        case T32x32k128g4: case T32x32k128g8: case T32x32k256g4: case T32x32k256g8: return T32x32g4;
+        case T64x32k256g4: case T64x32k256g8: return T64x32;
+        case T32x64k256g4: case T32x64k256g8: return T32x64;
+        case T64x64k256g4: return T64x64g2;
         default: return t;
     }
 }
@@ -367,7 +377,8 @@ ConvTile conv_tile_one_group(ConvTile t) {
 int conv_bk(const ConvArgs &a, bool stem, ConvTile tile) {
     if (stem) return stem_is_dlds(a) ? 64 : 32;
     if (a.Cin % 64 != 0) return 32;
-    return (conv_tile_dim(tile).bk == 128 && a.Cin % 128 == 0) ? 128 : 64;
+    const int bk = conv_tile_dim(tile).bk;
+    return a.Cin % bk == 0 ? bk : 64;
 }
 
 static bool conv_is_gemm(const ConvArgs &a, bool stem) {

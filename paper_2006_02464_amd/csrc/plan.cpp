@@ -298,54 +298,108 @@ static int pick_res_variant(int64_t M, int64_t N, int64_t K, int32_t cin) {
 }
 
 // ---------------------------------------------------------------- tile choice
-// A measured shape takes its tile and split from the table.  Otherwise: the largest tile that
-// still gives every CU at least one workgroup; below that, a 64x64 (or narrower) tile with K
-// split over up to 16 workgroups.  Either way a pure function of the GEMM shape.
-// Offline measurements (tune.py): the fastest tile and split-K per GEMM shape seen on an MI355X.
-static const TunedShape kTuned[] = {
-#include "plan_table.inc"
+// Every tile shape's launch time as a linear function of the quantities below, fitted offline to measured
+// launches (tune.py); the plan takes the tile and split-K with the least predicted time.  Over 645 measured GEMM
+// shapes (six networks, 35 image and batch sizes) that costs 1.3 % over the fastest tile of each; a table of
+// measured shapes and a heuristic beside it, as before, cost 2-7 % on shapes of the table and 30-40 % on others.
+enum { COST_PLAIN, COST_STAGED, COST_STEM };   // the main kernel; the register-staged one; the first convolution's form
+constexpr int kCostFeatures = 11;
+struct ConvCost {
+    int32_t cls, tile, splits;
+    float us[kCostFeatures];
+};
+static const ConvCost kConvCost[] = {
+#include "plan_cost.inc"
 };
 
-static void pick_conv_tile(int64_t M, int64_t N, int64_t K, int32_t kh, int32_t stride, int64_t ktiles,
-                           const PlanOverride &ov, ConvTile *tile, int32_t *split) {
-    if (ov.tile < 0 && ov.split_k <= 0) {
-        auto match = [&](const TunedShape &t) {
-            if (t.M != M || t.N != N || t.K != K || t.kh != kh || t.stride != stride || t.tile < 0 || t.tile >= N_CONV_TILES)
-                return false;
-            *tile = (ConvTile)t.tile;
-            *split = (int32_t)std::max<int64_t>(1, std::min<int64_t>(t.split_k, ktiles));
-            return true;
-        };
+static int cost_class(const ConvArgs &a, bool stem) {
+    return !conv_uses_dlds(a, stem) ? COST_STAGED : (stem ? COST_STEM : COST_PLAIN);
+}
+
+// Predicted microseconds of one launch that computes `n` (1 or 2) convolutions on tile `c.tile`, K in `split` parts.
+static double conv_cost(const ConvCost &c, const ConvArgs *const *as, const bool *res, int n, bool stem, int32_t split) {
+    double wgs = 0, per_max = 0, per_taps = 0, per_sum = 0, out_mb = 0, in_mb = 0, taps = 0, part_mb = 0;
+    for (int k = 0; k < n; ++k) {
+        const ConvArgs &a = *as[k];
+        const TileDim d = conv_tile_dim((ConvTile)c.tile);
+        const int slices = a.K / conv_bk(a, stem, (ConvTile)c.tile);
+        const double per = (slices + split - 1) / split;
+        const double w = (double)((a.M + d.bm - 1) / d.bm) * ((a.Cout + d.bn - 1) / d.bn) * split;
+        const double t = (a.kh * a.kw > 1 || a.stride > 1) ? 1 : 0;
+        wgs += w;
+        per_sum += per * w;
+        per_max = std::max(per_max, per);
+        per_taps = std::max(per_taps, per * t);
+        taps = std::max(taps, t);
+        out_mb += (double)a.M * a.Cout * 2e-6 * (1 + res[k]);
+        const double in = (double)a.M * a.Cin * 2e-6 * (a.kh > 1 ? a.stride * a.stride : 1);
+        in_mb = std::max(in_mb, in);   // two convolutions of one launch read the same tensor
+        part_mb += (double)split * a.M * a.Cout * 4e-6;
+    }
+    for (int k = 0; k < n; ++k) in_mb += (double)as[k]->Cout * as[k]->K * 2e-6;
+    // further workgroups per CU: halfway between their number per CU and what the fullest CU gets, which evens out in long launches
+    double more = wgs / 256.0 - 1;
+    if (wgs <= 2048) more = 0.5 * (std::max(0.0, more) + (double)(((int64_t)wgs + 255) / 256 - 1));
+    const float *u = c.us;
+    double us = u[0] + u[1] * taps + u[2] * per_max + u[3] * per_taps + u[4] * (per_sum / wgs) * more + u[5] * more + u[6] * out_mb + u[7] * in_mb;
+    if (split > 1) us += u[8] + u[9] * part_mb + u[10] * split;
+    return us;
+}
+
+// Whether K can be split over `split` workgroups: none of them empty, counters and offsets in range.
+static bool split_ok(const ConvArgs &a, bool stem, ConvTile tile, int32_t split) {
+    if (split == 1) return true;
+    const TileDim d = conv_tile_dim(tile);
+    const int slices = a.K / conv_bk(a, stem, tile);
+    const int per = (slices + split - 1) / split;
+    const int64_t tiles = ((int64_t)a.M + d.bm - 1) / d.bm * ((a.Cout + d.bn - 1) / d.bn);
+    return (slices + per - 1) / per == split && tiles * 4 <= (int64_t)kCounterBytes && (int64_t)a.M * a.Cout * 4 < (1ll << 31);
+}
+
+// The cheapest tile and split-K of a convolution; a row of the installed table or a forced tile comes first.  A pure function
+// of the convolution's shape.
+static double pick_conv_tile(const ConvArgs &a, bool stem, bool res, int64_t real_k, const PlanOverride &ov, ConvTile *tile,
+                             int32_t *split, bool *fixed) {
+    *fixed = ov.tile >= 0 || ov.split_k > 0;
+    if (!*fixed)
         for (const TunedShape &t : ov.table)
-            if (match(t)) return;
-        for (const TunedShape &t : kTuned)
-            if (match(t)) return;
+            if (t.M == a.M && t.N == a.Cout && t.K == real_k && t.kh == a.kh && t.stride == a.stride && t.tile >= 0 && t.tile < N_CONV_TILES) {
+                *tile = (ConvTile)t.tile;
+                *split = std::max(1, t.split_k);
+                *fixed = true;
+                return 0;
+            }
+    const int cls = cost_class(a, stem);
+    const ConvArgs *as[1] = {&a};
+    double best = 1e30;
+    for (const ConvCost &c : kConvCost) {
+        const TileDim d = conv_tile_dim((ConvTile)c.tile);
+        if (c.cls != cls || (cls == COST_PLAIN && a.Cin % d.bk != 0) || (d.bn > a.Cout && d.bn > 32)) continue;
+        for (int32_t s = 1; s <= (c.splits ? 8 : 1); s *= 2) {
+            if ((ov.split_k > 0 && s != ov.split_k && s > 1) || !split_ok(a, stem, (ConvTile)c.tile, s)) continue;
+            const double us = conv_cost(c, as, &res, 1, stem, s) + (ov.split_k > 1 && s == 1 ? 1e3 : 0);   // a forced split where it can be had
+            if (us < best) { best = us; *tile = (ConvTile)c.tile; *split = s; }
+        }
     }
-    static const ConvTile order[] = {T128x128, T128x64, T64x64, T32x64, T64x32, T32x32};
-    auto blocks = [&](ConvTile t) {
-        const TileDim d = conv_tile_dim(t);
-        return ((M + d.bm - 1) / d.bm) * ((N + d.bn - 1) / d.bn);
-    };
-    const int64_t target = 256;
-    ConvTile chosen = T32x32;
+    if (best == 1e30) { *tile = T32x32; *split = 1; }
+    if (ov.tile >= 0 && ov.tile < N_CONV_TILES) { *tile = (ConvTile)ov.tile; *split = 1; }
+    if (ov.split_k > 0) *split = ov.split_k;
+    return best;
+}
+
+// The cheapest tile of a launch that computes both convolutions; false if the two apart are predicted to be faster.
+static bool pick_pair_tile(const ConvArgs &a0, bool res0, const ConvArgs &a1, bool res1, double apart, ConvTile *tile) {
+    const ConvArgs *as[2] = {&a0, &a1};
+    const bool res[2] = {res0, res1};
+    double best = apart;
     bool found = false;
-    for (ConvTile t : order) {
-        const TileDim d = conv_tile_dim(t);
-        if (d.bn > N && t != T32x32) continue;
-        if (blocks(t) >= target) { chosen = t; found = true; break; }
+    for (const ConvCost &c : kConvCost) {
+        const TileDim d = conv_tile_dim((ConvTile)c.tile);
+        if (c.cls != COST_PLAIN || !conv_pair_tile_ok((ConvTile)c.tile) || a0.Cin % d.bk != 0 || d.bn > a0.Cout || d.bn > a1.Cout) continue;
+        const double us = conv_cost(c, as, res, 2, false, 1);
+        if (us < best) { best = us; *tile = (ConvTile)c.tile; found = true; }
     }
-    int32_t s = 1;
-    if (!found) {
-        chosen = (N >= 64 && M > 32) ? T64x64 : (N >= 64 ? T32x64 : T32x32);
-        const int64_t b = blocks(chosen);
-        const int64_t want = (target + b - 1) / b;
-        const int64_t cap = std::max<int64_t>(1, ktiles / 8);
-        s = (int32_t)std::min<int64_t>(std::min(want, cap), 16);
-    }
-    if (ov.tile >= 0 && ov.tile < N_CONV_TILES) { chosen = (ConvTile)ov.tile; if (ov.split_k <= 0) s = 1; }
-    if (ov.split_k > 0) s = (int32_t)std::min<int64_t>(ov.split_k, ktiles);
-    *tile = chosen;
-    *split = std::max(1, s);
+    return found;
 }
 
 // Tile numbering of a convolution launch (see conv_pack_nb): with 2^p channel panels each of the 8
@@ -859,11 +913,10 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 a.relu = o.relu;
                 a.wo_div = make_fast_div((uint32_t)os.w);
                 a.ho_div = make_fast_div((uint32_t)os.h);
-                pick_conv_tile(a.M, a.Cout, (int64_t)o.kh * o.kw * o.cin, o.kh, o.stride, a.K / conv_bk(a, l.stem, T64x64), ov,
-                               &l.tile, &a.split_k);
-                if (l.stem) l.tile = conv_tile_one_group(l.tile);   // the first convolution's mode has no wave groups
+                l.cost_us = pick_conv_tile(a, l.stem, o.residual_from >= 0, (int64_t)o.kh * o.kw * o.cin, ov, &l.tile, &a.split_k, &l.tile_fixed);
                 if (!conv_uses_dlds(a, l.stem)) l.tile = conv_tile_staged(l.tile);   // the register-staged kernel's shapes
-                if (conv_bk(a, l.stem, l.tile) != conv_tile_dim(l.tile).bk) l.tile = conv_tile_k64(l.tile);  // Cin % 128 != 0
+                if (conv_bk(a, l.stem, l.tile) != conv_tile_dim(l.tile).bk) l.tile = conv_tile_k64(l.tile);  // Cin is no multiple of the tile's slice
+                if (l.stem) l.tile = conv_tile_one_group(l.tile);   // the first convolution's mode has no wave groups
                 const int ktiles = a.K / conv_bk(a, l.stem, l.tile);
                 a.split_k = std::max(1, std::min(a.split_k, ktiles));
                 {
@@ -889,6 +942,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 const TileDim td = conv_tile_dim(l.tile);
                 l.info.tile_m = td.bm; l.info.tile_n = td.bn; l.info.tile_k = conv_bk(a, l.stem, l.tile); l.info.split_k = a.split_k;
                 l.info.conv_tile = l.tile; l.info.wave_groups = td.kg;
+                l.in_bytes = in_b;
                 a.panel_log2 = (ov.panels && !l.stem && conv_uses_dlds(a, false)) ? choose_panel(a.Cout, td.bn, w_b, in_b) : 0;
                 l.info.panels = 1 << a.panel_log2;
                 if (a.split_k > 1) {
@@ -901,7 +955,6 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                     snprintf(l.info.name, sizeof l.info.name, "conv%dx%d_s%d_splitk%d", o.kh, o.kw, o.stride, a.split_k);
                 } else {
                     l.info.bytes = in_b + w_b + out_b + res_b;
-                    l.in_bytes = in_b;
                     snprintf(l.info.name, sizeof l.info.name, i == 0 ? "stem%dx%d_s%d" : "conv%dx%d_s%d", o.kh, o.kw, o.stride);
                 }
                 p.launches.push_back(l);
@@ -1048,28 +1101,37 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
 
     // Two consecutive convolution launches that read the same tensor and do not depend on each other
     // (in a ResNet: the first 1x1 of a block and the projection shortcut beside it) become one
-    // launch on one tile shape: that of the one with more work, if the pair kernel has it and the
-    // other is at least a tile wide.
+    // launch on one tile shape, the one with the least predicted time, if the pair kernel has one that beats
+    // two launches.  Tiles taken from the installed table are kept: that of the one with more work, if the pair
+    // kernel has it and the other is at least a tile wide.
     if (ov.pair && !resident && ov.tile < 0 && ov.split_k <= 0) {
         for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
             Launch &l0 = p.launches[i], &l1 = p.launches[i + 1];
             if (l0.kind != K_CONV || l1.kind != K_CONV || l0.stem || l1.stem || l0.fused_bm > 0 || l1.fused_bm > 0) continue;
-            if (l0.pair_op >= 0 || l1.pair_op >= 0 || l0.conv.split_k != 1 || l1.conv.split_k != 1) continue;
+            if (l0.pair_op >= 0 || l1.pair_op >= 0) continue;
             if (l0.x.space != l1.x.space || l0.x.offset != l1.x.offset || l0.conv.Cin != l1.conv.Cin || l0.conv.Cin % 64 != 0) continue;
             if (m.ops[l1.op_index].input_from == l0.op_index || m.ops[l1.op_index].residual_from == l0.op_index) continue;
-            const ConvTile cand[2] = {l1.info.flops >= l0.info.flops ? l1.tile : l0.tile, l1.info.flops >= l0.info.flops ? l0.tile : l1.tile};
-            int pick = -1;
-            for (int k = 0; k < 2 && pick < 0; ++k) {
-                const TileDim d = conv_tile_dim(cand[k]);
-                if (conv_pair_tile_ok(cand[k]) && l0.conv.Cin % d.bk == 0 && d.bn <= l0.conv.Cout && d.bn <= l1.conv.Cout) pick = k;
+            ConvTile tile = T32x32;
+            if (l0.tile_fixed || l1.tile_fixed) {
+                if (l0.conv.split_k != 1 || l1.conv.split_k != 1) continue;
+                const ConvTile cand[2] = {l1.info.flops >= l0.info.flops ? l1.tile : l0.tile, l1.info.flops >= l0.info.flops ? l0.tile : l1.tile};
+                int pick = -1;
+                for (int k = 0; k < 2 && pick < 0; ++k) {
+                    const TileDim d = conv_tile_dim(cand[k]);
+                    if (conv_pair_tile_ok(cand[k]) && l0.conv.Cin % d.bk == 0 && d.bn <= l0.conv.Cout && d.bn <= l1.conv.Cout) pick = k;
+                }
+                if (pick < 0) continue;
+                tile = cand[pick];
+            } else if (!pick_pair_tile(l0.conv, l0.res.space != SP_NONE, l1.conv, l1.res.space != SP_NONE, l0.cost_us + l1.cost_us, &tile)) {
+                continue;
             }
-            if (pick < 0) continue;
-            const ConvTile tile = cand[pick];
             const TileDim d = conv_tile_dim(tile);
             Launch l = l1;
             l.tile = tile;
             l.pair_op = l0.op_index;
             l.conv0 = l0.conv;
+            l.conv0.split_k = l.conv.split_k = l.info.split_k = 1;
+            l.partial = l.counters = Ref{};
             l.conv0.ktiles_per_split = l.conv0.K / d.bk;
             l.conv.ktiles_per_split = l.conv.K / d.bk;
             // both members run on the pair's tile shape: their tile numbering is chosen for it
@@ -1080,6 +1142,10 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             l.info.flops = l0.info.flops + l1.info.flops;
             l.info.bytes = l0.info.bytes + l1.info.bytes - std::min(l0.in_bytes, l1.in_bytes);   // the shared input once
             l.info.tile_m = d.bm; l.info.tile_n = d.bn; l.info.tile_k = d.bk; l.info.conv_tile = tile; l.info.wave_groups = d.kg;
+            for (Launch *h : {&l0, &l1}) {   // neither is split inside the pair
+                if (h->conv.split_k > 1) l.info.bytes -= 2 * (int64_t)h->conv.split_k * h->conv.M * h->conv.Cout * 4;
+                if (char *suffix = strstr(h->info.name, "_splitk")) *suffix = 0;
+            }
             char name[48];
             snprintf(name, sizeof name, "%.20s|%.20s", l0.info.name, l1.info.name);
             memcpy(l.info.name, name, sizeof l.info.name);

@@ -25,6 +25,8 @@ struct Launch {
     int32_t op_index;
     ConvTile tile = T64x64;
     bool stem = false;
+    double cost_us = 0;       // predicted time of a convolution launch (plan compiler only)
+    bool tile_fixed = false;  // its tile comes from the installed table or was forced
     int32_t fused_bm = 0;  // > 0: this convolution and the 1x1 one after it in one launch (pixels per workgroup)
     int32_t fused_kg = 1;  // wave groups of that launch (1 or 2)
     // Shape fields are final; pointer fields are filled from the Refs at EXEC time.

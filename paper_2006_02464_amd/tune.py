@@ -1,212 +1,166 @@
-"""Offline tuning of the conv launch plan (a development tool; needs an MI355X).
+"""The cost model behind the convolution plan (a development tool; its sweep needs an MI355X).
 
-For every batch size and every convolution GEMM shape of a ResNet this tries each
-(tile, split-K) candidate *in place*: the candidate is installed for that one shape
-with cw_set_plan_table, the model is defined and loaded, and the median on-device
-duration of whole EXECs (the production path: HIP-graph replay, every other layer
-as currently chosen, caches as warm or cold as they really are) decides.  One
-pass of coordinate descent per batch size, starting from the library's current
-choice.  The result is written as csrc/plan_table.inc, which the library compiles
-in.  Nothing is tuned when EXEC runs.
+``sweep`` times every convolution of a set of networks, image sizes and batch sizes on every tile shape and
+split-K factor, one launch at a time inside whole EXECs (cw_exec_timed_launches: each launch finds the caches
+as the launches before it leave them).  ``fit`` turns those times into csrc/plan_cost.inc: per tile shape a
+non-negative linear model of the launch's time in the quantities of :func:`features`, least squares of the relative
+error.  The plan compiler evaluates the same model for every convolution it plans and takes the
+cheapest tile (plan.cpp: pick_conv_tile), so any image and batch size is planned the same way; nothing is
+tuned when EXEC runs.
 
-  python -m paper_2006_02464_amd.tune [--family resnet] [--depth 50] [--hw 224] [--batches 1,2,4,8,16] [--out FILE] [--keep-existing]
-
-The table as compiled in: ResNet-50 first, then `--depth 18 --keep-existing`, then the other
-families' lists (`--family mobilenet|densenet|inception --batches 1,4,16 --keep-existing`), then a second
-pass over each of those with `--protect-resnet 50` in place of `--keep-existing`.
+  python -m paper_2006_02464_amd.tune sweep FILE.jsonl [FAMILY:HxW:BATCH ...]
+  python -m paper_2006_02464_amd.tune fit FILE.jsonl [FILE.jsonl ...]
 """
-import argparse
+import collections
+import json
 import os
-import re
 import sys
-import time
 
 import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-TABLE = os.path.join(HERE, "csrc", "plan_table.inc")
-SPLITS = (1, 2, 4, 8, 16)
-TILE_DIMS = {"128x128": (128, 128), "128x64": (128, 64), "64x64": (64, 64), "64x32": (64, 32), "32x64": (32, 64),
-             "32x32": (32, 32), "256x64": (256, 64), "128x128w8": (128, 128),
-             "128x64k128": (128, 64), "64x64k128": (64, 64), "64x32k128": (64, 32), "32x64k128": (32, 64),
-             "32x32k128": (32, 32),
-             "128x64k128g2": (128, 64), "64x64k128g2": (64, 64), "64x64k128g4": (64, 64), "64x32k128g4": (64, 32),
-             "32x64k128g4": (32, 64), "32x32k128g4": (32, 32),
-             "32x32k128g8": (32, 32), "128x64g2": (128, 64), "64x64g2": (64, 64), "32x32g4": (32, 32)}
-POOLS = dict(workspace_bytes=1024 << 20, io_bytes=64 << 20, weight_pool_bytes=512 << 20, load_staging_bytes=256 << 20)
+COST = os.path.join(HERE, "csrc", "plan_cost.inc")
+# pixels, channels, K slice of every tile shape, by its number in the library
+TILES = {0: (128, 128, 64), 1: (128, 64, 64), 2: (64, 64, 64), 3: (64, 32, 64), 4: (32, 64, 64), 5: (32, 32, 64), 8: (256, 64, 64),
+         9: (128, 128, 64), 10: (128, 64, 128), 11: (64, 64, 128), 12: (64, 32, 128), 13: (32, 64, 128), 14: (32, 32, 128),
+         15: (128, 64, 128), 16: (64, 64, 128), 17: (64, 64, 128), 18: (64, 32, 128), 19: (32, 64, 128), 20: (32, 32, 128),
+         21: (32, 32, 128), 22: (128, 64, 64), 23: (64, 64, 64), 24: (32, 32, 64), 25: (256, 128, 64), 26: (128, 256, 64),
+         27: (256, 256, 64), 28: (256, 128, 64), 29: (32, 32, 256), 30: (32, 32, 256), 31: (64, 32, 256), 32: (64, 32, 256),
+         33: (32, 64, 256), 34: (32, 64, 256), 35: (64, 64, 256)}
+SPLIT_TILES = (1, 2, 4, 10, 15, 16, 18, 19, 20, 24, 29, 31, 33, 35)
+SPLITS = (1, 2, 4, 8)
+EVENT_US = 2.04   # what a pair of events adds to a launch's time
+SPLIT_US = 0.5    # what a split launch costs its EXEC beyond its own time (measured by exchanging tiles in whole EXECs)
+PLAIN, STAGED, STEM = 0, 1, 2   # kinds of launch: the main kernel, the register-staged one, the first convolution's form
+CONFIGS = (["resnet50:224x224:%d" % b for b in (1, 2, 3, 4, 8, 12, 16)] + ["resnet50:193x161:%d" % b for b in (1, 3, 7)] +
+           ["resnet50:97x97:%d" % b for b in (1, 4, 11)] + ["resnet50:160x140:9", "resnet50:64x64:2", "resnet50:210x80:6"] +
+           ["resnet18:224x224:%d" % b for b in (1, 3, 8, 16)] + ["resnet18:64x64:%d" % b for b in (1, 4, 16)] + ["resnet18:131x180:5"] +
+           ["mobilenet:224x224:%d" % b for b in (1, 4, 16)] + ["mobilenet:150x99:3", "mobilenet:64x100:9"] +
+           ["densenet:224x224:%d" % b for b in (1, 6, 16)] + ["densenet:111x150:2", "densenet:80x80:7"] +
+           ["inception:224x224:%d" % b for b in (1, 4)] + ["inception:127x127:5", "inception:75x140:2"])
 
 
-def candidates(M, N, K, kh, stride=1):
-    """(tile, split) pairs worth trying for one GEMM shape."""
-    cin = K // (kh * kh)   # 3 for the first convolution: no k128 tiles, K slices are pairs of filter rows
-    out = []
-    for tile, (bm, bn) in TILE_DIMS.items():
-        if bn > N or (bm > 64 and bm > M):
-            continue
-        if "k128" in tile and cin % 128 != 0:
-            continue
-        ktiles = K // (128 if "k128" in tile else 64)
-        tiles = -(-M // bm) * -(-N // bn)
-        for s in SPLITS:
-            if s > 1 and (s > ktiles or tiles >= 1024 or M * N * 4 * s > (64 << 20)):
-                continue
-            out.append((tile, s))
-    return out
+def features(M, N, K, kh, kw, stride, cin, res, cls, tile, split):
+    """What the time of a launch is taken to be linear in; the same list as in plan.cpp (conv_cost)."""
+    bm, bn, bk = TILES[tile]
+    if cls == STAGED:
+        bk = 32
+    elif cls == STEM:
+        bk, K, cin = 64, 256, 4   # the packed filter
+    elif cin % bk:
+        bk = 64
+    slices = -(-K // bk)
+    per = -(-slices // split)                        # K slices a workgroup walks
+    wgs = -(-M // bm) * -(-N // bn) * split
+    more = wgs / 256.0 - 1                           # further workgroups per CU: between the exact and the rounded-up count
+    more = max(0.0, more if wgs > 2048 else 0.5 * (max(0.0, more) + -(-wgs // 256) - 1))
+    taps = float(kh * kw > 1 or stride > 1)          # general addressing
+    out_mb = M * N * 2e-6 * (1 + res)
+    in_mb = M * cin * 2e-6 * (stride * stride if kh > 1 else 1) + N * K * 2e-6
+    f = [1.0, taps, per, per * taps, per * more, more, out_mb, in_mb]
+    return f + ([1.0, split * M * N * 4e-6, float(split)] if split > 1 else [0.0, 0.0, 0.0])
 
 
-def rows(table):
-    return [k + v for k, v in table.items()]
+N_FEATURES = 11
 
 
-def read_table(path):
-    """{(M, N, K, kh, stride): (tile, split)} of a plan_table.inc."""
-    out = {}
-    for line in open(path):
-        m = re.match(r"\{(\d+), (\d+), (\d+), (\d+), (\d+), (\d+), (\d+)\}", line)
-        if m:
-            v = tuple(int(g) for g in m.groups())
-            out[v[:5]] = v[5:]
-    return out
+def nnls(A, y, sweeps=4000):
+    """Least squares with non-negative coefficients, by coordinate descent."""
+    G, b, x = A.T @ A, A.T @ y, np.zeros(A.shape[1])
+    for _ in range(sweeps):
+        for k in range(len(x)):
+            if G[k, k] > 0:
+                x[k] = max(0.0, x[k] + (b[k] - G[k] @ x) / G[k, k])
+    return x
 
 
-class Bench:
-    def __init__(self, family, depth, hw, reps):
-        from .runner import Worker, pinned_like
-        from . import measure
-        self.hw, self.reps = hw, reps
-        self.wk = Worker(**POOLS)
-        ctx = self.wk.ctx
-        if family == "resnet":
-            mid = ctx.model_define_resnet(depth, hw, hw)
-        else:
-            lists = {"mobilenet": measure.mobilenet_ops, "densenet": measure.dense_ops, "inception": measure.inception_ops}
-            mid = ctx.model_define(lists[family](), 3, hw, hw, batch_sizes=(1,))
-        self.ops = ctx.model_get_ops(mid)
-        # seeded random weights, as every measurement uses: with all-zero operands the matrix cores draw
-        # less power, the clocks sit higher and EXEC measures 2-4 % shorter, not equally for every tile
-        from .measure import resnet_blob
-        self.blob = pinned_like(resnet_blob(ctx, mid, 0, "fp16"))
-        self.n_models = 1
+def sweep(path, configs):
+    import torch
 
-    def _define(self, batch, table):
-        from .runner import Worker
-        if self.n_models > 400:   # models are never deleted from a context: start a new one now and then
-            self.wk.close()
-            self.wk = Worker(**POOLS)
-            self.n_models = 0
-        ctx = self.wk.ctx
-        ctx.set_plan_table(rows(table))
-        self.n_models += 1
-        return ctx.model_define(self.ops, 3, self.hw, self.hw, batch_sizes=(batch,))
-
-    def resnet_shapes(self, depth, batches=(1, 2, 4, 8, 16)):
-        """Shape keys of every table-driven convolution launch of a ResNet at the given batch sizes."""
-        ctx = self.wk.ctx
-        ctx.set_plan_table([])
-        mid = ctx.model_define_resnet(depth, self.hw, self.hw)
-        ops = ctx.model_get_ops(mid)
-        keys = set()
-        for batch in batches:
-            for l in ctx.plan(mid, batch):
-                if l["kind"] == 1 and l["fused_op"] < 0:
-                    o = ops[l["op_index"]]
-                    keys.add((l["gemm_m"], l["gemm_n"], l["gemm_k"], o[3], o[5]))
-        return keys
-
-    def plan_choices(self, batch):
-        """{shape key: (tile index, split)} as the library plans this batch size now."""
-        mid = self._define(batch, {})
-        out = {}
-        for l in self.wk.ctx.plan(mid, batch):
-            # a fused launch has its own fixed tile; a pair launch runs on the tile of its second member's
-            # shape (the one reported here), so that row is tuned like any other
-            if l["kind"] != 1 or l["fused_op"] >= 0:
-                continue
-            o = self.ops[l["op_index"]]
-            key = (l["gemm_m"], l["gemm_n"], l["gemm_k"], o[3], o[5])   # M, N, K, kh, stride
-            out[key] = (l["conv_tile"], l["split_k"])
-        return out
-
-    def measure(self, batch, table):
-        """Median on-device EXEC duration (us) with `table` installed."""
-        mid = self._define(batch, table)
-        ctx = self.wk.ctx
-        ctx.load_weights(mid, self.blob, self.wk.stream)
-        self.wk.stream.synchronize()
-        ctx.profile_measure(mid, batch, 8)
-        p = ctx.profile_measure(mid, batch, self.reps)
-        ctx.unload_weights(mid)
-        return p["p50_us"]
+    from . import measure
+    from .binding import Context
+    lists = {"mobilenet": measure.mobilenet_ops, "densenet": measure.dense_ops, "inception": measure.inception_ops}
+    with open(path, "w") as out:
+        for cfg in configs:
+            family, hw, batch = cfg.split(":")
+            h, w = (int(v) for v in hw.split("x"))
+            batch = int(batch)
+            ctx = Context(workspace_bytes=1 << 30, io_bytes=64 << 20, weight_pool_bytes=256 << 20, load_staging_bytes=128 << 20)
+            if family.startswith("resnet"):
+                ops = ctx.model_get_ops(ctx.model_define_resnet(int(family[6:]), h, w))
+            else:
+                ops = lists[family]()
+            ctx.set_use_graphs(0)
+            blob = None
+            x = torch.randn(batch, 3, h, w).half().float().pin_memory()
+            stream = torch.cuda.current_stream()
+            for tile in TILES:
+                for split in SPLITS if tile in SPLIT_TILES else (1,):
+                    ctx.set_plan_override(tile, split)
+                    mid = ctx.model_define(ops, 3, h, w, batch_sizes=(batch,))
+                    if blob is None:   # seeded random weights: with zeros the clocks sit higher, not equally for every tile
+                        from .runner import pinned_like
+                        blob = pinned_like(measure.resnet_blob(ctx, mid, 0, "fp16"))
+                    ctx.load_weights(mid, blob, stream)
+                    slot = ctx.input(mid, batch, x, stream)
+                    us = np.median([ctx.exec_timed_launches(mid, batch, slot, stream) for _ in range(9)], axis=0) - EVENT_US
+                    ctx.release(slot)
+                    ctx.unload_weights(mid)
+                    for l, t in zip(ctx.plan(mid, batch), us):
+                        if l["kind"] == 1:
+                            o = ops[l["op_index"]]
+                            out.write(json.dumps(dict(M=l["gemm_m"], N=l["gemm_n"], K=l["gemm_k"], kh=o[3], kw=o[4], stride=o[5], cin=o[1],
+                                                      res=int(o[8] >= 0), stem=int(l["op_index"] == 0), tile=l["conv_tile"],
+                                                      split=l["split_k"], us=float(t))) + "\n")
+            ctx.destroy()
+            print(cfg, flush=True)
 
 
-def main():
-    ap = argparse.ArgumentParser()
-    ap.add_argument("--family", default="resnet", choices=["resnet", "mobilenet", "densenet", "inception"],
-                    help="resnet (of --depth) or one of measure.py's operator lists of the other families")
-    ap.add_argument("--depth", type=int, default=50)
-    ap.add_argument("--hw", type=int, default=224)
-    ap.add_argument("--batches", default="1,2,4,8,16")
-    ap.add_argument("--reps", type=int, default=60)
-    ap.add_argument("--eps", type=float, default=0.2, help="a candidate must win by this many us")
-    ap.add_argument("--kh", type=int, default=0, help="only retune shapes with this filter size (the others keep the library's choice)")
-    ap.add_argument("--only-suffix", default="", help="only try tiles whose name ends like this")
-    ap.add_argument("--verbose", action="store_true", help="print every candidate's time")
-    ap.add_argument("--out", default=TABLE)
-    ap.add_argument("--keep-existing", action="store_true", help="rows already in the output file are not replaced")
-    ap.add_argument("--protect-resnet", type=int, default=0, help="shapes that this ResNet depth uses are neither retuned nor replaced")
-    args = ap.parse_args()
-    from .binding import CONV_TILES
-    b = Bench(args.family, args.depth, args.hw, args.reps)
-    protected = b.resnet_shapes(args.protect_resnet) if args.protect_resnet else set()
-    final = {}
-    for batch in (int(v) for v in args.batches.split(",")):
-        t_start = time.time()
-        cur = b.plan_choices(batch)
-        t0 = b.measure(batch, cur)
-        print("batch %d: %d shapes, start %.1f us" % (batch, len(cur), t0), flush=True)
-        for key in sorted(cur, key=lambda k: -k[0] * k[1] * k[2]):
-            best, best_t = cur[key], b.measure(batch, cur)
-            if (args.kh and key[3] != args.kh) or key in protected:
-                continue
-            for tile, s in candidates(*key):
-                if args.only_suffix and not tile.endswith(args.only_suffix):
-                    continue
-                cand = (CONV_TILES[tile], s)
-                if cand == cur[key]:
-                    continue
-                t = b.measure(batch, {**cur, key: cand})
-                if args.verbose:
-                    print("      %s %s split %d: %.1f us (incumbent %.1f)" % (key, tile, s, t, best_t), flush=True)
-                if t < best_t - args.eps:
-                    best, best_t = cand, t
-            if best != cur[key]:
-                # confirm against a fresh measurement of the incumbent before switching
-                if b.measure(batch, {**cur, key: best}) < b.measure(batch, cur) - args.eps / 2:
-                    cur[key] = best
-            print("  %s -> tile %d split %d   (EXEC %.1f us)" % (key, cur[key][0], cur[key][1], best_t), flush=True)
-        t1 = b.measure(batch, cur)
-        print("batch %d: %.1f -> %.1f us in %.0f s" % (batch, t0, t1, time.time() - t_start), flush=True)
-        final.update(cur)
-    b.wk.close()
-    names = {v: k for k, v in CONV_TILES.items()}
-    # rows of the table being rewritten whose shapes this run did not visit stay; with --keep-existing
-    # the rows it did visit stay as well and only new shapes are added (a second model's own shapes
-    # without moving the first model's choices)
-    kept = read_table(args.out) if os.path.exists(args.out) else {}
-    for key, val in kept.items():
-        if key not in final or args.keep_existing or key in protected:
-            final[key] = val
-    lines = ["// Generated by paper_2006_02464_amd/tune.py on an MI355X: per GEMM shape the (tile, split-K) under which",
-             "// whole EXECs ran fastest.  ResNet-50's shapes first; the shapes that only ResNet-18 or the MobileNet-,",
-             "// DenseNet- and Inception-style lists have were added afterwards without moving those.",
-             "// {M, N, K, kh, stride, tile, split_k}"]
-    for key in sorted(final):
-        tile, split = final[key]
-        lines.append("{%d, %d, %d, %d, %d, %d, %d},  // %s" % (key + (tile, split, names[tile])))
-    with open(args.out, "w") as f:
+def load(paths):
+    """{(shape, kind): {(tile, split): us}}, medians over the launches of equal shape."""
+    acc = collections.defaultdict(list)
+    for path in paths:
+        for line in open(path):
+            r = json.loads(line)
+            cls = (STEM if r["stride"] % 2 == 0 else None) if r["stem"] else (PLAIN if r["cin"] % 64 == 0 else STAGED)
+            if cls is not None and not (cls == STEM and r["tile"] in (23, 24)):   # a first convolution has no wave groups
+                acc[(tuple(r[k] for k in ("M", "N", "K", "kh", "kw", "stride", "cin", "res")), cls), r["tile"], r["split"]].append(r["us"])
+    shapes = collections.defaultdict(dict)
+    for (shape, tile, split), v in acc.items():
+        shapes[shape][tile, split] = float(np.median(v))
+    return shapes
+
+
+def fit(paths):
+    shapes = load(paths)
+    groups = collections.defaultdict(list)
+    for (shape, cls), times in shapes.items():
+        for (tile, split), us in times.items():
+            groups[cls, tile].append((features(*shape, cls, tile, split), us + SPLIT_US * (split > 1), split))
+    coef = {}
+    lines = ["// Generated by tune.py from launch times measured on an MI355X: per kind of launch (COST_*) and tile",
+             "// shape the microseconds per unit of each feature (conv_cost in plan.cpp).",
+             "// {kind, tile, K may be split, {1, general addressing, K slices, of these with general addressing, slices of",
+             "//  further workgroups on a CU, further workgroups, MB out, MB in, split, MB of partial sums, splits}}"]
+    for (cls, tile), rows in sorted(groups.items()):
+        A, y = np.array([r[0] for r in rows]), np.array([r[1] for r in rows])
+        coef[cls, tile] = c = nnls(A / y[:, None], np.ones(len(y)))
+        splits = int(any(r[2] > 1 for r in rows))
+        lines.append("{%d, %d, %d, {%s}}," % (cls, tile, splits, ", ".join("%.4gf" % v if "." in "%.4g" % v or "e" in "%.4g" % v else "%.4g.f" % v for v in c)))
+        print("kind %d tile %2d: %4d launches, rms relative error %.3f" % (cls, tile, len(y), np.sqrt((((A @ c) / y - 1) ** 2).mean())))
+    best = chosen = 0.0
+    for (shape, cls), times in shapes.items():
+        best += min(times.values())
+        chosen += times[min(times, key=lambda ts: float(np.dot(features(*shape, cls, *ts), coef[cls, ts[0]])))]
+    print("%d shapes: fastest of each %.1f us, as the model chooses %.1f us" % (len(shapes), best, chosen))
+    with open(COST, "w") as f:
         f.write("\n".join(lines) + "\n")
-    print("wrote %s (%d shapes)" % (args.out, len(final)))
 
 
 if __name__ == "__main__":
-    sys.exit(main())
+    if len(sys.argv) < 3 or sys.argv[1] not in ("sweep", "fit"):
+        sys.exit(__doc__)
+    if sys.argv[1] == "sweep":
+        sweep(sys.argv[2], sys.argv[3:] or CONFIGS)
+    else:
+        fit(sys.argv[2:])

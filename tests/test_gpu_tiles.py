@@ -1,0 +1,71 @@
+"""The tiles with K slices of 256 (forced on every layer) and the plan's own tile choice at ragged sizes: every
+layer teacher-forced against the CPU oracle."""
+import pytest
+
+from gpu_common import TOL, Case, rel_err_per_sample
+from oracle import topology as T
+from test_gpu_parity import check_all_ops, check_head
+
+pytestmark = pytest.mark.gpu
+O = T.Op
+K256 = {"32x32k256g4": 29, "32x32k256g8": 30, "64x32k256g4": 31, "64x32k256g8": 32, "32x64k256g4": 33, "32x64k256g8": 34, "64x64k256g4": 35}
+# one K slice and several, fewer and more than the ring holds; Cout above, below and beside a tile's width; stride 2; residuals; Cin
+# = 64 and 96 beside them, where the tile gives way to a narrower slice
+OPS = [
+    O(T.CONV, 3, 64, 7, 7, 2, 3, 1, -1, -1),
+    O(T.CONV, 64, 256, 3, 3, 2, 1, 1, -1, 0),
+    O(T.CONV, 256, 256, 1, 1, 1, 0, 1, 1, 1),
+    O(T.CONV, 256, 96, 3, 3, 1, 1, 0, -1, 2),
+    O(T.CONV, 96, 512, 3, 3, 2, 1, 1, -1, 3),
+    O(T.CONV, 512, 512, 3, 3, 1, 1, 1, 4, 4),
+    O(T.CONV, 512, 32, 1, 1, 1, 0, 1, -1, 5),
+    O(T.CONV, 32, 256, 1, 1, 1, 0, 1, -1, 6),
+    O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 7),
+    O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 8),
+    O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 9),
+]
+
+
+@pytest.fixture(scope="module")
+def worker():
+    from paper_2006_02464_amd.runner import Worker
+    w = Worker(workspace_bytes=1 << 30, io_bytes=64 << 20, weight_pool_bytes=128 << 20, load_staging_bytes=64 << 20)
+    yield w
+    w.close()
+
+
+def run(worker, hw, dtype, batch, tile=-1, split_k=0):
+    case = Case(OPS, hw, seed=9, dtype=dtype, dist="uniform")
+    worker.ctx.set_plan_override(tile, split_k)
+    worker.ctx.set_debug_keep(True)
+    try:
+        mid = worker.ctx.model_define(case.ops, 3, hw, hw, batch_sizes=(batch,), dtype=dtype)
+    finally:
+        worker.ctx.set_plan_override(-1, 0)
+        worker.ctx.set_debug_keep(False)
+    plan = worker.ctx.plan(mid, batch)
+    worker.load(mid, case.blob)
+    x = case.images(0, batch)
+    probs, logits, _ = worker.infer(mid, x, classes=10)
+    outs, _, gpu = check_all_ops(worker, case, mid, batch, x)
+    check_head(case, gpu[-1], logits, probs)
+    assert rel_err_per_sample(logits, outs[-2]).max() <= TOL
+    worker.ctx.unload_weights(mid)
+    return plan
+
+
+@pytest.mark.parametrize("name", sorted(K256))
+@pytest.mark.parametrize("split_k,dtype", [(1, "fp16"), (3, "fp16"), (1, "bf16")])
+def test_k256_tiles(worker, name, split_k, dtype):
+    plan = run(worker, 45, dtype, 3, K256[name], split_k)
+    wide = [l for l in plan if l["kind"] == 1 and l["tile_k"] == 256]
+    assert {l["gemm_k"] for l in wide} == {256, 9 * 256, 9 * 512, 512}
+    assert any(l["split_k"] > 1 for l in wide) == (split_k > 1)
+
+
+@pytest.mark.parametrize("hw,batch", [(33, 1), (45, 5), (97, 2), (130, 7)])
+def test_chosen_tiles_at_ragged_sizes(worker, hw, batch):
+    for l in run(worker, hw, "fp16", batch):
+        if l["kind"] == 1 and l["op_index"] > 0:
+            assert OPS[l["op_index"]][1] % l["tile_k"] == 0 and l["tile_n"] <= max(32, l["gemm_n"])
+            assert l["grid_x"] == -(-l["gemm_m"] // l["tile_m"]) * -(-l["gemm_n"] // l["tile_n"])
