@@ -21,7 +21,7 @@ constexpr int kMaxSlots = 64;
 constexpr size_t kDefaultPageBytes = (size_t)16 << 20;  // the paper's page size (section 5.1)
 constexpr int kProfileEvents = 128;  // EXECs timed back to back between two host syncs
 
-enum SlotState { SLOT_FREE = 0, SLOT_INPUT, SLOT_EXECUTED };
+enum SlotState { SLOT_FREE = 0, SLOT_RELEASED, SLOT_INPUT, SLOT_EXECUTED };   // released: free once `released` is over
 
 struct Slot {
     SlotState state = SLOT_FREE;
@@ -29,7 +29,8 @@ struct Slot {
     size_t off = 0, bytes = 0;               // region in the IO cache
     size_t in_off = 0, logits_off = 0, probs_off = 0;
     hipEvent_t input_done = nullptr, exec_start = nullptr, exec_end = nullptr, released = nullptr;
-    bool release_pending = false;            // `released` guards reuse of the region
+    uint64_t release_seq = 0;                // order of release
+    hipStream_t taken_early = nullptr;       // its memory was given on before `released` was over: to requests on this stream, which wait
 };
 
 // The slot-independent middle of a plan (everything between the input cast and the FC) as one
@@ -126,6 +127,7 @@ struct cw_ctx {
     // one EXEC at a time: remember where the last one went
     hipStream_t last_exec_stream = nullptr;
     hipEvent_t last_exec_end = nullptr;
+    uint64_t release_seq = 0;
     unsigned *res_error = nullptr;   // pinned host word a resident launch raises when it gives up (see kernels_resident.hip)
     bool resident_capable = true;    // 256 CUs in 8 XCDs (planning-only contexts: assumed)
     std::string err;
@@ -329,7 +331,7 @@ int32_t exec_checks(cw_ctx *c, int32_t model_id, int32_t batch, int32_t slot, Mo
     Plan *p = get_plan(m, batch);
     if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
     if (!m->loaded) return set_err(c, CW_ERR_NOT_LOADED, "weights are not resident");
-    if (slot < 0 || slot >= kMaxSlots || c->slots[slot].state == SLOT_FREE)
+    if (slot < 0 || slot >= kMaxSlots || c->slots[slot].state < SLOT_INPUT)
         return set_err(c, CW_ERR_NO_INPUT, "slot holds no input");
     Slot *s = &c->slots[slot];
     if (s->model != model_id) return set_err(c, CW_ERR_NO_INPUT, "slot holds an input for another model");
@@ -370,31 +372,63 @@ void percentile_profile(std::vector<float> v, cw_profile *out) {
     out->mean_us = (float)(s / (double)n);
 }
 
+void reclaim_slot(cw_ctx *c, Slot *s) {
+    c->io_alloc.free(s->off, s->bytes);
+    s->state = SLOT_FREE;
+    s->model = -1;
+}
+
+// Gives a slot up.  With copies or an EXEC on it still queued (`pending`; its `released` event is recorded
+// behind them) its memory waits for them.
+void free_slot(cw_ctx *c, Slot *s, bool pending = false) {
+    if (s->state == SLOT_FREE || s->state == SLOT_RELEASED) return;
+    if (!pending) return reclaim_slot(c, s);
+    s->state = SLOT_RELEASED;
+    s->model = -1;
+    s->release_seq = ++c->release_seq;
+}
+
 int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hipStream_t st, int32_t *slot_out) {
+    // A freed slot keeps its region until its OUTPUT copies are over, and the slot and memory of a request
+    // that is long over are taken before those of one that is not: INPUT then has nothing to wait for on the
+    // GPU.  Only where no other slot or memory is left does the stream that is about to overwrite IO memory wait.
+    for (Slot &o : c->slots)
+        if (o.state == SLOT_RELEASED && hipEventQuery(o.released) == hipSuccess) reclaim_slot(c, &o);
+    auto reclaim_oldest = [&]() {
+        Slot *old = nullptr;
+        for (Slot &o : c->slots)
+            if (o.state == SLOT_RELEASED && (!old || o.release_seq < old->release_seq)) old = &o;
+        if (!old) return hipErrorNotFound;
+        const hipError_t e = hipStreamWaitEvent(st, old->released, 0);
+        if (e == hipSuccess) { reclaim_slot(c, old); old->taken_early = st; }
+        return e;
+    };
+    for (Slot &o : c->slots) {   // what is left of memory given on early may come to this request
+        if (!o.taken_early) continue;
+        const bool over = hipEventQuery(o.released) == hipSuccess;
+        const hipError_t e = (over || o.taken_early == st) ? hipSuccess : hipStreamWaitEvent(st, o.released, 0);
+        if (e != hipSuccess) return hip_fail(c, e, "hipStreamWaitEvent");
+        if (over) o.taken_early = nullptr;
+    }
     int idx = -1;
-    for (int i = 0; i < kMaxSlots; ++i)
-        if (c->slots[i].state == SLOT_FREE) { idx = i; break; }
-    if (idx < 0) return set_err(c, CW_ERR_NO_SLOT, "every IO slot is in use");
+    for (;;) {
+        for (int i = 0; i < kMaxSlots && idx < 0; ++i)
+            if (c->slots[i].state == SLOT_FREE) idx = i;
+        if (idx >= 0) break;
+        const hipError_t e = reclaim_oldest();
+        if (e == hipErrorNotFound) return set_err(c, CW_ERR_NO_SLOT, "every IO slot is in use");
+        if (e != hipSuccess) return hip_fail(c, e, "hipStreamWaitEvent");
+    }
     Slot &s = c->slots[idx];
     const size_t in_b = (size_t)batch * m->m.in_c * m->m.in_h * m->m.in_w * 4;
     const size_t out_b = (size_t)batch * m->m.classes * 4;
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t total = up(in_b) + 2 * up(out_b);
     size_t off = 0;
-    if (!c->io_alloc.alloc(total, &off)) return set_err(c, CW_ERR_NO_MEMORY, "IO cache is full");
-    // The region may have belonged to a slot whose OUTPUT copies are still in flight: every
-    // pending release is waited for by the stream that is about to overwrite IO memory.
-    for (int i = 0; i < kMaxSlots; ++i) {
-        Slot &o = c->slots[i];
-        if (o.release_pending) {
-            hipError_t q = hipEventQuery(o.released);
-            if (q == hipErrorNotReady) {
-                hipError_t e = hipStreamWaitEvent(st, o.released, 0);
-                if (e != hipSuccess) { c->io_alloc.free(off, total); return hip_fail(c, e, "hipStreamWaitEvent"); }
-            } else {
-                o.release_pending = false;
-            }
-        }
+    while (!c->io_alloc.alloc(total, &off)) {
+        const hipError_t e = reclaim_oldest();
+        if (e == hipErrorNotFound) return set_err(c, CW_ERR_NO_MEMORY, "IO cache is full");
+        if (e != hipSuccess) return hip_fail(c, e, "hipStreamWaitEvent");
     }
     s.state = SLOT_INPUT;
     s.model = model_id; s.batch = batch;
@@ -406,12 +440,6 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
     return CW_OK;
 }
 
-void free_slot(cw_ctx *c, Slot *s) {
-    if (s->state == SLOT_FREE) return;
-    c->io_alloc.free(s->off, s->bytes);
-    s->state = SLOT_FREE;
-    s->model = -1;
-}
 
 
 bool slot_free(const Launch &l) {
@@ -583,7 +611,9 @@ int32_t cw_create(cw_ctx **out, const cw_config *cfg) {
     for (int i = 0; ok && i < kMaxSlots; ++i) {
         Slot &s = p->slots[i];
         ok = hipEventCreateWithFlags(&s.input_done, hipEventDisableTiming) == hipSuccess &&
-             hipEventCreate(&s.exec_start) == hipSuccess && hipEventCreate(&s.exec_end) == hipSuccess &&
+             // what waits for an EXEC's end runs on this GPU: the events need no system-scope fence (2 us each)
+             hipEventCreateWithFlags(&s.exec_start, hipEventDisableSystemFence) == hipSuccess &&
+             hipEventCreateWithFlags(&s.exec_end, hipEventDisableSystemFence) == hipSuccess &&
              hipEventCreateWithFlags(&s.released, hipEventDisableTiming) == hipSuccess;
     }
     for (int i = 0; ok && i < 2 * kProfileEvents; ++i) ok = hipEventCreate(&p->prof_ev[i]) == hipSuccess;
@@ -1105,15 +1135,15 @@ int32_t cw_output(cw_ctx *c, int32_t slot, float *host_probs, float *host_logits
     CW_HIP(c, hipMemcpyAsync(host_probs, c->io + s.probs_off, out_b, hipMemcpyDeviceToHost, st));
     if (host_logits) CW_HIP(c, hipMemcpyAsync(host_logits, c->io + s.logits_off, out_b, hipMemcpyDeviceToHost, st));
     CW_HIP(c, hipEventRecord(s.released, st));
-    s.release_pending = true;
-    free_slot(c, &s);
+    free_slot(c, &s, true);
     return CW_OK;
 }
 
 int32_t cw_release(cw_ctx *c, int32_t slot) {
     if (!c || slot < 0 || slot >= kMaxSlots) return set_err(c, CW_ERR_INVALID, "bad slot");
     Slot &s = c->slots[slot];
-    if (s.state == SLOT_FREE) return CW_OK;
+    if (s.state == SLOT_FREE || s.state == SLOT_RELEASED) return CW_OK;
+    bool pending = false;
     if (c->device >= 0) {
         // Work that reads or writes the slot may still be queued: whoever reuses the memory waits
         // for the last EXEC that touched it.
@@ -1121,10 +1151,10 @@ int32_t cw_release(cw_ctx *c, int32_t slot) {
         if (s.state == SLOT_EXECUTED) {
             CW_HIP(c, hipStreamWaitEvent(c->internal_stream, s.exec_end, 0));
             CW_HIP(c, hipEventRecord(s.released, c->internal_stream));
-            s.release_pending = true;
+            pending = true;
         }
     }
-    free_slot(c, &s);
+    free_slot(c, &s, pending);
     return CW_OK;
 }
 
@@ -1168,7 +1198,7 @@ int32_t cw_profile_measure(cw_ctx *c, int32_t model_id, int32_t batch, int32_t s
         e = launch_fill_zero(c->io + c->slots[slot].in_off, in_b, st);
         if (e == hipSuccess) e = hipEventRecord(c->slots[slot].input_done, st);
     } else {
-        if (slot >= kMaxSlots || c->slots[slot].state == SLOT_FREE) return set_err(c, CW_ERR_NO_INPUT, "slot holds no input");
+        if (slot >= kMaxSlots || c->slots[slot].state < SLOT_INPUT) return set_err(c, CW_ERR_NO_INPUT, "slot holds no input");
         if (c->slots[slot].model != model_id) return set_err(c, CW_ERR_NO_INPUT, "slot holds an input for another model");
         if (c->slots[slot].batch != batch) return set_err(c, CW_ERR_BAD_BATCH, "slot holds an input of another batch size");
         e = hipStreamWaitEvent(st, c->slots[slot].input_done, 0);

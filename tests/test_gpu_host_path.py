@@ -1,0 +1,33 @@
+"""INPUT, EXEC and OUTPUT queued far ahead of the GPU: the slots and IO memory of requests that are not over yet are given on."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import Case
+from oracle import topology as T
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rooms", [1, 2, 3, 80])   # requests the IO cache holds; with 80 the 64 slots run out first
+def test_requests_queued_ahead_of_the_gpu(rooms):
+    from paper_2006_02464_amd.runner import Worker
+    case = Case(T.resnet(18), 64, seed=2, dist="uniform")
+    one = 4 * 3 * 64 * 64 + 2 * 4096
+    wk = Worker(workspace_bytes=256 << 20, io_bytes=rooms * one, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = wk.ctx.model_define(case.ops, 3, 64, 64, batch_sizes=(1,))
+        wk.load(mid, case.blob)
+        x = [torch.from_numpy(np.ascontiguousarray(case.images(i, 1), dtype=np.float32)).pin_memory() for i in range(5)]
+        want = [wk.infer(mid, v.numpy())[1] for v in x]
+        ins, exe, outs = [torch.cuda.Stream() for _ in range(2)], torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(2)]
+        got = [(torch.empty(1, 1000, pin_memory=True), torch.empty(1, 1000, pin_memory=True)) for _ in range(150)]
+        for k, (probs, logits) in enumerate(got):
+            slot = wk.ctx.input(mid, 1, x[k % 5], ins[k % 2])
+            wk.ctx.exec(mid, 1, slot, exe)
+            wk.ctx.output(slot, probs, logits, outs[k // 2 % 2])
+        torch.cuda.synchronize()
+        for k, (_, logits) in enumerate(got):
+            assert np.array_equal(logits.numpy(), want[k % 5])
+    finally:
+        wk.close()
