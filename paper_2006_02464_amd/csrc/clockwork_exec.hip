@@ -861,22 +861,26 @@ int32_t cw_load_weights_begin(cw_ctx *c, int32_t model_id, const void *host_blob
             if (c->page_guard[pg2] == guard) c->page_guard[pg2] = nullptr;   // waited for (or over) once for all of them
     }
     auto at = [&](size_t off) { return c->pool + (size_t)m->pages[off / c->page_bytes] * c->page_bytes + off % c->page_bytes; };
+    std::vector<PackItem> items;
+    items.reserve(m->m.wslots.size());
     for (const WeightSlot &ws : m->m.wslots) {
-        const bool is_conv = m->m.ops[ws.op_index].op == CW_OP_CONV;
-        if (ws.depthwise)
-            e = launch_pack_depthwise(c->staging + ws.blob_w_off, at(ws.packed_w_off), ws.cout, ws.kh, ws.kw, st);
-        else
-            e = launch_pack_weights(c->staging + ws.blob_w_off, at(ws.packed_w_off), ws.cout, ws.cin, ws.kh, ws.kw, ws.khp,
-                                    ws.kwp, ws.cinp, is_conv, st);
-        if (e != hipSuccess) return bail(e, "pack_weights");
+        PackItem t{};
+        t.src = reinterpret_cast<const uint16_t *>(c->staging + ws.blob_w_off);
+        t.dst = reinterpret_cast<uint16_t *>(at(ws.packed_w_off));
+        t.bias_src = reinterpret_cast<const float *>(c->staging + ws.blob_b_off);
+        t.bias_dst = reinterpret_cast<float *>(at(ws.packed_b_off));
+        t.cout = ws.cout; t.cin = ws.cin; t.cinp = ws.cinp;
+        t.kh = (uint16_t)ws.kh; t.kw = (uint16_t)ws.kw; t.khp = (uint16_t)ws.khp; t.kwp = (uint16_t)ws.kwp;
+        t.permute = !ws.depthwise && m->m.ops[ws.op_index].op == CW_OP_CONV;
+        t.depthwise = ws.depthwise;
+        items.push_back(t);
+    }
+    if ((e = launch_pack_model(items.data(), (int)items.size(), st)) != hipSuccess) return bail(e, "pack_model");
+    for (const WeightSlot &ws : m->m.wslots)
         if (ws.wino_bytes) {
             e = launch_pack_winograd(m->m.dtype, c->staging + ws.blob_w_off, at(ws.wino_w_off), ws.cout, ws.cin, st);
             if (e != hipSuccess) return bail(e, "pack_winograd");
         }
-        e = launch_copy_f32(reinterpret_cast<const float *>(c->staging + ws.blob_b_off),
-                            reinterpret_cast<float *>(at(ws.packed_b_off)), ws.cout, st);
-        if (e != hipSuccess) return bail(e, "copy bias");
-    }
     // resident programs: every member's arguments with the weights' addresses of this placement;
     // activations stay workspace offsets (res + 1, so that 0 means none)
     m->res_programs.clear();

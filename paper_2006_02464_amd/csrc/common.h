@@ -308,13 +308,31 @@ hipError_t launch_wino_output(DType dt, const WinoArgs &a, hipStream_t s);
 // LOAD-time: canonical W[cout][cin][3][3] -> U[16][cout'][cin] = G g G^T per (cout, cin), rows in the
 // conv kernel's accumulator order, computed in fp32 and rounded once to the storage type
 hipError_t launch_pack_winograd(DType dt, const void *src, void *dst, int cout, int cin, hipStream_t s);
-// LOAD-time re-layout of depthwise weights: canonical W[C][1][kh][kw] -> [kh][kw][C]
-hipError_t launch_pack_depthwise(const void *src, void *dst, int c, int kh, int kw, hipStream_t s);
-// LOAD-time re-layout: canonical W[cout][cin][kh][kw] -> [cout'][khp][kwp][cinp] (zero padded);
-// permute = rows in the conv kernel's MFMA accumulator order (conv weights), else plain (FC).
-hipError_t launch_pack_weights(const void *src, void *dst, int cout, int cin, int kh, int kw,
-                               int khp, int kwp, int cinp, bool permute, hipStream_t s);
-hipError_t launch_copy_f32(const float *src, float *dst, size_t n, hipStream_t s);
+// Workgroups of a LOAD-side launch: at most one per compute unit, each striding over its work.
+// (Measured with EXECs running beside continuous LOADs: caps of 16, 48, 256 and no cap all leave
+// the EXEC p50 within 0.6 % of EXEC alone.)
+constexpr unsigned kLoadGridCap = 256;
+// LOAD-time re-layout of one tensor and its bias: canonical W[cout][cin][kh][kw] -> [cout'][khp][kwp][cinp] (zero padded);
+// permute = rows in the conv kernel's MFMA accumulator order (conv weights), else plain (FC);
+// depthwise = W[C][1][kh][kw] -> [kh][kw][C].  The launcher fills in mode and first_chunk.
+struct PackItem {
+    const uint16_t *src;
+    uint16_t *dst;
+    const float *bias_src;
+    float *bias_dst;
+    int32_t cout, cin, cinp;
+    uint16_t kh, kw, khp, kwp;
+    uint8_t permute, depthwise, mode;
+    uint32_t first_chunk;
+};
+constexpr int kPackItems = 60;
+struct PackArgs {
+    PackItem items[kPackItems];
+    int32_t n;
+    uint32_t chunks;
+};
+static_assert(sizeof(PackArgs) <= 4096, "kernel arguments");
+hipError_t launch_pack_model(PackItem *items, int n, hipStream_t s);
 // debug read-back: NHWC storage type (ld elements per pixel) -> fp32 NCHW
 hipError_t launch_nhwc_to_nchw_f32(DType dt, const void *src, float *dst, int B, int C, int H,
                                    int W, int ld, hipStream_t s);

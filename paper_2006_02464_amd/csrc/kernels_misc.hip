@@ -764,16 +764,6 @@ __global__ __launch_bounds__(256) void copy_channels_kernel(const CopyArgs a) {
     *reinterpret_cast<uint4 *>(static_cast<uint16_t *>(a.dst) + (size_t)m * a.ld_dst + cg * 8u) = v;
 }
 
-// LOAD-time re-layout of depthwise weights: canonical W[C][1][kh][kw] -> [kh][kw][C].
-__global__ __launch_bounds__(256) void pack_depthwise_kernel(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int C, int taps) {
-    const size_t total = (size_t)C * taps;
-    const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-        const int c = (int)(i % C), t = (int)(i / C);
-        dst[i] = src[(size_t)c * taps + t];
-    }
-}
-
 // ---- Winograd F(2x2, 3x3) transforms (3x3 stride-1 pad-1 convolution) ------------------------
 //   Y = A^T [ (G g G^T) .* (B^T d B) ] A,  d = 4x4 input patch of a 2x2 output tile,
 //   B^T = [1 0 -1 0; 0 1 1 0; 0 -1 1 0; 0 1 0 -1],  G = [1 0 0; .5 .5 .5; .5 -.5 .5; 0 0 1],
@@ -941,43 +931,6 @@ __global__ __launch_bounds__(256) void pack_winograd_kernel(const T *__restrict_
     }
 }
 
-// Workgroups of a LOAD-side launch: at most one per compute unit, each striding over its tensor.
-// (Measured with EXECs running beside continuous LOADs: caps of 16, 48, 256 and no cap all leave
-// the EXEC p50 within 0.6 % of EXEC alone; a LOAD of ResNet-50 takes 5.4, 2.6, 1.4 and 1.2 ms.)
-constexpr unsigned kLoadGridCap = 256;
-
-// row i of every group of 32 output channels receives channel sigma(i) of that group,
-//     i = 8g + 4h + k  ->  sigma(i) = 16*(g/2) + 8h + 4*(g%2) + k,
-// the order in which the conv kernel's MFMA accumulators come out as runs of 8 channels.
-__global__ __launch_bounds__(256) void pack_weights_kernel(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst,
-                                                           int cout, int cin, int kh, int kw, int khp, int kwp, int cinp,
-                                                           int permute) {
-    // A bounded grid that strides over the tensor: LOAD runs beside EXEC (paper section 5.2), and a
-    // launch as wide as a large tensor would queue thousands of workgroups behind the EXEC kernels' own.
-    const size_t total = (size_t)cout * khp * kwp * cinp;
-    const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-        const int c = (int)(i % cinp);
-        size_t t = i / cinp;
-        const int s = (int)(t % kwp);
-        t /= kwp;
-        const int r = (int)(t % khp);
-        int k = (int)(t / khp);
-        if (permute) {
-            const int row = k & 31, g = row >> 3, h = (row >> 2) & 1, kk = row & 3;
-            k = (k & ~31) + (g >> 1) * 16 + h * 8 + (g & 1) * 4 + kk;
-        }
-        uint16_t v = 0;
-        if (c < cin && s < kw && r < kh) v = src[(((size_t)k * cin + c) * kh + r) * kw + s];
-        dst[i] = v;
-    }
-}
-
-__global__ __launch_bounds__(256) void copy_f32_kernel(const float *__restrict__ src, float *__restrict__ dst, size_t n) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) dst[i] = src[i];
-}
-
 __global__ __launch_bounds__(256) void fill_zero_kernel(uint4 *dst, size_t n16) {
     size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * 256;
@@ -1123,23 +1076,6 @@ hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_pack_weights(const void *src, void *dst, int cout, int cin, int kh, int kw, int khp, int kwp, int cinp,
-                               bool permute, hipStream_t s) {
-    if (permute && cout % 32 != 0) return hipErrorInvalidValue;
-    const size_t total = (size_t)cout * khp * kwp * cinp;
-    const unsigned want = blocks_for(total, 256);
-    pack_weights_kernel<<<dim3(want < kLoadGridCap ? want : kLoadGridCap), 256, 0, s>>>(static_cast<const uint16_t *>(src),
-                                                                    static_cast<uint16_t *>(dst), cout, cin, kh, kw,
-                                                                    khp, kwp, cinp, permute ? 1 : 0);
-    return hipGetLastError();
-}
-
-hipError_t launch_copy_f32(const float *src, float *dst, size_t n, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    copy_f32_kernel<<<dim3(blocks_for(n, 256)), 256, 0, s>>>(src, dst, n);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s) {
     if (bytes % 16 != 0) return hipErrorInvalidValue;
     if (bytes == 0) return hipSuccess;
@@ -1211,13 +1147,6 @@ hipError_t launch_pack_winograd(DType dt, const void *src, void *dst, int cout, 
     const dim3 grid(want < kLoadGridCap ? want : kLoadGridCap);
     if (dt == DT_F16) pack_winograd_kernel<f16><<<grid, 256, 0, s>>>(static_cast<const f16 *>(src), static_cast<f16 *>(dst), cout, cin);
     else pack_winograd_kernel<bf16><<<grid, 256, 0, s>>>(static_cast<const bf16 *>(src), static_cast<bf16 *>(dst), cout, cin);
-    return hipGetLastError();
-}
-
-hipError_t launch_pack_depthwise(const void *src, void *dst, int c, int kh, int kw, hipStream_t s) {
-    if (c < 1 || kh < 1 || kw < 1) return hipErrorInvalidValue;
-    const unsigned want = blocks_for((size_t)c * kh * kw, 256);
-    pack_depthwise_kernel<<<dim3(want < kLoadGridCap ? want : kLoadGridCap), 256, 0, s>>>(static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst), c, kh * kw);
     return hipGetLastError();
 }
 
