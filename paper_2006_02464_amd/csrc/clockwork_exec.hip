@@ -180,6 +180,7 @@ Plan *get_plan(ModelRt *m, int32_t batch) {
 struct Bases {
     char *workspace = nullptr, *input = nullptr, *logits = nullptr, *probs = nullptr;
     const int32_t *pages = nullptr;  // pool page of each of the model's weight pages
+    int32_t clear_counters = 0;      // arrival counters the first launch clears (where the last user of the workspace is not known)
 };
 
 Bases bases_of(const cw_ctx *c, const ModelRt *m, const Slot *s) {
@@ -208,6 +209,8 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
             CastArgs a = l.cast;
             a.x = reinterpret_cast<const float *>(resolve(c, m, s, l.x));
             a.y = resolve(c, m, s, l.y);
+            a.zero = reinterpret_cast<int32_t *>(s.workspace);
+            a.n_zero = s.clear_counters;
             return launch_cast_input(dt, a, st);
         }
         case K_CONV: {
@@ -1068,12 +1071,11 @@ int32_t cw_exec_static(cw_ctx *c, int32_t model_id, int32_t batch, const float *
     b.input = const_cast<char *>(reinterpret_cast<const char *>(dev_input_nchw));
     b.logits = reinterpret_cast<char *>(dev_logits);
     b.probs = reinterpret_cast<char *>(dev_probs);
-    // The arena keeps what the last call left: the split-K arrival counters at its start must be
-    // zero (a fill kernel, not a memset, so that the call may be recorded into a graph).
-    hipError_t e = launch_fill_zero(c->static_scratch, kCounterBytes, st);
-    if (e != hipSuccess) return hip_fail(c, e, "clearing the arrival counters");
+    // The arena keeps what the last call left: the arrival counters at its start must be zero.  The cast of the input,
+    // which every plan begins with, clears those that the launches behind it use (a launch of its own took 3 us).
+    b.clear_counters = p->n_counters;
     for (const Launch &l : p->launches) {
-        e = issue(c, m, b, l, st);
+        const hipError_t e = issue(c, m, b, l, st);
         if (e != hipSuccess) return hip_fail(c, e, l.info.name);
     }
     return CW_OK;

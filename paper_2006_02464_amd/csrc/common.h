@@ -208,6 +208,8 @@ struct CastArgs {
     void *y;         // NHWC4 [B][Hp][Wp][4]: the image inside a zero border of `pad` pixels
     int32_t B, C, H, W;
     int32_t pad, Hp, Wp;  // Hp = H + 2*pad, Wp = W + 2*pad rounded up to even
+    int32_t *zero;        // n_zero words the launch also clears (the arrival counters of the launches behind it)
+    int32_t n_zero;
 };
 
 struct PoolArgs {

@@ -14,12 +14,13 @@ static __device__ __forceinline__ float to_f32(T v) { return (float)v; }
 // One thread per pixel of the padded output: inside the image C strided 4-byte reads (each
 // coalesced across the wave along W), zeros in the border; one 8-byte write either way.
 template <typename T>
-__global__ __launch_bounds__(256) void cast_input_kernel(const float *x, void *y, int B, int C, int H, int W, int pad, int Hp, int Wp) {
-    const CastArgs a{x, y, B, C, H, W, pad, Hp, Wp};
+__global__ __launch_bounds__(256) void cast_input_kernel(const float *x, void *y, int B, int C, int H, int W, int pad, int Hp, int Wp, int32_t *zero, int n_zero) {
+    const CastArgs a{x, y, B, C, H, W, pad, Hp, Wp, zero, n_zero};
     // 32-bit index arithmetic: the launch code checks that the padded output has fewer than 2^31 pixels
     const unsigned hwp = (unsigned)a.Hp * a.Wp;
     const unsigned total = (unsigned)a.B * hwp;
     const unsigned i = blockIdx.x * 256u + threadIdx.x;
+    for (unsigned j = i; j < (unsigned)a.n_zero; j += gridDim.x * 256u) a.zero[j] = 0;
     if (i >= total) return;
     const unsigned n = i / hwp, pp = i - n * hwp;
     const unsigned row = pp / (unsigned)a.Wp;
@@ -965,8 +966,8 @@ static inline unsigned blocks_for(size_t n, int per) { return (unsigned)((n + pe
 hipError_t launch_cast_input(DType dt, const CastArgs &a, hipStream_t s) {
     if (a.C < 1 || a.C > 4 || a.B < 1 || a.pad < 0 || a.Hp != a.H + 2 * a.pad || a.Wp < a.W + 2 * a.pad) return hipErrorInvalidValue;
     const size_t total = (size_t)a.B * a.Hp * a.Wp;
-    if (total >= (1ull << 31)) return hipErrorInvalidValue;
-    CW_DISPATCH(dt, cast_input_kernel, dim3(blocks_for(total, 256)), 256, s, a.x, a.y, a.B, a.C, a.H, a.W, a.pad, a.Hp, a.Wp);
+    if (total >= (1ull << 31) || a.n_zero < 0 || (a.n_zero > 0 && !a.zero)) return hipErrorInvalidValue;
+    CW_DISPATCH(dt, cast_input_kernel, dim3(blocks_for(total, 256)), 256, s, a.x, a.y, a.B, a.C, a.H, a.W, a.pad, a.Hp, a.Wp, a.zero, a.n_zero);
     return hipGetLastError();
 }
 

@@ -1153,6 +1153,12 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             p.launches.erase(p.launches.begin() + i + 1);
         }
     }
+    for (const Launch &l : p.launches) {
+        if (l.counters.space == SP_NONE) continue;
+        const TileDim d = conv_tile_dim(l.tile);
+        p.n_counters = std::max<int32_t>(p.n_counters, l.kind == K_FC ? (l.fc.Out + 15) / 16 + 1
+                                                                     : ((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn));
+    }
     // Resident runs: every maximal run of two or more plain convolution launches (direct-to-LDS
     // kernel, whole K per workgroup) becomes one launch whose members keep partition 0's arguments.
     if (res_mode) {

@@ -85,6 +85,7 @@ struct WeightSlot {        // one op that owns weights
 
 struct Plan {
     int32_t batch = 0;
+    int32_t n_counters = 0;   // arrival counters its launches use, from the start of the workspace
     std::vector<Launch> launches;
     std::vector<Ref> op_out;  // workspace (or slot) location of every op's output
     std::vector<int32_t> op_ld;  // elements from one pixel of that output to the next (> its channels where it is a
