@@ -242,6 +242,10 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
                 a0.y = resolve(c, m, s, l.y0);
                 return launch_conv_pair(dt, l.tile, a0, a, st);
             }
+            if (l.ahead_bytes > 0) {
+                a.w2 = resolve(c, m, s, l.ahead);
+                a.Cout2 = l.ahead_bytes / 128;
+            }
             return launch_conv(dt, l.tile, l.stem, a, st);
         }
         case K_MAXPOOL:

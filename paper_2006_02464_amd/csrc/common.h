@@ -78,6 +78,8 @@ struct alignas(64) ConvArgs {
     // Fused second layer (launch_conv_fused only): a 1x1 stride-1 convolution over this one's
     // output, y = act2(res + bias2 + W2 * act(bias + W * x)).  `res`, `y` then belong to the second
     // layer ([M][Cout2]); the first layer's output is never stored.
+    // In the plain form w2 and Cout2 name memory the launch reads ahead for a later one (conv_prefetch_*): Cout2 pieces
+    // of 128 bytes from w2 on, 0 for none.
     const void *w2;      // packed [Cout2][Cout]
     const float *bias2;  // [Cout2]
     int32_t Cout2;
@@ -121,6 +123,15 @@ __host__ __device__ inline int conv_ldx(const ConvArgs &a) { return a.ld & 0xfff
 __host__ __device__ inline int conv_ldy(const ConvArgs &a) { return (int)((unsigned)a.ld >> 16); }
 inline void conv_set_pad(ConvArgs &a, int pad_h, int pad_w) { a.pad = pad_h | (pad_w << 16); }
 inline void conv_set_ld(ConvArgs &a, int ldx, int ldy) { a.ld = ldx | (ldy << 16); }
+// Reading ahead.  A launch with few tiles leaves CUs idle, and the weights of the launches behind it may have to come
+// from HBM (several resident models outgrow the 256 MB last-level cache): workgroups behind its tiles read one word
+// of every 128 bytes of them, which brings them into that cache.  Measured, 3x3 of 256 channels at 14x14, batch 16, whose weights
+// come from HBM: 12.0 -> 10.1 us a launch; with weights already in the cache 10.0 either way.
+constexpr int kPrefetchMinBytes = 256 * 1024;   // of a smaller tensor every workgroup that uses it waits for a miss or two at most
+constexpr int kPrefetchMaxTiles = 512;   // more tiles than that: the workgroups would only come behind them
+constexpr int kPrefetchLines = 256;      // per workgroup: a CU has only so many misses in flight (one workgroup per 4096 made ResNet-152 4 % slower)
+constexpr int kPrefetchPerThread = 4;    // reads a thread has in flight
+inline int conv_prefetch_wgs(int lines) { return lines < 64 * kPrefetchLines ? (lines + kPrefetchLines - 1) / kPrefetchLines : 64; }
 constexpr int kMaxChannels = 32768;  // channel counts and pitches travel in 16 bits
 
 // Maps of at least this many pixels are averaged by the 16-wave kernel (one wave per 64 channels below).

@@ -26,7 +26,23 @@ __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(
             a.y = static_cast<char *>(y) + (long long)blockIdx.z * rest.zs_y;
         }
     }
-    conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG>(a, blockIdx.x, nb);
+    if constexpr (FUSED || SPLITK || MODE == MODE_STEM) {
+        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG>(a, blockIdx.x, nb);
+    } else if (__builtin_expect((int)blockIdx.x < conv_nb_tiles(nb), 1)) {
+        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG>(a, blockIdx.x, nb);
+    } else {   // a workgroup that reads ahead (its code behind the convolution's, which most launches find cold)
+        const int first = (int)blockIdx.x - conv_nb_tiles(nb), nt = ((int)gridDim.x - conv_nb_tiles(nb)) * (int)blockDim.x;
+        const int lines = rest.Cout2;
+        const char *p = static_cast<const char *>(rest.w2);
+        for (int i = first * (int)blockDim.x + (int)threadIdx.x; i < lines; i += nt * kPrefetchPerThread) {
+            unsigned v[kPrefetchPerThread];
+#pragma unroll
+            for (int u = 0; u < kPrefetchPerThread; ++u)
+                v[u] = *reinterpret_cast<const unsigned *>(p + (size_t)min(i + u * nt, lines - 1) * 128);
+#pragma unroll
+            for (int u = 0; u < kPrefetchPerThread; ++u) asm volatile("" : : "v"(v[u]));
+        }
+    }
 }
 
 // A tile numbering in 2^p panels needs the channel tiles to divide evenly, and the tile count must
@@ -55,6 +71,7 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     if (attr != hipSuccess) return attr;
     // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
     // at the end needs its own room)
+    if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && grid.z == 1) grid.x += conv_prefetch_wgs(a.Cout2);
     const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG - 1) * BM * BN * 4);
     kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a);
     return hipGetLastError();

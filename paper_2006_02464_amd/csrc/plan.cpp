@@ -1226,6 +1226,28 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         }
         p.launches.swap(out);
     }
+    // Weights are read ahead by the nearest of the four launches before the one that uses them which has CUs to spare.
+    {
+        auto host = [&](const Launch &l) {
+            if (l.kind != K_CONV || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
+            if (!conv_uses_dlds(l.conv, false) || l.ahead_bytes > 0) return false;
+            const TileDim d = conv_tile_dim(l.tile);
+            return (int64_t)((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn) <= kPrefetchMaxTiles;
+        };
+        for (int t = 1; t < (int)p.launches.size(); ++t)
+            for (const Ref &w : {p.launches[t].w, p.launches[t].w0, p.launches[t].w2, p.launches[t].w3, p.launches[t].wd}) {
+                if (w.space != SP_WEIGHTS) continue;
+                int32_t bytes = 0;
+                for (const WeightSlot &ws : m.wslots)
+                    if (ws.packed_w_off == w.offset) bytes = (int32_t)std::min<size_t>(ws.packed_w_bytes, 1u << 30);
+                for (int h = t - 1; h >= 0 && h >= t - 4; --h)
+                    if (bytes >= kPrefetchMinBytes && host(p.launches[h])) {
+                        p.launches[h].ahead = w;
+                        p.launches[h].ahead_bytes = bytes;
+                        break;
+                    }
+            }
+    }
     // grid/block of every launch, for introspection
     for (Launch &l : p.launches) {
         dim3 g(1, 1, 1);

@@ -55,6 +55,8 @@ struct Launch {
     int32_t pair_op = -1;
     ConvArgs conv0{};
     Ref w0, bias0, res0, y0;
+    Ref ahead;             // weights of a later launch that this one reads ahead (plain convolution launches)
+    int32_t ahead_bytes = 0;
     int64_t in_bytes = 0;  // algorithmic bytes of the input tensor (counted once in a pair)
     cw_launch_info info{};
     // K_RESIDENT: the convolution layers of the run, each with partition 0's arguments (conv), its
