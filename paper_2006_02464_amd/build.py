@@ -9,7 +9,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libclockwork_exec.so")
-SOURCES = ["clockwork_exec.hip", "plan.cpp", "kernels_conv.hip", "kernels_conv_dlds.hip", "kernels_conv_k256.hip", "kernels_resident.hip", "kernels_misc.hip", "kernels_load.hip", "worker.hip"]
+SOURCES = ["clockwork_exec.hip", "plan.cpp", "kernels_conv.hip", "kernels_conv_dlds.hip", "kernels_conv_k256.hip", "kernels_conv_tail.hip", "kernels_resident.hip", "kernels_misc.hip", "kernels_load.hip", "worker.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-fno-gpu-rdc",
@@ -23,6 +23,7 @@ FLAGS = [
 # without the feature.
 EXTRA_FLAGS = {"kernels_conv_dlds.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"],
                "kernels_conv_k256.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"],
+               "kernels_conv_tail.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=10"],
                "kernels_misc.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=11"]}
 
 

@@ -276,6 +276,8 @@ ConvTile conv_tile_one_group(ConvTile t);
 // The largest tile of the register-staged kernel that is no larger than t (that kernel has the ten
 // basic shapes only; it serves Cin % 64 != 0 and first convolutions outside the stem form).
 ConvTile conv_tile_staged(ConvTile t);
+// The tile of the 1x1 form that ends in part of a K slice (which has some of the one-group shapes) nearest to t.
+ConvTile conv_tile_tail(ConvTile t);
 // Whether a convolution runs on the direct-to-LDS kernel (else on the register-staged one).
 bool conv_uses_dlds(const ConvArgs &a, bool stem);
 
@@ -285,6 +287,7 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
 // (called by launch_conv after its checks); mode = the kernel's addressing mode.
 hipError_t launch_conv_dlds(DType dt, ConvTile tile, int bk, int mode, const ConvArgs &a, hipStream_t s);
 // Its K slices of 256 (kernels_conv_k256.hip; called by launch_conv_dlds).
+hipError_t launch_conv_dlds_tail(DType dt, ConvTile tile, bool splitk, const ConvArgs &a, hipStream_t s);
 hipError_t launch_conv_dlds_k256(DType dt, ConvTile tile, int mode, bool splitk, const ConvArgs &a, hipStream_t s);
 // A convolution (Cin % 64 == 0, Cout 64 or 128) and the 1x1 convolution that consumes it, in one
 // launch (kernels_conv_dlds.hip).  bm = pixels per workgroup (64 or 128).

@@ -10,7 +10,8 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr unsigned kOob = 0x80000000u;  // byte offset beyond any buffer (buffers are < 2 GiB)
 
-enum ConvMode : int { MODE_CONV = 0, MODE_GEMM = 1, MODE_STEM = 2 };
+// MODE_TAIL: MODE_GEMM whose K ends in part of a slice (a form of its own: the masks cost the plain one 1.5 %)
+enum ConvMode : int { MODE_CONV = 0, MODE_GEMM = 1, MODE_STEM = 2, MODE_TAIL = 3 };
 
 // n / d for a divisor prepared on the host (round-up multiplier; exact for every 32-bit n).
 static __device__ __forceinline__ unsigned fast_div(unsigned n, const FastDiv &d) {

@@ -145,7 +145,9 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
-    const int ktiles = a.K / BK;
+    constexpr bool GEMM = MODE == MODE_GEMM || MODE == MODE_TAIL;
+    // a first convolution's filter rows beyond kh are padding
+    const int ktiles = MODE == MODE_STEM ? (a.kh + 1) / 2 : MODE == MODE_TAIL ? (a.K + BK - 1) / BK : a.K / BK;
     const int kt0 = SPLITK ? blockIdx.y * a.ktiles_per_split : 0;
     const int kt1 = SPLITK ? min(ktiles, kt0 + a.ktiles_per_split) : ktiles;  // no split: the whole K
     const int nsteps = kt1 - kt0;
@@ -168,7 +170,8 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     // at the filter's centre pixel, and which taps fall inside the image (bit r*kw+s; for the
     // 1x1 stride-1 case bit 0 = the pixel exists).
     unsigned x_voff[X_PER], x_mask[X_PER];
-    if constexpr (MODE == MODE_GEMM) {
+    const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)
+    if constexpr (GEMM) {
 #pragma unroll
         for (int j = 0; j < X_PER; ++j) {
             const int cid = tid + j * NT;
@@ -176,7 +179,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             const int c = (cid % CPR) ^ swz_key<BK>(row);
             const unsigned m = m0 + row;
             x_voff[j] = m * ldx * 2u + c * 16u;
-            x_mask[j] = m < (unsigned)a.M ? 1u : 0u;
+            x_mask[j] = m < (unsigned)a.M ? (MODE == MODE_TAIL && c * 8 < k_last ? 3u : 1u) : 0u;   // bit 1: also in the last slice
         }
     } else {
         // The pixel arithmetic (two divisions and the tap mask) is done once per tile row, by
@@ -226,7 +229,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             x_mask[j] = ri.y;
         }
     }
-    unsigned w_off[W_PER];
+    unsigned w_off[W_PER], w_last = 0;   // bit j of w_last: piece j is also in the last slice (MODE_TAIL)
 #pragma unroll
     for (int j = 0; j < W_PER; ++j) {
         const int cid = tid + j * NT;
@@ -234,6 +237,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         const int c = (cid % CPR) ^ swz_key<BK>(row);
         const int n = n0 + row;
         w_off[j] = n < a.Cout ? ((unsigned)n * a.K + c * 8) * 2u : kOob;
+        if (MODE == MODE_TAIL && c * 8 < k_last) w_last |= 1u << j;
     }
     if constexpr (FUSED) {
         float *sb = reinterpret_cast<float *>(cw_dyn_lds + BIAS_OFF);
@@ -250,7 +254,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     int fr = 0, fs = 0, fc0 = 0;
     if (!SPLITK) {
         // one workgroup walks the whole K: it starts at (0, 0, 0), no divisions needed
-    } else if (MODE == MODE_GEMM) {
+    } else if (GEMM) {
         fc0 = kt0 * BK;
     } else if (MODE == MODE_CONV) {
         const int k0 = kt0 * BK;
@@ -265,10 +269,10 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     // one load, end() advances (r, s, c0).
     unsigned is_soff = 0, is_tbit = 0, is_dst = 0, is_kb = 0;
     auto issue_begin = [&](int kt, int stage) {
-        is_soff = MODE == MODE_GEMM   ? (unsigned)fc0 * 2u
+        is_soff = GEMM                ? (unsigned)fc0 * 2u
                   : MODE == MODE_STEM ? (unsigned)kt * (2u * a.W * 8u)
                                       : ((unsigned)(fr * a.W + fs) * ldx + (unsigned)fc0) * 2u;
-        is_tbit = MODE == MODE_CONV ? (1u << (fr * a.kw + fs)) : 1u;
+        is_tbit = MODE == MODE_CONV ? (1u << (fr * a.kw + fs)) : MODE == MODE_TAIL && kt == ktiles - 1 ? 2u : 1u;
         is_dst = lds_base + (unsigned)stage * STAGE_BYTES + (unsigned)wave * 1024u;
         is_kb = (unsigned)kt * (BK * 2u);
     };
@@ -276,7 +280,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         if (idx < X_PER)
             load_to_lds(dx, (x_mask[idx] & is_tbit) ? x_voff[idx] : kOob, is_soff, is_dst + idx * (NT * 16));
         else
-            load_to_lds(dw, w_off[idx - X_PER], is_kb, is_dst + BM * BK * 2 + (idx - X_PER) * (NT * 16));
+            load_to_lds(dw, MODE == MODE_TAIL && is_tbit == 2u && !(w_last >> (idx - X_PER) & 1u) ? kOob : w_off[idx - X_PER], is_kb, is_dst + BM * BK * 2 + (idx - X_PER) * (NT * 16));
     };
     auto issue_end = [&]() {
         fc0 += BK;

@@ -358,7 +358,21 @@ ConvTile conv_tile_staged(ConvTile t) {
     }
 }
 
-bool conv_uses_dlds(const ConvArgs &a, bool stem) { return stem ? stem_is_dlds(a) : a.Cin % 64 == 0; }
+static bool conv_is_gemm(const ConvArgs &a, bool stem) {
+    return !stem && a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.Cin % 32 == 0;
+}
+
+// The 1x1 stride-1 form ends in part of a K slice where Cin does not divide.
+bool conv_uses_dlds(const ConvArgs &a, bool stem) { return stem ? stem_is_dlds(a) : a.Cin % 64 == 0 || conv_is_gemm(a, stem); }
+
+ConvTile conv_tile_tail(ConvTile t) {
+    switch (t) {
+        case T64x64k128: case T128x64k128: return t;
+        case T128x64w2: case T256x64: return T128x64;
+        case T64x128w2: return T64x64;
+        default: t = conv_tile_staged(t); return t == T256x64 || t == T128x64w2 ? T128x64 : t == T64x128w2 ? T64x64 : t;
+    }
+}
 
 ConvTile conv_tile_one_group(ConvTile t) {
     switch (t) {
@@ -376,13 +390,10 @@ ConvTile conv_tile_one_group(ConvTile t) {
 
 int conv_bk(const ConvArgs &a, bool stem, ConvTile tile) {
     if (stem) return stem_is_dlds(a) ? 64 : 32;
-    if (a.Cin % 64 != 0) return 32;
+    if (!conv_uses_dlds(a, stem)) return 32;
+    // part of a wide slice only behind two whole ones: what is padded stays below a third
     const int bk = conv_tile_dim(tile).bk;
-    return a.Cin % bk == 0 ? bk : 64;
-}
-
-static bool conv_is_gemm(const ConvArgs &a, bool stem) {
-    return !stem && a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.Cin % 64 == 0;
+    return a.Cin % bk == 0 || (bk == 128 && a.Cin > 2 * bk && conv_is_gemm(a, stem) && conv_tile_tail(tile) == tile) ? bk : 64;
 }
 
 void conv_grid(ConvTile tile, const ConvArgs &a, dim3 *grid, int *block) {
@@ -425,14 +436,15 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
     // Shapes the kernel's indexing relies on; the plan compiler guarantees them, checked again
     // here so that a bad launch is an error instead of an out-of-bounds access.
     const int bk = conv_bk(a, stem, tile);
-    if (a.K % bk != 0 || a.M <= 0 || a.Cout <= 0 || a.Cout % 32 != 0 || a.split_k < 1 || a.ktiles_per_split < 1)
+    const bool gemm = conv_is_gemm(a, stem);
+    if ((a.K % bk != 0 && !gemm) || a.M <= 0 || a.Cout <= 0 || a.Cout % 32 != 0 || a.split_k < 1 || a.ktiles_per_split < 1)
         return hipErrorInvalidValue;
     if (stem ? (a.Cin != 4 || a.kwp != 8 || a.khp < a.kh || a.K != a.khp * 32) : (a.Cin % 32 != 0 || a.kwp != a.kw || a.K != a.kh * a.kw * a.Cin))
         return hipErrorInvalidValue;
     if (stem ? a.kh > 30 : a.kh * a.kw > 32) return hipErrorInvalidValue;  // tap masks are 32 bits
-    if ((long long)a.split_k * a.ktiles_per_split < a.K / bk) return hipErrorInvalidValue;
+    if ((long long)a.split_k * a.ktiles_per_split < (a.K + bk - 1) / bk) return hipErrorInvalidValue;
     if (a.split_k > 1 && (!a.partial || !a.counters)) return hipErrorInvalidValue;
-    if (a.nz > 1 && (stem || !conv_is_gemm(a, stem) || a.split_k != 1 || a.bias || a.res)) return hipErrorInvalidValue;   // batched: 1x1 form only
+    if (a.nz > 1 && (!gemm || a.Cin % 64 != 0 || a.split_k != 1 || a.bias || a.res)) return hipErrorInvalidValue;   // batched: 1x1 form only
     if (a.nz <= 1 && !a.bias) return hipErrorInvalidValue;
     if (a.split_k == 1 && a.partial) return hipErrorInvalidValue;
     // buffer descriptors address less than 2 GiB each
@@ -444,7 +456,7 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
     // K slices of 64 go global -> LDS directly (kernels_conv_dlds.hip); the stem and Cin % 64 != 0
     // keep the register-staged kernel of this file.
     if (stem && stem_is_dlds(a)) return launch_conv_dlds(dt, tile, bk, MODE_STEM, a, s);
-    if (!stem && a.Cin % 64 == 0) return launch_conv_dlds(dt, tile, bk, conv_is_gemm(a, stem) ? MODE_GEMM : MODE_CONV, a, s);
+    if (!stem && conv_uses_dlds(a, false)) return launch_conv_dlds(dt, tile, bk, !gemm ? MODE_CONV : a.K % bk ? MODE_TAIL : MODE_GEMM, a, s);
     if (a.split_k > 1) return dt == DT_F16 ? launch_conv_dt<f16, true>(tile, stem, a, s) : launch_conv_dt<bf16, true>(tile, stem, a, s);
     return dt == DT_F16 ? launch_conv_dt<f16, false>(tile, stem, a, s) : launch_conv_dt<bf16, false>(tile, stem, a, s);
 }

@@ -236,9 +236,10 @@ hipError_t launch_conv_dlds(DType dt, ConvTile tile, int bk, int mode, const Con
             return hipErrorInvalidValue;
         // every 8-tap window must start inside the (padded) image
         if ((a.Ho - 1) * a.stride >= a.H || (a.Wo - 1) * a.stride >= a.W) return hipErrorInvalidValue;
-    } else if ((bk != 64 && bk != 128 && bk != 256) || a.Cin % bk != 0 || a.K != a.kh * a.kw * a.Cin) {
+    } else if ((bk != 64 && bk != 128 && bk != 256) || (a.Cin % bk != 0) != (mode == MODE_TAIL) || a.K != a.kh * a.kw * a.Cin) {
         return hipErrorInvalidValue;
     }
+    if (mode == MODE_TAIL) return launch_conv_dlds_tail(dt, tile, a.split_k > 1, a, s);
     if (a.split_k > 1) return dt == DT_F16 ? launch_mode<f16, true>(tile, bk, mode, a, s) : launch_mode<bf16, true>(tile, bk, mode, a, s);
     return dt == DT_F16 ? launch_mode<f16, false>(tile, bk, mode, a, s) : launch_mode<bf16, false>(tile, bk, mode, a, s);
 }

@@ -322,7 +322,7 @@ static double conv_cost(const ConvCost &c, const ConvArgs *const *as, const bool
     for (int k = 0; k < n; ++k) {
         const ConvArgs &a = *as[k];
         const TileDim d = conv_tile_dim((ConvTile)c.tile);
-        const int slices = a.K / conv_bk(a, stem, (ConvTile)c.tile);
+        const int bk = conv_bk(a, stem, (ConvTile)c.tile), slices = (a.K + bk - 1) / bk;
         const double per = (slices + split - 1) / split;
         const double w = (double)((a.M + d.bm - 1) / d.bm) * ((a.Cout + d.bn - 1) / d.bn) * split;
         const double t = (a.kh * a.kw > 1 || a.stride > 1) ? 1 : 0;
@@ -350,7 +350,7 @@ static double conv_cost(const ConvCost &c, const ConvArgs *const *as, const bool
 static bool split_ok(const ConvArgs &a, bool stem, ConvTile tile, int32_t split) {
     if (split == 1) return true;
     const TileDim d = conv_tile_dim(tile);
-    const int slices = a.K / conv_bk(a, stem, tile);
+    const int bk = conv_bk(a, stem, tile), slices = (a.K + bk - 1) / bk;
     const int per = (slices + split - 1) / split;
     const int64_t tiles = ((int64_t)a.M + d.bm - 1) / d.bm * ((a.Cout + d.bn - 1) / d.bn);
     return (slices + per - 1) / per == split && tiles * 4 <= (int64_t)kCounterBytes && (int64_t)a.M * a.Cout * 4 < (1ll << 31);
@@ -374,7 +374,7 @@ static double pick_conv_tile(const ConvArgs &a, bool stem, bool res, int64_t rea
     double best = 1e30;
     for (const ConvCost &c : kConvCost) {
         const TileDim d = conv_tile_dim((ConvTile)c.tile);
-        if (c.cls != cls || (cls == COST_PLAIN && a.Cin % d.bk != 0) || (d.bn > a.Cout && d.bn > 32)) continue;
+        if (c.cls != cls || (cls == COST_PLAIN && (conv_bk(a, stem, (ConvTile)c.tile) != d.bk || (a.Cin % 64 != 0 && conv_tile_tail((ConvTile)c.tile) != c.tile))) || (d.bn > a.Cout && d.bn > 32)) continue;
         for (int32_t s = 1; s <= (c.splits ? 8 : 1); s *= 2) {
             if ((ov.split_k > 0 && s != ov.split_k && s > 1) || !split_ok(a, stem, (ConvTile)c.tile, s)) continue;
             const double us = conv_cost(c, as, &res, 1, stem, s) + (ov.split_k > 1 && s == 1 ? 1e3 : 0);   // a forced split where it can be had
@@ -914,10 +914,11 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 a.wo_div = make_fast_div((uint32_t)os.w);
                 a.ho_div = make_fast_div((uint32_t)os.h);
                 l.cost_us = pick_conv_tile(a, l.stem, o.residual_from >= 0, (int64_t)o.kh * o.kw * o.cin, ov, &l.tile, &a.split_k, &l.tile_fixed);
+                if (!l.stem && a.Cin % 64 != 0 && conv_uses_dlds(a, false)) l.tile = conv_tile_tail(l.tile);   // 1x1, part of a slice at the end
                 if (!conv_uses_dlds(a, l.stem)) l.tile = conv_tile_staged(l.tile);   // the register-staged kernel's shapes
                 if (conv_bk(a, l.stem, l.tile) != conv_tile_dim(l.tile).bk) l.tile = conv_tile_k64(l.tile);  // Cin is no multiple of the tile's slice
                 if (l.stem) l.tile = conv_tile_one_group(l.tile);   // the first convolution's mode has no wave groups
-                const int ktiles = a.K / conv_bk(a, l.stem, l.tile);
+                const int bk = conv_bk(a, l.stem, l.tile), ktiles = (a.K + bk - 1) / bk;
                 a.split_k = std::max(1, std::min(a.split_k, ktiles));
                 {
                     const TileDim tdc = conv_tile_dim(l.tile);

@@ -40,6 +40,10 @@ CONFIGS = (["resnet50:224x224:%d" % b for b in (1, 2, 3, 4, 8, 12, 16)] + ["resn
            ["inception:224x224:%d" % b for b in (1, 4)] + ["inception:127x127:5", "inception:75x140:2"])
 
 
+def gemm_form(kh, kw, stride, cin):
+    return kh == kw == stride == 1 and cin % 32 == 0
+
+
 def features(M, N, K, kh, kw, stride, cin, res, cls, tile, split):
     """What the time of a launch is taken to be linear in; the same list as in plan.cpp (conv_cost)."""
     bm, bn, bk = TILES[tile]
@@ -47,7 +51,7 @@ def features(M, N, K, kh, kw, stride, cin, res, cls, tile, split):
         bk = 32
     elif cls == STEM:
         bk, K, cin = 64, 256, 4   # the packed filter
-    elif cin % bk:
+    elif cin % bk and not (gemm_form(kh, kw, stride, cin) and cin > 2 * bk and tile in (10, 11)):
         bk = 64
     slices = -(-K // bk)
     per = -(-slices // split)                        # K slices a workgroup walks
@@ -122,7 +126,7 @@ def load(paths):
     for path in paths:
         for line in open(path):
             r = json.loads(line)
-            cls = (STEM if r["stride"] % 2 == 0 else None) if r["stem"] else (PLAIN if r["cin"] % 64 == 0 else STAGED)
+            cls = (STEM if r["stride"] % 2 == 0 else None) if r["stem"] else (PLAIN if r["cin"] % 64 == 0 or gemm_form(r["kh"], r["kw"], r["stride"], r["cin"]) else STAGED)
             if cls is not None and not (cls == STEM and r["tile"] in (23, 24)):   # a first convolution has no wave groups
                 acc[(tuple(r[k] for k in ("M", "N", "K", "kh", "kw", "stride", "cin", "res")), cls), r["tile"], r["split"]].append(r["us"])
     shapes = collections.defaultdict(dict)

@@ -34,8 +34,8 @@ def worker():
     w.close()
 
 
-def run(worker, hw, dtype, batch, tile=-1, split_k=0):
-    case = Case(OPS, hw, seed=9, dtype=dtype, dist="uniform")
+def run(worker, hw, dtype, batch, tile=-1, split_k=0, ops=OPS):
+    case = Case(ops, hw, seed=9, dtype=dtype, dist="uniform")
     worker.ctx.set_plan_override(tile, split_k)
     worker.ctx.set_debug_keep(True)
     try:
@@ -63,9 +63,23 @@ def test_k256_tiles(worker, name, split_k, dtype):
     assert any(l["split_k"] > 1 for l in wide) == (split_k > 1)
 
 
+@pytest.mark.parametrize("tile,split_k", [("64x64", 1), ("64x64", 3), ("64x64k128", 1), ("32x32k128g4", 2), ("32x32k256g4", 1), ("128x128w8", 1)])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_1x1_ending_in_part_of_a_slice(worker, tile, split_k, dtype):
+    """Input channels just above whole slices of 64, 128 and 256, as part of one slice, and as a range of a CONCAT."""
+    ops = [O(T.CONV, 3, 64, 3, 3, 2, 1, 1, -1, -1)]
+    for n in (32, 96, 160, 288, 352, 544, 224):
+        ops.append(O(T.CONV, ops[-1].cout, n, 1, 1, 1, 0, 1, -1, len(ops) - 1))
+    ops += [O(T.CONV, 224, 64, 1, 1, 1, 0, 1, -1, 7), O(T.CONV, 64, 32, 3, 3, 1, 1, 1, -1, 8), O(T.CONCAT, 64, 96, 0, 0, 1, 0, 0, 9, 8),
+            O(T.CONV, 96, 256, 1, 1, 1, 0, 1, -1, 10), O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 11), O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 12),
+            O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 13)]
+    run(worker, 26, dtype, 3, K256.get(tile, tile), split_k, ops)
+
+
 @pytest.mark.parametrize("hw,batch", [(33, 1), (45, 5), (97, 2), (130, 7)])
 def test_chosen_tiles_at_ragged_sizes(worker, hw, batch):
     for l in run(worker, hw, "fp16", batch):
         if l["kind"] == 1 and l["op_index"] > 0:
-            assert OPS[l["op_index"]][1] % l["tile_k"] == 0 and l["tile_n"] <= max(32, l["gemm_n"])
+            o = OPS[l["op_index"]]
+            assert (o[1] % l["tile_k"] == 0 or (o[3] == 1 and l["tile_k"] == 64)) and l["tile_n"] <= max(32, l["gemm_n"])
             assert l["grid_x"] == -(-l["gemm_m"] // l["tile_m"]) * -(-l["gemm_n"] // l["tile_n"])
