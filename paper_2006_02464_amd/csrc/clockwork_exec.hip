@@ -30,7 +30,6 @@ struct Slot {
     size_t in_off = 0, logits_off = 0, probs_off = 0;
     hipEvent_t input_done = nullptr, exec_start = nullptr, exec_end = nullptr, released = nullptr;
     uint64_t release_seq = 0;                // order of release
-    hipStream_t taken_early = nullptr;       // its memory was given on before `released` was over: to requests on this stream, which wait
 };
 
 // The slot-independent middle of a plan (everything between the input cast and the FC) as one
@@ -128,6 +127,10 @@ struct cw_ctx {
     hipStream_t last_exec_stream = nullptr;
     hipEvent_t last_exec_end = nullptr;
     uint64_t release_seq = 0;
+    // Set while IO memory that was given on before its copies were over may still be in use: `given_on` is then over
+    // once all of it is free.
+    hipEvent_t given_on = nullptr;
+    bool given_on_pending = false;
     unsigned *res_error = nullptr;   // pinned host word a resident launch raises when it gives up (see kernels_resident.hip)
     bool resident_capable = true;    // 256 CUs in 8 XCDs (planning-only contexts: assumed)
     std::string err;
@@ -401,22 +404,26 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
     // GPU.  Only where no other slot or memory is left does the stream that is about to overwrite IO memory wait.
     for (Slot &o : c->slots)
         if (o.state == SLOT_RELEASED && hipEventQuery(o.released) == hipSuccess) reclaim_slot(c, &o);
+    // What is left of a region given on early may come to any later request, on whatever stream: each waits for
+    // `given_on`.  It says nothing about streams (their handles come back for other streams, and the default stream's is
+    // null); a wait for an event of the same stream costs nothing.
+    if (c->given_on_pending) {
+        const hipError_t q = hipEventQuery(c->given_on);
+        const hipError_t e = q == hipErrorNotReady ? hipStreamWaitEvent(st, c->given_on, 0) : q;
+        if (e != hipSuccess) return hip_fail(c, e, "wait for IO memory given on");
+        if (q == hipSuccess) c->given_on_pending = false;
+    }
+    // Recorded on `st`, which by now waits for this release and for everything given on before it.
     auto reclaim_oldest = [&]() {
         Slot *old = nullptr;
         for (Slot &o : c->slots)
             if (o.state == SLOT_RELEASED && (!old || o.release_seq < old->release_seq)) old = &o;
         if (!old) return hipErrorNotFound;
-        const hipError_t e = hipStreamWaitEvent(st, old->released, 0);
-        if (e == hipSuccess) { reclaim_slot(c, old); old->taken_early = st; }
+        hipError_t e = hipStreamWaitEvent(st, old->released, 0);
+        if (e == hipSuccess) e = hipEventRecord(c->given_on, st);
+        if (e == hipSuccess) { reclaim_slot(c, old); c->given_on_pending = true; }
         return e;
     };
-    for (Slot &o : c->slots) {   // what is left of memory given on early may come to this request
-        if (!o.taken_early) continue;
-        const bool over = hipEventQuery(o.released) == hipSuccess;
-        const hipError_t e = (over || o.taken_early == st) ? hipSuccess : hipStreamWaitEvent(st, o.released, 0);
-        if (e != hipSuccess) return hip_fail(c, e, "hipStreamWaitEvent");
-        if (over) o.taken_early = nullptr;
-    }
     int idx = -1;
     for (;;) {
         for (int i = 0; i < kMaxSlots && idx < 0; ++i)
@@ -615,6 +622,7 @@ int32_t cw_create(cw_ctx **out, const cw_config *cfg) {
     bool ok = hipStreamCreateWithFlags(&p->internal_stream, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&p->staging_free, hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&p->given_on, hipEventDisableTiming) == hipSuccess;
     for (int i = 0; ok && i < kMaxSlots; ++i) {
         Slot &s = p->slots[i];
         ok = hipEventCreateWithFlags(&s.input_done, hipEventDisableTiming) == hipSuccess &&
@@ -653,6 +661,7 @@ int32_t cw_destroy(cw_ctx *c) {
         for (hipEvent_t e : c->prof_ev)
             if (e) (void)hipEventDestroy(e);
         if (c->staging_free) (void)hipEventDestroy(c->staging_free);
+        if (c->given_on) (void)hipEventDestroy(c->given_on);
         if (c->internal_stream) (void)hipStreamDestroy(c->internal_stream);
         if (c->res_error) (void)hipHostFree(c->res_error);
         if (c->workspace) (void)hipFree(c->workspace);

@@ -31,3 +31,34 @@ def test_requests_queued_ahead_of_the_gpu(rooms):
             assert np.array_equal(logits.numpy(), want[k % 5])
     finally:
         wk.close()
+
+
+@pytest.mark.parametrize("order", [(0, 1, 2), (1, 0, 2), (2, 2, 0), (0, 0, 1)])   # 0 = the default stream, whose handle is null
+def test_io_memory_given_on_in_parts_to_requests_on_several_streams(order):
+    """The IO cache holds one request of two images or two of one image.  With OUTPUT held up, a request of one image takes
+    half of an unfinished request's memory early, and the next one, on another stream, what is left of it: it must wait too."""
+    from paper_2006_02464_amd.runner import Worker
+    case = Case(T.resnet(18), 64, seed=4, dist="uniform")
+    wk = Worker(workspace_bytes=256 << 20, io_bytes=2 * (4 * 3 * 64 * 64 + 2 * 4096), weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = wk.ctx.model_define(case.ops, 3, 64, 64, batch_sizes=(1, 2))
+        wk.load(mid, case.blob)
+        x = [torch.from_numpy(np.ascontiguousarray(case.images(2 * i, n), dtype=np.float32)).pin_memory() for i, n in enumerate((2, 1, 1))]
+        want = [wk.infer(mid, v.numpy())[:2] for v in x]
+        streams = [torch.cuda.default_stream(), torch.cuda.Stream(), torch.cuda.Stream()]
+        exe, out = torch.cuda.Stream(), torch.cuda.Stream()
+        got = []
+        for k in range(9):
+            b = x[k % 3].shape[0]
+            if k % 3 == 0:
+                with torch.cuda.stream(out):
+                    torch.cuda._sleep(20_000_000)
+            slot = wk.ctx.input(mid, b, x[k % 3], streams[order[(k + k // 3) % 3]])
+            wk.ctx.exec(mid, b, slot, exe)
+            got.append((torch.empty(b, 1000, pin_memory=True), torch.empty(b, 1000, pin_memory=True)))
+            wk.ctx.output(slot, got[-1][0], got[-1][1], out)
+        torch.cuda.synchronize()
+        for k, (probs, logits) in enumerate(got):
+            assert np.array_equal(probs.numpy(), want[k % 3][0]) and np.array_equal(logits.numpy(), want[k % 3][1]), k
+    finally:
+        wk.close()
