@@ -231,7 +231,8 @@ int32_t cw_output(cw_ctx *ctx, int32_t slot, float *host_probs, float *host_logi
                   void *stream);
 /* Section 5.2, INFER: an action that is rejected after its INPUT (its window passed, its EXEC
  * failed) must give its IO-cache entry back without an OUTPUT.  Releases the slot without
- * copying anything out; the memory is reused only after the slot's last EXEC has finished.
+ * copying anything out; the memory is reused only after its INPUT copy and its last EXEC have
+ * finished.
  * Succeeds on a slot that is already free. */
 int32_t cw_release(cw_ctx *ctx, int32_t slot);
 /* On-device duration of the slot's last EXEC (the "timing" field of a result).

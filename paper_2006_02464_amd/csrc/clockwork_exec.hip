@@ -1162,18 +1162,14 @@ int32_t cw_release(cw_ctx *c, int32_t slot) {
     if (!c || slot < 0 || slot >= kMaxSlots) return set_err(c, CW_ERR_INVALID, "bad slot");
     Slot &s = c->slots[slot];
     if (s.state == SLOT_FREE || s.state == SLOT_RELEASED) return CW_OK;
-    bool pending = false;
     if (c->device >= 0) {
-        // Work that reads or writes the slot may still be queued: whoever reuses the memory waits
-        // for the last EXEC that touched it.
+        // The copy into the slot or an EXEC on it may still be queued: whoever reuses the memory waits for the
+        // last of them (an EXEC waits for the copy itself).
         DeviceGuard g(c->device);
-        if (s.state == SLOT_EXECUTED) {
-            CW_HIP(c, hipStreamWaitEvent(c->internal_stream, s.exec_end, 0));
-            CW_HIP(c, hipEventRecord(s.released, c->internal_stream));
-            pending = true;
-        }
+        CW_HIP(c, hipStreamWaitEvent(c->internal_stream, s.state == SLOT_EXECUTED ? s.exec_end : s.input_done, 0));
+        CW_HIP(c, hipEventRecord(s.released, c->internal_stream));
     }
-    free_slot(c, &s, pending);
+    free_slot(c, &s, c->device >= 0);
     return CW_OK;
 }
 

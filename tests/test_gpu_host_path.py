@@ -62,3 +62,29 @@ def test_io_memory_given_on_in_parts_to_requests_on_several_streams(order):
             assert np.array_equal(probs.numpy(), want[k % 3][0]) and np.array_equal(logits.numpy(), want[k % 3][1]), k
     finally:
         wk.close()
+
+
+def test_memory_of_a_released_input_waits_for_its_copy():
+    """A request is released while its INPUT copy is still queued behind other work of its stream; the next one takes the
+    same memory through another stream and is executed later than both copies."""
+    from paper_2006_02464_amd.runner import Worker
+    case = Case(T.resnet(18), 64, seed=5, dist="uniform")
+    wk = Worker(workspace_bytes=256 << 20, io_bytes=4 * 3 * 64 * 64 + 2 * 4096, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = wk.ctx.model_define(case.ops, 3, 64, 64, batch_sizes=(1,))
+        wk.load(mid, case.blob)
+        x = [torch.from_numpy(np.ascontiguousarray(case.images(i, 1), dtype=np.float32)).pin_memory() for i in range(2)]
+        want = wk.infer(mid, x[1].numpy())[1]
+        late, soon, exe = (torch.cuda.Stream() for _ in range(3))
+        for stream, cycles in ((late, 10_000_000), (exe, 40_000_000)):
+            with torch.cuda.stream(stream):
+                torch.cuda._sleep(cycles)
+        wk.ctx.release(wk.ctx.input(mid, 1, x[0], late))
+        slot = wk.ctx.input(mid, 1, x[1], soon)
+        wk.ctx.exec(mid, 1, slot, exe)
+        probs, logits = torch.empty(1, 1000, pin_memory=True), torch.empty(1, 1000, pin_memory=True)
+        wk.ctx.output(slot, probs, logits, exe)
+        torch.cuda.synchronize()
+        assert np.array_equal(logits.numpy(), want)
+    finally:
+        wk.close()
