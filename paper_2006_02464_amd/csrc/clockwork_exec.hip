@@ -29,6 +29,8 @@ struct Slot {
     size_t off = 0, bytes = 0;               // region in the IO cache
     size_t in_off = 0, logits_off = 0, probs_off = 0;
     hipEvent_t input_done = nullptr, exec_start = nullptr, exec_end = nullptr, released = nullptr;
+    hipEvent_t exec_seen = nullptr;          // behind exec_end, with its fence, of an EXEC whose launches may raise the error word
+    bool raises_error = false;               // its last EXEC was one
     uint64_t release_seq = 0;                // order of release
 };
 
@@ -532,6 +534,19 @@ int32_t enqueue_plan(cw_ctx *c, ModelRt *m, const Plan *p, const Slot *s, hipStr
     return CW_OK;
 }
 
+// Records the end of an EXEC that has been enqueued on `st` and remembers where it went.
+int32_t record_exec_end(cw_ctx *c, ModelRt *m, const Plan *p, Slot *s, hipStream_t st) {
+    CW_HIP(c, hipEventRecord(s->exec_end, st));
+    s->raises_error = false;
+    for (const Launch &l : p->launches) s->raises_error |= l.kind == K_RESIDENT;
+    if (s->raises_error) CW_HIP(c, hipEventRecord(s->exec_seen, st));
+    s->state = SLOT_EXECUTED;
+    c->last_exec_stream = st;
+    c->last_exec_end = s->exec_end;
+    m->last_exec_end = s->exec_end;
+    return CW_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -626,9 +641,15 @@ int32_t cw_create(cw_ctx **out, const cw_config *cfg) {
     for (int i = 0; ok && i < kMaxSlots; ++i) {
         Slot &s = p->slots[i];
         ok = hipEventCreateWithFlags(&s.input_done, hipEventDisableTiming) == hipSuccess &&
-             // what waits for an EXEC's end runs on this GPU: the events need no system-scope fence (2 us each)
+             // Without the system-scope fence, 2 us each (5 us from host to host with exec_end's own; a release to device scope
+             // costs as much).  It would make device memory visible to the host and to other devices; here the host reads
+             // none behind these events, and other streams of this GPU see an EXEC's results as its own next launch would,
+             // on another XCD: every launch ends with a release to device scope, after which the XCDs' L2s, which are not coherent
+             // with one another, hold nothing that is not in memory too.  There OUTPUT's copy reads it, as a kernel or by a copy
+             // engine; the copy's own end is fenced.  What the host does read is the error word: see exec_seen.
              hipEventCreateWithFlags(&s.exec_start, hipEventDisableSystemFence) == hipSuccess &&
              hipEventCreateWithFlags(&s.exec_end, hipEventDisableSystemFence) == hipSuccess &&
+             hipEventCreateWithFlags(&s.exec_seen, hipEventDisableTiming) == hipSuccess &&
              hipEventCreateWithFlags(&s.released, hipEventDisableTiming) == hipSuccess;
     }
     for (int i = 0; ok && i < 2 * kProfileEvents; ++i) ok = hipEventCreate(&p->prof_ev[i]) == hipSuccess;
@@ -656,6 +677,7 @@ int32_t cw_destroy(cw_ctx *c) {
             if (s.input_done) (void)hipEventDestroy(s.input_done);
             if (s.exec_start) (void)hipEventDestroy(s.exec_start);
             if (s.exec_end) (void)hipEventDestroy(s.exec_end);
+            if (s.exec_seen) (void)hipEventDestroy(s.exec_seen);
             if (s.released) (void)hipEventDestroy(s.released);
         }
         for (hipEvent_t e : c->prof_ev)
@@ -1047,12 +1069,7 @@ int32_t cw_exec(cw_ctx *c, int32_t model_id, int32_t batch, int32_t slot, void *
     CW_HIP(c, hipEventRecord(s->exec_start, st));
     rc = enqueue_plan(c, m, p, s, st);
     if (rc != CW_OK) return rc;
-    CW_HIP(c, hipEventRecord(s->exec_end, st));
-    s->state = SLOT_EXECUTED;
-    c->last_exec_stream = st;
-    c->last_exec_end = s->exec_end;
-    m->last_exec_end = s->exec_end;
-    return CW_OK;
+    return record_exec_end(c, m, p, s, st);
 }
 
 int32_t cw_exec_static(cw_ctx *c, int32_t model_id, int32_t batch, const float *dev_input_nchw, float *dev_logits,
@@ -1131,11 +1148,9 @@ int32_t cw_exec_timed_launches(cw_ctx *c, int32_t model_id, int32_t batch, int32
             launch_us[base + i] = ms * 1000.f / (float)inner;
         }
     }
-    CW_HIP(c, hipEventRecord(s->exec_end, st));
+    rc = record_exec_end(c, m, p, s, st);
+    if (rc != CW_OK) return rc;
     CW_HIP(c, hipStreamSynchronize(st));
-    s->state = SLOT_EXECUTED;
-    c->last_exec_stream = st;
-    c->last_exec_end = s->exec_end;
     return CW_OK;
 }
 
@@ -1179,7 +1194,7 @@ int32_t cw_exec_duration_ns(cw_ctx *c, int32_t slot, uint64_t *ns) {
         return set_err(c, CW_ERR_NO_INPUT, "slot holds no result");
     Slot &s = c->slots[slot];
     DeviceGuard g(c->device);
-    CW_HIP(c, hipEventSynchronize(s.exec_end));
+    CW_HIP(c, hipEventSynchronize(s.raises_error ? s.exec_seen : s.exec_end));
     float ms = 0.f;
     CW_HIP(c, hipEventElapsedTime(&ms, s.exec_start, s.exec_end));
     *ns = (uint64_t)((double)ms * 1e6 + 0.5);
