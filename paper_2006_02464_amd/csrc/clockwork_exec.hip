@@ -129,8 +129,7 @@ struct cw_ctx {
     hipStream_t last_exec_stream = nullptr;
     hipEvent_t last_exec_end = nullptr;
     uint64_t release_seq = 0;
-    // Set while IO memory that was given on before its copies were over may still be in use: `given_on` is then over
-    // once all of it is free.
+    // Set while free IO memory may still be in use by the request it was taken from: `given_on` is over once none is.
     hipEvent_t given_on = nullptr;
     bool given_on_pending = false;
     unsigned *res_error = nullptr;   // pinned host word a resident launch raises when it gives up (see kernels_resident.hip)
@@ -400,6 +399,12 @@ void free_slot(cw_ctx *c, Slot *s, bool pending = false) {
     s->release_seq = ++c->release_seq;
 }
 
+// From here on free IO memory may still be in use by work that `st` waits for.
+void mark_given_on(cw_ctx *c, hipStream_t st) {
+    if (hipEventRecord(c->given_on, st) == hipSuccess) c->given_on_pending = true;
+    else (void)hipStreamSynchronize(st);
+}
+
 int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hipStream_t st, int32_t *slot_out) {
     // A freed slot keeps its region until its OUTPUT copies are over, and the slot and memory of a request
     // that is long over are taken before those of one that is not: INPUT then has nothing to wait for on the
@@ -407,24 +412,31 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
     for (Slot &o : c->slots)
         if (o.state == SLOT_RELEASED && hipEventQuery(o.released) == hipSuccess) reclaim_slot(c, &o);
     // What is left of a region given on early may come to any later request, on whatever stream: each waits for
-    // `given_on`.  It says nothing about streams (their handles come back for other streams, and the default stream's is
-    // null); a wait for an event of the same stream costs nothing.
+    // `given_on`, which says nothing about streams (their handles come back for other streams, and the default stream's is
+    // null).
     if (c->given_on_pending) {
         const hipError_t q = hipEventQuery(c->given_on);
         const hipError_t e = q == hipErrorNotReady ? hipStreamWaitEvent(st, c->given_on, 0) : q;
         if (e != hipSuccess) return hip_fail(c, e, "wait for IO memory given on");
         if (q == hipSuccess) c->given_on_pending = false;
     }
-    // Recorded on `st`, which by now waits for this release and for everything given on before it.
+    size_t low = SIZE_MAX, high = 0;   // bounds of the regions taken early in this call
     auto reclaim_oldest = [&]() {
         Slot *old = nullptr;
         for (Slot &o : c->slots)
             if (o.state == SLOT_RELEASED && (!old || o.release_seq < old->release_seq)) old = &o;
         if (!old) return hipErrorNotFound;
-        hipError_t e = hipStreamWaitEvent(st, old->released, 0);
-        if (e == hipSuccess) e = hipEventRecord(c->given_on, st);
-        if (e == hipSuccess) { reclaim_slot(c, old); c->given_on_pending = true; }
+        const hipError_t e = hipStreamWaitEvent(st, old->released, 0);
+        if (e == hipSuccess) {
+            low = std::min(low, old->off);
+            high = std::max(high, old->off + old->bytes);
+            reclaim_slot(c, old);
+        }
         return e;
+    };
+    auto give_up = [&](int32_t status) {
+        if (high > 0) mark_given_on(c, st);
+        return status;
     };
     int idx = -1;
     for (;;) {
@@ -432,8 +444,8 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
             if (c->slots[i].state == SLOT_FREE) idx = i;
         if (idx >= 0) break;
         const hipError_t e = reclaim_oldest();
-        if (e == hipErrorNotFound) return set_err(c, CW_ERR_NO_SLOT, "every IO slot is in use");
-        if (e != hipSuccess) return hip_fail(c, e, "hipStreamWaitEvent");
+        if (e == hipErrorNotFound) return give_up(set_err(c, CW_ERR_NO_SLOT, "every IO slot is in use"));
+        if (e != hipSuccess) return give_up(hip_fail(c, e, "hipStreamWaitEvent"));
     }
     Slot &s = c->slots[idx];
     const size_t in_b = (size_t)batch * m->m.in_c * m->m.in_h * m->m.in_w * 4;
@@ -443,9 +455,10 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
     size_t off = 0;
     while (!c->io_alloc.alloc(total, &off)) {
         const hipError_t e = reclaim_oldest();
-        if (e == hipErrorNotFound) return set_err(c, CW_ERR_NO_MEMORY, "IO cache is full");
-        if (e != hipSuccess) return hip_fail(c, e, "hipStreamWaitEvent");
+        if (e == hipErrorNotFound) return give_up(set_err(c, CW_ERR_NO_MEMORY, "IO cache is full"));
+        if (e != hipSuccess) return give_up(hip_fail(c, e, "hipStreamWaitEvent"));
     }
+    if (high > 0 && (low < off || high > off + total)) mark_given_on(c, st);   // not all of it is this request's now
     s.state = SLOT_INPUT;
     s.model = model_id; s.batch = batch;
     s.off = off; s.bytes = total;
@@ -455,8 +468,6 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
     *slot_out = idx;
     return CW_OK;
 }
-
-
 
 bool slot_free(const Launch &l) {
     for (const Ref *r : {&l.x, &l.w, &l.bias, &l.res, &l.y, &l.partial, &l.counters, &l.probs, &l.y3})
@@ -1051,6 +1062,7 @@ int32_t cw_input(cw_ctx *c, int32_t model_id, int32_t batch, const float *host_n
     hipError_t e = hipMemcpyAsync(c->io + s.in_off, host_nchw, in_b, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipEventRecord(s.input_done, st);
     if (e != hipSuccess) {
+        mark_given_on(c, st);
         free_slot(c, &s);
         return hip_fail(c, e, "input copy");
     }
@@ -1236,7 +1248,7 @@ int32_t cw_profile_measure(cw_ctx *c, int32_t model_id, int32_t batch, int32_t s
     Slot &s = c->slots[slot];
     if (e == hipSuccess) e = hipStreamWaitEvent(st, m->load_done, 0);
     if (e != hipSuccess) {
-        if (own_slot) free_slot(c, &s);
+        if (own_slot) { mark_given_on(c, st); free_slot(c, &s); }
         return hip_fail(c, e, "profile setup");
     }
     std::vector<float> samples;
