@@ -357,6 +357,8 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s);
 // K-slice width the conv kernel uses for a shape under a tile: the tile's (128 or 64) when Cin
 // is a multiple of it, else 64, else 32 (the stem and Cin % 64 != 0).
 int conv_bk(const ConvArgs &a, bool stem, ConvTile tile);
+// How many of them it walks.  The direct-to-LDS kernel ends a first convolution's walk at the last pair of real filter rows.
+int conv_slices(const ConvArgs &a, bool stem, ConvTile tile);
 // Bytes at the start of the workspace reserved for split-K arrival counters (one int per tile).
 constexpr size_t kCounterBytes = 256 * 1024;
 // Grid and block of a conv launch (pure function of tile and shape).

@@ -59,7 +59,7 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     if (!conv_panel_ok(a, BN, grid.x)) return hipErrorInvalidValue;
     a.nb = conv_pack_nb((int)grid.x, a.panel_log2);
     if (MODE == MODE_TAIL ? a.nz > 1 : a.K % BK != 0 && MODE != MODE_STEM) return hipErrorInvalidValue;
-    if (!SPLITK && a.ktiles_per_split != (a.K + BK - 1) / BK) return hipErrorInvalidValue;  // the kernel walks the whole K
+    if (!SPLITK && a.ktiles_per_split != (MODE == MODE_STEM ? (a.kh + 1) / 2 : (a.K + BK - 1) / BK)) return hipErrorInvalidValue;  // the kernel walks the whole K
     if (a.nz > 1 && (MODE != MODE_GEMM || SPLITK || a.bias || a.res || grid.z != (unsigned)a.nz)) return hipErrorInvalidValue;
     if (a.nz <= 1 && grid.z != 1) return hipErrorInvalidValue;
     constexpr int NS = RingDepth<BM, BN, BK>::value;
@@ -73,8 +73,7 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
     // at the end needs its own room)
     if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && grid.z == 1) grid.x += conv_prefetch_wgs(a.Cout2);
-    const int slices = MODE == MODE_STEM ? (a.kh + 1) / 2 : a.ktiles_per_split;
-    const size_t used = std::max((size_t)std::min(NS, slices) * stage_bytes, (size_t)(KG - 1) * BM * BN * 4);
+    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG - 1) * BM * BN * 4);
     kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a);
     return hipGetLastError();
 }

@@ -396,6 +396,11 @@ int conv_bk(const ConvArgs &a, bool stem, ConvTile tile) {
     return a.Cin % bk == 0 || (bk == 128 && a.Cin > 2 * bk && conv_is_gemm(a, stem) && conv_tile_tail(tile) == tile) ? bk : 64;
 }
 
+int conv_slices(const ConvArgs &a, bool stem, ConvTile tile) {
+    const int bk = conv_bk(a, stem, tile);
+    return stem && conv_uses_dlds(a, true) ? (a.kh + 1) / 2 : (a.K + bk - 1) / bk;
+}
+
 void conv_grid(ConvTile tile, const ConvArgs &a, dim3 *grid, int *block) {
     const TileDim d = conv_tile_dim(tile);
     const unsigned tm = (a.M + d.bm - 1) / d.bm, tn = (a.Cout + d.bn - 1) / d.bn;
@@ -442,7 +447,7 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
     if (stem ? (a.Cin != 4 || a.kwp != 8 || a.khp < a.kh || a.K != a.khp * 32) : (a.Cin % 32 != 0 || a.kwp != a.kw || a.K != a.kh * a.kw * a.Cin))
         return hipErrorInvalidValue;
     if (stem ? a.kh > 30 : a.kh * a.kw > 32) return hipErrorInvalidValue;  // tap masks are 32 bits
-    if ((long long)a.split_k * a.ktiles_per_split < (a.K + bk - 1) / bk) return hipErrorInvalidValue;
+    if ((long long)a.split_k * a.ktiles_per_split < conv_slices(a, stem, tile)) return hipErrorInvalidValue;
     if (a.split_k > 1 && (!a.partial || !a.counters)) return hipErrorInvalidValue;
     if (a.nz > 1 && (!gemm || a.Cin % 64 != 0 || a.split_k != 1 || a.bias || a.res)) return hipErrorInvalidValue;   // batched: 1x1 form only
     if (a.nz <= 1 && !a.bias) return hipErrorInvalidValue;

@@ -322,7 +322,7 @@ static double conv_cost(const ConvCost &c, const ConvArgs *const *as, const bool
     for (int k = 0; k < n; ++k) {
         const ConvArgs &a = *as[k];
         const TileDim d = conv_tile_dim((ConvTile)c.tile);
-        const int bk = conv_bk(a, stem, (ConvTile)c.tile), slices = (a.K + bk - 1) / bk;
+        const int slices = conv_slices(a, stem, (ConvTile)c.tile);
         const double per = (slices + split - 1) / split;
         const double w = (double)((a.M + d.bm - 1) / d.bm) * ((a.Cout + d.bn - 1) / d.bn) * split;
         const double t = (a.kh * a.kw > 1 || a.stride > 1) ? 1 : 0;
@@ -350,7 +350,7 @@ static double conv_cost(const ConvCost &c, const ConvArgs *const *as, const bool
 static bool split_ok(const ConvArgs &a, bool stem, ConvTile tile, int32_t split) {
     if (split == 1) return true;
     const TileDim d = conv_tile_dim(tile);
-    const int bk = conv_bk(a, stem, tile), slices = (a.K + bk - 1) / bk;
+    const int slices = conv_slices(a, stem, tile);
     const int per = (slices + split - 1) / split;
     const int64_t tiles = ((int64_t)a.M + d.bm - 1) / d.bm * ((a.Cout + d.bn - 1) / d.bn);
     return (slices + per - 1) / per == split && tiles * 4 <= (int64_t)kCounterBytes && (int64_t)a.M * a.Cout * 4 < (1ll << 31);
@@ -918,7 +918,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 if (!conv_uses_dlds(a, l.stem)) l.tile = conv_tile_staged(l.tile);   // the register-staged kernel's shapes
                 if (conv_bk(a, l.stem, l.tile) != conv_tile_dim(l.tile).bk) l.tile = conv_tile_k64(l.tile);  // Cin is no multiple of the tile's slice
                 if (l.stem) l.tile = conv_tile_one_group(l.tile);   // the first convolution's mode has no wave groups
-                const int bk = conv_bk(a, l.stem, l.tile), ktiles = (a.K + bk - 1) / bk;
+                const int ktiles = conv_slices(a, l.stem, l.tile);
                 a.split_k = std::max(1, std::min(a.split_k, ktiles));
                 {
                     const TileDim tdc = conv_tile_dim(l.tile);

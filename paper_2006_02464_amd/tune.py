@@ -50,7 +50,7 @@ def features(M, N, K, kh, kw, stride, cin, res, cls, tile, split):
     if cls == STAGED:
         bk = 32
     elif cls == STEM:
-        bk, K, cin = 64, 256, 4   # the packed filter
+        bk, K, cin = 64, (kh + 1) // 2 * 64, 4   # a slice is two filter rows of the packed filter
     elif cin % bk and not (gemm_form(kh, kw, stride, cin) and cin > 2 * bk and tile in (10, 11)):
         bk = 64
     slices = -(-K // bk)

@@ -120,6 +120,20 @@ def test_plan_override_reaches_every_tile(ctx):
     ctx.set_plan_override(-1, 0)
 
 
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 7, 8])
+@pytest.mark.parametrize("split", [1, 2, 3, 4, 8])
+def test_a_first_convolution_is_split_over_its_real_filter_rows(ctx, k, split):
+    """A K slice of it is two filter rows; those that pad the packed filter to eight rows are not walked."""
+    ctx.set_plan_override(3, split)
+    m = ctx.model_define(_ops((0, 3, 256, k, k, 2, k // 2, 1, -1, -1, 0, 0), (2, 256, 256, 0, 0, 1, 0, 0, -1, 0, 0, 0),
+                              (3, 256, 10, 1, 1, 1, 0, 0, -1, 1, 0, 0), (4, 10, 10, 0, 0, 1, 0, 0, -1, 2, 0, 0)),
+                         3, 64, 64, batch_sizes=(1,))
+    stem = next(l for l in ctx.plan(m, 1) if l["kind"] == 1)
+    slices = (k + 1) // 2
+    per = -(-slices // min(split, slices))
+    assert stem["split_k"] == stem["grid_y"] == -(-slices // per)   # no workgroup without a slice
+
+
 def _ops(*rows):
     return [tuple(r) for r in rows]
 
