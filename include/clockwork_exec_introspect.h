@@ -27,7 +27,7 @@ typedef struct {
     int32_t proj_op;       /* -1, or the projection-shortcut op this launch computes as well */
     int32_t pair_op;       /* -1, or a second, independent convolution over the same input computed by this launch */
     int32_t kind;          /* internal kernel family id */
-    int32_t grid_x, grid_y, grid_z, block;
+    int32_t grid_x, grid_y, grid_z, block;   /* without the workgroups that read ahead: cw_plan_launch_ahead */
     int32_t tile_m, tile_n, tile_k, split_k; /* conv: pixels x channels per workgroup, K slice */
     int32_t conv_tile;     /* conv: the tile variant in cw_set_plan_override's numbering; -1 for a fused pair and for other kinds */
     int32_t wave_groups;   /* conv: groups of waves that split every K slice (1 = none) */
@@ -36,16 +36,22 @@ typedef struct {
     int32_t panels;        /* conv: channel panels of the tile numbering (1 = row by row; see cw_set_panels); a pair
                               launch: of op_index's convolution in the low byte, of pair_op's in the next */
     int64_t gemm_m, gemm_n, gemm_k; /* 0 for non-GEMM launches */
-    int64_t bytes;         /* algorithmic HBM bytes: inputs + weights + outputs, once each */
+    int64_t bytes;         /* algorithmic HBM bytes: inputs + weights + outputs, once each (weights with the launch that uses them) */
     int64_t flops;         /* 2 * MACs */
     char name[48];
 } cw_launch_info;
 int32_t cw_plan_launch_info(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index,
                             cw_launch_info *out);
+/* A convolution launch may carry further workgroups along x that read the weights of one of the next four
+ * launches into the last-level cache.  *workgroups receives their number and *bytes what they read (one word of
+ * every 128 bytes, hence as many lines), 0 and 0 for a launch that reads nothing ahead. */
+int32_t cw_plan_launch_ahead(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index,
+                             int32_t *workgroups, int64_t *bytes);
 /* Runs EXEC like cw_exec but times every launch of the plan with its own pair of
  * events, issuing it `inner` (>= 1) times back to back between them (a launch is
  * idempotent); launch_us [host] receives cw_plan_num_launches() averages, each
- * including the dispatch cost of one launch.  Synchronous. */
+ * including the dispatch cost of one launch, and for a launch that reads ahead (above) the traffic it takes
+ * off a later one.  Synchronous. */
 int32_t cw_exec_timed_launches(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t slot,
                                int32_t inner, float *launch_us, void *stream);
 /* Copies the output of op `op_index` from the slot's last EXEC to host_out [host]

@@ -1306,6 +1306,18 @@ int32_t cw_plan_launch_info(cw_ctx *c, int32_t model_id, int32_t batch, int32_t 
     return CW_OK;
 }
 
+int32_t cw_plan_launch_ahead(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index, int32_t *workgroups, int64_t *bytes) {
+    ModelRt *m = get_model(c, model_id);
+    if (!m || !workgroups || !bytes) return set_err(c, CW_ERR_INVALID, "unknown model id or null pointer");
+    Plan *p = get_plan(m, batch);
+    if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
+    if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
+    const int32_t lines = p->launches[index].ahead_bytes / 128;
+    *workgroups = conv_prefetch_wgs(lines);
+    *bytes = (int64_t)lines * 128;
+    return CW_OK;
+}
+
 int32_t cw_debug_read_op(cw_ctx *c, int32_t model_id, int32_t batch, int32_t op_index, float *host_out, size_t cap) {
     if (!c || !host_out) return CW_ERR_INVALID;
     if (c->device < 0) return set_err(c, CW_ERR_INVALID, "planning-only context has no device");

@@ -120,6 +120,27 @@ def test_plan_override_reaches_every_tile(ctx):
     ctx.set_plan_override(-1, 0)
 
 
+def test_weights_read_ahead_are_reported(ctx):
+    m = ctx.model_define_resnet(50, 224, 224)
+    ops = ctx.model_get_ops(m)
+    for batch in (1, 16):
+        plan = ctx.plan(m, batch)
+        ahead = [ctx.plan_launch_ahead(m, batch, i) for i in range(len(plan))]
+        assert sum(b for _, b in ahead) > (10 << 20)
+        for i, (wgs, nbytes) in enumerate(ahead):
+            l = plan[i]
+            if l["kind"] == 1:
+                tiles = -(-l["gemm_m"] // l["tile_m"]) * -(-l["gemm_n"] // l["tile_n"])
+                assert l["pair_op"] >= 0 or l["fused_op"] >= 0 or l["grid_x"] == tiles   # the tiles alone
+            assert wgs == min(64, -(-nbytes // (128 * 256)))
+            if nbytes:
+                assert l["kind"] == 1 and l["op_index"] > 0 and l["pair_op"] < 0 and l["fused_op"] < 0 and l["split_k"] == 1 and tiles <= 512
+                behind = [ops[nl[f]] for nl in plan[i + 1:i + 5] for f in ("op_index", "fused_op", "proj_op", "pair_op", "next_op") if nl[f] >= 0]
+                assert nbytes in [2 * o[1] * o[2] * o[3] * o[4] for o in behind]   # a whole weight tensor of one of the next four
+    with pytest.raises(cw.CwError):
+        ctx.plan_launch_ahead(m, 1, 999)
+
+
 @pytest.mark.parametrize("k", [1, 2, 3, 5, 7, 8])
 @pytest.mark.parametrize("split", [1, 2, 3, 4, 8])
 def test_a_first_convolution_is_split_over_its_real_filter_rows(ctx, k, split):
