@@ -4,8 +4,8 @@
  *
  * None of these calls is part of the paper's action model; they exist for the parity tests
  * (every kernel instantiation must be reachable and every layer comparable with the CPU
- * oracle), for the tuner that writes the plan table offline, and for the per-launch roofline
- * report.  A worker serving requests needs only clockwork_exec.h.  Same conventions as there:
+ * oracle), for the tool that fits the plan compiler's cost model offline, and for the per-launch
+ * roofline report.  A worker serving requests needs only clockwork_exec.h.  Same conventions as there:
  * int32_t status, [host] pointers owned by the caller, no exception crosses the boundary.
  * What they expose is the paper's "kernels per batch size" and "memory metadata" of a model
  * (section 5.1): the fixed launch list of a (model, batch) and where its tensors live.
@@ -68,15 +68,18 @@ int32_t cw_set_debug_keep(cw_ctx *ctx, int32_t keep);
  * issue every kernel as its own launch instead; on != 0 restores the default.  Takes effect
  * for the next EXEC; graphs are recorded by LOADs issued while the setting is on. */
 int32_t cw_set_use_graphs(cw_ctx *ctx, int32_t on);
-/* Test hook: models defined afterwards use conv tile variant `conv_tile` (0..28 =
+/* Test hook: models defined afterwards use conv tile variant `conv_tile` (0..35 =
  * 128x128, 128x64, 64x64, 64x32, 32x64, 32x32, 128x64 on 2 waves, 64x128 on 2 waves,
  * 256x64, 128x128 on 8 waves, then 128x64, 64x64, 64x32, 32x64, 32x32 with K slices of 128
  * instead of 64 (used where cin % 128 == 0, else their 64 form), then tiles whose waves come in
  * 2, 4 or 8 groups that share every K slice (128 wide: 128x64 in 2, 64x64 in 2 and 4, 64x32,
  * 32x64, 32x32 in 4, then 32x32 in 8; 64 wide: 128x64 in 2, 64x64 in 2, 32x32 in 4; the first
  * convolution takes a grouped tile's one-group form); then the tiles for large GEMMs: 256x128,
- * 128x256 and 256x256 on 8 waves, 256x128 on 4 waves (a convolution with cin % 64 != 0 takes the
- * largest basic shape below them);
+ * 128x256 and 256x256 on 8 waves, 256x128 on 4 waves; then K slices of 256 (used where cin % 256
+ * == 0, else 64): 32x32 in 4 and 8 groups, 64x32 in 4 and 8, 32x64 in 4 and 8, 64x64 in 4.  A
+ * convolution with cin % 64 != 0 takes the largest basic shape below its tile (1x1 stride 1: the
+ * nearest of 128x128 on 4 or 8 waves, 128x64, 64x64, 64x32, 32x64, 32x32, and of 128x64 and 64x64
+ * with K slices of 128);
  * pixels x channels per workgroup; -1 = the plan compiler's own choice)
  * and split-K factor `split_k` (0 = own choice) for every convolution, so parity
  * tests can reach every kernel instantiation.  Still fixed at plan time. */
@@ -162,12 +165,11 @@ int32_t cw_set_resident(cw_ctx *ctx, int32_t on);
  * direct kernel.  Applies to models defined afterwards. */
 int32_t cw_set_winograd(cw_ctx *ctx, int32_t on);
 /* Plan table (section 5.1: the kernels of a model are fixed per batch size ahead of time).
- * The plan compiler takes the tile variant and split-K factor of a convolution from a table
- * keyed by its GEMM shape; the library has one built in for the ResNets.  This call installs
- * `n_rows` rows that take precedence over it for models defined afterwards (n_rows == 0
- * removes them).  rows [host]: n_rows x 7 int32 = {M = batch*Ho*Wo, N = cout, K = kh*kw*cin,
- * kh, stride, conv_tile (0..28 as above), split_k >= 1}; copied.  Shapes in neither table get
- * a heuristic choice.  Plans stay a pure function of (model, batch, tables). */
+ * The plan compiler takes the tile variant and split-K factor of a convolution that its cost model
+ * predicts to be the fastest.  This call installs `n_rows` rows, keyed by GEMM shape, that take
+ * precedence over the model for models defined afterwards (n_rows == 0 removes them).  rows [host]:
+ * n_rows x 7 int32 = {M = batch*Ho*Wo, N = cout, K = kh*kw*cin, kh, stride, conv_tile (0..35 as
+ * above), split_k >= 1}; copied.  Plans stay a pure function of (model, batch, rows). */
 int32_t cw_set_plan_table(cw_ctx *ctx, const int32_t *rows, int32_t n_rows);
 
 

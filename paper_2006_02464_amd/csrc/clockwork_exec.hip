@@ -1114,7 +1114,7 @@ int32_t cw_exec_static(cw_ctx *c, int32_t model_id, int32_t batch, const float *
     b.logits = reinterpret_cast<char *>(dev_logits);
     b.probs = reinterpret_cast<char *>(dev_probs);
     // The arena keeps what the last call left: the arrival counters at its start must be zero.  The cast of the input,
-    // which every plan begins with, clears those that the launches behind it use (a launch of its own took 3 us).
+    // which every plan begins with, clears those that the launches behind it use (a launch of its own took 1.2-2 us).
     b.clear_counters = p->n_counters;
     for (const Launch &l : p->launches) {
         const hipError_t e = issue(c, m, b, l, st);

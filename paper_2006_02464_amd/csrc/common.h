@@ -123,12 +123,12 @@ __host__ __device__ inline int conv_ldx(const ConvArgs &a) { return a.ld & 0xfff
 __host__ __device__ inline int conv_ldy(const ConvArgs &a) { return (int)((unsigned)a.ld >> 16); }
 inline void conv_set_pad(ConvArgs &a, int pad_h, int pad_w) { a.pad = pad_h | (pad_w << 16); }
 inline void conv_set_ld(ConvArgs &a, int ldx, int ldy) { a.ld = ldx | (ldy << 16); }
-// Reading ahead.  A launch with few tiles leaves CUs idle, and the weights of the launches behind it may have to come
-// from HBM (several resident models outgrow the 256 MB last-level cache): workgroups behind its tiles read one word
-// of every 128 bytes of them, which brings them into that cache.  Measured, 3x3 of 256 channels at 14x14, batch 16, whose weights
-// come from HBM: 12.0 -> 10.1 us a launch; with weights already in the cache 10.0 either way.
+// Reading ahead.  The weights of the next launches may have to come from HBM (several resident models outgrow the
+// 256 MB last-level cache): workgroups behind a launch's tiles read one word of every 128 bytes of them, which brings them
+// into that cache.  Measured, 3x3 of 256 channels at 14x14, batch 16, whose weights come from HBM: 12.0 -> 10.1 us a
+// launch; with weights already in the cache 10.0 either way, and a whole ResNet-50 EXEC at batch 1 is 0.6 us longer for it.
 constexpr int kPrefetchMinBytes = 256 * 1024;   // of a smaller tensor every workgroup that uses it waits for a miss or two at most
-constexpr int kPrefetchMaxTiles = 512;   // more tiles than that: the workgroups would only come behind them
+constexpr int kPrefetchMaxTiles = 512;   // two a CU, most of which run at once; behind more, the reads would come late
 constexpr int kPrefetchLines = 256;      // per workgroup: a CU has only so many misses in flight (one workgroup per 4096 made ResNet-152 4 % slower)
 constexpr int kPrefetchPerThread = 4;    // reads a thread has in flight
 inline int conv_prefetch_wgs(int lines) { return lines < 64 * kPrefetchLines ? (lines + kPrefetchLines - 1) / kPrefetchLines : 64; }
@@ -254,9 +254,9 @@ struct SoftmaxArgs {
 // Tile shapes the conv kernel is instantiated for (fixed at plan time per layer).
 // (pixels x channels per workgroup; "wN" = N waves when not 4, each wave then owning 64x64;
 // "k128" = K slices of 128 instead of 64, for Cin % 128 == 0; "gN" = N groups of waves that split
-// every K slice between them and add up at the end; the last four are for large GEMMs: 8 waves of
-// 64x64 or 64x128 each, and 256x128 on 4 waves of 128x64; "k256": K slices of 256 for long K and
-// few tiles, Cin % 256 == 0)
+// every K slice between them and add up at the end; the four from 256x128w8 on are for large GEMMs:
+// 8 waves of 64x64 or 64x128 each, and 256x128 on 4 waves of 128x64; "k256": K slices of 256 for
+// long K and few tiles, Cin % 256 == 0)
 enum ConvTile : int32_t {
     T128x128 = 0, T128x64, T64x64, T64x32, T32x64, T32x32, T128x64w2, T64x128w2, T256x64, T128x128w8,
     T128x64k128, T64x64k128, T64x32k128, T32x64k128, T32x32k128,
@@ -274,7 +274,7 @@ ConvTile conv_tile_k64(ConvTile t);
 // The same tile with one group of waves (split-K needs that).
 ConvTile conv_tile_one_group(ConvTile t);
 // The largest tile of the register-staged kernel that is no larger than t (that kernel has the ten
-// basic shapes only; it serves Cin % 64 != 0 and first convolutions outside the stem form).
+// basic shapes only; it serves what conv_uses_dlds does not name).
 ConvTile conv_tile_staged(ConvTile t);
 // The tile of the 1x1 form that ends in part of a K slice (which has some of the one-group shapes) nearest to t.
 ConvTile conv_tile_tail(ConvTile t);
@@ -283,10 +283,11 @@ bool conv_uses_dlds(const ConvArgs &a, bool stem);
 
 // Launchers (kernels_*.hip).  All only enqueue; they return the launch's error state.
 hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hipStream_t s);
-// The direct-to-LDS kernel for Cin % 64 == 0 and for a first convolution in its stem form
-// (called by launch_conv after its checks); mode = the kernel's addressing mode.
+// The direct-to-LDS kernel for Cin % 64 == 0, for 1x1 stride-1 convolutions over any Cin % 32 == 0 and for a first
+// convolution in its stem form (called by launch_conv after its checks); mode = the kernel's addressing mode.
 hipError_t launch_conv_dlds(DType dt, ConvTile tile, int bk, int mode, const ConvArgs &a, hipStream_t s);
-// Its K slices of 256 (kernels_conv_k256.hip; called by launch_conv_dlds).
+// Its 1x1 form whose K ends in part of a slice (kernels_conv_tail.hip) and its K slices of 256 (kernels_conv_k256.hip;
+// both called by launch_conv_dlds).
 hipError_t launch_conv_dlds_tail(DType dt, ConvTile tile, bool splitk, const ConvArgs &a, hipStream_t s);
 hipError_t launch_conv_dlds_k256(DType dt, ConvTile tile, int mode, bool splitk, const ConvArgs &a, hipStream_t s);
 // A convolution (Cin % 64 == 0, Cout 64 or 128) and the 1x1 convolution that consumes it, in one
@@ -354,8 +355,8 @@ hipError_t launch_nhwc_to_nchw_f32(DType dt, const void *src, float *dst, int B,
                                    int W, int ld, hipStream_t s);
 hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s);
 
-// K-slice width the conv kernel uses for a shape under a tile: the tile's (128 or 64) when Cin
-// is a multiple of it, else 64, else 32 (the stem and Cin % 64 != 0).
+// K-slice width the conv kernel uses for a shape under a tile: the tile's (256, 128 or 64) when Cin is a multiple of it or,
+// 128 in a 1x1 stride-1 convolution, more than twice as large; else 64; 32 on the register-staged kernel.
 int conv_bk(const ConvArgs &a, bool stem, ConvTile tile);
 // How many of them it walks.  The direct-to-LDS kernel ends a first convolution's walk at the last pair of real filter rows.
 int conv_slices(const ConvArgs &a, bool stem, ConvTile tile);

@@ -1,10 +1,11 @@
 // Implicit-GEMM convolution on gfx950 MFMA (v_mfma_f32_32x32x16_{f16,bf16}), fp32 accumulate:
 // the register-staged kernel, the tile table and the launch entry point.
 //
-// launch_conv() sends every convolution with Cin % 64 == 0, and a first convolution with an even
-// stride, to the direct-to-LDS kernel (kernels_conv_dlds.hip).  The kernel in this file serves
-// what is left: Cin % 64 != 0 (K slices of 32) and a first convolution with an odd stride.  What
-// follows describes the layout and conventions both kernels share, and this kernel's pipeline.
+// launch_conv() sends every convolution with Cin % 64 == 0, every 1x1 stride-1 convolution, and a
+// first convolution with an even stride to the direct-to-LDS kernel (kernels_conv_dlds.hip).  The
+// kernel in this file serves what is left: Cin % 64 != 0 with more taps or a stride, and a first
+// convolution with an odd stride.  What follows describes the layout and conventions both kernels
+// share, and this kernel's pipeline.
 //
 // GEMM view: M = B*Ho*Wo output pixels (NHWC, so a pixel's Cout values are contiguous),
 // N = Cout, K = kh*kwp*Cin ordered (r, s, c), so that for one filter tap the K slice is the
@@ -458,8 +459,7 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
     if ((long long)a.B * a.H * a.W * conv_ldx(a) * 2 + (long long)(conv_pad_h(a) * a.W + conv_pad_w(a)) * conv_ldx(a) * 2 >= (1ll << 31)) return hipErrorInvalidValue;
     if ((long long)a.M * (a.partial ? a.Cout * 4ll : conv_ldy(a) * 2ll) >= (1ll << 31) || (long long)a.M * conv_ldy(a) * 2 >= (1ll << 31) || (long long)a.Cout * a.K * 2 >= (1ll << 31))
         return hipErrorInvalidValue;
-    // K slices of 64 go global -> LDS directly (kernels_conv_dlds.hip); the stem and Cin % 64 != 0
-    // keep the register-staged kernel of this file.
+    // What the direct-to-LDS kernel does not take stays on the register-staged kernel of this file.
     if (stem && stem_is_dlds(a)) return launch_conv_dlds(dt, tile, bk, MODE_STEM, a, s);
     if (!stem && conv_uses_dlds(a, false)) return launch_conv_dlds(dt, tile, bk, !gemm ? MODE_CONV : a.K % bk ? MODE_TAIL : MODE_GEMM, a, s);
     if (a.split_k > 1) return dt == DT_F16 ? launch_conv_dt<f16, true>(tile, stem, a, s) : launch_conv_dt<bf16, true>(tile, stem, a, s);

@@ -1,7 +1,7 @@
 // The direct-to-LDS convolution, 1x1 stride-1 form, for input channels that are no multiple of the K slice (Cin % 32 == 0): the
 // last slice's missing chunks are fetched out of range, as zeros.  The register-staged kernel, which took these
 // shapes with K slices of 32, needs 1.4-2.2 us more for 160-480 channels than its neighbours of whole slices here
-// (DenseNet batch 6: 237.7 -> 227.6 us).
+// (DenseNet batch 6: 238 -> 228 us).  The plan never splits K here; a forced or installed split does.
 #include "conv_dlds_launch.h"
 
 namespace cw {

@@ -299,9 +299,13 @@ static int pick_res_variant(int64_t M, int64_t N, int64_t K, int32_t cin) {
 
 // ---------------------------------------------------------------- tile choice
 // Every tile shape's launch time as a linear function of the quantities below, fitted offline to measured
-// launches (tune.py); the plan takes the tile and split-K with the least predicted time.  Over 645 measured GEMM
-// shapes (six networks, 35 image and batch sizes) that costs 1.3 % over the fastest tile of each; a table of
-// measured shapes and a heuristic beside it, as before, cost 2-7 % on shapes of the table and 30-40 % on others.
+// launches (tune.py); the plan takes the tile and split-K with the least predicted time.  Over 645 GEMM shapes (five
+// networks, 38 combinations with image and batch sizes) timed on the kernels as they are, that costs 1.3 % over the
+// fastest tile of each (1x1 ending in part of a slice, on the same coefficients: 1.8 %); a table of measured shapes
+// with a heuristic beside it, as before, costs 4 % on the table's shapes and 22 % on the others.  What the fit cannot
+// see: a pair of events times nothing below 4.2 us, where more than half of a batch-1 plan's launches are, and what a
+// launch does to its neighbours.  Exchanged inside whole EXECs, single choices are worth up to 1 % more (ResNet-50
+// batch 1: the stage-3 expands on 32x64 instead of 32x32k256g4 1.6 us).
 enum { COST_PLAIN, COST_STAGED, COST_STEM };   // the main kernel; the register-staged one; the first convolution's form
 constexpr int kCostFeatures = 11;
 struct ConvCost {

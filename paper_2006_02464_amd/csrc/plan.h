@@ -96,7 +96,7 @@ struct Plan {
     cw_profile profile{};
 };
 
-// Tile and split-K of one convolution GEMM shape (a row of the plan table).
+// Tile and split-K of one convolution GEMM shape (a row of the table that cw_set_plan_table installs).
 struct TunedShape {
     int32_t M, N, K, kh, stride, tile, split_k;
 };
@@ -117,7 +117,7 @@ struct PlanOverride {
     bool fuse_pool = true;   // a 3x3 max pool over 64 channels and the 1x1 convolution 64 -> 64 or 128 that reads it as one launch
     bool fuse_dw = true;     // a depthwise 3x3 convolution and the 1x1 convolution that reads it as one launch (small channel counts)
     bool panels = false;   // tile numbering in channel panels where that moves fewer bytes into the XCDs' L2s
-    std::vector<TunedShape> table;  // rows that take precedence over the built-in table
+    std::vector<TunedShape> table;  // rows that take precedence over the cost model
 };
 
 struct Model {

@@ -82,8 +82,8 @@ def test_mobilenet_224_batch16_and_small_batches(worker):
 
 @pytest.mark.parametrize("name", ["resnet18", "dense", "inception"])
 def test_models_with_tuned_shapes_at_224(worker, name):
-    """ResNet-18 and the DenseNet- and Inception-style lists at 224x224, where their convolution shapes
-    have rows of their own in the plan table: batch 16, re-cut at batch 4 and 1, logits against the oracle."""
+    """ResNet-18 and the DenseNet- and Inception-style lists at 224x224, on the tiles the plan chooses for their
+    convolution shapes: batch 16, re-cut at batch 4 and 1, logits against the oracle."""
     make = {"resnet18": lambda: T.resnet(18), "dense": T.dense_net, "inception": T.inception_net}[name]
     case = Case(make(), 224, seed=0, dist="normal")
     ctx = worker.ctx

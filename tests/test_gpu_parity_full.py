@@ -174,7 +174,7 @@ def _report(key, value):
 
 @pytest.mark.parametrize("batch", [16, 8])
 def test_resnet50_224_every_launch_teacher_forced(worker, batch):
-    """The plans bench.py times (fusion, pair launches and the built-in table on), with debug
+    """The plans bench.py times (fusion, pair launches and the cost model's tiles), with debug
     retention: 7 fused launches at batch 16, 3 at batch 8, every stored tensor against the oracle."""
     case = Case(T.resnet(50), 224, seed=0, dist="normal")
     ctx = worker.ctx
