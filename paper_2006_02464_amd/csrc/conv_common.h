@@ -223,6 +223,122 @@ static __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[TM][TN
     else epilogue_store_act<T, TM, TN, false>(acc, e, a, p);
 }
 
+// ---- epilogue of a tile whose K was split over groups of waves ---------------------------------
+// The groups' accumulators meet in LDS in units of four registers: a unit is four consecutive channels of the
+// lane's pixel, 64 lanes = 1 KiB, so every access is 16 bytes a lane and runs of lanes are consecutive.  Every wave
+// writes all its units, and after one barrier group g adds up units g*UPG .. g*UPG+UPG-1 of the tile (over the groups
+// in group order: the sum is the one a single finishing group would make) and carries them through bias, residual,
+// activation and store.  With one finishing group its waves read KG-1 times 16 single registers and convert and
+// store 16 values, 0.64 us from the last matrix instruction to the last store of a 32x32 tile in four groups, most of a 1x1
+// launch's own time.
+template <int TM, int TN, int KG>
+struct GroupUnits {
+    static constexpr int UNITS = TM * TN * 4;                  // per wave
+    static constexpr int UPG = (UNITS + KG - 1) / KG;          // finished by each group; groups beyond UNITS / UPG have none
+    static constexpr int W = UPG % 2 == 0 ? 2 : 1;             // units per load and store: two make eight consecutive channels
+};
+
+// Pixel and first channel of unit u (see EpiPos for the accumulator layout).
+template <int TN>
+static __device__ __forceinline__ void unit_pos(const EpiPos &p, int u, unsigned *m, unsigned *n) {
+    const int t = u >> 2, r = u & 3, i = t / TN, j = t - i * TN;
+    *m = p.m0 + p.wm0 + i * 32 + p.lrow;
+    *n = p.n0 + p.wn0 + j * 32 + 16 * (r >> 1) + 8 * p.lhalf + 4 * (r & 1);
+}
+
+template <int TM, int TN, int KG>
+struct GroupOperands {
+    typedef GroupUnits<TM, TN, KG> G;
+    u32x4 bv[G::UPG];
+    u32x2 rv[G::UPG];
+};
+
+template <int TM, int TN, int KG>
+static __device__ __forceinline__ void group_epilogue_load(GroupOperands<TM, TN, KG> &e, const ConvArgs &a, const EpiPos &p, int kg) {
+    typedef GroupUnits<TM, TN, KG> G;
+    const bool has_bias = a.bias != nullptr, has_res = a.res != nullptr;
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(has_res ? a.res : a.y, (unsigned)a.M * a.Cout * 2u);
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(has_bias ? static_cast<const void *>(a.bias) : a.y, (unsigned)a.Cout * 4u);
+#pragma unroll
+    for (int k = 0; k < G::UPG; k += G::W) {
+        unsigned m, n;
+        unit_pos<TN>(p, kg * G::UPG + k, &m, &n);
+        const bool n_ok = kg * G::UPG + k < G::UNITS && n < (unsigned)a.Cout;   // Cout % 32 == 0: all of a unit or none
+        const unsigned ob = has_bias && n_ok ? n * 4u : kOob;
+        const unsigned orr = has_res && n_ok && m < (unsigned)a.M ? (m * a.Cout + n) * 2u : kOob;
+        if constexpr (G::W == 2) {
+            e.bv[k] = __builtin_amdgcn_raw_buffer_load_b128(rb, ob, 0, 0);
+            e.bv[k + 1] = __builtin_amdgcn_raw_buffer_load_b128(rb, has_bias ? ob + 16u : kOob, 0, 0);
+            const u32x4 r = __builtin_amdgcn_raw_buffer_load_b128(rr, orr, 0, 0);
+            e.rv[k] = u32x2{r.x, r.y};
+            e.rv[k + 1] = u32x2{r.z, r.w};
+        } else {
+            e.bv[k] = __builtin_amdgcn_raw_buffer_load_b128(rb, ob, 0, 0);
+            e.rv[k] = __builtin_amdgcn_raw_buffer_load_b64(rr, orr, 0, 0);
+        }
+    }
+}
+
+// xch: KG * WAVES * UNITS KiB of LDS that no wave reads any more; wq = the wave's place in its group.
+template <int TM, int TN, int KG, int WAVES>
+static __device__ __forceinline__ void group_exchange_write(const f32x16 (&acc)[TM][TN], float *xch, int kg, int wq, int lane) {
+    typedef GroupUnits<TM, TN, KG> G;
+    float *dst = xch + (kg * WAVES + wq) * (G::UNITS * 256) + lane * 4;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<float4 *>(dst + ((i * TN + j) * 4 + r) * 256) =
+                    make_float4(acc[i][j][4 * r], acc[i][j][4 * r + 1], acc[i][j][4 * r + 2], acc[i][j][4 * r + 3]);
+}
+
+template <typename T, int TM, int TN, int KG, int WAVES, bool HSWISH>
+static __device__ __forceinline__ void group_epilogue_store_act(const float *xch, const GroupOperands<TM, TN, KG> &e, const ConvArgs &a, const EpiPos &p,
+                                                                int kg, int wq, int lane) {
+    typedef GroupUnits<TM, TN, KG> G;
+    const unsigned ldy = (unsigned)conv_ldy(a);
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(a.y, (((unsigned)a.M - 1u) * ldy + (unsigned)a.Cout) * 2u);
+    float4 v[G::UPG][KG];
+#pragma unroll
+    for (int k = 0; k < G::UPG; ++k)
+#pragma unroll
+        for (int g = 0; g < KG; ++g)
+            v[k][g] = *reinterpret_cast<const float4 *>(xch + ((g * WAVES + wq) * G::UNITS + kg * G::UPG + k) * 256 + lane * 4);
+#pragma unroll
+    for (int k = 0; k < G::UPG; k += G::W) {
+        unsigned m, n;
+        unit_pos<TN>(p, kg * G::UPG + k, &m, &n);
+        T out[4 * G::W];
+#pragma unroll
+        for (int w = 0; w < G::W; ++w) {
+            const float *b = reinterpret_cast<const float *>(&e.bv[k + w]);
+            const T *r = reinterpret_cast<const T *>(&e.rv[k + w]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float s = reinterpret_cast<const float *>(&v[k + w][0])[c];
+#pragma unroll
+                for (int g = 1; g < KG; ++g) s += reinterpret_cast<const float *>(&v[k + w][g])[c];
+                s = s + b[c] + (float)r[c];
+                if (HSWISH) out[4 * w + c] = (T)(s * fminf(fmaxf(s + 3.f, 0.f), 6.f) * (1.f / 6.f));
+                else out[4 * w + c] = (T)(a.relu ? fmaxf(s, 0.f) : s);
+            }
+        }
+        const unsigned o = m < (unsigned)a.M && n < (unsigned)a.Cout ? (m * ldy + n) * 2u : kOob;
+        if constexpr (G::W == 2) __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(out), ry, o, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2 *>(out), ry, o, 0, 0);
+    }
+}
+
+template <typename T, int TM, int TN, int KG, int WAVES>
+static __device__ __forceinline__ void group_epilogue_store(const float *xch, const GroupOperands<TM, TN, KG> &e, const ConvArgs &a, const EpiPos &p, int kg,
+                                                            int wq, int lane) {
+    if (kg * GroupUnits<TM, TN, KG>::UPG >= GroupUnits<TM, TN, KG>::UNITS) return;   // eight groups, four units
+    if (a.relu == ACT_HSWISH) group_epilogue_store_act<T, TM, TN, KG, WAVES, true>(xch, e, a, p, kg, wq, lane);
+    else group_epilogue_store_act<T, TM, TN, KG, WAVES, false>(xch, e, a, p, kg, wq, lane);
+}
+
 // Workgroups go to the 8 XCDs round-robin; give each XCD a contiguous run of tiles so that
 // tiles sharing pixels (same tile_m) meet in one XCD's L2.
 static __device__ __forceinline__ int xcd_tile_id(int bid, int nb) {

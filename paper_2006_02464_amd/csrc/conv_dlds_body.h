@@ -50,6 +50,9 @@ static __device__ __forceinline__ void wait_lds_loads_and_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
 }
 
+// Waits for this thread's LDS accesses alone, then the workgroup barrier.
+static __device__ __forceinline__ void wait_lds_and_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
+
 // Raw buffer descriptor (stride 0) as four scalars, for use as an asm operand.
 static __device__ __forceinline__ u32x4 make_desc(const void *p, unsigned bytes) {
     const unsigned long long v = reinterpret_cast<unsigned long long>(p);
@@ -72,7 +75,8 @@ constexpr unsigned fused_lds_bytes(int bm, int bn, int kg) {
 constexpr int kFusedMaxCout2 = 1024;
 
 // KG > 1: KG groups of WARPS_M x WARPS_N waves share the tile; group g takes the 16-k steps
-// g, g+KG, ... of every slice and the groups' accumulators are added through LDS at the end.  For
+// g, g+KG, ... of every slice and the groups' accumulators are added through LDS at the end, each
+// group finishing its share of the tile (GroupUnits).  For
 // small tiles with a long K this shortens the per-slice MFMA chain of a wave (and puts several
 // waves on each SIMD) without the global exchange of split-K; with split-K on top (tiny M*N, very
 // long K) the first group carries the workgroup's sum into that exchange and the others end.
@@ -345,7 +349,15 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     };
 
     const EpiPos pos{m0, n0, wm0, wn0, lrow, lhalf};
+    // Four and eight groups finish the tile together.  Two (128x64, 64x64) keep one finishing group, which moves half as
+    // much through LDS.
+    constexpr bool SHARED = KG >= 4 && !FUSED && !SPLITK;
     EpiOperands<TM, TN> eo;
+    GroupOperands<TM, TN, KG> go;
+    auto load_operands = [&]() {
+        if constexpr (SHARED) group_epilogue_load<TM, TN, KG>(go, a, pos, kg);
+        else if (!SPLITK && !FUSED && kg == 0) epilogue_load<TM, TN>(eo, a, pos);
+    };
 
     // Prologue: the first min(NS-1, nsteps) slices into stages 0, 1, ...
     const int ahead = min(NS - 1, nsteps);
@@ -373,7 +385,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         constexpr int u = decltype(behind)::value;  // slices still in flight behind this one
         if (u < kt1 - kt) {                         // uniform
             wait_loads_and_barrier<u * LOADS>();
-            if (!SPLITK && !FUSED && u == 0 && kg == 0) epilogue_load<TM, TN>(eo, a, pos);
+            if (u == 0) load_operands();
             compute(cur, std::false_type{});
             cur = cur + 1 == NS ? 0 : cur + 1;
             ++kt;
@@ -383,7 +395,17 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     if constexpr (NS >= 3) tail(std::integral_constant<int, 1>{});
     tail(std::integral_constant<int, 0>{});
 
-    if (!SPLITK && !FUSED && nsteps <= 0 && kg == 0) epilogue_load<TM, TN>(eo, a, pos);
+    if (nsteps <= 0) load_operands();
+    if constexpr (SHARED) {
+        // the ring is free once every wave has passed the first barrier
+        static_assert(KG * BM * BN * 4 <= NS * (int)STAGE_BYTES, "K-group exchange does not fit the ring");
+        float *xch = reinterpret_cast<float *>(cw_dyn_lds);
+        wait_lds_and_barrier();   // no slice is in flight any more; the operands just requested stay so
+        group_exchange_write<TM, TN, KG, WARPS_M * WARPS_N>(acc, xch, kg, wq, lane);
+        wait_lds_and_barrier();
+        group_epilogue_store<T, TM, TN, KG, WARPS_M * WARPS_N>(xch, go, a, pos, kg, wq, lane);
+        return;
+    }
     if constexpr (KG > 1 && !FUSED) {
         // Groups 1.. hand their accumulators to group 0 through LDS (the ring is free once every
         // wave has passed the barrier); group 0 adds them in group order and goes on alone.

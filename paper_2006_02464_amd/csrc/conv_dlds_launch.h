@@ -73,7 +73,7 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
     // at the end needs its own room)
     if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && grid.z == 1) grid.x += conv_prefetch_wgs(a.Cout2);
-    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG - 1) * BM * BN * 4);
+    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG >= 4 && !SPLITK ? KG : KG - 1) * BM * BN * 4);
     kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a);
     return hipGetLastError();
 }

@@ -161,7 +161,7 @@ static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, 
     auto kern = conv_dlds_pair_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, KG>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
     if (attr != hipSuccess) return attr;
-    const size_t used = std::max((size_t)std::min(NS, std::max(a0.ktiles_per_split, a1.ktiles_per_split)) * stage_bytes, (size_t)(KG - 1) * BM * BN * 4);
+    const size_t used = std::max((size_t)std::min(NS, std::max(a0.ktiles_per_split, a1.ktiles_per_split)) * stage_bytes, (size_t)(KG >= 4 ? KG : KG - 1) * BM * BN * 4);
     const unsigned nb0 = ((a0.M + BM - 1) / BM) * ((a0.Cout + BN - 1) / BN), nb1 = ((a1.M + BM - 1) / BM) * ((a1.Cout + BN - 1) / BN);
     if (!conv_panel_ok(a0, BN, nb0) || !conv_panel_ok(a1, BN, nb1)) return hipErrorInvalidValue;
     a0.nb = conv_pack_nb((int)nb0, a0.panel_log2);
