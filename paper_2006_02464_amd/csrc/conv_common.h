@@ -229,8 +229,9 @@ static __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[TM][TN
 // writes all its units, and after one barrier group g adds up units g*UPG .. g*UPG+UPG-1 of the tile (over the groups
 // in group order: the sum is the one a single finishing group would make) and carries them through bias, residual,
 // activation and store.  With one finishing group its waves read KG-1 times 16 single registers and convert and
-// store 16 values, 0.64 us from the last matrix instruction to the last store of a 32x32 tile in four groups, most of a 1x1
-// launch's own time.
+// store 16 values, 0.64 us from the last matrix instruction to the last store of a 32x32 tile in four groups, a quarter
+// of a 1x1 launch at batch 1.  ResNet-50 batch 1 245.4 -> 236.9 us, 193x161 batch 3 263.2 -> 256.6, MobileNet batch 1
+// 126.9 -> 122.6.
 template <int TM, int TN, int KG>
 struct GroupUnits {
     static constexpr int UNITS = TM * TN * 4;                  // per wave

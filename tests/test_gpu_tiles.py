@@ -63,6 +63,13 @@ def test_k256_tiles(worker, name, split_k, dtype):
     assert any(l["split_k"] > 1 for l in wide) == (split_k > 1)
 
 
+@pytest.mark.parametrize("tile", [17, 18, 19, 20, 21, 24])
+@pytest.mark.parametrize("hw,dtype", [(45, "fp16"), (33, "bf16")])
+def test_tiles_whose_wave_groups_finish_together(worker, tile, hw, dtype):
+    """64x64, 64x32, 32x64 and 32x32 in four groups, 32x32 in eight (half of them finish nothing), K slices of 64 and 128."""
+    run(worker, hw, dtype, 3, tile)
+
+
 @pytest.mark.parametrize("tile,split_k", [("64x64", 1), ("64x64", 3), ("64x64k128", 1), ("32x32k128g4", 2), ("32x32k256g4", 1), ("128x128w8", 1)])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 def test_1x1_ending_in_part_of_a_slice(worker, tile, split_k, dtype):
