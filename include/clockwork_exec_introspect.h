@@ -68,7 +68,7 @@ int32_t cw_set_debug_keep(cw_ctx *ctx, int32_t keep);
  * issue every kernel as its own launch instead; on != 0 restores the default.  Takes effect
  * for the next EXEC; graphs are recorded by LOADs issued while the setting is on. */
 int32_t cw_set_use_graphs(cw_ctx *ctx, int32_t on);
-/* Test hook: models defined afterwards use conv tile variant `conv_tile` (0..35 =
+/* Test hook: models defined afterwards use conv tile variant `conv_tile` (0..40 =
  * 128x128, 128x64, 64x64, 64x32, 32x64, 32x32, 128x64 on 2 waves, 64x128 on 2 waves,
  * 256x64, 128x128 on 8 waves, then 128x64, 64x64, 64x32, 32x64, 32x32 with K slices of 128
  * instead of 64 (used where cin % 128 == 0, else their 64 form), then tiles whose waves come in
@@ -76,7 +76,10 @@ int32_t cw_set_use_graphs(cw_ctx *ctx, int32_t on);
  * 32x64, 32x32 in 4, then 32x32 in 8; 64 wide: 128x64 in 2, 64x64 in 2, 32x32 in 4; the first
  * convolution takes a grouped tile's one-group form); then the tiles for large GEMMs: 256x128,
  * 128x256 and 256x256 on 8 waves, 256x128 on 4 waves; then K slices of 256 (used where cin % 256
- * == 0, else 64): 32x32 in 4 and 8 groups, 64x32 in 4 and 8, 32x64 in 4 and 8, 64x64 in 4.  A
+ * == 0, else 64): 32x32 in 4 and 8 groups, 64x32 in 4 and 8, 32x64 in 4 and 8, 64x64 in 4; then
+ * 32x32 tiles in parts on workgroups of their own (grid_z of them a tile), in 4 groups: quarters, halves
+ * of the channels and halves of the pixels with slices of 128, quarters and halves of the channels
+ * with slices of 256 (a convolution that cannot take them runs on 32x32 in 4 groups).  A
  * convolution with cin % 64 != 0 takes the largest basic shape below its tile (1x1 stride 1: the
  * nearest of 128x128 on 4 or 8 waves, 128x64, 64x64, 64x32, 32x64, 32x32, and of 128x64 and 64x64
  * with K slices of 128);
@@ -168,7 +171,7 @@ int32_t cw_set_winograd(cw_ctx *ctx, int32_t on);
  * The plan compiler takes the tile variant and split-K factor of a convolution that its cost model
  * predicts to be the fastest.  This call installs `n_rows` rows, keyed by GEMM shape, that take
  * precedence over the model for models defined afterwards (n_rows == 0 removes them).  rows [host]:
- * n_rows x 7 int32 = {M = batch*Ho*Wo, N = cout, K = kh*kw*cin, kh, stride, conv_tile (0..35 as
+ * n_rows x 7 int32 = {M = batch*Ho*Wo, N = cout, K = kh*kw*cin, kh, stride, conv_tile (0..40 as
  * above), split_k >= 1}; copied.  Plans stay a pure function of (model, batch, rows). */
 int32_t cw_set_plan_table(cw_ctx *ctx, const int32_t *rows, int32_t n_rows);
 

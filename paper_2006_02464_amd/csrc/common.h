@@ -256,19 +256,25 @@ struct SoftmaxArgs {
 // "k128" = K slices of 128 instead of 64, for Cin % 128 == 0; "gN" = N groups of waves that split
 // every K slice between them and add up at the end; the four from 256x128w8 on are for large GEMMs:
 // 8 waves of 64x64 or 64x128 each, and 256x128 on 4 waves of 128x64; "k256": K slices of 256 for
-// long K and few tiles, Cin % 256 == 0)
+// long K and few tiles, Cin % 256 == 0; the last five: a 32x32 tile in parts on workgroups of their own,
+// "q" quarters, "n" halves of its channels, "m" halves of its pixels, on 16x16x32 matrix instructions)
 enum ConvTile : int32_t {
     T128x128 = 0, T128x64, T64x64, T64x32, T32x64, T32x32, T128x64w2, T64x128w2, T256x64, T128x128w8,
     T128x64k128, T64x64k128, T64x32k128, T32x64k128, T32x32k128,
     T128x64k128g2, T64x64k128g2, T64x64k128g4, T64x32k128g4, T32x64k128g4, T32x32k128g4,
     T32x32k128g8, T128x64g2, T64x64g2, T32x32g4,
     T256x128w8, T128x256w8, T256x256w8, T256x128,
-    T32x32k256g4, T32x32k256g8, T64x32k256g4, T64x32k256g8, T32x64k256g4, T32x64k256g8, T64x64k256g4, N_CONV_TILES
+    T32x32k256g4, T32x32k256g8, T64x32k256g4, T64x32k256g8, T32x64k256g4, T32x64k256g8, T64x64k256g4,
+    T32x32k128g4q, T32x32k128g4n, T32x32k128g4m, T32x32k256g4q, T32x32k256g4n, N_CONV_TILES
 };
 struct TileDim {
     int bm, bn, threads, bk, kg;
+    int pm = bm, pn = bn;   // what one workgroup computes of it
+    int parts() const { return (bm / pm) * (bn / pn); }
 };
 TileDim conv_tile_dim(ConvTile t);
+// Split-K arrival counters of an output tile: one, or one per wave where the wave groups finish the tile together.
+inline int conv_counters_per_tile(ConvTile t) { const TileDim d = conv_tile_dim(t); return d.kg >= 4 ? d.parts() * (d.threads / 64) : 1; }
 // The same tile with K slices of 64 (for shapes a k128 tile cannot take).
 ConvTile conv_tile_k64(ConvTile t);
 // The same tile with one group of waves (split-K needs that).
@@ -281,6 +287,9 @@ ConvTile conv_tile_tail(ConvTile t);
 // Whether a convolution runs on the direct-to-LDS kernel (else on the register-staged one).
 bool conv_uses_dlds(const ConvArgs &a, bool stem);
 
+// Tiles in parts (kernels_conv_small.hip): a launch has grid.x * grid.z workgroups, grid.z = parts of a tile.
+inline bool conv_tile_small(ConvTile t) { return t >= T32x32k128g4q && t < N_CONV_TILES; }
+
 // Launchers (kernels_*.hip).  All only enqueue; they return the launch's error state.
 hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hipStream_t s);
 // The direct-to-LDS kernel for Cin % 64 == 0, for 1x1 stride-1 convolutions over any Cin % 32 == 0 and for a first
@@ -288,6 +297,9 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
 hipError_t launch_conv_dlds(DType dt, ConvTile tile, int bk, int mode, const ConvArgs &a, hipStream_t s);
 // Its 1x1 form whose K ends in part of a slice (kernels_conv_tail.hip) and its K slices of 256 (kernels_conv_k256.hip;
 // both called by launch_conv_dlds).
+hipError_t launch_conv_tiles_f16(ConvTile tile, int bk, int mode, const ConvArgs &a, hipStream_t s);    // its tiles by storage type
+hipError_t launch_conv_tiles_bf16(ConvTile tile, int bk, int mode, const ConvArgs &a, hipStream_t s);
+hipError_t launch_conv_dlds_small(DType dt, ConvTile tile, int mode, bool splitk, const ConvArgs &a, hipStream_t s);
 hipError_t launch_conv_dlds_tail(DType dt, ConvTile tile, bool splitk, const ConvArgs &a, hipStream_t s);
 hipError_t launch_conv_dlds_k256(DType dt, ConvTile tile, int mode, bool splitk, const ConvArgs &a, hipStream_t s);
 // A convolution (Cin % 64 == 0, Cout 64 or 128) and the 1x1 convolution that consumes it, in one

@@ -1,6 +1,8 @@
 // Shared pieces of the convolution kernels: MFMA wrappers, buffer descriptors, the LDS swizzle
 // and the fused epilogue (bias + residual + ReLU + store, and the in-kernel split-K reduction).
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace cw {
@@ -38,6 +40,23 @@ struct Mfma<bf16> {
     typedef __bf16 v8 __attribute__((ext_vector_type(8)));
     static __device__ __forceinline__ f32x16 mma(v8 rows, v8 cols, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows, cols, c, 0, 0, 0);
+    }
+};
+
+// One MFMA tile of MT pixels x MT channels: 32 (16-deep steps, 16 accumulators a lane) or 16 (32-deep, 4).
+template <typename T, int MT>
+struct MfmaTile {
+    typedef f32x16 acc;
+    static constexpr int K = 16, REGS = 16;
+    static __device__ __forceinline__ acc mma(typename Mfma<T>::v8 rows, typename Mfma<T>::v8 cols, acc c) { return Mfma<T>::mma(rows, cols, c); }
+};
+template <typename T>
+struct MfmaTile<T, 16> {
+    typedef float acc __attribute__((ext_vector_type(4)));
+    static constexpr int K = 32, REGS = 4;
+    static __device__ __forceinline__ acc mma(typename Mfma<T>::v8 rows, typename Mfma<T>::v8 cols, acc c) {
+        if constexpr (std::is_same<T, f16>::value) return __builtin_amdgcn_mfma_f32_16x16x32_f16(rows, cols, c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(rows, cols, c, 0, 0, 0);
     }
 };
 
@@ -232,38 +251,41 @@ static __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[TM][TN
 // store 16 values, 0.64 us from the last matrix instruction to the last store of a 32x32 tile in four groups, a quarter
 // of a 1x1 launch at batch 1.  ResNet-50 batch 1 245.4 -> 236.9 us, 193x161 batch 3 263.2 -> 256.6, MobileNet batch 1
 // 126.9 -> 122.6.
-template <int TM, int TN, int KG>
+template <int MT, int TM, int TN, int KG>
 struct GroupUnits {
-    static constexpr int UNITS = TM * TN * 4;                  // per wave
+    static constexpr int PER_TILE = MT == 32 ? 4 : 1;
+    static constexpr int UNITS = TM * TN * PER_TILE;           // per wave
     static constexpr int UPG = (UNITS + KG - 1) / KG;          // finished by each group; groups beyond UNITS / UPG have none
-    static constexpr int W = UPG % 2 == 0 ? 2 : 1;             // units per load and store: two make eight consecutive channels
+    static constexpr int W = MT == 32 && UPG % 2 == 0 ? 2 : 1;   // units per load and store: two make eight consecutive channels
 };
 
-// Pixel and first channel of unit u (see EpiPos for the accumulator layout).
-template <int TN>
+// Pixel and first channel of unit u (see EpiPos for the accumulator layout).  In a 16x16 tile the lane's four
+// accumulators are weight rows 4*(lane/16) .. +3, which the packed order makes channels 8*h + 4*g .. +3 for lane/16 = 2g + h.
+template <int MT, int TN>
 static __device__ __forceinline__ void unit_pos(const EpiPos &p, int u, unsigned *m, unsigned *n) {
-    const int t = u >> 2, r = u & 3, i = t / TN, j = t - i * TN;
-    *m = p.m0 + p.wm0 + i * 32 + p.lrow;
-    *n = p.n0 + p.wn0 + j * 32 + 16 * (r >> 1) + 8 * p.lhalf + 4 * (r & 1);
+    constexpr int PT = MT == 32 ? 4 : 1;
+    const int t = u / PT, r = u - t * PT, i = t / TN, j = t - i * TN;
+    *m = p.m0 + p.wm0 + i * MT + p.lrow;
+    *n = p.n0 + p.wn0 + j * MT + (MT == 32 ? 16 * (r >> 1) + 8 * p.lhalf + 4 * (r & 1) : 8 * (p.lhalf & 1) + 4 * (p.lhalf >> 1));
 }
 
-template <int TM, int TN, int KG>
+template <int MT, int TM, int TN, int KG>
 struct GroupOperands {
-    typedef GroupUnits<TM, TN, KG> G;
+    typedef GroupUnits<MT, TM, TN, KG> G;
     u32x4 bv[G::UPG];
     u32x2 rv[G::UPG];
 };
 
-template <int TM, int TN, int KG>
-static __device__ __forceinline__ void group_epilogue_load(GroupOperands<TM, TN, KG> &e, const ConvArgs &a, const EpiPos &p, int kg) {
-    typedef GroupUnits<TM, TN, KG> G;
+template <int MT, int TM, int TN, int KG>
+static __device__ __forceinline__ void group_epilogue_load(GroupOperands<MT, TM, TN, KG> &e, const ConvArgs &a, const EpiPos &p, int kg) {
+    typedef GroupUnits<MT, TM, TN, KG> G;
     const bool has_bias = a.bias != nullptr, has_res = a.res != nullptr;
     const __amdgpu_buffer_rsrc_t rr = make_rsrc(has_res ? a.res : a.y, (unsigned)a.M * a.Cout * 2u);
     const __amdgpu_buffer_rsrc_t rb = make_rsrc(has_bias ? static_cast<const void *>(a.bias) : a.y, (unsigned)a.Cout * 4u);
 #pragma unroll
     for (int k = 0; k < G::UPG; k += G::W) {
         unsigned m, n;
-        unit_pos<TN>(p, kg * G::UPG + k, &m, &n);
+        unit_pos<MT, TN>(p, kg * G::UPG + k, &m, &n);
         const bool n_ok = kg * G::UPG + k < G::UNITS && n < (unsigned)a.Cout;   // Cout % 32 == 0: all of a unit or none
         const unsigned ob = has_bias && n_ok ? n * 4u : kOob;
         const unsigned orr = has_res && n_ok && m < (unsigned)a.M ? (m * a.Cout + n) * 2u : kOob;
@@ -281,63 +303,129 @@ static __device__ __forceinline__ void group_epilogue_load(GroupOperands<TM, TN,
 }
 
 // xch: KG * WAVES * UNITS KiB of LDS that no wave reads any more; wq = the wave's place in its group.
-template <int TM, int TN, int KG, int WAVES>
-static __device__ __forceinline__ void group_exchange_write(const f32x16 (&acc)[TM][TN], float *xch, int kg, int wq, int lane) {
-    typedef GroupUnits<TM, TN, KG> G;
+template <int MT, int TM, int TN, int KG, int WAVES, typename ACC>
+static __device__ __forceinline__ void group_exchange_write(const ACC (&acc)[TM][TN], float *xch, int kg, int wq, int lane) {
+    typedef GroupUnits<MT, TM, TN, KG> G;
     float *dst = xch + (kg * WAVES + wq) * (G::UNITS * 256) + lane * 4;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                *reinterpret_cast<float4 *>(dst + ((i * TN + j) * 4 + r) * 256) =
+            for (int r = 0; r < G::PER_TILE; ++r)
+                *reinterpret_cast<float4 *>(dst + ((i * TN + j) * G::PER_TILE + r) * 256) =
                     make_float4(acc[i][j][4 * r], acc[i][j][4 * r + 1], acc[i][j][4 * r + 2], acc[i][j][4 * r + 3]);
 }
 
-template <typename T, int TM, int TN, int KG, int WAVES, bool HSWISH>
-static __device__ __forceinline__ void group_epilogue_store_act(const float *xch, const GroupOperands<TM, TN, KG> &e, const ConvArgs &a, const EpiPos &p,
-                                                                int kg, int wq, int lane) {
-    typedef GroupUnits<TM, TN, KG> G;
-    const unsigned ldy = (unsigned)conv_ldy(a);
-    const __amdgpu_buffer_rsrc_t ry = make_rsrc(a.y, (((unsigned)a.M - 1u) * ldy + (unsigned)a.Cout) * 2u);
+// This group's units, added up over the groups in group order.
+template <int MT, int TM, int TN, int KG, int WAVES>
+static __device__ __forceinline__ void group_sum(const float *xch, float4 (&s)[GroupUnits<MT, TM, TN, KG>::UPG], int kg, int wq, int lane) {
+    typedef GroupUnits<MT, TM, TN, KG> G;
     float4 v[G::UPG][KG];
 #pragma unroll
     for (int k = 0; k < G::UPG; ++k)
 #pragma unroll
         for (int g = 0; g < KG; ++g)
-            v[k][g] = *reinterpret_cast<const float4 *>(xch + ((g * WAVES + wq) * G::UNITS + kg * G::UPG + k) * 256 + lane * 4);
+            v[k][g] = *reinterpret_cast<const float4 *>(xch + ((g * WAVES + wq) * G::UNITS + min(kg * G::UPG + k, G::UNITS - 1)) * 256 + lane * 4);
+#pragma unroll
+    for (int k = 0; k < G::UPG; ++k) {
+        s[k] = v[k][0];
+#pragma unroll
+        for (int g = 1; g < KG; ++g) { s[k].x += v[k][g].x; s[k].y += v[k][g].y; s[k].z += v[k][g].z; s[k].w += v[k][g].w; }
+    }
+}
+
+// splitk_exchange for units: every wave's partial sums go out device-scope, the wave that draws its place's last ticket
+// adds those of all splits in split order.  false: another workgroup's wave finishes the units.  `counter` is the arrival
+// counter of this place: conv_counters_per_tile of them a tile.
+template <int MT, int TM, int TN, int KG>
+static __device__ __forceinline__ bool group_splitk(const ConvArgs &a, const EpiPos &p, float4 (&s)[GroupUnits<MT, TM, TN, KG>::UPG], int kg, int lane, int32_t *counter) {
+    typedef GroupUnits<MT, TM, TN, KG> G;
+    constexpr int kDeviceScope = 16;  // cache-policy operand: sc1
+    const unsigned mn = (unsigned)a.M * a.Cout;
+    unsigned o[G::UPG];
+#pragma unroll
+    for (int k = 0; k < G::UPG; ++k) {
+        unsigned m, n;
+        unit_pos<MT, TN>(p, kg * G::UPG + k, &m, &n);
+        o[k] = kg * G::UPG + k < G::UNITS && m < (unsigned)a.M && n < (unsigned)a.Cout ? (m * a.Cout + n) * 4u : kOob;
+    }
+    const __amdgpu_buffer_rsrc_t rp = make_rsrc(a.partial + (size_t)blockIdx.y * mn, mn * 4u);
+#pragma unroll
+    for (int k = 0; k < G::UPG; ++k)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(s[k].x), __float_as_uint(s[k].y), __float_as_uint(s[k].z), __float_as_uint(s[k].w)}, rp, o[k], 0, kDeviceScope);
+    // Each wave draws tickets of its own, for the units it holds: no barrier, and waves without units are long gone.
+    __builtin_amdgcn_s_waitcnt(0);  // vmcnt(0): the wave's partial sums have been written
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    int last = 0;
+    if (lane == 0) {
+        const int ticket = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = ticket == a.split_k - 1;
+        if (last) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // Four splits' sums are requested together; this workgroup's own are the registers that it stored.
+    float4 own[G::UPG];
+#pragma unroll
+    for (int k = 0; k < G::UPG; ++k) { own[k] = s[k]; s[k] = make_float4(0.f, 0.f, 0.f, 0.f); }
+    for (int z0 = 0; z0 < a.split_k; z0 += 4) {
+        u32x4 v[4][G::UPG];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int z = min(z0 + u, a.split_k - 1);
+            const __amdgpu_buffer_rsrc_t rz = make_rsrc(a.partial + (size_t)z * mn, mn * 4u);
+#pragma unroll
+            for (int k = 0; k < G::UPG; ++k) v[u][k] = __builtin_amdgcn_raw_buffer_load_b128(rz, z0 + u < a.split_k && z != (int)blockIdx.y ? o[k] : kOob, 0, kDeviceScope);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < G::UPG; ++k) {   // past the last split: zeros
+                const bool mine = z0 + u == (int)blockIdx.y;
+                s[k].x += mine ? own[k].x : __uint_as_float(v[u][k].x);
+                s[k].y += mine ? own[k].y : __uint_as_float(v[u][k].y);
+                s[k].z += mine ? own[k].z : __uint_as_float(v[u][k].z);
+                s[k].w += mine ? own[k].w : __uint_as_float(v[u][k].w);
+            }
+    }
+    return true;
+}
+
+template <typename T, int MT, int TM, int TN, int KG, bool HSWISH>
+static __device__ __forceinline__ void group_epilogue_store_act(const float4 (&s)[GroupUnits<MT, TM, TN, KG>::UPG], const GroupOperands<MT, TM, TN, KG> &e,
+                                                                const ConvArgs &a, const EpiPos &p, int kg) {
+    typedef GroupUnits<MT, TM, TN, KG> G;
+    const unsigned ldy = (unsigned)conv_ldy(a);
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(a.y, (((unsigned)a.M - 1u) * ldy + (unsigned)a.Cout) * 2u);
 #pragma unroll
     for (int k = 0; k < G::UPG; k += G::W) {
         unsigned m, n;
-        unit_pos<TN>(p, kg * G::UPG + k, &m, &n);
+        unit_pos<MT, TN>(p, kg * G::UPG + k, &m, &n);
         T out[4 * G::W];
 #pragma unroll
         for (int w = 0; w < G::W; ++w) {
             const float *b = reinterpret_cast<const float *>(&e.bv[k + w]);
             const T *r = reinterpret_cast<const T *>(&e.rv[k + w]);
+            const float f[4] = {s[k + w].x, s[k + w].y, s[k + w].z, s[k + w].w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                float s = reinterpret_cast<const float *>(&v[k + w][0])[c];
-#pragma unroll
-                for (int g = 1; g < KG; ++g) s += reinterpret_cast<const float *>(&v[k + w][g])[c];
-                s = s + b[c] + (float)r[c];
-                if (HSWISH) out[4 * w + c] = (T)(s * fminf(fmaxf(s + 3.f, 0.f), 6.f) * (1.f / 6.f));
-                else out[4 * w + c] = (T)(a.relu ? fmaxf(s, 0.f) : s);
+                const float v = f[c] + b[c] + (float)r[c];
+                if (HSWISH) out[4 * w + c] = (T)(v * fminf(fmaxf(v + 3.f, 0.f), 6.f) * (1.f / 6.f));
+                else out[4 * w + c] = (T)(a.relu ? fmaxf(v, 0.f) : v);
             }
         }
-        const unsigned o = m < (unsigned)a.M && n < (unsigned)a.Cout ? (m * ldy + n) * 2u : kOob;
+        const unsigned o = kg * G::UPG + k < G::UNITS && m < (unsigned)a.M && n < (unsigned)a.Cout ? (m * ldy + n) * 2u : kOob;
         if constexpr (G::W == 2) __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(out), ry, o, 0, 0);
         else __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2 *>(out), ry, o, 0, 0);
     }
 }
 
-template <typename T, int TM, int TN, int KG, int WAVES>
-static __device__ __forceinline__ void group_epilogue_store(const float *xch, const GroupOperands<TM, TN, KG> &e, const ConvArgs &a, const EpiPos &p, int kg,
-                                                            int wq, int lane) {
-    if (kg * GroupUnits<TM, TN, KG>::UPG >= GroupUnits<TM, TN, KG>::UNITS) return;   // eight groups, four units
-    if (a.relu == ACT_HSWISH) group_epilogue_store_act<T, TM, TN, KG, WAVES, true>(xch, e, a, p, kg, wq, lane);
-    else group_epilogue_store_act<T, TM, TN, KG, WAVES, false>(xch, e, a, p, kg, wq, lane);
+template <typename T, int MT, int TM, int TN, int KG>
+static __device__ __forceinline__ void group_epilogue_store(const float4 (&s)[GroupUnits<MT, TM, TN, KG>::UPG], const GroupOperands<MT, TM, TN, KG> &e,
+                                                            const ConvArgs &a, const EpiPos &p, int kg) {
+    if (a.relu == ACT_HSWISH) group_epilogue_store_act<T, MT, TM, TN, KG, true>(s, e, a, p, kg);
+    else group_epilogue_store_act<T, MT, TM, TN, KG, false>(s, e, a, p, kg);
 }
 
 // Workgroups go to the 8 XCDs round-robin; give each XCD a contiguous run of tiles so that

@@ -79,20 +79,26 @@ constexpr int kFusedMaxCout2 = 1024;
 // group finishing its share of the tile (GroupUnits).  For
 // small tiles with a long K this shortens the per-slice MFMA chain of a wave (and puts several
 // waves on each SIMD) without the global exchange of split-K; with split-K on top (tiny M*N, very
-// long K) the first group carries the workgroup's sum into that exchange and the others end.
+// long K) the groups' shares of the workgroup's sum go into that exchange.
 // The body takes the launch's arguments and this workgroup's place bid among the nb workgroups of
 // the convolution (a launch may hold two convolutions, see conv_dlds_pair_kernel).
 // RAW: bid is the tile index itself (the caller has chosen which tile this workgroup computes).
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, bool RAW = false>
+// MT: edge of the MFMA tiles, 32 or (wave groups that finish the tile together only) 16.
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, bool RAW = false, int MT = 32>
 static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const int bid, const int nb_packed) {
     // nb_packed: the convolution's tile count with its tile numbering in the top bits (conv_pack_nb)
-    const int nb = conv_nb_tiles(nb_packed), panel = conv_nb_panel(nb_packed);
+    // (16x16 MFMA: of 32x32 tiles, which are numbered and computed in PARTS parts of BM x BN)
+    constexpr int PARTS = MT == 16 ? (32 / BM) * (32 / BN) : 1, ROUND = MT == 16 ? 32 : BM;
+    const int nb = conv_nb_tiles(nb_packed) * PARTS, panel = conv_nb_panel(nb_packed);
     static_assert(BK == 64 || BK == 128 || BK == 256, "K slices of 64, 128 or 256");
-    static_assert(KG == 1 || ((BK / 16) % KG == 0 && (!FUSED || KG == 2)), "K groups: whole steps per group");
+    typedef MfmaTile<T, MT> MF;
+    typedef typename MF::acc acc_t;
+    static_assert(MT == 32 || (KG >= 4 && !FUSED && MODE != MODE_STEM), "16x16 MFMA tiles: plain form in wave groups");
+    static_assert(KG == 1 || ((BK / MF::K) % KG == 0 && (!FUSED || KG == 2)), "K groups: whole steps per group");
     static_assert(!FUSED || (!SPLITK && MODE != MODE_STEM && (BN == 64 || BN == 128)), "fused form: whole first layer in one tile");
     constexpr int NT = 64 * WARPS_M * WARPS_N * KG;
     constexpr int WM = BM / WARPS_M, WN = BN / WARPS_N;
-    constexpr int TM = WM / 32, TN = WN / 32;
+    constexpr int TM = WM / MT, TN = WN / MT;
     constexpr int CPR = BK / 8;  // 16-byte chunks per LDS row
     constexpr int X_CHUNKS = BM * CPR, W_CHUNKS = BN * CPR;
     static_assert(X_CHUNKS % NT == 0 && W_CHUNKS % NT == 0, "tile/threads mismatch");
@@ -130,8 +136,8 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const int wq = wave - kg * (WARPS_M * WARPS_N);   // its place in the WARPS_M x WARPS_N layout
     const int wm0 = (wq / WARPS_N) * WM;
     const int wn0 = (wq % WARPS_N) * WN;
-    const int lrow = lane & 31;
-    const int lhalf = lane >> 5;
+    const int lrow = lane & (MT - 1);
+    const int lhalf = lane / MT;   // which 8 of a step's K the lane holds
 
     const int tile_id = RAW ? bid : xcd_tile_id(bid, nb);
     const int tiles_n = a.Cout / BN + (a.Cout % BN != 0);
@@ -142,12 +148,13 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     } else {
         // panel after panel of tiles_n >> panel channel tiles, row by row inside a panel
         const int pw = tiles_n >> panel;
-        const int per = ((a.M + BM - 1) / BM) * pw;
+        const int per = (a.M + ROUND - 1) / ROUND * (ROUND / BM) * pw;
         const int p = tile_id / per, r = tile_id - p * per;
         tile_m = r / pw;
         tile_n = p * pw + (r - tile_m * pw);
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
+    if (MT == 16 && m0 >= a.M) return;   // the lower part of the last pixels' tile
 
     constexpr bool GEMM = MODE == MODE_GEMM || MODE == MODE_TAIL;
     // a first convolution's filter rows beyond kh are padding
@@ -300,13 +307,13 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         issue_end();
     };
 
-    f32x16 acc[TM][TN];  // [pixel tile][channel tile]; MFMA rows = channels, columns = pixels
+    acc_t acc[TM][TN];  // [pixel tile][channel tile]; MFMA rows = channels, columns = pixels
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < MF::REGS; ++e) acc[i][j][e] = 0.f;
 
     // MFMAs of one K slice.  Operand fragments are fetched from LDS DEPTH-1 16-k steps ahead of
     // the MFMAs that use them.  A wave tile of 64x64 has 4 MFMAs per step, enough to cover the
@@ -319,7 +326,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     auto compute = [&](int stage, auto with_loads) {
         const T *sX = lds + stage * STAGE;
         const T *sW = sX + BM * BK;
-        constexpr int KK = BK / 16 / KG;                               // 16-k steps of this wave per slice
+        constexpr int KK = BK / MF::K / KG;                            // k steps of this wave per slice
         constexpr int DEPTH0 = TM * TN >= 4 ? 2 : 4;
         constexpr int DEPTH = DEPTH0 < KK ? DEPTH0 : (KK > 1 ? KK : 2);  // fragment sets held
         v8 fx[DEPTH][TM], fw[DEPTH][TN];
@@ -327,10 +334,10 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             const int kk = KG == 1 ? t : kg + t * KG;
 #pragma unroll
             for (int i = 0; i < TM; ++i)
-                qx[i] = *reinterpret_cast<const v8 *>(sX + swz<BK>(wm0 + i * 32 + lrow, kk * 2 + lhalf));
+                qx[i] = *reinterpret_cast<const v8 *>(sX + swz<BK>(wm0 + i * MT + lrow, kk * (MF::K / 8) + lhalf));
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                qw[j] = *reinterpret_cast<const v8 *>(sW + swz<BK>(wn0 + j * 32 + lrow, kk * 2 + lhalf));
+                qw[j] = *reinterpret_cast<const v8 *>(sW + swz<BK>(wn0 + j * MT + lrow, kk * (MF::K / 8) + lhalf));
         };
 #pragma unroll
         for (int t = 0; t < DEPTH - 1 && t < KK; ++t) fetch(t, fx[t], fw[t]);
@@ -340,7 +347,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::mma(fw[t % DEPTH][j], fx[t % DEPTH][i], acc[i][j]);
+                for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fw[t % DEPTH][j], fx[t % DEPTH][i], acc[i][j]);
             if (decltype(with_loads)::value) {
 #pragma unroll
                 for (int idx = t * LOADS / KK; idx < (t + 1) * LOADS / KK; ++idx) issue_piece(idx);
@@ -351,12 +358,14 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const EpiPos pos{m0, n0, wm0, wn0, lrow, lhalf};
     // Four and eight groups finish the tile together.  Two (128x64, 64x64) keep one finishing group, which moves half as
     // much through LDS.
-    constexpr bool SHARED = KG >= 4 && !FUSED && !SPLITK;
+    constexpr bool SHARED = KG >= 4 && !FUSED;
     EpiOperands<TM, TN> eo;
-    GroupOperands<TM, TN, KG> go;
+    GroupOperands<MT, TM, TN, KG> go;
     auto load_operands = [&]() {
-        if constexpr (SHARED) group_epilogue_load<TM, TN, KG>(go, a, pos, kg);
-        else if (!SPLITK && !FUSED && kg == 0) epilogue_load<TM, TN>(eo, a, pos);
+        if constexpr (SHARED && !SPLITK) group_epilogue_load<MT, TM, TN, KG>(go, a, pos, kg);
+        else if constexpr (!SPLITK && !FUSED) {
+            if (kg == 0) epilogue_load<TM, TN>(eo, a, pos);
+        }
     };
 
     // Prologue: the first min(NS-1, nsteps) slices into stages 0, 1, ...
@@ -401,11 +410,19 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         static_assert(KG * BM * BN * 4 <= NS * (int)STAGE_BYTES, "K-group exchange does not fit the ring");
         float *xch = reinterpret_cast<float *>(cw_dyn_lds);
         wait_lds_and_barrier();   // no slice is in flight any more; the operands just requested stay so
-        group_exchange_write<TM, TN, KG, WARPS_M * WARPS_N>(acc, xch, kg, wq, lane);
+        group_exchange_write<MT, TM, TN, KG, WARPS_M * WARPS_N>(acc, xch, kg, wq, lane);
         wait_lds_and_barrier();
-        group_epilogue_store<T, TM, TN, KG, WARPS_M * WARPS_N>(xch, go, a, pos, kg, wq, lane);
+        typedef GroupUnits<MT, TM, TN, KG> G;
+        if (kg * G::UPG >= G::UNITS) return;   // more groups than units
+        float4 sum[G::UPG];
+        group_sum<MT, TM, TN, KG, WARPS_M * WARPS_N>(xch, sum, kg, wq, lane);
+        if constexpr (SPLITK) {
+            group_epilogue_load<MT, TM, TN, KG>(go, a, pos, kg);   // here behind the partial sums' way out
+            if (!group_splitk<MT, TM, TN, KG>(a, pos, sum, kg, lane, a.counters + tile_id * (NT / 64) + wave)) return;
+        }
+        group_epilogue_store<T, MT, TM, TN, KG>(sum, go, a, pos, kg);
         return;
-    }
+    } else {
     if constexpr (KG > 1 && !FUSED) {
         // Groups 1.. hand their accumulators to group 0 through LDS (the ring is free once every
         // wave has passed the barrier); group 0 adds them in group order and goes on alone.
@@ -704,6 +721,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         epilogue_load<TM, TN>(eo, a, pos);
     }
     epilogue_store<T, TM, TN>(acc, eo, a, pos);
+    }
 }
 
 // LDS stages per tile: 4 where that still lets two workgroups share a CU's 160 KiB, else 3.

@@ -4,10 +4,36 @@
 
 namespace cw {
 
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1>
+#ifdef CW_STAMPS
+// A build for tune.py: workgroup b of the process's convolution launch number l leaves {start, end} in ticks of 10 ns at
+// cw_stamps[(l % kStampLaunches) * kStampGroups + b], end = its stores have been taken.
+constexpr unsigned kStampLaunches = 256, kStampGroups = 16384;
+extern ulonglong2 *cw_stamps;
+extern unsigned cw_stamp_next;
+#define CW_STAMP_ARG , ulonglong2 *stamps
+#define CW_STAMP_BEGIN const unsigned long long stamp_from = __builtin_amdgcn_s_memrealtime();
+#define CW_STAMP_END                                                                                            \
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                                            \
+    const unsigned stamp = blockIdx.x + conv_nb_tiles(nb) * conv_parts<BM, BN, MT>() * blockIdx.y;              \
+    if (threadIdx.x == 0 && stamp < kStampGroups)                                                               \
+        stamps[stamp] = make_ulonglong2(stamp_from, __builtin_amdgcn_s_memrealtime());
+#define CW_STAMP_PASS , cw_stamps + (size_t)(cw_stamp_next++ % kStampLaunches) * kStampGroups
+#else
+#define CW_STAMP_ARG
+#define CW_STAMP_BEGIN
+#define CW_STAMP_END
+#define CW_STAMP_PASS
+#endif
+
+// Workgroups of a tile: of the forms on 16x16 MFMA tiles a workgroup computes a BM x BN part of a 32x32 tile.
+template <int BM, int BN, int MT>
+constexpr int conv_parts() { return MT == 16 ? (32 / BM) * (32 / BN) : 1; }
+
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, int MT = 32>
 __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
                                                                                  int M, int K, int cout_ldy, int cin_ldx, int nb, int relu,
-                                                                                 const ConvArgs rest) {
+                                                                                 const ConvArgs rest CW_STAMP_ARG) {
+    CW_STAMP_BEGIN
     // The ten leading arguments (14 dwords, all the user SGPRs there are beside the argument
     // pointer) repeat fields of `rest`: this file is compiled with kernel-argument preloading, so
     // they are in SGPRs when a wave starts and the first address arithmetic does not wait for a
@@ -18,7 +44,7 @@ __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(
     a.x = x; a.w = w; a.res = res; a.y = y;
     a.M = M; a.K = K; a.Cout = cout_ldy & 0xffff; a.Cin = cin_ldx & 0xffff; a.nb = nb; a.relu = relu;
     a.ld = (int)(((unsigned)cin_ldx >> 16) | ((unsigned)cout_ldy & 0xffff0000u));
-    if constexpr (MODE == MODE_GEMM && !SPLITK && !FUSED) {
+    if constexpr (MODE == MODE_GEMM && !SPLITK && !FUSED && MT == 32) {
         // batched form: one GEMM per blockIdx.z, operands advanced by the strides in the last argument line
         if (blockIdx.z != 0) {
             a.x = static_cast<const char *>(x) + (long long)blockIdx.z * rest.zs_x;
@@ -27,11 +53,14 @@ __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(
         }
     }
     if constexpr (FUSED || SPLITK || MODE == MODE_STEM) {
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG>(a, blockIdx.x, nb);
-    } else if (__builtin_expect((int)blockIdx.x < conv_nb_tiles(nb), 1)) {
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG>(a, blockIdx.x, nb);
+        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, blockIdx.x, nb);
+        CW_STAMP_END
+    } else if (__builtin_expect((int)blockIdx.x < conv_nb_tiles(nb) * conv_parts<BM, BN, MT>(), 1)) {
+        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, blockIdx.x, nb);
+        CW_STAMP_END
     } else {   // a workgroup that reads ahead (its code behind the convolution's, which most launches find cold)
-        const int first = (int)blockIdx.x - conv_nb_tiles(nb), nt = ((int)gridDim.x - conv_nb_tiles(nb)) * (int)blockDim.x;
+        const int wgs = conv_nb_tiles(nb) * conv_parts<BM, BN, MT>();
+        const int first = (int)blockIdx.x - wgs, nt = ((int)gridDim.x - wgs) * (int)blockDim.x;
         const int lines = rest.Cout2;
         const char *p = static_cast<const char *>(rest.w2);
         for (int i = first * (int)blockDim.x + (int)threadIdx.x; i < lines; i += nt * kPrefetchPerThread) {
@@ -53,28 +82,30 @@ static bool conv_panel_ok(const ConvArgs &a, int bn, unsigned tiles) {
     return a.panel_log2 == 0 || tiles_n % (1 << a.panel_log2) == 0;
 }
 
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int MODE, bool SPLITK, int KG = 1>
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int MODE, bool SPLITK, int KG = 1, int MT = 32>
 static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStream_t s) {
     ConvArgs a = a_in;
     if (!conv_panel_ok(a, BN, grid.x)) return hipErrorInvalidValue;
     a.nb = conv_pack_nb((int)grid.x, a.panel_log2);
     if (MODE == MODE_TAIL ? a.nz > 1 : a.K % BK != 0 && MODE != MODE_STEM) return hipErrorInvalidValue;
     if (!SPLITK && a.ktiles_per_split != (MODE == MODE_STEM ? (a.kh + 1) / 2 : (a.K + BK - 1) / BK)) return hipErrorInvalidValue;  // the kernel walks the whole K
-    if (a.nz > 1 && (MODE != MODE_GEMM || SPLITK || a.bias || a.res || grid.z != (unsigned)a.nz)) return hipErrorInvalidValue;
-    if (a.nz <= 1 && grid.z != 1) return hipErrorInvalidValue;
+    if (a.nz > 1 && (MT != 32 || MODE != MODE_GEMM || SPLITK || a.bias || a.res || grid.z != (unsigned)a.nz)) return hipErrorInvalidValue;
+    constexpr unsigned PARTS = conv_parts<BM, BN, MT>();
+    if (a.nz <= 1 && grid.z != PARTS) return hipErrorInvalidValue;
+    if (PARTS > 1) grid = dim3(grid.x * PARTS, grid.y, 1);   // the workgroups that read ahead come behind all the parts
     constexpr int NS = RingDepth<BM, BN, BK>::value;
     constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
     static_assert(NS * stage_bytes <= 160 * 1024, "ring does not fit the LDS");
-    auto kern = conv_dlds_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, false, KG>;
+    auto kern = conv_dlds_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, false, KG, MT>;
     // More than 64 KiB of LDS per workgroup has to be requested once per kernel; done on first
     // use (under LOAD's graph recording or the first plain EXEC), never per launch afterwards.
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
     if (attr != hipSuccess) return attr;
     // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
     // at the end needs its own room)
-    if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && grid.z == 1) grid.x += conv_prefetch_wgs(a.Cout2);
-    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG >= 4 && !SPLITK ? KG : KG - 1) * BM * BN * 4);
-    kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a);
+    if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && a.nz <= 1) grid.x += conv_prefetch_wgs(a.Cout2);
+    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG >= 4 ? KG : KG - 1) * BM * BN * 4);
+    kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a CW_STAMP_PASS);
     return hipGetLastError();
 }
 

@@ -323,6 +323,11 @@ TileDim conv_tile_dim(ConvTile t) {
         case T32x64k256g4: return {32, 64, 512, 256, 4};
         case T32x64k256g8: return {32, 64, 1024, 256, 8};
         case T64x64k256g4: return {64, 64, 1024, 256, 4};
+        case T32x32k128g4q: return {32, 32, 256, 128, 4, 16, 16};
+        case T32x32k128g4n: return {32, 32, 256, 128, 4, 32, 16};
+        case T32x32k128g4m: return {32, 32, 256, 128, 4, 16, 32};
+        case T32x32k256g4q: return {32, 32, 256, 256, 4, 16, 16};
+        case T32x32k256g4n: return {32, 32, 256, 256, 4, 32, 16};
         default: return {32, 32, 64, 64, 1};
     }
 }
@@ -339,7 +344,8 @@ ConvTile conv_tile_k64(ConvTile t) {
         case T64x32k128: case T64x32k128g4: return T64x32;
         case T32x64k128: case T32x64k128g4: return T32x64;
         case T32x32k128: return T32x32;
-        case T32x32k128g4: case T32x32k128g8: case T32x32k256g4: case T32x32k256g8: return T32x32g4;
+        case T32x32k128g4: case T32x32k128g8: case T32x32k256g4: case T32x32k256g8: case T32x32k128g4q: case T32x32k128g4n: case T32x32k128g4m:
+        case T32x32k256g4q: case T32x32k256g4n: return T32x32g4;
         case T64x32k256g4: case T64x32k256g8: return T64x32;
         case T32x64k256g4: case T32x64k256g8: return T32x64;
         case T64x64k256g4: return T64x64g2;
@@ -405,7 +411,7 @@ int conv_slices(const ConvArgs &a, bool stem, ConvTile tile) {
 void conv_grid(ConvTile tile, const ConvArgs &a, dim3 *grid, int *block) {
     const TileDim d = conv_tile_dim(tile);
     const unsigned tm = (a.M + d.bm - 1) / d.bm, tn = (a.Cout + d.bn - 1) / d.bn;
-    *grid = dim3(tm * tn, a.split_k, a.nz > 1 ? a.nz : 1);
+    *grid = dim3(tm * tn, a.split_k, a.nz > 1 ? a.nz : d.parts());
     *block = d.threads;
 }
 

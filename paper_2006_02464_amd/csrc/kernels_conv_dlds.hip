@@ -1,5 +1,5 @@
-// Per-layer launches of the direct-to-LDS implicit-GEMM convolution: kernel entry points, tile
-// dispatch and the fused / pair forms.  The per-tile body is in conv_dlds_body.h.
+// Launches of the direct-to-LDS implicit-GEMM convolution: checks, dispatch and the fused / pair forms.  The per-tile
+// body is in conv_dlds_body.h, the plain forms' tiles in conv_dlds_tiles.h.
 #include "conv_dlds_launch.h"
 
 namespace cw {
@@ -8,85 +8,13 @@ namespace cw {
 // projection shortcut beside it) in one launch: the first nb0 workgroups take the first, the rest
 // the second.  Same instantiation for both (general addressing mode, no split-K); one dispatch,
 // one set-up latency and one tail instead of two.
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int KG>
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int KG, int MT>
 __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_pair_kernel(const ConvArgs a0, const ConvArgs a1) {
-    const int nb0 = conv_nb_tiles(a0.nb);
+    const int nb0 = conv_nb_tiles(a0.nb) * conv_parts<BM, BN, MT>();
     if ((int)blockIdx.x < nb0)
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG>(a0, blockIdx.x, a0.nb);
+        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, false, MT>(a0, blockIdx.x, a0.nb);
     else
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG>(a1, blockIdx.x - nb0, a1.nb);
-}
-
-template <typename T, int MODE, bool SPLITK>
-static hipError_t launch_tile(ConvTile tile, int bk, const ConvArgs &a, hipStream_t s) {
-    if (MODE == MODE_STEM) tile = conv_tile_one_group(tile);
-    if (bk == 64) tile = conv_tile_k64(tile);
-    else if (bk == 256) return launch_conv_dlds_k256(std::is_same<T, f16>::value ? DT_F16 : DT_BF16, tile, MODE, SPLITK, a, s);
-    dim3 grid;
-    int block;
-    conv_grid(tile, a, &grid, &block);
-    switch (tile) {
-        case T128x128: return launch_one<T, 128, 128, 2, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        case T128x64: return launch_one<T, 128, 64, 2, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        case T64x64: return launch_one<T, 64, 64, 2, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        case T64x32: return launch_one<T, 64, 32, 2, 1, 64, MODE, SPLITK>(grid, block, a, s);
-        case T32x64: return launch_one<T, 32, 64, 1, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        case T32x32: return launch_one<T, 32, 32, 1, 1, 64, MODE, SPLITK>(grid, block, a, s);
-        case T128x64w2: return launch_one<T, 128, 64, 2, 1, 64, MODE, SPLITK>(grid, block, a, s);
-        case T64x128w2: return launch_one<T, 64, 128, 1, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        case T256x64: return launch_one<T, 256, 64, 4, 1, 64, MODE, SPLITK>(grid, block, a, s);
-        case T128x128w8: return launch_one<T, 128, 128, 2, 4, 64, MODE, SPLITK>(grid, block, a, s);
-        case T128x64k128:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 128, 64, 2, 2, 128, MODE, SPLITK>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T64x64k128:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 64, 64, 2, 2, 128, MODE, SPLITK>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T64x32k128:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 64, 32, 2, 1, 128, MODE, SPLITK>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T32x64k128:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 32, 64, 1, 2, 128, MODE, SPLITK>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T32x32k128:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 32, 32, 1, 1, 128, MODE, SPLITK>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T128x64k128g2:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 128, 64, 2, 2, 128, MODE, SPLITK, 2>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T64x64k128g2:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 64, 64, 2, 2, 128, MODE, SPLITK, 2>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T64x64k128g4:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 64, 64, 2, 2, 128, MODE, SPLITK, 4>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T64x32k128g4:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 64, 32, 2, 1, 128, MODE, SPLITK, 4>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T32x64k128g4:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 32, 64, 1, 2, 128, MODE, SPLITK, 4>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T32x32k128g4:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 32, 32, 1, 1, 128, MODE, SPLITK, 4>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T32x32k128g8:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 32, 32, 1, 1, 128, MODE, SPLITK, 8>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T128x64g2:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 128, 64, 2, 2, 64, MODE, SPLITK, 2>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T64x64g2:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 64, 64, 2, 2, 64, MODE, SPLITK, 2>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T32x32g4:
-            if constexpr (MODE != MODE_STEM) return launch_one<T, 32, 32, 1, 1, 64, MODE, SPLITK, 4>(grid, block, a, s);
-            return hipErrorInvalidValue;
-        case T256x128w8: return launch_one<T, 256, 128, 4, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        case T128x256w8: return launch_one<T, 128, 256, 2, 4, 64, MODE, SPLITK>(grid, block, a, s);
-        case T256x256w8: return launch_one<T, 256, 256, 4, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        case T256x128: return launch_one<T, 256, 128, 2, 2, 64, MODE, SPLITK>(grid, block, a, s);
-        default: return hipErrorInvalidValue;
-    }
+        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, false, MT>(a1, blockIdx.x - nb0, a1.nb);
 }
 
 template <typename T, int BM, int BN, int MODE, int KG>
@@ -104,7 +32,7 @@ static hipError_t launch_fused_one(const ConvArgs &a_in, hipStream_t s) {
     if (attr != hipSuccess) return attr;
     if (a.Cout2 % fused_chunk(BN, KG) != 0) return hipErrorInvalidValue;
     if (a.w3 && BN / (2 * KG) < 32) return hipErrorInvalidValue;   // the third layer needs whole 32-channel tiles per wave
-    kern<<<dim3((a.M + BM - 1) / BM, 1, 1), 256 * KG, need, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a);
+    kern<<<dim3((a.M + BM - 1) / BM, 1, 1), 256 * KG, need, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a CW_STAMP_PASS);
     return hipGetLastError();
 }
 
@@ -153,27 +81,29 @@ hipError_t launch_conv_fused(DType dt, int bm, int kg, const ConvArgs &a, hipStr
 #undef CW_FUSED_T
 }
 
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int KG>
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int KG, int MT = 32>
 static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, hipStream_t s) {
     ConvArgs a0 = a0_in, a1 = a1_in;
     constexpr int NS = RingDepth<BM, BN, BK>::value;
     constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
-    auto kern = conv_dlds_pair_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, KG>;
+    auto kern = conv_dlds_pair_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, KG, MT>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
     if (attr != hipSuccess) return attr;
     const size_t used = std::max((size_t)std::min(NS, std::max(a0.ktiles_per_split, a1.ktiles_per_split)) * stage_bytes, (size_t)(KG >= 4 ? KG : KG - 1) * BM * BN * 4);
-    const unsigned nb0 = ((a0.M + BM - 1) / BM) * ((a0.Cout + BN - 1) / BN), nb1 = ((a1.M + BM - 1) / BM) * ((a1.Cout + BN - 1) / BN);
-    if (!conv_panel_ok(a0, BN, nb0) || !conv_panel_ok(a1, BN, nb1)) return hipErrorInvalidValue;
+    constexpr int TM = MT == 16 ? 32 : BM, TN = MT == 16 ? 32 : BN;
+    const unsigned nb0 = ((a0.M + TM - 1) / TM) * ((a0.Cout + TN - 1) / TN), nb1 = ((a1.M + TM - 1) / TM) * ((a1.Cout + TN - 1) / TN);
+    if (!conv_panel_ok(a0, TN, nb0) || !conv_panel_ok(a1, TN, nb1)) return hipErrorInvalidValue;
     a0.nb = conv_pack_nb((int)nb0, a0.panel_log2);
     a1.nb = conv_pack_nb((int)nb1, a1.panel_log2);
-    kern<<<dim3(nb0 + nb1, 1, 1), 64 * WARPS_M * WARPS_N * KG, used, s>>>(a0, a1);
+    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), 64 * WARPS_M * WARPS_N * KG, used, s>>>(a0, a1);
     return hipGetLastError();
 }
 
 bool conv_pair_tile_ok(ConvTile tile) {
     switch (tile) {
         case T128x64: case T128x64k128: case T64x64: case T64x64k128: case T64x32k128: case T32x64k128: case T32x32k128:
-        case T32x32k128g4: case T64x64k128g2: case T128x128: case T128x128w8: case T32x32: case T32x32g4: return true;
+        case T32x32k128g4: case T64x64k128g2: case T128x128: case T128x128w8: case T32x32: case T32x32g4:
+        case T32x32k128g4q: case T32x32k128g4n: case T32x32k128g4m: return true;
         default: return false;
     }
 }
@@ -188,7 +118,7 @@ static bool conv_pair_member_ok(const ConvArgs &a, int bk) {
 
 void conv_pair_grid(ConvTile tile, const ConvArgs &a0, const ConvArgs &a1, dim3 *grid, int *block) {
     const TileDim d = conv_tile_dim(tile);
-    *grid = dim3(((a0.M + d.bm - 1) / d.bm) * ((a0.Cout + d.bn - 1) / d.bn) + ((a1.M + d.bm - 1) / d.bm) * ((a1.Cout + d.bn - 1) / d.bn), 1, 1);
+    *grid = dim3(((a0.M + d.bm - 1) / d.bm) * ((a0.Cout + d.bn - 1) / d.bn) + ((a1.M + d.bm - 1) / d.bm) * ((a1.Cout + d.bn - 1) / d.bn), 1, d.parts());
     *block = d.threads;
 }
 
@@ -196,8 +126,8 @@ hipError_t launch_conv_pair(DType dt, ConvTile tile, const ConvArgs &a0, const C
     if (!conv_pair_tile_ok(tile)) return hipErrorInvalidValue;
     const int bk = conv_tile_dim(tile).bk;
     if (!conv_pair_member_ok(a0, bk) || !conv_pair_member_ok(a1, bk)) return hipErrorInvalidValue;
-#define CW_PAIR(BM_, BN_, WM_, WN_, BK_, KG_)                                                           \
-    return dt == DT_F16 ? launch_pair_one<f16, BM_, BN_, WM_, WN_, BK_, KG_>(a0, a1, s) : launch_pair_one<bf16, BM_, BN_, WM_, WN_, BK_, KG_>(a0, a1, s)
+#define CW_PAIR(BM_, BN_, WM_, WN_, BK_, ...)                                                           \
+    return dt == DT_F16 ? launch_pair_one<f16, BM_, BN_, WM_, WN_, BK_, __VA_ARGS__>(a0, a1, s) : launch_pair_one<bf16, BM_, BN_, WM_, WN_, BK_, __VA_ARGS__>(a0, a1, s)
     switch (tile) {
         case T128x64: CW_PAIR(128, 64, 2, 2, 64, 1);
         case T128x64k128: CW_PAIR(128, 64, 2, 2, 128, 1);
@@ -212,19 +142,12 @@ hipError_t launch_conv_pair(DType dt, ConvTile tile, const ConvArgs &a0, const C
         case T128x128w8: CW_PAIR(128, 128, 2, 4, 64, 1);
         case T32x32: CW_PAIR(32, 32, 1, 1, 64, 1);
         case T32x32g4: CW_PAIR(32, 32, 1, 1, 64, 4);
+        case T32x32k128g4q: CW_PAIR(16, 16, 1, 1, 128, 4, 16);
+        case T32x32k128g4n: CW_PAIR(32, 16, 1, 1, 128, 4, 16);
+        case T32x32k128g4m: CW_PAIR(16, 32, 1, 1, 128, 4, 16);
         default: return hipErrorInvalidValue;
     }
 #undef CW_PAIR
-}
-
-template <typename T, bool SPLITK>
-static hipError_t launch_mode(ConvTile tile, int bk, int mode, const ConvArgs &a, hipStream_t s) {
-    switch (mode) {
-        case MODE_GEMM: return launch_tile<T, MODE_GEMM, SPLITK>(tile, bk, a, s);
-        case MODE_CONV: return launch_tile<T, MODE_CONV, SPLITK>(tile, bk, a, s);
-        case MODE_STEM: return launch_tile<T, MODE_STEM, SPLITK>(tile, 64, a, s);
-        default: return hipErrorInvalidValue;
-    }
 }
 
 // Called by launch_conv (which has validated the shapes) for every convolution with
@@ -240,8 +163,26 @@ hipError_t launch_conv_dlds(DType dt, ConvTile tile, int bk, int mode, const Con
         return hipErrorInvalidValue;
     }
     if (mode == MODE_TAIL) return launch_conv_dlds_tail(dt, tile, a.split_k > 1, a, s);
-    if (a.split_k > 1) return dt == DT_F16 ? launch_mode<f16, true>(tile, bk, mode, a, s) : launch_mode<bf16, true>(tile, bk, mode, a, s);
-    return dt == DT_F16 ? launch_mode<f16, false>(tile, bk, mode, a, s) : launch_mode<bf16, false>(tile, bk, mode, a, s);
+    return dt == DT_F16 ? launch_conv_tiles_f16(tile, bk, mode, a, s) : launch_conv_tiles_bf16(tile, bk, mode, a, s);
 }
 
 }  // namespace cw
+
+#ifdef CW_STAMPS
+ulonglong2 *cw::cw_stamps = nullptr;
+unsigned cw::cw_stamp_next = 0;
+extern "C" {
+// The next convolution launch is number 0 again (call it before the first one); the stamps of launch l's first workgroups.
+int32_t cw_stamps_reset(void) {
+    const size_t bytes = (size_t)cw::kStampLaunches * cw::kStampGroups * sizeof(ulonglong2);
+    if (!cw::cw_stamps && (hipMalloc(reinterpret_cast<void **>(&cw::cw_stamps), bytes) != hipSuccess ||
+                           hipMemset(cw::cw_stamps, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess)) return -1;
+    cw::cw_stamp_next = 0;
+    return 0;
+}
+int32_t cw_stamps_read(uint32_t launch, uint32_t groups, unsigned long long *host) {
+    return hipMemcpy(host, cw::cw_stamps + (size_t)(launch % cw::kStampLaunches) * cw::kStampGroups,
+                     (groups < cw::kStampGroups ? groups : cw::kStampGroups) * sizeof(ulonglong2), hipMemcpyDeviceToHost) == hipSuccess ? 0 : -1;
+}
+}
+#endif

@@ -12,6 +12,7 @@ namespace cw {
 
 template <typename T, int MODE, bool SPLITK>
 static hipError_t launch_k256(ConvTile tile, const ConvArgs &a, hipStream_t s) {
+    if (conv_tile_small(tile)) return launch_conv_dlds_small(std::is_same<T, f16>::value ? DT_F16 : DT_BF16, tile, MODE, SPLITK, a, s);
     dim3 grid;
     int block;
     conv_grid(tile, a, &grid, &block);

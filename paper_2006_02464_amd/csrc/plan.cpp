@@ -299,13 +299,11 @@ static int pick_res_variant(int64_t M, int64_t N, int64_t K, int32_t cin) {
 
 // ---------------------------------------------------------------- tile choice
 // Every tile shape's launch time as a linear function of the quantities below, fitted offline to measured
-// launches (tune.py); the plan takes the tile and split-K with the least predicted time.  Over 645 GEMM shapes (five
-// networks, 38 combinations with image and batch sizes) timed on the kernels as they are, that costs 1.3 % over the
-// fastest tile of each (1x1 ending in part of a slice, on the same coefficients: 1.8 %); a table of measured shapes
-// with a heuristic beside it, as before, costs 4 % on the table's shapes and 22 % on the others.  What the fit cannot
-// see: a pair of events times nothing below 4.2 us, where more than half of a batch-1 plan's launches are, and what a
-// launch does to its neighbours.  Exchanged inside whole EXECs, single choices are worth up to 1 % more (ResNet-50
-// batch 1: the stage-3 expands on 32x64 instead of 32x32k256g4 1.6 us).
+// launches (tune.py); the plan takes the tile and split-K with the least predicted time.  A launch's time runs from its first
+// workgroup to the next launch's, by time stamps.  Over 641 GEMM shapes (five networks, 38 combinations with image
+// and batch sizes) the choice costs 1.7 % over the fastest tile of each.  Fitted to pairs of events, which see nothing below
+// 4.2 us, whole EXECs of the 38 combinations took 5.1 % longer in the mean on the tiles there were before the 16-wide
+// ones (with these, chosen by spans without the time to the next launch, 0.6 % longer).
 enum { COST_PLAIN, COST_STAGED, COST_STEM };   // the main kernel; the register-staged one; the first convolution's form
 constexpr int kCostFeatures = 11;
 struct ConvCost {
@@ -328,7 +326,7 @@ static double conv_cost(const ConvCost &c, const ConvArgs *const *as, const bool
         const TileDim d = conv_tile_dim((ConvTile)c.tile);
         const int slices = conv_slices(a, stem, (ConvTile)c.tile);
         const double per = (slices + split - 1) / split;
-        const double w = (double)((a.M + d.bm - 1) / d.bm) * ((a.Cout + d.bn - 1) / d.bn) * split;
+        const double w = (double)((a.M + d.pm - 1) / d.pm) * ((a.Cout + d.pn - 1) / d.pn) * split;
         const double t = (a.kh * a.kw > 1 || a.stride > 1) ? 1 : 0;
         wgs += w;
         per_sum += per * w;
@@ -357,7 +355,7 @@ static bool split_ok(const ConvArgs &a, bool stem, ConvTile tile, int32_t split)
     const int slices = conv_slices(a, stem, tile);
     const int per = (slices + split - 1) / split;
     const int64_t tiles = ((int64_t)a.M + d.bm - 1) / d.bm * ((a.Cout + d.bn - 1) / d.bn);
-    return (slices + per - 1) / per == split && tiles * 4 <= (int64_t)kCounterBytes && (int64_t)a.M * a.Cout * 4 < (1ll << 31);
+    return (slices + per - 1) / per == split && tiles * conv_counters_per_tile(tile) * 4 <= (int64_t)kCounterBytes && (int64_t)a.M * a.Cout * 4 < (1ll << 31);
 }
 
 // The cheapest tile and split-K of a convolution; a row of the installed table or a forced tile comes first.  A pure function
@@ -379,6 +377,9 @@ static double pick_conv_tile(const ConvArgs &a, bool stem, bool res, int64_t rea
     for (const ConvCost &c : kConvCost) {
         const TileDim d = conv_tile_dim((ConvTile)c.tile);
         if (c.cls != cls || (cls == COST_PLAIN && (conv_bk(a, stem, (ConvTile)c.tile) != d.bk || (a.Cin % 64 != 0 && conv_tile_tail((ConvTile)c.tile) != c.tile))) || (d.bn > a.Cout && d.bn > 32)) continue;
+        // Groups do nothing for the walk of a single slice of 64, they only share the epilogue: from 1.5 workgroups a CU on that is as
+        // fast without (6027..6875 pixels, 64 -> 64: 3.39..3.52 us in four groups, 3.34..3.49 on 32x64; 3136 x 128 3.08, 3.20).
+        if (cls == COST_PLAIN && d.kg > 1 && a.K == 64 && (int64_t)((a.M + d.bm - 1) / d.bm) * ((a.Cout + d.bn - 1) / d.bn) > 384) continue;
         for (int32_t s = 1; s <= (c.splits ? 8 : 1); s *= 2) {
             if ((ov.split_k > 0 && s != ov.split_k && s > 1) || !split_ok(a, stem, (ConvTile)c.tile, s)) continue;
             const double us = conv_cost(c, as, &res, 1, stem, s) + (ov.split_k > 1 && s == 1 ? 1e3 : 0);   // a forced split where it can be had
@@ -927,7 +928,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 {
                     const TileDim tdc = conv_tile_dim(l.tile);
                     const int64_t tiles = ((int64_t)a.M + tdc.bm - 1) / tdc.bm * ((a.Cout + tdc.bn - 1) / tdc.bn);
-                    if (tiles * 4 > (int64_t)kCounterBytes || (int64_t)a.M * a.Cout * 4 >= (1ll << 31)) a.split_k = 1;
+                    if (tiles * conv_counters_per_tile(l.tile) * 4 > (int64_t)kCounterBytes || (int64_t)a.M * a.Cout * 4 >= (1ll << 31)) a.split_k = 1;
                 }
                 a.ktiles_per_split = (ktiles + a.split_k - 1) / a.split_k;
                 a.split_k = (ktiles + a.ktiles_per_split - 1) / a.ktiles_per_split;  // no empty splits
@@ -1162,7 +1163,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         if (l.counters.space == SP_NONE) continue;
         const TileDim d = conv_tile_dim(l.tile);
         p.n_counters = std::max<int32_t>(p.n_counters, l.kind == K_FC ? (l.fc.Out + 15) / 16 + 1
-                                                                     : ((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn));
+                                                                     : ((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn) * conv_counters_per_tile(l.tile));
     }
     // Resident runs: every maximal run of two or more plain convolution launches (direct-to-LDS
     // kernel, whole K per workgroup) becomes one launch whose members keep partition 0's arguments.
@@ -1237,7 +1238,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             if (l.kind != K_CONV || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
             if (!conv_uses_dlds(l.conv, false) || l.ahead_bytes > 0) return false;
             const TileDim d = conv_tile_dim(l.tile);
-            return (int64_t)((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn) <= kPrefetchMaxTiles;
+            return (int64_t)((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn) * d.parts() <= kPrefetchMaxTiles;
         };
         for (int t = 1; t < (int)p.launches.size(); ++t)
             for (const Ref &w : {p.launches[t].w, p.launches[t].w0, p.launches[t].w2, p.launches[t].w3, p.launches[t].wd}) {

@@ -1,8 +1,10 @@
 """The cost model behind the convolution plan (a development tool; its sweep needs an MI355X).
 
 ``sweep`` times every convolution of a set of networks, image sizes and batch sizes on every tile shape and
-split-K factor, one launch at a time inside whole EXECs (cw_exec_timed_launches: each launch finds the caches
-as the launches before it leave them).  ``fit`` turns those times into csrc/plan_cost.inc: per tile shape a
+split-K factor, inside whole EXECs (each launch finds the caches as the launches before it leave them), from the start
+of a launch's first workgroup to that of the next launch: the stamps of a library built for it (`python -m
+paper_2006_02464_amd.build stamps`).  A pair of events around a launch sees nothing below 4.2 us, where more than half of
+a batch-1 plan's launches are.  ``fit`` turns those times into csrc/plan_cost.inc: per tile shape a
 non-negative linear model of the launch's time in the quantities of :func:`features`, least squares of the relative
 error.  The plan compiler evaluates the same model for every convolution it plans and takes the
 cheapest tile (plan.cpp: pick_conv_tile), so any image and batch size is planned the same way; nothing is
@@ -20,17 +22,17 @@ import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 COST = os.path.join(HERE, "csrc", "plan_cost.inc")
-# pixels, channels, K slice of every tile shape, by its number in the library
+# pixels and channels per workgroup and K slice of every tile shape, by its number in the library
 TILES = {0: (128, 128, 64), 1: (128, 64, 64), 2: (64, 64, 64), 3: (64, 32, 64), 4: (32, 64, 64), 5: (32, 32, 64), 8: (256, 64, 64),
          9: (128, 128, 64), 10: (128, 64, 128), 11: (64, 64, 128), 12: (64, 32, 128), 13: (32, 64, 128), 14: (32, 32, 128),
          15: (128, 64, 128), 16: (64, 64, 128), 17: (64, 64, 128), 18: (64, 32, 128), 19: (32, 64, 128), 20: (32, 32, 128),
          21: (32, 32, 128), 22: (128, 64, 64), 23: (64, 64, 64), 24: (32, 32, 64), 25: (256, 128, 64), 26: (128, 256, 64),
          27: (256, 256, 64), 28: (256, 128, 64), 29: (32, 32, 256), 30: (32, 32, 256), 31: (64, 32, 256), 32: (64, 32, 256),
-         33: (32, 64, 256), 34: (32, 64, 256), 35: (64, 64, 256)}
-SPLIT_TILES = (1, 2, 4, 10, 15, 16, 18, 19, 20, 24, 29, 31, 33, 35)
+         33: (32, 64, 256), 34: (32, 64, 256), 35: (64, 64, 256), 36: (16, 16, 128), 37: (32, 16, 128), 38: (16, 32, 128),
+         39: (16, 16, 256), 40: (32, 16, 256)}
+SPLIT_TILES = (1, 2, 4, 10, 15, 16, 18, 19, 20, 24, 29, 31, 33, 35, 36, 37, 38, 39, 40)
 SPLITS = (1, 2, 4, 8)
-EVENT_US = 2.04   # what a pair of events adds to a launch's time
-SPLIT_US = 0.5    # what a split launch costs its EXEC beyond its own time (measured by exchanging tiles in whole EXECs)
+LAUNCH_US = 1.2   # from one launch's last store to the next one's first workgroup
 PLAIN, STAGED, STEM = 0, 1, 2   # kinds of launch: the main kernel, the register-staged one, the first convolution's form
 CONFIGS = (["resnet50:224x224:%d" % b for b in (1, 2, 3, 4, 8, 12, 16)] + ["resnet50:193x161:%d" % b for b in (1, 3, 7)] +
            ["resnet50:97x97:%d" % b for b in (1, 4, 11)] + ["resnet50:160x140:9", "resnet50:64x64:2", "resnet50:210x80:6"] +
@@ -79,10 +81,26 @@ def nnls(A, y, sweeps=4000):
 
 
 def sweep(path, configs):
+    import ctypes
+
     import torch
 
-    from . import measure
+    from . import binding, build, measure
     from .binding import Context
+    binding.LIB_PATH = build.STAMPED_LIB
+    stamps = ctypes.CDLL(binding.lib()._name)
+    assert stamps.cw_stamps_reset() == 0
+
+    def times(convs):
+        """Microseconds of the launches since the last reset, up to the first workgroup of the next one where that is stamped too."""
+        ends = []
+        for i, l in enumerate(convs):
+            t = np.zeros((min(16384, l["grid_x"] * l["grid_y"] * l["grid_z"]), 2), np.uint64)
+            assert stamps.cw_stamps_read(i, len(t), ctypes.c_void_p(t.ctypes.data)) == 0 and t.all()
+            ends.append((t[:, 0].min() / 100.0, t[:, 1].max() / 100.0))
+        return [ends[i + 1][0] - ends[i][0] if i + 1 < len(convs) and convs[i + 1]["index"] == l["index"] + 1 else ends[i][1] - ends[i][0] + LAUNCH_US
+                for i, l in enumerate(convs)]
+
     lists = {"mobilenet": measure.mobilenet_ops, "densenet": measure.dense_ops, "inception": measure.inception_ops}
     with open(path, "w") as out:
         for cfg in configs:
@@ -107,11 +125,18 @@ def sweep(path, configs):
                         blob = pinned_like(measure.resnet_blob(ctx, mid, 0, "fp16"))
                     ctx.load_weights(mid, blob, stream)
                     slot = ctx.input(mid, batch, x, stream)
-                    us = np.median([ctx.exec_timed_launches(mid, batch, slot, stream) for _ in range(9)], axis=0) - EVENT_US
+                    convs = [dict(l, index=i) for i, l in enumerate(ctx.plan(mid, batch)) if l["kind"] == 1 and l["tile_k"] >= 64]   # the main kernel's
+                    us = []
+                    for _ in range(7):
+                        ctx.exec(mid, batch, slot, stream)
+                        assert stamps.cw_stamps_reset() == 0
+                        ctx.exec(mid, batch, slot, stream)
+                        torch.cuda.synchronize()
+                        us.append(times(convs))
                     ctx.release(slot)
                     ctx.unload_weights(mid)
-                    for l, t in zip(ctx.plan(mid, batch), us):
-                        if l["kind"] == 1:
+                    for l, t in zip(convs, np.median(us, axis=0)):
+                        if l["pair_op"] < 0 and l["fused_op"] < 0:
                             o = ops[l["op_index"]]
                             out.write(json.dumps(dict(M=l["gemm_m"], N=l["gemm_n"], K=l["gemm_k"], kh=o[3], kw=o[4], stride=o[5], cin=o[1],
                                                       res=int(o[8] >= 0), stem=int(l["op_index"] == 0), tile=l["conv_tile"],
@@ -140,8 +165,9 @@ def fit(paths):
     groups = collections.defaultdict(list)
     for (shape, cls), times in shapes.items():
         for (tile, split), us in times.items():
-            groups[cls, tile].append((features(*shape, cls, tile, split), us + SPLIT_US * (split > 1), split))
+            groups[cls, tile].append((features(*shape, cls, tile, split), us, split))
     coef = {}
+    kept = [l.rstrip() for l in open(COST) if l.startswith("{") and int(l[1]) not in {cls for cls, _ in groups}]   # no such launch in the files
     lines = ["// Generated by tune.py from launch times measured on an MI355X: per kind of launch (COST_*) and tile",
              "// shape the microseconds per unit of each feature (conv_cost in plan.cpp).",
              "// {kind, tile, K may be split, {1, general addressing, K slices, of these with general addressing, slices of",
@@ -152,6 +178,7 @@ def fit(paths):
         splits = int(any(r[2] > 1 for r in rows))
         lines.append("{%d, %d, %d, {%s}}," % (cls, tile, splits, ", ".join("%.4gf" % v if "." in "%.4g" % v or "e" in "%.4g" % v else "%.4g.f" % v for v in c)))
         print("kind %d tile %2d: %4d launches, rms relative error %.3f" % (cls, tile, len(y), np.sqrt((((A @ c) / y - 1) ** 2).mean())))
+    lines += kept
     best = chosen = 0.0
     for (shape, cls), times in shapes.items():
         best += min(times.values())

@@ -1,5 +1,5 @@
-"""The tiles with K slices of 256 (forced on every layer) and the plan's own tile choice at ragged sizes: every
-layer teacher-forced against the CPU oracle."""
+"""The tiles with K slices of 256 or in parts (forced on every layer) and the plan's own tile choice at ragged sizes:
+every layer teacher-forced against the CPU oracle."""
 import pytest
 
 from gpu_common import TOL, Case, rel_err_per_sample
@@ -68,6 +68,29 @@ def test_k256_tiles(worker, name, split_k, dtype):
 def test_tiles_whose_wave_groups_finish_together(worker, tile, hw, dtype):
     """64x64, 64x32, 32x64 and 32x32 in four groups, 32x32 in eight (half of them finish nothing), K slices of 64 and 128."""
     run(worker, hw, dtype, 3, tile)
+
+
+@pytest.mark.parametrize("tile", [36, 37, 38, 39, 40])
+@pytest.mark.parametrize("hw,dtype,batch,split_k", [(45, "fp16", 3, 1), (33, "bf16", 3, 1), (9, "fp16", 1, 1), (45, "fp16", 3, 3), (9, "bf16", 1, 2)])
+def test_tiles_in_parts(worker, tile, hw, dtype, batch, split_k):
+    """32x32 in quarters and halves on workgroups of their own, slices of 128 and 256, whole and split K."""
+    small = [l for l in run(worker, hw, dtype, batch, tile, split_k) if l["kind"] == 1 and l["conv_tile"] == tile]
+    assert any(l["split_k"] > 1 for l in small) == (split_k > 1)
+    assert {l["gemm_k"] for l in small} == {256, 2304, 4608, 512}
+
+
+@pytest.mark.parametrize("tile", [36, 37, 38])
+def test_pair_launches_on_tiles_in_parts(worker, tile):
+    """A 3x3 of stride 2 and the projection beside it in one launch, the last tile of pixels part full (3 x 6 x 6 = 108)."""
+    ops = OPS[:1] + [O(T.CONV, 64, 128, 3, 3, 2, 1, 1, -1, 0), O(T.CONV, 128, 256, 3, 3, 2, 1, 1, -1, 1), O(T.CONV, 128, 256, 1, 1, 2, 0, 0, -1, 1),
+                     O(T.CONV, 256, 256, 3, 3, 1, 1, 1, 3, 2), O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 4),
+                     O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 5), O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 6)]
+    worker.ctx.set_plan_table([(108, 256, 1152, 3, 2, tile, 1), (108, 256, 128, 1, 2, tile, 1)])
+    try:
+        plan = run(worker, 45, "fp16", 3, ops=ops)
+    finally:
+        worker.ctx.set_plan_table([])
+    assert [l["conv_tile"] for l in plan if l["pair_op"] >= 0] == [tile]
 
 
 @pytest.mark.parametrize("tile,split_k", [("64x64", 1), ("64x64", 3), ("64x64k128", 1), ("32x32k128g4", 2), ("32x32k256g4", 1), ("128x128w8", 1)])
