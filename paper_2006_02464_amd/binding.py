@@ -98,6 +98,7 @@ SIGNATURES = {
     "cw_plan_num_launches": (c_int32, [c_void_p, c_int32, c_int32]),
     "cw_plan_launch_info": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(cw_launch_info)]),
     "cw_plan_launch_ahead": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(c_int32), POINTER(c_int64)]),
+    "cw_plan_launch_joined": (c_int32, [c_void_p, c_int32, c_int32, c_int32]),
     "cw_exec_timed_launches": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_int32, c_void_p, c_void_p]),
     "cw_debug_read_op": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_void_p, c_size_t]),
     "cw_set_debug_keep": (c_int32, [c_void_p, c_int32]),
@@ -317,6 +318,10 @@ class Context:
         wgs, nbytes = c_int32(0), c_int64(0)
         self._check(lib().cw_plan_launch_ahead(self._h, model_id, batch, index, byref(wgs), byref(nbytes)))
         return wgs.value, nbytes.value
+
+    def plan_launch_joined(self, model_id, batch, index):
+        """Whether plan entry `index` is computed inside the first convolution's launch."""
+        return bool(self._check(lib().cw_plan_launch_joined(self._h, model_id, batch, index)))
 
     def plan(self, model_id, batch):
         return [self.plan_launch_info(model_id, batch, i) for i in range(self.plan_num_launches(model_id, batch))]

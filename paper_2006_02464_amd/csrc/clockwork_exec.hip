@@ -208,6 +208,20 @@ char *resolve(cw_ctx *c, const ModelRt *m, const Bases &b, const Ref &r) {
 
 hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, hipStream_t st) {
     const DType dt = m->m.dtype;
+    if (l.in_head == 1) return hipSuccess;   // computed by the first convolution's launch
+    if (l.in_head == 2) {
+        HeadArgs a = l.head;
+        a.x = reinterpret_cast<const float *>(resolve(c, m, s, l.head_x));
+        a.w = resolve(c, m, s, l.w);
+        a.bias = reinterpret_cast<const float *>(resolve(c, m, s, l.bias));
+        a.y = resolve(c, m, s, l.head_y);
+        a.w1 = resolve(c, m, s, l.head_w1);
+        a.bias1 = reinterpret_cast<const float *>(resolve(c, m, s, l.head_bias1));
+        a.y1 = resolve(c, m, s, l.head_y1);
+        a.zero = reinterpret_cast<int32_t *>(s.workspace);
+        a.n_zero = s.clear_counters;
+        return launch_head(dt, a, st);
+    }
     switch (l.kind) {
         case K_CAST_INPUT: {
             CastArgs a = l.cast;
@@ -470,6 +484,7 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
 }
 
 bool slot_free(const Launch &l) {
+    if (l.in_head) return false;
     for (const Ref *r : {&l.x, &l.w, &l.bias, &l.res, &l.y, &l.partial, &l.counters, &l.probs, &l.y3})
         if (r->space == SP_SLOT_INPUT || r->space == SP_SLOT_LOGITS || r->space == SP_SLOT_PROBS) return false;
     return true;
@@ -1113,8 +1128,8 @@ int32_t cw_exec_static(cw_ctx *c, int32_t model_id, int32_t batch, const float *
     b.input = const_cast<char *>(reinterpret_cast<const char *>(dev_input_nchw));
     b.logits = reinterpret_cast<char *>(dev_logits);
     b.probs = reinterpret_cast<char *>(dev_probs);
-    // The arena keeps what the last call left: the arrival counters at its start must be zero.  The cast of the input,
-    // which every plan begins with, clears those that the launches behind it use (a launch of its own took 1.2-2 us).
+    // The arena keeps what the last call left: the arrival counters at its start must be zero.  The cast of the input
+    // (or the launch that computes it), which every plan begins with, clears those that the launches behind it use (a launch of its own took 1.2-2 us).
     b.clear_counters = p->n_counters;
     for (const Launch &l : p->launches) {
         const hipError_t e = issue(c, m, b, l, st);
@@ -1316,6 +1331,15 @@ int32_t cw_plan_launch_ahead(cw_ctx *c, int32_t model_id, int32_t batch, int32_t
     *workgroups = conv_prefetch_wgs(lines);
     *bytes = (int64_t)lines * 128;
     return CW_OK;
+}
+
+int32_t cw_plan_launch_joined(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index) {
+    ModelRt *m = get_model(c, model_id);
+    if (!m) return set_err(c, CW_ERR_INVALID, "unknown model id");
+    Plan *p = get_plan(m, batch);
+    if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
+    if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
+    return p->launches[index].in_head == 1;
 }
 
 int32_t cw_debug_read_op(cw_ctx *c, int32_t model_id, int32_t batch, int32_t op_index, float *host_out, size_t cap) {

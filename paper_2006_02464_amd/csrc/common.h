@@ -223,6 +223,23 @@ struct CastArgs {
     int32_t n_zero;
 };
 
+// The head of a network as one launch (kernels_head.hip): first convolution (kh x kh, stride 2, packed filter rows of 8 taps x 4
+// channels) over the fp32 images, with a 3x3 stride-2 pad-1 max pool and a 1x1 convolution cout -> n1 behind it or without.
+struct HeadArgs {
+    const float *x;       // NCHW fp32 [B][C][H][W]
+    const void *w;        // packed [cout][8][8][4]
+    const float *bias;
+    void *y;              // NHWC: the pooled tensor, or the convolution's output
+    const void *w1;       // packed [n1][cout]
+    const float *bias1;
+    void *y1;             // NHWC [B][Po][Qo]
+    int32_t *zero;        // n_zero words the launch also clears
+    int32_t n_zero, B, C, H, W, pad, Ho, Wo, Po, Qo, act, act1, ldy, ldy1;
+    int32_t kh, cout, n1, pool;
+    int32_t tiles_h, tiles_w;   // tiles of an image (set by the launch code)
+};
+constexpr int kHeadTallFrom = 256;   // pooled tiles of 7 x 8 from so many on (one a CU), 3 x 8 below, which is the shorter chain
+
 struct PoolArgs {
     const void *x;  // NHWC
     void *y;        // NHWC (maxpool) / fp32 [B][C] (global average)
@@ -314,6 +331,8 @@ hipError_t launch_conv_pair(DType dt, ConvTile tile, const ConvArgs &a0, const C
 bool conv_pair_tile_ok(ConvTile tile);
 void conv_pair_grid(ConvTile tile, const ConvArgs &a0, const ConvArgs &a1, dim3 *grid, int *block);
 hipError_t launch_cast_input(DType dt, const CastArgs &a, hipStream_t s);
+bool head_form_ok(int kh, int cout, bool pool, int n1);
+hipError_t launch_head(DType dt, const HeadArgs &a, hipStream_t s);
 hipError_t launch_maxpool(DType dt, const PoolArgs &a, hipStream_t s);
 hipError_t launch_gavgpool(DType dt, const PoolArgs &a, hipStream_t s);
 // A 3x3 max pool over 64 channels and the 1x1 stride-1 convolution 64 -> 64 or 128 that reads it, in one launch;

@@ -1232,6 +1232,35 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         }
         p.launches.swap(out);
     }
+    // The head as one launch (kernels_head.hip).  The convolution's own output is then never stored where a pool follows, so
+    // nothing else may read it, and debug retention keeps the launches apart.
+    if (ov.fuse && !ov.keep_all && ov.tile < 0 && ov.split_k <= 0 && p.launches.size() > 3) {
+        Launch &lc = p.launches[0], &ls = p.launches[1], &lp = p.launches[2];
+        const cw_op &o = m.ops[0];
+        int readers = 0;
+        for (const cw_op &q : m.ops)
+            readers += (q.input_from == 0) + ((q.op == CW_OP_CONV || q.op == CW_OP_CONCAT) && q.residual_from == 0);
+        const bool stem = lc.kind == K_CAST_INPUT && ls.kind == K_CONV && ls.stem && ls.op_index == 0 && o.kh == o.kw && o.stride == 2 && o.residual_from < 0 &&
+                          ls.conv.khp == 8 && ls.conv.kwp == 8 && ls.conv.split_k == 1 && !ls.tile_fixed;
+        const bool pool = lp.kind == K_MAXPOOL && m.ops[lp.op_index].input_from == 0 && readers == 1 && lp.pool.k == 3 && lp.pool.stride == 2 && lp.pool.pad == 1;
+        const int n1 = pool && lp.pool_bm > 0 ? lp.conv.Cout : 0;
+        if (stem && head_form_ok(o.kh, o.cout, pool, n1)) {
+            HeadArgs &h = ls.head;
+            h.B = batch; h.C = m.in_c; h.H = m.in_h; h.W = m.in_w; h.pad = o.pad; h.Ho = ls.conv.Ho; h.Wo = ls.conv.Wo;
+            h.kh = o.kh; h.cout = o.cout; h.act = o.relu; h.pool = pool; h.n1 = n1;
+            h.ldy = pool ? o.cout : conv_ldy(ls.conv);
+            ls.head_x = lc.x;
+            ls.head_y = pool ? lp.y : ls.y;
+            if (pool) { h.Po = lp.pool.Ho; h.Qo = lp.pool.Wo; }
+            if (n1 > 0) {
+                h.act1 = lp.conv.relu; h.ldy1 = conv_ldy(lp.conv);
+                ls.head_w1 = lp.w; ls.head_bias1 = lp.bias; ls.head_y1 = lp.y2;
+            }
+            lc.in_head = 1;
+            ls.in_head = 2;
+            if (pool) lp.in_head = 1;
+        }
+    }
     // Weights are read ahead by the nearest of the four launches before the one that uses them which has CUs to spare.
     {
         auto host = [&](const Launch &l) {

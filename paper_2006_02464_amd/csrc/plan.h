@@ -63,6 +63,11 @@ struct Launch {
     // tile shape (res_variant), tiles per partition and the members it waits for; `w` of the
     // resident launch itself points at the program's place in the model's weight pages.
     std::vector<Launch> members;
+    // Input cast, first convolution and (if it follows) max pool issued as one launch: 2 = the convolution's entry, which
+    // issues it, 1 = the others, which then issue nothing.
+    int32_t in_head = 0;
+    HeadArgs head{};
+    Ref head_x, head_y, head_w1, head_bias1, head_y1;
     int32_t res_variant = 0, res_tiles = 0, res_dep[2] = {-1, -1}, res_flag_base = 0;
     long long res_ps_x = 0, res_ps_y = 0, res_ps_res = 0;
     int32_t res_flags_per_part = 0;

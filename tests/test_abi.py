@@ -312,6 +312,32 @@ def test_max_pool_with_the_1x1_behind_it(ctx):
     assert [l["fused_op"] for l in ctx.plan(m18, 16) if l["kind"] == 3] == [-1]
 
 
+def test_entries_joined_into_the_first_convolutions_launch(ctx):
+    """Input cast and max pool are computed by the first convolution's launch where it has the form: not with fusion off, a
+    forced tile, debug retention, another reader of the convolution's output, or another filter."""
+    def joined(define):
+        m = define()
+        return [i for i in range(ctx.plan_num_launches(m, 1)) if ctx.plan_launch_joined(m, 1, i)]
+    r50 = lambda: ctx.model_define_resnet(50, 224, 224)
+    assert joined(r50) == [0, 2] and joined(lambda: ctx.model_define_resnet(18, 64, 64)) == [0, 2]
+    for on, off in ((lambda: ctx.set_fusion(0), lambda: ctx.set_fusion(1)), (lambda: ctx.set_debug_keep(True), lambda: ctx.set_debug_keep(False)),
+                    (lambda: ctx.set_plan_override(2, 0), lambda: ctx.set_plan_override(-1, 0)), (lambda: ctx.set_plan_override(-1, 2), lambda: ctx.set_plan_override(-1, 0))):
+        on()
+        try:
+            assert joined(r50) == []
+        finally:
+            off()
+    tail = lambda k, c: [(2, c, c, 0, 0, 1, 0, 0, -1, k), (3, c, 10, 1, 1, 1, 0, 0, -1, k + 1), (4, 10, 10, 0, 0, 1, 0, 0, -1, k + 2)]
+    net = lambda *ops: (lambda: ctx.model_define([tuple(o) for o in ops] + tail(len(ops) - 1, 256), 3, 64, 64, batch_sizes=(1,)))
+    stem, pool = (0, 3, 64, 7, 7, 2, 3, 1, -1, -1), (1, 64, 64, 3, 3, 2, 1, 0, -1, 0)
+    assert joined(net(stem, pool, (0, 64, 256, 1, 1, 1, 0, 1, -1, 1))) == [0, 2]
+    assert joined(net(stem, pool, (0, 64, 256, 1, 1, 2, 0, 1, -1, 0), (0, 64, 256, 1, 1, 1, 0, 1, 2, 1))) == []       # the pool is not the only reader
+    assert joined(net(stem, (1, 64, 64, 2, 2, 2, 0, 0, -1, 0), (0, 64, 256, 1, 1, 1, 0, 1, -1, 1))) == []             # a 2x2 pool
+    assert joined(net((0, 3, 64, 5, 5, 2, 2, 1, -1, -1), pool, (0, 64, 256, 1, 1, 1, 0, 1, -1, 1))) == []             # a 5x5 filter
+    assert joined(net((0, 3, 32, 3, 3, 2, 1, 1, -1, -1), (0, 32, 256, 1, 1, 1, 0, 1, -1, 0))) == [0]                  # 3x3 of 32 channels, no pool
+    assert joined(net((0, 3, 32, 3, 3, 1, 1, 1, -1, -1), (0, 32, 256, 1, 1, 1, 0, 1, -1, 0))) == []                   # stride 1
+
+
 def test_depthwise_with_the_1x1_behind_it(ctx):
     """MobileNet's first two depthwise-separable blocks (32 and 64 channels) are one launch each where the launch has
     96 workgroups of 64 pixels; the 128-channel ones and everything behind them stay two launches."""
