@@ -164,3 +164,23 @@ def test_depthwise_shapes_off_the_mobilenet_path(worker):
         ref = case.oracle(x)["logits"]
         assert rel_err_per_sample(logits, ref).max() <= TOL
         ctx.unload_weights(mid)
+
+
+@pytest.mark.parametrize("batch", [32, 33])
+def test_depthwise_3x3_at_the_line_between_its_two_forms(worker, batch):
+    """32x32x64 at batch 32 is 1024 workgroups, which all run at once (all taps requested together), at batch 33 more (tap after tap)."""
+    O = T.Op
+    ops = [O(T.CONV, 3, 64, 3, 3, 1, 1, 1, -1, -1), O(T.CONV, 64, 64, 3, 3, 1, 1, 1, 0, 0, 0, 64), O(T.CONV, 64, 256, 1, 1, 2, 0, 1, -1, 1),
+           O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 2), O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 3), O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 4)]
+    case = Case(ops, 32, seed=5, dtype="fp16", dist="normal")
+    worker.ctx.set_debug_keep(True)
+    try:
+        mid = worker.ctx.model_define(case.ops, 3, 32, 32, batch_sizes=(batch,), dtype="fp16")
+    finally:
+        worker.ctx.set_debug_keep(False)
+    assert [l["grid_x"] for l in worker.ctx.plan(mid, batch) if l["name"].startswith("dwconv")] == [32 * batch]
+    worker.load(mid, case.blob)
+    x = case.images(0, batch)
+    worker.infer(mid, x, classes=10)
+    check_every_launch(worker, case, mid, batch, x)
+    worker.ctx.unload_weights(mid)
