@@ -29,18 +29,79 @@ extern unsigned cw_stamp_next;
 template <int BM, int BN, int MT>
 constexpr int conv_parts() { return MT == 16 ? (32 / BM) * (32 / BN) : 1; }
 
+// What a form of the kernel reads of ConvArgs beyond the leading scalars.  The runtime copies a launch's arguments to the device
+// by the byte: 320 of them cost the issuing thread 0.4 us more than 128, as much as a ninth of the launch.
+template <int MODE, bool SPLITK, bool FUSED>
+struct alignas(64) ConvRest {   // general addressing: one line of geometry, then what is needed late
+    int32_t B, H, W, Ho, Wo, kh, kw, stride, pad;
+    FastDiv wo_div, ho_div;
+    int32_t Cout2;
+    const float *bias;
+    const void *w2;
+    int32_t split_k, ktiles_per_split;
+    float *partial;
+    int32_t *counters;
+    void pack(const ConvArgs &a) {
+        B = a.B; H = a.H; W = a.W; Ho = a.Ho; Wo = a.Wo; kh = a.kh; kw = a.kw; stride = a.stride; pad = a.pad; wo_div = a.wo_div; ho_div = a.ho_div;
+        Cout2 = a.Cout2; bias = a.bias; w2 = a.w2; split_k = a.split_k; ktiles_per_split = a.ktiles_per_split; partial = a.partial; counters = a.counters;
+    }
+    __device__ __forceinline__ void unpack(ConvArgs &a) const {
+        a.B = B; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.kh = kh; a.kw = kw; a.stride = stride; a.pad = pad; a.wo_div = wo_div; a.ho_div = ho_div;
+        a.bias = bias;
+        if constexpr (SPLITK) { a.split_k = split_k; a.ktiles_per_split = ktiles_per_split; a.partial = partial; a.counters = counters; }
+    }
+};
+template <int MODE>
+struct alignas(64) ConvRestGemm {   // 1x1 stride 1: B*H*W = M, one tap
+    const float *bias;
+    const void *w2;
+    int32_t Cout2;
+    int32_t split_k;
+    union {
+        struct { long long zs_x, zs_w, zs_y; };   // batched form
+        struct { float *partial; int32_t *counters; long long ktiles_per_split; };
+    };
+    void pack(const ConvArgs &a) {
+        bias = a.bias; w2 = a.w2; Cout2 = a.Cout2; split_k = a.split_k;
+        if (a.split_k > 1) { partial = a.partial; counters = a.counters; ktiles_per_split = a.ktiles_per_split; }
+        else { zs_x = a.zs_x; zs_w = a.zs_w; zs_y = a.zs_y; }
+    }
+    template <bool SPLITK>
+    __device__ __forceinline__ void unpack_gemm(ConvArgs &a) const {
+        a.B = 1; a.H = 1; a.W = a.M; a.Ho = 1; a.Wo = a.M; a.kh = 1; a.kw = 1; a.stride = 1; a.pad = 0;
+        a.bias = bias;
+        if constexpr (SPLITK) { a.split_k = split_k; a.ktiles_per_split = (int)ktiles_per_split; a.partial = partial; a.counters = counters; }
+    }
+};
+template <bool SPLITK>
+struct alignas(64) ConvRest<MODE_GEMM, SPLITK, false> : ConvRestGemm<MODE_GEMM> {
+    __device__ __forceinline__ void unpack(ConvArgs &a) const { this->template unpack_gemm<SPLITK>(a); }
+};
+template <bool SPLITK>
+struct alignas(64) ConvRest<MODE_TAIL, SPLITK, false> : ConvRestGemm<MODE_TAIL> {
+    __device__ __forceinline__ void unpack(ConvArgs &a) const { this->template unpack_gemm<SPLITK>(a); }
+};
+template <int MODE>
+struct ConvRest<MODE, false, true> : ConvArgs {   // the fused form reads all of it
+    void pack(const ConvArgs &a) { static_cast<ConvArgs &>(*this) = a; }
+    __device__ __forceinline__ void unpack(ConvArgs &a) const { a = *this; }
+};
+
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, int MT = 32>
 __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
                                                                                  int M, int K, int cout_ldy, int cin_ldx, int nb, int relu,
-                                                                                 const ConvArgs rest CW_STAMP_ARG) {
+                                                                                 const ConvRest<MODE, SPLITK, FUSED> rest CW_STAMP_ARG) {
     CW_STAMP_BEGIN
     // The ten leading arguments (14 dwords, all the user SGPRs there are beside the argument
-    // pointer) repeat fields of `rest`: this file is compiled with kernel-argument preloading, so
+    // pointer): this file is compiled with kernel-argument preloading, so
     // they are in SGPRs when a wave starts and the first address arithmetic does not wait for a
     // load of the argument block.  Everything else is read from `rest` when it is needed.
     // Cout and Cin carry the pixel pitches of y and x in their upper halves, so that the 1x1 form
     // still needs nothing beyond the preloaded scalars for its addressing.
-    ConvArgs a = rest;
+    ConvArgs a;
+    a.x = x; a.w = w; a.res = res; a.y = y;
+    a.M = M; a.K = K;
+    rest.unpack(a);
     a.x = x; a.w = w; a.res = res; a.y = y;
     a.M = M; a.K = K; a.Cout = cout_ldy & 0xffff; a.Cin = cin_ldx & 0xffff; a.nb = nb; a.relu = relu;
     a.ld = (int)(((unsigned)cin_ldx >> 16) | ((unsigned)cout_ldy & 0xffff0000u));
@@ -93,6 +154,8 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     constexpr unsigned PARTS = conv_parts<BM, BN, MT>();
     if (a.nz <= 1 && grid.z != PARTS) return hipErrorInvalidValue;
     if (PARTS > 1) grid = dim3(grid.x * PARTS, grid.y, 1);   // the workgroups that read ahead come behind all the parts
+    ConvRest<MODE, SPLITK, false> rest;
+    rest.pack(a);
     constexpr int NS = RingDepth<BM, BN, BK>::value;
     constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
     static_assert(NS * stage_bytes <= 160 * 1024, "ring does not fit the LDS");
@@ -105,7 +168,7 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     // at the end needs its own room)
     if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && a.nz <= 1) grid.x += conv_prefetch_wgs(a.Cout2);
     const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG >= 4 ? KG : KG - 1) * BM * BN * 4);
-    kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a CW_STAMP_PASS);
+    kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, rest CW_STAMP_PASS);
     return hipGetLastError();
 }
 

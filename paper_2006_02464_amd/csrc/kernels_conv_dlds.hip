@@ -1,5 +1,7 @@
 // Launches of the direct-to-LDS implicit-GEMM convolution: checks, dispatch and the fused / pair forms.  The per-tile
 // body is in conv_dlds_body.h, the plain forms' tiles in conv_dlds_tiles.h.
+#include <cstring>
+
 #include "conv_dlds_launch.h"
 
 namespace cw {
@@ -8,8 +10,13 @@ namespace cw {
 // projection shortcut beside it) in one launch: the first nb0 workgroups take the first, the rest
 // the second.  Same instantiation for both (general addressing mode, no split-K); one dispatch,
 // one set-up latency and one tail instead of two.
+struct alignas(64) ConvLines { unsigned long long v[16]; };   // of each its first two argument lines, which hold all it reads
+static_assert(offsetof(ConvArgs, khp) == sizeof(ConvLines), "argument lines");
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int KG, int MT>
-__global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_pair_kernel(const ConvArgs a0, const ConvArgs a1) {
+__global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_pair_kernel(const ConvLines l0, const ConvLines l1) {
+    ConvArgs a0, a1;
+    __builtin_memcpy(&a0, &l0, sizeof l0);
+    __builtin_memcpy(&a1, &l1, sizeof l1);
     const int nb0 = conv_nb_tiles(a0.nb) * conv_parts<BM, BN, MT>();
     if ((int)blockIdx.x < nb0)
         conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, false, MT>(a0, blockIdx.x, a0.nb);
@@ -32,7 +39,9 @@ static hipError_t launch_fused_one(const ConvArgs &a_in, hipStream_t s) {
     if (attr != hipSuccess) return attr;
     if (a.Cout2 % fused_chunk(BN, KG) != 0) return hipErrorInvalidValue;
     if (a.w3 && BN / (2 * KG) < 32) return hipErrorInvalidValue;   // the third layer needs whole 32-channel tiles per wave
-    kern<<<dim3((a.M + BM - 1) / BM, 1, 1), 256 * KG, need, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, a CW_STAMP_PASS);
+    ConvRest<MODE, false, true> rest;
+    rest.pack(a);
+    kern<<<dim3((a.M + BM - 1) / BM, 1, 1), 256 * KG, need, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, rest CW_STAMP_PASS);
     return hipGetLastError();
 }
 
@@ -95,7 +104,10 @@ static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, 
     if (!conv_panel_ok(a0, TN, nb0) || !conv_panel_ok(a1, TN, nb1)) return hipErrorInvalidValue;
     a0.nb = conv_pack_nb((int)nb0, a0.panel_log2);
     a1.nb = conv_pack_nb((int)nb1, a1.panel_log2);
-    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), 64 * WARPS_M * WARPS_N * KG, used, s>>>(a0, a1);
+    ConvLines l0, l1;
+    memcpy(&l0, &a0, sizeof l0);
+    memcpy(&l1, &a1, sizeof l1);
+    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), 64 * WARPS_M * WARPS_N * KG, used, s>>>(l0, l1);
     return hipGetLastError();
 }
 
