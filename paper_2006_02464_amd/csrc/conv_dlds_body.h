@@ -59,6 +59,14 @@ static __device__ __forceinline__ u32x4 make_desc(const void *p, unsigned bytes)
     return u32x4{(unsigned)v, (unsigned)(v >> 32) & 0xffffu, bytes, 0x00020000u};
 }
 
+// t / d of workgroup-uniform values, 0 <= t, 0 < d: exact below 2^21, where t/d's rounding errors (a few 2^-23 of it) stay
+// below the half d-th that separates (t + 0.5)/d from the integers; the compiler's integer division takes three
+// times as long, and every address waits for it (0.5 % of an EXEC at batch 1).
+static __device__ __forceinline__ int tile_div(int t, int d) {
+    if (__builtin_expect(t >= 1 << 21, 0)) return t / d;
+    return __builtin_amdgcn_readfirstlane((int)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)d)));
+}
+
 extern __shared__ __attribute__((aligned(16))) unsigned char cw_dyn_lds[];
 
 // LDS bytes of the fused second layer (see the end of the kernel): the first layer's tile, two
@@ -143,7 +151,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const int tiles_n = a.Cout / BN + (a.Cout % BN != 0);
     int tile_m, tile_n;
     if (RAW || FUSED || panel == 0) {   // uniform
-        tile_m = tile_id / tiles_n;
+        tile_m = tile_div(tile_id, tiles_n);
         tile_n = tile_id - tile_m * tiles_n;
     } else {
         // panel after panel of tiles_n >> panel channel tiles, row by row inside a panel
@@ -175,13 +183,34 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const u32x4 dx = make_desc(static_cast<const char *>(a.x) - x_shift, x_bytes + x_shift);
     const u32x4 dw = make_desc(a.w, (unsigned)a.Cout * a.K * 2u);
 
+    // With general addressing the first slice's weights are requested before the pixel arithmetic and the argument line that it
+    // waits for: ResNet-18 batch 8 138.9 -> 134.6 us, ResNet-50 batch 1 201.1 -> 198.4.  (All weights of the prologue there make the
+    // first slice wait for the later ones': ResNet-18 3 % slower.)
+    constexpr bool WFIRST = !GEMM && !FUSED;
+    const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)
+    unsigned w_off[W_PER], w_last = 0;   // bit j of w_last: piece j is also in the last slice (MODE_TAIL)
+#pragma unroll
+    for (int j = 0; j < W_PER; ++j) {
+        const int cid = tid + j * NT;
+        const int row = cid / CPR;
+        const int c = (cid % CPR) ^ swz_key<BK>(row);
+        const int n = n0 + row;
+        w_off[j] = n < a.Cout ? ((unsigned)n * a.K + c * 8) * 2u : kOob;
+        if (MODE == MODE_TAIL && c * 8 < k_last) w_last |= 1u << j;
+    }
+    if constexpr (WFIRST) {
+        if (nsteps > 0) {   // uniform
+#pragma unroll
+            for (int j = 0; j < W_PER; ++j) load_to_lds(dw, w_off[j], (unsigned)kt0 * (BK * 2u), lds_base + (unsigned)wave * 1024u + BM * BK * 2 + j * (NT * 16));
+        }
+    }
+
     // This thread's pieces of a slice.  Piece j is LDS position cid = tid + j*NT of the operand's
     // [rows][CPR chunks] stage: row cid/CPR, chunk position cid%CPR, holding logical chunk
     // (cid%CPR) ^ key(row).  Per piece, fixed for the whole K walk: the byte offset of that chunk
     // at the filter's centre pixel, and which taps fall inside the image (bit r*kw+s; for the
     // 1x1 stride-1 case bit 0 = the pixel exists).
     unsigned x_voff[X_PER], x_mask[X_PER];
-    const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)
     if constexpr (GEMM) {
 #pragma unroll
         for (int j = 0; j < X_PER; ++j) {
@@ -240,16 +269,6 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             x_mask[j] = ri.y;
         }
     }
-    unsigned w_off[W_PER], w_last = 0;   // bit j of w_last: piece j is also in the last slice (MODE_TAIL)
-#pragma unroll
-    for (int j = 0; j < W_PER; ++j) {
-        const int cid = tid + j * NT;
-        const int row = cid / CPR;
-        const int c = (cid % CPR) ^ swz_key<BK>(row);
-        const int n = n0 + row;
-        w_off[j] = n < a.Cout ? ((unsigned)n * a.K + c * 8) * 2u : kOob;
-        if (MODE == MODE_TAIL && c * 8 < k_last) w_last |= 1u << j;
-    }
     if constexpr (FUSED) {
         float *sb = reinterpret_cast<float *>(cw_dyn_lds + BIAS_OFF);
         if (tid < BN) sb[tid] = bias1_v;
@@ -300,10 +319,10 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             if (++fs == a.kw) { fs = 0; ++fr; }
         }
     };
-    auto issue = [&](int kt, int stage) {
+    auto issue = [&](int kt, int stage, auto pieces) {
         issue_begin(kt, stage);
 #pragma unroll
-        for (int idx = 0; idx < LOADS; ++idx) issue_piece(idx);
+        for (int idx = 0; idx < decltype(pieces)::value; ++idx) issue_piece(idx);
         issue_end();
     };
 
@@ -372,7 +391,10 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const int ahead = min(NS - 1, nsteps);
 #pragma unroll
     for (int u = 0; u < NS - 1; ++u)
-        if (u < ahead) issue(kt0 + u, u);  // uniform
+        if (u < ahead) {  // uniform
+            if (WFIRST && u == 0) issue(kt0, 0, std::integral_constant<int, X_PER>{});
+            else issue(kt0 + u, u, std::integral_constant<int, LOADS>{});
+        }
 
     // Steady state: slice kt sits in stage `cur`; behind it NS-2 more slices are in flight.  After
     // the barrier every wave has finished the MFMAs of slice kt-1, so its stage (the one before
