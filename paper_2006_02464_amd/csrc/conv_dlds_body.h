@@ -123,19 +123,22 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)cw_dyn_lds;
 
     const int tid = threadIdx.x;
-    // Fused form: both layers' biases are requested now, with ordinary loads, and go to LDS at the
-    // end of the set-up arithmetic below, which covers their latency; no counted load is in
-    // flight yet at that point (visible to every wave after the first barrier).
+    // Fused form: the layers' biases are requested now, without a branch (what is missing is a load out of range), and go to LDS
+    // behind the K walk, by when they have long arrived: no counted load waits for them.  (Stored to LDS before the first slices
+    // were requested they were 0.7-1 us of every fused launch's set-up: ResNet-50 batch 16 425.9 -> 421.7 us, 160x140 batch 9
+    // 275.9 -> 265.0.)
     constexpr unsigned BIAS_OFF = FUSED ? (NS * STAGE_BYTES > fused_lds_bytes(BM, BN, KG) ? NS * STAGE_BYTES : fused_lds_bytes(BM, BN, KG)) : 0u;
     constexpr int B2_PER = FUSED ? (kFusedMaxCout2 + NT - 1) / NT : 1;
-    float bias1_v = 0.f, bias2_v[B2_PER], bias3_v = 0.f;
+    unsigned bias1_v = 0, bias2_v[B2_PER], biasd_v[B2_PER], bias3_v = 0;
     if constexpr (FUSED) {
-        if (tid < BN) bias1_v = a.bias[tid];
-        if (tid < BN && a.w3) bias3_v = a.bias3[tid];
+        const __amdgpu_buffer_rsrc_t r1 = make_rsrc(a.bias, BN * 4u), r2 = make_rsrc(a.bias2, (unsigned)a.Cout2 * 4u);
+        const __amdgpu_buffer_rsrc_t rd = make_rsrc(a.wd ? a.biasd : a.bias2, (unsigned)a.Cout2 * 4u), r3 = make_rsrc(a.w3 ? a.bias3 : a.bias, BN * 4u);
+        bias1_v = __builtin_amdgcn_raw_buffer_load_b32(r1, (unsigned)tid * 4u, 0, 0);
+        bias3_v = __builtin_amdgcn_raw_buffer_load_b32(r3, a.w3 ? (unsigned)tid * 4u : kOob, 0, 0);
 #pragma unroll
         for (int j = 0; j < B2_PER; ++j) {
-            const int n = tid + j * NT;
-            bias2_v[j] = n < a.Cout2 ? a.bias2[n] + (a.wd ? a.biasd[n] : 0.f) : 0.f;
+            bias2_v[j] = __builtin_amdgcn_raw_buffer_load_b32(r2, (unsigned)(tid + j * NT) * 4u, 0, 0);
+            biasd_v[j] = __builtin_amdgcn_raw_buffer_load_b32(rd, a.wd ? (unsigned)(tid + j * NT) * 4u : kOob, 0, 0);
         }
     }
     const int lane = tid & 63;
@@ -186,7 +189,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     // With general addressing the first slice's weights are requested before the pixel arithmetic and the argument line that it
     // waits for: ResNet-18 batch 8 138.9 -> 134.6 us, ResNet-50 batch 1 201.1 -> 198.4.  (All weights of the prologue there make the
     // first slice wait for the later ones': ResNet-18 3 % slower.)
-    constexpr bool WFIRST = !GEMM && !FUSED;
+    constexpr bool WFIRST = !GEMM;
     const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)
     unsigned w_off[W_PER], w_last = 0;   // bit j of w_last: piece j is also in the last slice (MODE_TAIL)
 #pragma unroll
@@ -269,17 +272,6 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             x_mask[j] = ri.y;
         }
     }
-    if constexpr (FUSED) {
-        float *sb = reinterpret_cast<float *>(cw_dyn_lds + BIAS_OFF);
-        if (tid < BN) sb[tid] = bias1_v;
-#pragma unroll
-        for (int j = 0; j < B2_PER; ++j) {
-            const int n = tid + j * NT;
-            if (n < a.Cout2) sb[BN + n] = bias2_v[j];
-        }
-        if (tid < BN && a.w3) sb[BN + a.Cout2 + tid] = bias3_v;
-    }
-
     // (r, s, c0) of the next K slice to load: k0 = kt*BK = (r*kw + s)*Cin + c0.
     int fr = 0, fs = 0, fc0 = 0;
     if (!SPLITK) {
@@ -586,8 +578,18 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             }
         };
 
-        // every wave is done with the ring (the last slice's barrier came before its MFMAs)
-        wait_loads_and_barrier<0>();
+        {
+            float *sb = reinterpret_cast<float *>(cw_dyn_lds + BIAS_OFF);
+            if (tid < BN) sb[tid] = __uint_as_float(bias1_v);
+#pragma unroll
+            for (int j = 0; j < B2_PER; ++j) {
+                const int n = tid + j * NT;
+                if (n < a.Cout2) sb[BN + n] = __uint_as_float(bias2_v[j]) + __uint_as_float(biasd_v[j]);
+            }
+            if (tid < BN && a.w3) sb[BN + a.Cout2 + tid] = __uint_as_float(bias3_v);
+        }
+        // every wave is done with the ring (the last slice's barrier came before its MFMAs), the biases are visible
+        wait_lds_loads_and_barrier<0>();
         issue_chunk(0);
         if constexpr (KG > 1) {
             // The second group hands its accumulators to the first through the room of chunk
