@@ -359,10 +359,10 @@ hipError_t launch_wino_output(DType dt, const WinoArgs &a, hipStream_t s);
 // LOAD-time: canonical W[cout][cin][3][3] -> U[16][cout'][cin] = G g G^T per (cout, cin), rows in the
 // conv kernel's accumulator order, computed in fp32 and rounded once to the storage type
 hipError_t launch_pack_winograd(DType dt, const void *src, void *dst, int cout, int cin, hipStream_t s);
-// Workgroups of a LOAD-side launch: at most one per compute unit, each striding over its work.
-// (Measured with EXECs running beside continuous LOADs: caps of 16, 48, 256 and no cap all leave
-// the EXEC p50 within 0.6 % of EXEC alone.)
-constexpr unsigned kLoadGridCap = 256;
+// Workgroups of a LOAD-side launch: at most four per compute unit, which is what the pack kernel's LDS lets run at once, each striding
+// over its work.  (ResNet-50's 51 MB behind the copy: 53 us with one per CU, 37 with four, the same with eight.  Measured with
+// EXECs running beside continuous LOADs: caps of 16, 48, 256 and no cap all leave the EXEC p50 within 0.6 % of EXEC alone.)
+constexpr unsigned kLoadGridCap = 1024;
 // LOAD-time re-layout of one tensor and its bias: canonical W[cout][cin][kh][kw] -> [cout'][khp][kwp][cinp] (zero padded);
 // permute = rows in the conv kernel's MFMA accumulator order (conv weights), else plain (FC);
 // depthwise = W[C][1][kh][kw] -> [kh][kw][C].  The launcher fills in mode and first_chunk.

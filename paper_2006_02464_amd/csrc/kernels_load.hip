@@ -6,7 +6,7 @@ namespace cw {
 // A launch packs up to kPackItems tensors, described in its kernel arguments, and their biases.  (One launch per tensor and
 // one per bias, as before, took 4 us each: 108 launches and 480 us behind the 930 us of ResNet-50's copy.)
 // Bound: HBM (every byte read once, written once).  The tensors are cut into chunks of 256 threads' work and the
-// workgroups, at most one per CU, stride over the chunks of all of them: LOAD runs beside EXEC (paper section 5.2), and
+// workgroups, at most four per CU, stride over the chunks of all of them: LOAD runs beside EXEC (paper section 5.2), and
 // a launch as wide as a large tensor would queue thousands of workgroups behind the EXEC kernels' own.
 //
 // Row i of every group of 32 output channels of a convolution receives channel sigma(i) of that group,
