@@ -48,8 +48,9 @@ int32_t cw_plan_launch_info(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_
 int32_t cw_plan_launch_ahead(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index,
                              int32_t *workgroups, int64_t *bytes);
 /* 1 where entry `index` of the plan is no launch of its own: the input cast and, if it follows, the 3x3 stride-2 max pool,
- * whose work the first convolution's launch does (7x7 of 64 channels with the pool, 3x3 of 32 without, stride 2; not under
- * cw_set_fusion(0), a plan override or debug retention).  0 otherwise, negative on error. */
+ * whose work the first convolution's launch does (7x7 of 64 channels with the pool, 3x3 of 32 without, stride 2), and the
+ * global average pool of few and small maps, which the FC's launch does; not under cw_set_fusion(0), a plan override or debug
+ * retention.  0 otherwise, negative on error. */
 int32_t cw_plan_launch_joined(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
 /* Runs EXEC like cw_exec but times every launch of the plan with its own pair of
  * events, issuing it `inner` (>= 1) times back to back between them (a launch is

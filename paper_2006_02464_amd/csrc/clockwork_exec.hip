@@ -208,7 +208,7 @@ char *resolve(cw_ctx *c, const ModelRt *m, const Bases &b, const Ref &r) {
 
 hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, hipStream_t st) {
     const DType dt = m->m.dtype;
-    if (l.in_head == 1) return hipSuccess;   // computed by the first convolution's launch
+    if (l.in_head == 1 || l.in_fc) return hipSuccess;   // computed by the first convolution's launch, or the FC's
     if (l.in_head == 2) {
         HeadArgs a = l.head;
         a.x = reinterpret_cast<const float *>(resolve(c, m, s, l.head_x));
@@ -286,6 +286,7 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
             a.w = resolve(c, m, s, l.w);
             a.bias = reinterpret_cast<const float *>(resolve(c, m, s, l.bias));
             a.z = reinterpret_cast<float *>(resolve(c, m, s, l.y));
+            if (a.hw > 0) a.px = resolve(c, m, s, l.pool_x);
             if (l.probs.space == SP_SLOT_PROBS) {
                 a.p = reinterpret_cast<float *>(resolve(c, m, s, l.probs));
                 a.partial = reinterpret_cast<float *>(resolve(c, m, s, l.partial));
@@ -484,7 +485,7 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
 }
 
 bool slot_free(const Launch &l) {
-    if (l.in_head) return false;
+    if (l.in_head || l.in_fc) return false;
     for (const Ref *r : {&l.x, &l.w, &l.bias, &l.res, &l.y, &l.partial, &l.counters, &l.probs, &l.y3})
         if (r->space == SP_SLOT_INPUT || r->space == SP_SLOT_LOGITS || r->space == SP_SLOT_PROBS) return false;
     return true;
@@ -1339,7 +1340,7 @@ int32_t cw_plan_launch_joined(cw_ctx *c, int32_t model_id, int32_t batch, int32_
     Plan *p = get_plan(m, batch);
     if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
     if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
-    return p->launches[index].in_head == 1;
+    return p->launches[index].in_head == 1 || p->launches[index].in_fc;
 }
 
 int32_t cw_debug_read_op(cw_ctx *c, int32_t model_id, int32_t batch, int32_t op_index, float *host_out, size_t cap) {

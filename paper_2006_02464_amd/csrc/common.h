@@ -262,7 +262,20 @@ struct FcArgs {
     float *partial;     // [split_k][16][Out] fp32 (split_k > 1)
     int32_t *counters;  // ceil(Out/16) + 1 arrival counters, zero between launches
     int32_t split_k;    // 1, 2 or 4; In % (128 * split_k) == 0
+    // The global average pool in the FC's launch (px != nullptr): f is written (by the first workgroup), not read.
+    const void *px;     // [B][hw][In] in the storage type
+    int32_t hw;
 };
+// Every workgroup of the FC then pools the whole map: each of its eight waves its own part of the channels, in items of 64 channels of a
+// sample.  The pool's launch and round trip are worth 8 loads a lane, 1, 2 or 4 items (the return value, 0: launches of their
+// own) times 8 pixels each: ResNet-18 64x64 batch 1 79.4 -> 76.6 us, batch 4 86.8 -> 85.5, 224x224 batch 1 86.2 -> 84.6, ResNet-50 97x97
+// batch 1 177.0 -> 175.5; with 16 to 32 loads it is the other way round (ResNet-50 224x224 batch 1, 28 loads, 197.7 -> 200.3;
+// MobileNet 150x99 batch 3, 18, 88.6 -> 95.6), and eight items do not fit the registers beside their weights.
+constexpr int pool_fc_items(int64_t B, int64_t in, int64_t hw) {
+    if (B < 1 || in < 1 || hw < 1 || in % 512 != 0 || in / 512 * B > 4) return 0;
+    const int items = (int)(in / 512 * B), g = items == 3 ? 4 : items;
+    return g * ((hw + 7) / 8) <= 8 ? g : 0;
+}
 constexpr int kFcSoftmaxMaxBatch = 16, kFcSoftmaxMaxOut = 1024;
 
 struct SoftmaxArgs {

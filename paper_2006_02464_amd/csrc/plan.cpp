@@ -301,7 +301,7 @@ static int pick_res_variant(int64_t M, int64_t N, int64_t K, int32_t cin) {
 // Every tile shape's launch time as a linear function of the quantities below, fitted offline to measured
 // launches (tune.py); the plan takes the tile and split-K with the least predicted time.  A launch's time runs from its first
 // workgroup to the next launch's, by time stamps.  Over 641 GEMM shapes (five networks, 38 combinations with image
-// and batch sizes) the choice costs 1.7 % over the fastest tile of each.  Fitted to pairs of events, which see nothing below
+// and batch sizes) the choice costs 1.9 % over the fastest tile of each.  Fitted to pairs of events, which see nothing below
 // 4.2 us, whole EXECs of the 38 combinations took 5.1 % longer in the mean on the tiles there were before the 16-wide
 // ones (with these, chosen by spans without the time to the next launch, 0.6 % longer).
 enum { COST_PLAIN, COST_STAGED, COST_STEM };   // the main kernel; the register-staged one; the first convolution's form
@@ -1261,6 +1261,18 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             if (pool) lp.in_head = 1;
         }
     }
+    // The global average pool inside the FC's launch.  The FC's own result goes to the IO slot, so nothing that is placed after the pool
+    // can lie over the pool's input; the pooled values are still written, for other readers.
+    if (ov.fuse && !ov.keep_all && ov.tile < 0 && ov.split_k <= 0)
+        for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
+            Launch &lp = p.launches[i], &lf = p.launches[i + 1];
+            if (lp.kind != K_GAVGPOOL || lf.kind != K_FC || lf.probs.space == SP_SLOT_PROBS || lf.y.space != SP_SLOT_LOGITS) continue;
+            if (lf.x.space != lp.y.space || lf.x.offset != lp.y.offset || lf.fc.In != lp.pool.C || lf.fc.B != lp.pool.B) continue;
+            if (!pool_fc_items(lf.fc.B, lf.fc.In, (int64_t)lp.pool.H * lp.pool.W)) continue;
+            lp.in_fc = true;
+            lf.pool_x = lp.x;
+            lf.fc.hw = lp.pool.H * lp.pool.W;
+        }
     // Weights are read ahead by the nearest of the four launches before the one that uses them which has CUs to spare.
     {
         auto host = [&](const Launch &l) {

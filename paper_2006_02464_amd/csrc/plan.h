@@ -67,6 +67,8 @@ struct Launch {
     // issues it, 1 = the others, which then issue nothing.
     int32_t in_head = 0;
     HeadArgs head{};
+    bool in_fc = false;    // a global average pool that the FC's launch right behind it computes
+    Ref pool_x;            // that FC: the pool's input
     Ref head_x, head_y, head_w1, head_bias1, head_y1;
     int32_t res_variant = 0, res_tiles = 0, res_dep[2] = {-1, -1}, res_flag_base = 0;
     long long res_ps_x = 0, res_ps_y = 0, res_ps_res = 0;

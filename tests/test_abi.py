@@ -319,7 +319,7 @@ def test_entries_joined_into_the_first_convolutions_launch(ctx):
         m = define()
         return [i for i in range(ctx.plan_num_launches(m, 1)) if ctx.plan_launch_joined(m, 1, i)]
     r50 = lambda: ctx.model_define_resnet(50, 224, 224)
-    assert joined(r50) == [0, 2] and joined(lambda: ctx.model_define_resnet(18, 64, 64)) == [0, 2]
+    assert joined(r50) == [0, 2] and joined(lambda: ctx.model_define_resnet(18, 64, 64)) == [0, 2, 19]   # and the average pool of 4 pixels
     for on, off in ((lambda: ctx.set_fusion(0), lambda: ctx.set_fusion(1)), (lambda: ctx.set_debug_keep(True), lambda: ctx.set_debug_keep(False)),
                     (lambda: ctx.set_plan_override(2, 0), lambda: ctx.set_plan_override(-1, 0)), (lambda: ctx.set_plan_override(-1, 2), lambda: ctx.set_plan_override(-1, 0))):
         on()

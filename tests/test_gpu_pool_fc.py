@@ -1,0 +1,54 @@
+"""Global average pool and FC as one launch against the plan that debug retention makes, which has the two as launches of their own
+(held against the CPU oracle by other tests).  Sums, products and roundings in the same order: same bits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import topology as T
+from test_gpu_head import ctx, O   # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def logits(ctx, c, h, w, out, batch, dtype, keep, blob, x):
+    ops = [O(T.CONV, 3, 32, 3, 3, 2, 1, 1, -1, -1), O(T.CONV, 32, c, 1, 1, 1, 0, 0, -1, 0), O(T.GAVGPOOL, c, c, 0, 0, 1, 0, 0, -1, 1),
+           O(T.FC, c, out, 1, 1, 1, 0, 0, -1, 2), O(T.SOFTMAX, out, out, 0, 0, 1, 0, 0, -1, 3)]
+    ctx.set_debug_keep(keep)
+    try:
+        m = ctx.model_define([tuple(o) for o in ops], 3, 2 * h, 2 * w, batch_sizes=(batch,), dtype=dtype)
+    finally:
+        ctx.set_debug_keep(False)
+    plan = ctx.plan(m, batch)
+    joined = any(ctx.plan_launch_joined(m, batch, i) for i, l in enumerate(plan) if l["kind"] == 4)
+    st = torch.cuda.current_stream()
+    ctx.load_weights(m, blob, st)
+    z, probs = (torch.zeros(batch, out).pin_memory() for _ in range(2))
+    slot = ctx.input(m, batch, x, st)
+    ctx.exec(m, batch, slot, st)
+    ctx.output(slot, probs, z, st)
+    torch.cuda.synchronize()
+    ctx.unload_weights(m)
+    return z.numpy().copy(), joined
+
+
+# one to four items of 64 channels a wave with maps up to the pixels that the number allows, and beyond: one pixel more, five
+# items, channels that do not divide; several samples; part of a tile of outputs
+@pytest.mark.parametrize("c,h,w,out,batch,dtype,one", [
+    (512, 1, 1, 40, 1, "fp16", True), (512, 2, 4, 1000, 1, "bf16", True), (512, 3, 3, 17, 1, "fp16", True), (512, 7, 7, 1000, 1, "fp16", True), (512, 8, 8, 10, 1, "bf16", True),
+    (512, 2, 4, 33, 2, "fp16", True), (1024, 4, 8, 1000, 1, "fp16", True), (512, 3, 5, 40, 2, "bf16", True), (1536, 4, 4, 16, 1, "fp16", True), (1536, 1, 5, 1, 1, "bf16", True),
+    (1024, 3, 3, 40, 2, "bf16", True), (512, 2, 4, 1000, 4, "fp16", True), (512, 3, 5, 40, 3, "fp16", True), (2048, 4, 4, 1000, 1, "fp16", True),
+    (512, 5, 13, 40, 1, "fp16", False), (1024, 3, 11, 40, 1, "fp16", False), (2048, 1, 17, 40, 1, "fp16", False), (2560, 1, 1, 40, 1, "fp16", False),
+    (768, 2, 2, 40, 1, "fp16", False), (512, 1, 1, 40, 5, "fp16", False),
+])
+def test_pool_and_fc_in_one_launch(ctx, c, h, w, out, batch, dtype, one):   # noqa: F811
+    g = np.random.default_rng(c + h * 100 + w)
+    half = torch.float16 if dtype == "fp16" else torch.bfloat16
+    shapes = [(32, 27), (c, 32), (out, c)]
+    wb = torch.cat([torch.from_numpy(g.normal(0, (2.0 / k) ** 0.5, n * k).astype(np.float32)).to(half) for n, k in shapes]).view(torch.uint8)
+    bs = torch.cat([torch.from_numpy(g.normal(0, 0.3, n).astype(np.float32)) for n, _ in shapes])
+    blob = torch.cat([wb, torch.zeros(-wb.numel() % 4, dtype=torch.uint8), bs.view(torch.uint8)]).pin_memory()
+    x = torch.from_numpy(g.normal(0, 1, (batch, 3, 2 * h, 2 * w)).astype(np.float32)).pin_memory()
+    a, apart = logits(ctx, c, h, w, out, batch, dtype, True, blob, x)
+    b, joined = logits(ctx, c, h, w, out, batch, dtype, False, blob, x)
+    assert not apart and joined == one
+    assert np.array_equal(a, b) and np.isfinite(a).all() and np.any(a != 0)
