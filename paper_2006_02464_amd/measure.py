@@ -395,10 +395,14 @@ def config7(args, log):
                     whole.append(ctx.exec_duration_ns(slot) / 1e3)
                 raw = np.median(np.stack([ctx.exec_timed_launches(mid, B, slot, ex, inner=1) for _ in range(60)]), axis=0)
                 ctx.set_use_graphs(1)
-                over = (float(raw.sum()) - float(np.median(whole[10:]))) / len(plan)
-                us = raw - over
+                own = np.array([not ctx.plan_launch_joined(mid, B, i) for i in range(len(plan))])   # the others have no launch
+                raw = raw * own
+                over = (float(raw.sum()) - float(np.median(whole[10:]))) / int(own.sum())
+                us = raw - over * own
                 groups = {}
-                for l, u in zip(plan, us):
+                for l, u, o in zip(plan, us, own):
+                    if not o:
+                        continue
                     key = l["name"].split("_s")[0] if l["name"].startswith(("dwconv", "conv")) else l["name"]
                     g = groups.setdefault(key, [0, 0.0, 0, 0])
                     g[0] += 1; g[1] += float(u); g[2] += l["bytes"]; g[3] += l["flops"]
@@ -409,7 +413,7 @@ def config7(args, log):
                 tables.append("%-26s %9s %6s %6s %8s %8s %8s %8s" % ("launch", "M", "N", "K", "MB", "us", "GB/s", "TFLOP/s"))
                 for l, u in zip(plan, us):
                     tables.append("%-26s %9d %6d %6d %8.2f %8.2f %8.0f %8.1f" % (l["name"], l["gemm_m"], l["gemm_n"], l["gemm_k"], l["bytes"] / 1e6, u,
-                                                                                   l["bytes"] / (u * 1e-6) / 1e9, l["flops"] / (u * 1e-6) / 1e12))
+                                                                                   l["bytes"] / (u * 1e-6) / 1e9 if u else 0, l["flops"] / (u * 1e-6) / 1e12 if u else 0))
             ctx.release(slot)
         ctx.unload_weights(mid)
         out["families"][name] = fam
