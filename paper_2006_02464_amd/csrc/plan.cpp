@@ -359,8 +359,8 @@ static bool split_ok(const ConvArgs &a, bool stem, ConvTile tile, int32_t split)
 }
 
 // The cheapest tile and split-K of a convolution; a row of the installed table or a forced tile comes first.  A pure function
-// of the convolution's shape.
-static double pick_conv_tile(const ConvArgs &a, bool stem, bool res, int64_t real_k, const PlanOverride &ov, ConvTile *tile,
+// of the convolution's shape and of `one_group`: no tile whose wave groups share a slice's products.
+static double pick_conv_tile(const ConvArgs &a, bool stem, bool res, int64_t real_k, bool one_group, const PlanOverride &ov, ConvTile *tile,
                              int32_t *split, bool *fixed) {
     *fixed = ov.tile >= 0 || ov.split_k > 0;
     if (!*fixed)
@@ -377,9 +377,7 @@ static double pick_conv_tile(const ConvArgs &a, bool stem, bool res, int64_t rea
     for (const ConvCost &c : kConvCost) {
         const TileDim d = conv_tile_dim((ConvTile)c.tile);
         if (c.cls != cls || (cls == COST_PLAIN && (conv_bk(a, stem, (ConvTile)c.tile) != d.bk || (a.Cin % 64 != 0 && conv_tile_tail((ConvTile)c.tile) != c.tile))) || (d.bn > a.Cout && d.bn > 32)) continue;
-        // Groups do nothing for the walk of a single slice of 64, they only share the epilogue: from 1.5 workgroups a CU on that is as
-        // fast without (6027..6875 pixels, 64 -> 64: 3.39..3.52 us in four groups, 3.34..3.49 on 32x64; 3136 x 128 3.08, 3.20).
-        if (cls == COST_PLAIN && d.kg > 1 && a.K == 64 && (int64_t)((a.M + d.bm - 1) / d.bm) * ((a.Cout + d.bn - 1) / d.bn) > 384) continue;
+        if (one_group && d.kg > 1) continue;   // see plan_build
         for (int32_t s = 1; s <= (c.splits ? 8 : 1); s *= 2) {
             if ((ov.split_k > 0 && s != ov.split_k && s > 1) || !split_ok(a, stem, (ConvTile)c.tile, s)) continue;
             const double us = conv_cost(c, as, &res, 1, stem, s) + (ov.split_k > 1 && s == 1 ? 1e3 : 0);   // a forced split where it can be had
@@ -518,7 +516,13 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     // convolution too, from the pooled tile in LDS, where the launch has enough workgroups; the pooled
     // tensor is still written for its other readers.
     std::vector<int> pool_conv(n_ops, -1), in_pool(n_ops, -1), pool_bm(n_ops, 0);
-    if (ov.fuse && ov.fuse_pool && !resident && ov.tile < 0 && ov.split_k <= 0) {
+    // Where such a convolution is planned as a launch of its own after all (cw_set_fusion_pool(0), cw_set_fusion(0)), it takes a
+    // tile of one wave group: the two plans promise the same bits, and wave groups add a slice's products up in another order.
+    // That is the whole reason: with a single slice of 64 groups cost and gain next to nothing (3136 pixels, 64 -> 128 in MobileNet batch 1:
+    // 3.08 us in four groups, 3.20 on 32x32, whole EXECs 119.6 and 120.6, runs of one side differ by 2; 12544 pixels, 64 -> 32 with a residual,
+    // eight of them in an EXEC: 95.4 and 95.9 on 64x32), and everywhere else the cost model chooses.
+    std::vector<char> one_group(n_ops, 0);
+    if (!resident && ov.tile < 0 && ov.split_k <= 0) {
         for (int j = 0; j + 1 < n_ops; ++j) {
             const cw_op &op = m.ops[j];
             if (op.op != CW_OP_MAXPOOL || op.kh != 3 || op.kw != 3 || m.shapes[j].c != 64) continue;
@@ -533,6 +537,10 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             if (concat_reader) continue;
             const int64_t M = (int64_t)batch * m.shapes[j].h * m.shapes[j].w;
             if (M * 8 >= ((int64_t)1 << 31) || (M + 63) / 64 < 96) continue;   // as for the fused bottleneck tails
+            if (!ov.fuse || !ov.fuse_pool) {
+                one_group[k] = 1;
+                continue;
+            }
             pool_conv[j] = k; in_pool[k] = j; pool_bm[j] = 64;
         }
     }
@@ -918,7 +926,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 a.relu = o.relu;
                 a.wo_div = make_fast_div((uint32_t)os.w);
                 a.ho_div = make_fast_div((uint32_t)os.h);
-                l.cost_us = pick_conv_tile(a, l.stem, o.residual_from >= 0, (int64_t)o.kh * o.kw * o.cin, ov, &l.tile, &a.split_k, &l.tile_fixed);
+                l.cost_us = pick_conv_tile(a, l.stem, o.residual_from >= 0, (int64_t)o.kh * o.kw * o.cin, one_group[i], ov, &l.tile, &a.split_k, &l.tile_fixed);
                 if (!l.stem && a.Cin % 64 != 0 && conv_uses_dlds(a, false)) l.tile = conv_tile_tail(l.tile);   // 1x1, part of a slice at the end
                 if (!conv_uses_dlds(a, l.stem)) l.tile = conv_tile_staged(l.tile);   // the register-staged kernel's shapes
                 if (conv_bk(a, l.stem, l.tile) != conv_tile_dim(l.tile).bk) l.tile = conv_tile_k64(l.tile);  // Cin is no multiple of the tile's slice

@@ -312,6 +312,27 @@ def test_max_pool_with_the_1x1_behind_it(ctx):
     assert [l["fused_op"] for l in ctx.plan(m18, 16) if l["kind"] == 3] == [-1]
 
 
+def test_one_wave_group_only_where_the_max_pool_computes_the_convolution(ctx):
+    """The 1x1 behind a max pool, planned as a launch of its own, keeps the order of additions of the pool's launch, which
+    computes it from 96 workgroups of 64 pixels up: one wave group at every size.  No other 64-deep convolution is held to it."""
+    pooled = lambda n: [(0, 3, 64, 7, 7, 2, 3, 1, -1, -1), (1, 64, 64, 3, 3, 2, 1, 0, -1, 0), (0, 64, n, 1, 1, 1, 0, 1, -1, 1), (0, n, 256, 3, 3, 2, 1, 1, -1, 2)]
+    plain = [(0, 3, 64, 7, 7, 2, 3, 1, -1, -1), (0, 64, 32, 3, 3, 1, 1, 1, -1, 0), (0, 64, 32, 1, 1, 1, 0, 1, 1, 0), (0, 32, 256, 3, 3, 2, 1, 1, -1, 2)]
+    tail = [(2, 256, 256, 0, 0, 1, 0, 0, -1, 3), (3, 256, 10, 1, 1, 1, 0, 0, -1, 4), (4, 10, 10, 0, 0, 1, 0, 0, -1, 5)]
+    launch = lambda m, b: [l for l in ctx.plan(m, b) if l["kind"] == 1 and l["op_index"] == 2][0]
+    batches = (25, 26, 27, 28, 29, 30, 33, 40, 51, 63, 80, 100, 128, 200)   # of 16x16 pooled pixels
+    for setter in (ctx.set_fusion_pool, ctx.set_fusion):
+        setter(0)
+        try:
+            for n in (64, 128):
+                m = ctx.model_define(pooled(n) + tail, 3, 64, 64, batch_sizes=batches)
+                assert {launch(m, b)["wave_groups"] for b in batches} == {1}
+        finally:
+            setter(1)
+    m = ctx.model_define(plain + tail, 3, 224, 224, batch_sizes=(1,))
+    l = launch(m, 1)
+    assert (l["gemm_m"], l["gemm_n"], l["gemm_k"]) == (12544, 32, 64) and l["wave_groups"] == 4   # as the cost model has it
+
+
 def test_entries_joined_into_the_first_convolutions_launch(ctx):
     """Input cast and max pool are computed by the first convolution's launch where it has the form: not with fusion off, a
     forced tile, debug retention, another reader of the convolution's output, or another filter."""
