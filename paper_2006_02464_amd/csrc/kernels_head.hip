@@ -270,8 +270,7 @@ hipError_t launch_head(DType dt, const HeadArgs &a_in, hipStream_t s) {
     if (a.H + 2 * a.pad < a.kh || a.W + 2 * a.pad < a.kh || a.Ho != (a.H + 2 * a.pad - a.kh) / 2 + 1 || a.Wo != (a.W + 2 * a.pad - a.kh) / 2 + 1) return hipErrorInvalidValue;
     if (a.pool && (a.Po != (a.Ho - 1) / 2 + 1 || a.Qo != (a.Wo - 1) / 2 + 1)) return hipErrorInvalidValue;
     if (a.ldy < a.cout || (a.n1 > 0 && (!a.w1 || !a.bias1 || !a.y1 || a.ldy1 < a.n1)) || a.n_zero < 0 || (a.n_zero > 0 && !a.zero)) return hipErrorInvalidValue;
-    // One image's planes are read through one descriptor, and what lies outside is asked for at 2 GiB.
-    if ((long long)a.C * a.H * a.W * 4 >= (1ll << 31) || (long long)a.B * a.Ho * a.Wo >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!head_image_ok(a.C, a.H, a.W) || (long long)a.B * a.Ho * a.Wo >= (1ll << 31)) return hipErrorInvalidValue;
     const int oh = a.pool ? a.Po : a.Ho, ow = a.pool ? a.Qo : a.Wo;
     const int th = !a.pool ? 8 : a.n1 > 0 || (long long)a.B * ((oh + 6) / 7) * ((ow + 7) / 8) >= kHeadTallFrom ? 7 : 3;
     a.tiles_h = (oh + th - 1) / th;

@@ -1252,7 +1252,8 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                           ls.conv.khp == 8 && ls.conv.kwp == 8 && ls.conv.split_k == 1 && !ls.tile_fixed;
         const bool pool = lp.kind == K_MAXPOOL && m.ops[lp.op_index].input_from == 0 && readers == 1 && lp.pool.k == 3 && lp.pool.stride == 2 && lp.pool.pad == 1;
         const int n1 = pool && lp.pool_bm > 0 ? lp.conv.Cout : 0;
-        if (stem && head_form_ok(o.kh, o.cout, pool, n1)) {
+        // An image of 2 GiB and more is left to the launches of their own, which read it as padded pixels of the storage type.
+        if (stem && head_form_ok(o.kh, o.cout, pool, n1) && head_image_ok(m.in_c, m.in_h, m.in_w)) {
             HeadArgs &h = ls.head;
             h.B = batch; h.C = m.in_c; h.H = m.in_h; h.W = m.in_w; h.pad = o.pad; h.Ho = ls.conv.Ho; h.Wo = ls.conv.Wo;
             h.kh = o.kh; h.cout = o.cout; h.act = o.relu; h.pool = pool; h.n1 = n1;

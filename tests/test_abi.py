@@ -359,6 +359,14 @@ def test_entries_joined_into_the_first_convolutions_launch(ctx):
     assert joined(net((0, 3, 32, 3, 3, 1, 1, 1, -1, -1), (0, 32, 256, 1, 1, 1, 0, 1, -1, 0))) == []                   # stride 1
 
 
+def test_an_image_of_2_gib_is_not_joined(ctx):
+    """The head's launch reads an image through one descriptor of below 2 GiB; the cast and the convolution take larger ones."""
+    tail = [(0, 32, 256, 1, 1, 64, 0, 1, -1, 0), (2, 256, 256, 0, 0, 1, 0, 0, -1, 1), (3, 256, 10, 1, 1, 1, 0, 0, -1, 2), (4, 10, 10, 0, 0, 1, 0, 0, -1, 3)]
+    for w, joined in ((1 << 20, True), (59652323, True), (59652324, False), (1 << 26, False)):   # 3 planes of 3 x w
+        m = ctx.model_define([(0, 3, 32, 3, 3, 2, 0, 1, -1, -1)] + tail, 3, 3, w, batch_sizes=(1,))
+        assert ctx.plan_launch_joined(m, 1, 0) == joined
+
+
 def test_depthwise_with_the_1x1_behind_it(ctx):
     """MobileNet's first two depthwise-separable blocks (32 and 64 channels) are one launch each where the launch has
     96 workgroups of 64 pixels; the 128-channel ones and everything behind them stay two launches."""
