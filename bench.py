@@ -155,9 +155,7 @@ def main():
     # events on the EXEC stream (a separate pass: event pairs inside the timed region would perturb
     # it).  An event pair adds the same dispatch-and-marker overhead to every launch; it is fixed by
     # requiring the launches to add up to the on-device duration of whole EXECs issued the same way
-    # (plain launches, one event pair around the EXEC), and taken off every launch.  Entries that another
-    # entry's launch computes (cast and max pool in the first convolution's) issue nothing: no time, no pair.
-    plan = ctx.plan(mid, B)
+    # (plain launches, one event pair around the EXEC), and taken off every launch.
     ctx.set_use_graphs(0)
     for _ in range(20):
         ctx.exec(mid, B, slot, stream)
@@ -170,10 +168,11 @@ def main():
     passes = np.stack([ctx.exec_timed_launches(mid, B, slot, stream, inner=1) for _ in range(args.launch_reps)])
     if not args.no_graphs:
         ctx.set_use_graphs(1)
-    own = np.array([not ctx.plan_launch_joined(mid, B, i) for i in range(len(plan))])
-    raw = np.median(passes, axis=0) * own
-    overhead = (float(raw.sum()) - t_exec_plain) / int(own.sum())
-    per = raw - overhead * own
+    plan = ctx.issued(mid, B)     # (entry, launch); an entry that another one's launch computes issues nothing
+    raw = np.median(passes, axis=0)[[i for i, _ in plan]]
+    plan = [l for _, l in plan]
+    overhead = (float(raw.sum()) - t_exec_plain) / len(plan)
+    per = raw - overhead
     conv = [i for i, l in enumerate(plan) if l["kind"] == 1]
     conv_us = float(sum(per[i] for i in conv))
     conv_flops = float(sum(plan[i]["flops"] for i in conv))
@@ -181,12 +180,12 @@ def main():
     achieved = conv_flops / (conv_us * 1e-6) / 1e12
     roof_us = [max(l["flops"] / (PEAK_MFMA_F16_TFLOPS * 1e6), l["bytes"] / (PEAK_HBM_GBS * 1e3)) for l in plan]
     conv_roof_us = float(sum(roof_us[i] for i in conv))
-    lines = ["%-22s %4s %9s %6s %5s %7s %10s %9s %8s %8s %7s %8s" % (
+    lines = ["%-34s %4s %9s %6s %5s %7s %10s %9s %8s %8s %7s %8s" % (
         "launch", "op", "M", "N", "K", "grid", "GFLOP", "MB", "us", "TFLOP/s", "GB/s", "roof us")]
     for l, us, r in zip(plan, per, roof_us):
-        lines.append("%-22s %4d %9d %6d %5d %7d %10.3f %9.2f %8.2f %8.1f %7.0f %8.2f" % (
-            l["name"], l["op_index"], l["gemm_m"], l["gemm_n"], l["gemm_k"], l["grid_x"] * l["grid_y"],
-            l["flops"] / 1e9, l["bytes"] / 1e6, us, l["flops"] / (us * 1e-6) / 1e12 if us else 0, l["bytes"] / (us * 1e-6) / 1e9 if us else 0, r))
+        lines.append("%-34s %4d %9d %6d %5d %7d %10.3f %9.2f %8.2f %8.1f %7.0f %8.2f" % (
+            l["name"], l["op_index"], l["gemm_m"], l["gemm_n"], l["gemm_k"], l["grid_x"] * l["grid_y"] * l["grid_z"],
+            l["flops"] / 1e9, l["bytes"] / 1e6, us, l["flops"] / (us * 1e-6) / 1e12, l["bytes"] / (us * 1e-6) / 1e9, r))
     lines.append("whole EXEC (plain launches) %.1f us on-device; event overhead taken off every launch %.2f us; "
                  "conv launches %d, %.1f us; composite roof of the conv launches %.1f us" % (
                      t_exec_plain, overhead, len(conv), conv_us, conv_roof_us))

@@ -19,7 +19,8 @@
 extern "C" {
 #endif
 
-/* Number of kernel launches in the plan of (model, batch); negative on error. */
+/* Number of entries in the plan of (model, batch), each a kernel launch but for those that cw_plan_launch_joined
+ * names; negative on error. */
 int32_t cw_plan_num_launches(cw_ctx *ctx, int32_t model_id, int32_t batch);
 typedef struct {
     int32_t op_index;      /* which op of the model this launch belongs to (fused launch: the last) */
@@ -40,6 +41,7 @@ typedef struct {
     int64_t flops;         /* 2 * MACs */
     char name[48];
 } cw_launch_info;
+/* Entry `index` as a launch of its own. */
 int32_t cw_plan_launch_info(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index,
                             cw_launch_info *out);
 /* A convolution launch may carry further workgroups along x that read the weights of one of the next four
@@ -52,6 +54,11 @@ int32_t cw_plan_launch_ahead(cw_ctx *ctx, int32_t model_id, int32_t batch, int32
  * global average pool of few and small maps, which the FC's launch does; not under cw_set_fusion(0), a plan override or debug
  * retention.  0 otherwise, negative on error. */
 int32_t cw_plan_launch_joined(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
+/* What EXEC issues for entry `index`: the same as cw_plan_launch_info but for joined entries and those that compute them.  The
+ * first have no bytes, flops, grid or block; the others have the launch's own grid and name, its tile (pixels of the stored
+ * tensor x channels) and the flops and bytes of all its work, without the tensors that it does not store.  The sums
+ * over a plan's entries are those of an EXEC. */
+int32_t cw_plan_launch_issued(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index, cw_launch_info *out);
 /* Runs EXEC like cw_exec but times every launch of the plan with its own pair of
  * events, issuing it `inner` (>= 1) times back to back between them (a launch is
  * idempotent); launch_us [host] receives cw_plan_num_launches() averages, each

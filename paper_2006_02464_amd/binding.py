@@ -99,6 +99,7 @@ SIGNATURES = {
     "cw_plan_launch_info": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(cw_launch_info)]),
     "cw_plan_launch_ahead": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(c_int32), POINTER(c_int64)]),
     "cw_plan_launch_joined": (c_int32, [c_void_p, c_int32, c_int32, c_int32]),
+    "cw_plan_launch_issued": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(cw_launch_info)]),
     "cw_exec_timed_launches": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_int32, c_void_p, c_void_p]),
     "cw_debug_read_op": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_void_p, c_size_t]),
     "cw_set_debug_keep": (c_int32, [c_void_p, c_int32]),
@@ -307,8 +308,11 @@ class Context:
         return self._check(lib().cw_plan_num_launches(self._h, model_id, batch))
 
     def plan_launch_info(self, model_id, batch, index):
+        return self._launch_info(lib().cw_plan_launch_info, model_id, batch, index)
+
+    def _launch_info(self, call, model_id, batch, index):
         info = cw_launch_info()
-        self._check(lib().cw_plan_launch_info(self._h, model_id, batch, index, byref(info)))
+        self._check(call(self._h, model_id, batch, index, byref(info)))
         d = {f: getattr(info, f) for f, _ in cw_launch_info._fields_}
         d["name"] = d["name"].decode()
         return d
@@ -320,11 +324,21 @@ class Context:
         return wgs.value, nbytes.value
 
     def plan_launch_joined(self, model_id, batch, index):
-        """Whether plan entry `index` is computed inside the first convolution's launch."""
+        """Whether plan entry `index` has no launch of its own: the first convolution's launch computes it (cast, max pool), or
+        the FC's (average pool)."""
         return bool(self._check(lib().cw_plan_launch_joined(self._h, model_id, batch, index)))
+
+    def plan_launch_issued(self, model_id, batch, index):
+        """What EXEC issues for plan entry `index`: the work of joined entries stands with the entry that launches it."""
+        return self._launch_info(lib().cw_plan_launch_issued, model_id, batch, index)
 
     def plan(self, model_id, batch):
         return [self.plan_launch_info(model_id, batch, i) for i in range(self.plan_num_launches(model_id, batch))]
+
+    def issued(self, model_id, batch):
+        """The launches of an EXEC: (entry of the plan, what it issues)."""
+        return [(i, self.plan_launch_issued(model_id, batch, i)) for i in range(self.plan_num_launches(model_id, batch))
+                if not self.plan_launch_joined(model_id, batch, i)]
 
     def exec_timed_launches(self, model_id, batch, slot, stream=None, inner=1):
         us = np.empty(self.plan_num_launches(model_id, batch), np.float32)

@@ -68,7 +68,7 @@ def main():
             l = plan[idx]
             tf = l["flops"] / (us * 1e-6) / 1e12
             lines.append("%-6s %-14s %6d %9.1f %10.1f %9.3f" % (name, tile,
-                                                                l["grid_x"] * l["grid_y"], us, tf, tf / 2500.0))
+                                                                l["grid_x"] * l["grid_y"] * l["grid_z"], us, tf, tf / 2500.0))
             print(lines[-1], file=sys.stderr, flush=True)
             ctx.release(slot)
             ctx.unload_weights(mid)

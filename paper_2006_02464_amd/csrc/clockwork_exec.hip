@@ -1343,6 +1343,16 @@ int32_t cw_plan_launch_joined(cw_ctx *c, int32_t model_id, int32_t batch, int32_
     return p->launches[index].in_head == 1 || p->launches[index].in_fc;
 }
 
+int32_t cw_plan_launch_issued(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index, cw_launch_info *out) {
+    ModelRt *m = get_model(c, model_id);
+    if (!m || !out) return set_err(c, CW_ERR_INVALID, "unknown model id or null pointer");
+    Plan *p = get_plan(m, batch);
+    if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
+    if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
+    *out = p->launches[index].issued;
+    return CW_OK;
+}
+
 int32_t cw_debug_read_op(cw_ctx *c, int32_t model_id, int32_t batch, int32_t op_index, float *host_out, size_t cap) {
     if (!c || !host_out) return CW_ERR_INVALID;
     if (c->device < 0) return set_err(c, CW_ERR_INVALID, "planning-only context has no device");

@@ -348,6 +348,8 @@ bool conv_pair_tile_ok(ConvTile tile);
 void conv_pair_grid(ConvTile tile, const ConvArgs &a0, const ConvArgs &a1, dim3 *grid, int *block);
 hipError_t launch_cast_input(DType dt, const CastArgs &a, hipStream_t s);
 bool head_form_ok(int kh, int cout, bool pool, int n1);
+int head_tile_rows(const HeadArgs &a);     // rows of a workgroup's tile of the result, 8 (pooled) or 16 columns wide
+unsigned head_tiles(const HeadArgs &a, int32_t *tiles_h, int32_t *tiles_w);   // workgroups; 0: too many for a launch
 // One image's planes are read through one descriptor of the launch, whose out-of-range offset is 2 GiB.
 constexpr bool head_image_ok(int64_t c, int64_t h, int64_t w) { return c * h * w * 4 < (1ll << 31); }
 hipError_t launch_head(DType dt, const HeadArgs &a, hipStream_t s);

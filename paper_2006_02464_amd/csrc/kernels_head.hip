@@ -263,6 +263,18 @@ bool head_form_ok(int kh, int cout, bool pool, int n1) {
     return pool ? kh == 7 && cout == 64 && (n1 == 0 || n1 == 64 || n1 == 128) : kh == 3 && cout == 32 && n1 == 0;
 }
 
+int head_tile_rows(const HeadArgs &a) {
+    return !a.pool ? 8 : a.n1 > 0 || (long long)a.B * ((a.Po + 6) / 7) * ((a.Qo + 7) / 8) >= kHeadTallFrom ? 7 : 3;
+}
+
+unsigned head_tiles(const HeadArgs &a, int32_t *tiles_h, int32_t *tiles_w) {
+    const int th = head_tile_rows(a);
+    *tiles_h = ((a.pool ? a.Po : a.Ho) + th - 1) / th;
+    *tiles_w = a.pool ? (a.Qo + 7) / 8 : (a.Wo + 15) / 16;
+    const long long tiles = (long long)a.B * *tiles_h * *tiles_w;
+    return tiles < (1ll << 31) ? (unsigned)tiles : 0;
+}
+
 hipError_t launch_head(DType dt, const HeadArgs &a_in, hipStream_t s) {
     HeadArgs a = a_in;
     if (!head_form_ok(a.kh, a.cout, a.pool, a.n1) || a.B < 1 || a.C < 1 || a.C > 4 || a.H < 1 || a.W < 1 || a.pad < 0 || !a.x || !a.w || !a.bias || !a.y)
@@ -271,16 +283,13 @@ hipError_t launch_head(DType dt, const HeadArgs &a_in, hipStream_t s) {
     if (a.pool && (a.Po != (a.Ho - 1) / 2 + 1 || a.Qo != (a.Wo - 1) / 2 + 1)) return hipErrorInvalidValue;
     if (a.ldy < a.cout || (a.n1 > 0 && (!a.w1 || !a.bias1 || !a.y1 || a.ldy1 < a.n1)) || a.n_zero < 0 || (a.n_zero > 0 && !a.zero)) return hipErrorInvalidValue;
     if (!head_image_ok(a.C, a.H, a.W) || (long long)a.B * a.Ho * a.Wo >= (1ll << 31)) return hipErrorInvalidValue;
-    const int oh = a.pool ? a.Po : a.Ho, ow = a.pool ? a.Qo : a.Wo;
-    const int th = !a.pool ? 8 : a.n1 > 0 || (long long)a.B * ((oh + 6) / 7) * ((ow + 7) / 8) >= kHeadTallFrom ? 7 : 3;
-    a.tiles_h = (oh + th - 1) / th;
-    a.tiles_w = (ow + (a.pool ? 7 : 15)) / (a.pool ? 8 : 16);
-    const long long tiles = (long long)a.B * a.tiles_h * a.tiles_w;
-    if (tiles >= (1ll << 31)) return hipErrorInvalidValue;
+    const int th = head_tile_rows(a);
+    const unsigned tiles = head_tiles(a, &a.tiles_h, &a.tiles_w);
+    if (tiles == 0) return hipErrorInvalidValue;
 #define CW_HEAD(KH_, CO_, POOL_, N1_, TH_)                                                                              \
     do {                                                                                                                \
-        if (dt == DT_F16) head_kernel<f16, KH_, CO_, POOL_, N1_, TH_><<<dim3((unsigned)tiles), 256, 0, s>>>(a);         \
-        else head_kernel<bf16, KH_, CO_, POOL_, N1_, TH_><<<dim3((unsigned)tiles), 256, 0, s>>>(a);                     \
+        if (dt == DT_F16) head_kernel<f16, KH_, CO_, POOL_, N1_, TH_><<<dim3(tiles), 256, 0, s>>>(a);         \
+        else head_kernel<bf16, KH_, CO_, POOL_, N1_, TH_><<<dim3(tiles), 256, 0, s>>>(a);                     \
     } while (0)
     if (!a.pool) CW_HEAD(3, 32, false, 0, 8);
     else if (a.n1 == 64) CW_HEAD(7, 64, true, 64, 7);

@@ -1349,6 +1349,34 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         if (l.kind != K_CONV) { l.info.conv_tile = -1; l.info.wave_groups = 1; }
         l.info.grid_x = g.x; l.info.grid_y = g.y; l.info.grid_z = g.z; l.info.block = b;
         if (l.info.split_k == 0) l.info.split_k = 1;
+        l.issued = l.info;
+    }
+    // What is really issued where entries are joined: the work moves to the entry that launches it, without the tensors that never
+    // leave the chip then.
+    for (size_t i = 0; i < p.launches.size(); ++i) {
+        Launch &l = p.launches[i];
+        cw_launch_info &d = l.issued;
+        if (l.in_head == 1 || l.in_fc) {
+            d.bytes = d.flops = 0;
+            d.grid_x = d.grid_y = d.grid_z = d.block = 0;
+        } else if (l.in_head == 2) {
+            const HeadArgs &h = l.head;
+            const int64_t out = (int64_t)batch * (h.pool ? h.Po * h.Qo : h.Ho * h.Wo);
+            int32_t tiles_h, tiles_w;
+            d.grid_x = (int32_t)head_tiles(h, &tiles_h, &tiles_w); d.grid_y = d.grid_z = 1; d.block = 256;
+            d.tile_m = head_tile_rows(h) * (h.pool ? 8 : 16); d.tile_n = h.cout; d.tile_k = 0; d.conv_tile = -1;   // of the stored tensor
+            d.bytes = (int64_t)batch * h.C * h.H * h.W * 4 + (int64_t)h.cout * h.kh * h.kh * h.C * esz + h.cout * 4 + out * h.cout * (int64_t)esz;
+            char name[sizeof d.name];
+            snprintf(name, sizeof name, "cast+%s%s%s", l.info.name, h.pool ? "+" : "", h.pool ? p.launches[i + 1].info.name : "");
+            memcpy(d.name, name, sizeof name);
+            if (h.n1 > 0) {
+                d.flops += p.launches[i + 1].info.flops;
+                d.bytes += (int64_t)h.n1 * h.cout * esz + h.n1 * 4 + out * h.n1 * (int64_t)esz;
+            }
+        } else if (l.kind == K_FC && l.fc.hw > 0) {
+            d.bytes += (int64_t)batch * l.fc.hw * l.fc.In * esz - (int64_t)batch * l.fc.In * 4;   // the map, and no pooled values
+            snprintf(d.name, sizeof d.name, "%s+%s", p.launches[i - 1].info.name, l.info.name);
+        }
     }
     p.workspace_bytes = arena.high_water();
     *out = std::move(p);

@@ -59,6 +59,7 @@ struct Launch {
     int32_t ahead_bytes = 0;
     int64_t in_bytes = 0;  // algorithmic bytes of the input tensor (counted once in a pair)
     cw_launch_info info{};
+    cw_launch_info issued{};   // what the entry really issues (cw_plan_launch_issued)
     // K_RESIDENT: the convolution layers of the run, each with partition 0's arguments (conv), its
     // tile shape (res_variant), tiles per partition and the members it waits for; `w` of the
     // resident launch itself points at the program's place in the model's weight pages.

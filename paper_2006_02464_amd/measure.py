@@ -127,7 +127,7 @@ def config4(args, log):
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     prof = ctx.profile_measure(mid, B, 1000, slot=slot)
-    plan = ctx.plan(mid, B)
+    plan = [l for _, l in ctx.issued(mid, B)]
     wk.close()
     return {"config": 4, "workload": "ResNet-152 224x224 bf16 storage (fp16 overflows with these weights), batch 16",
             "inferences_per_s": round(B * args.execs / dt, 1), "ms_per_exec_wall": round(dt / args.execs * 1e3, 4),
@@ -385,9 +385,8 @@ def config7(args, log):
             ctx.profile_measure(mid, B, 50, slot=slot)
             p = ctx.profile_measure(mid, B, 1000, slot=slot)
             fam["exec"][str(B)] = {"p50_us": round(p["p50_us"], 2), "p999_over_p50": round(p["p999_us"] / p["p50_us"], 4),
-                                   "inferences_per_s": round(B / (p["p50_us"] * 1e-6), 1), "launches": ctx.plan_num_launches(mid, B)}
+                                   "inferences_per_s": round(B / (p["p50_us"] * 1e-6), 1), "launches": len(ctx.issued(mid, B))}
             if B == 16:
-                plan = ctx.plan(mid, B)
                 ctx.set_use_graphs(0)
                 whole = []
                 for _ in range(60):
@@ -395,14 +394,12 @@ def config7(args, log):
                     whole.append(ctx.exec_duration_ns(slot) / 1e3)
                 raw = np.median(np.stack([ctx.exec_timed_launches(mid, B, slot, ex, inner=1) for _ in range(60)]), axis=0)
                 ctx.set_use_graphs(1)
-                own = np.array([not ctx.plan_launch_joined(mid, B, i) for i in range(len(plan))])   # the others have no launch
-                raw = raw * own
-                over = (float(raw.sum()) - float(np.median(whole[10:]))) / int(own.sum())
-                us = raw - over * own
+                entries = ctx.issued(mid, B)
+                plan, raw = [l for _, l in entries], raw[[i for i, _ in entries]]
+                over = (float(raw.sum()) - float(np.median(whole[10:]))) / len(plan)
+                us = raw - over
                 groups = {}
-                for l, u, o in zip(plan, us, own):
-                    if not o:
-                        continue
+                for l, u in zip(plan, us):
                     key = l["name"].split("_s")[0] if l["name"].startswith(("dwconv", "conv")) else l["name"]
                     g = groups.setdefault(key, [0, 0.0, 0, 0])
                     g[0] += 1; g[1] += float(u); g[2] += l["bytes"]; g[3] += l["flops"]
@@ -410,10 +407,10 @@ def config7(args, log):
                                             "TFLOPs": round(v[3] / (v[1] * 1e-6) / 1e12, 1), "frac_of_8TBps": round(v[2] / (v[1] * 1e-6) / 8e12, 3)}
                                         for k, v in groups.items()}
                 tables.append("== %s, %dx%d, batch 16: every launch (us net of %.2f us event overhead)" % (name, hw, hw, over))
-                tables.append("%-26s %9s %6s %6s %8s %8s %8s %8s" % ("launch", "M", "N", "K", "MB", "us", "GB/s", "TFLOP/s"))
+                tables.append("%-34s %9s %6s %6s %8s %8s %8s %8s" % ("launch", "M", "N", "K", "MB", "us", "GB/s", "TFLOP/s"))
                 for l, u in zip(plan, us):
-                    tables.append("%-26s %9d %6d %6d %8.2f %8.2f %8.0f %8.1f" % (l["name"], l["gemm_m"], l["gemm_n"], l["gemm_k"], l["bytes"] / 1e6, u,
-                                                                                   l["bytes"] / (u * 1e-6) / 1e9 if u else 0, l["flops"] / (u * 1e-6) / 1e12 if u else 0))
+                    tables.append("%-34s %9d %6d %6d %8.2f %8.2f %8.0f %8.1f" % (l["name"], l["gemm_m"], l["gemm_n"], l["gemm_k"], l["bytes"] / 1e6, u,
+                                                                                   l["bytes"] / (u * 1e-6) / 1e9, l["flops"] / (u * 1e-6) / 1e12))
             ctx.release(slot)
         ctx.unload_weights(mid)
         out["families"][name] = fam
@@ -461,7 +458,7 @@ def config8(args, log):
             slot = ctx.input(mid, B, pinned_like(gen.images(0, 0, B, 3, 224, 224, "normal", "fp16")), ex)
             ctx.profile_measure(mid, B, 50, slot=slot)
             p = ctx.profile_measure(mid, B, 1000, slot=slot)
-            row["b%d" % B] = {"launches": ctx.plan_num_launches(mid, B), "p50_us": round(p["p50_us"], 1), "p999_over_p50": round(p["p999_us"] / p["p50_us"], 4)}
+            row["b%d" % B] = {"launches": len(ctx.issued(mid, B)), "p50_us": round(p["p50_us"], 1), "p999_over_p50": round(p["p999_us"] / p["p50_us"], 4)}
             ctx.release(slot)
         ctx.set_use_graphs(1)
         ctx.unload_weights(mid)

@@ -359,6 +359,39 @@ def test_entries_joined_into_the_first_convolutions_launch(ctx):
     assert joined(net((0, 3, 32, 3, 3, 1, 1, 1, -1, -1), (0, 32, 256, 1, 1, 1, 0, 1, -1, 0))) == []                   # stride 1
 
 
+@pytest.mark.parametrize("batch", [1, 4, 16])
+def test_issued_launches_hold_the_work_of_joined_entries(ctx, batch):
+    """Per launch of ResNet-50 what it reads and stores, from the operator list alone: the first convolution's output and the padded
+    image, which the head's launch never stores, are in no launch's bytes."""
+    m = ctx.model_define_resnet(50, 224, 224)
+    plan, issued = ctx.plan(m, batch), dict(ctx.issued(m, batch))
+    gone = [i for i in range(len(plan)) if i not in issued]
+    for i in gone:
+        l = ctx.plan_launch_issued(m, batch, i)
+        assert (l["bytes"], l["flops"], l["grid_x"], l["block"]) == (0, 0, 0, 0)
+    assert gone == [0, 2]
+    assert sum(l["flops"] for l in issued.values()) == 2 * batch * T.mac_count(T.resnet(50), 224, 224)
+    px = batch * 56 * 56
+    head = issued[1]
+    reduce1 = (64 * 64 * 2 + 64 * 4 + px * 64 * 2) if batch > 1 else 0      # the 1x1 over the pooled tile
+    assert head["bytes"] == batch * 3 * 224 * 224 * 4 + 64 * 147 * 2 + 64 * 4 + px * 64 * 2 + reduce1
+    assert head["flops"] == 2 * batch * 112 * 112 * 64 * 147 + (2 * px * 64 * 64 if batch > 1 else 0)
+    assert head["name"] == "cast+stem7x7_s2+maxpool3x3_s2" + ("+1x1" if batch > 1 else "")
+    assert (head["grid_x"], head["block"], head["conv_tile"]) == (batch * (8 if batch > 1 else 19) * 7, 256, -1)   # 7 x 8 or 3 x 8 pooled pixels
+    assert sum(l["bytes"] for l in plan) - sum(l["bytes"] for l in issued.values()) == sum(plan[i]["bytes"] for i in range(3)) - head["bytes"] > 0
+    for i, l in issued.items():
+        assert i == 1 or l == plan[i]
+
+
+def test_issued_launch_of_the_average_pool_and_the_fc(ctx):
+    m = ctx.model_define_resnet(18, 64, 64)
+    plan, issued = ctx.plan(m, 1), dict(ctx.issued(m, 1))
+    fc = next(l for l in issued.values() if l["kind"] == 5)
+    assert fc["name"] == "global_avgpool+fc" and fc["flops"] == 2 * 512 * 1000
+    assert fc["bytes"] == 4 * 512 * 2 + 512 * 1000 * 2 + 1000 * 4 + 1000 * 4    # the map of 2 x 2, weights, bias, logits
+    assert len(issued) == len(plan) - 3
+
+
 def test_an_image_of_2_gib_is_not_joined(ctx):
     """The head's launch reads an image through one descriptor of below 2 GiB; the cast and the convolution take larger ones."""
     tail = [(0, 32, 256, 1, 1, 64, 0, 1, -1, 0), (2, 256, 256, 0, 0, 1, 0, 0, -1, 1), (3, 256, 10, 1, 1, 1, 0, 0, -1, 2), (4, 10, 10, 0, 0, 1, 0, 0, -1, 3)]
