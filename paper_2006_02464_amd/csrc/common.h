@@ -262,7 +262,7 @@ struct FcArgs {
     float *partial;     // [split_k][16][Out] fp32 (split_k > 1)
     int32_t *counters;  // ceil(Out/16) + 1 arrival counters, zero between launches
     int32_t split_k;    // 1, 2 or 4; In % (128 * split_k) == 0
-    // The global average pool in the FC's launch (px != nullptr): f is written (by the first workgroup), not read.
+    // The global average pool in the FC's launch (px != nullptr): no f, the averages stay in LDS.
     const void *px;     // [B][hw][In] in the storage type
     int32_t hw;
 };

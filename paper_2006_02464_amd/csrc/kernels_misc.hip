@@ -400,7 +400,7 @@ __global__ __launch_bounds__(64 * kFcWaves) void fc_kernel(const float *f, const
 // What bounds it: one round trip, then 24 vector instructions for each of the G x U <= 8 loads a lane.  Whole requests, two launches ->
 // one: ResNet-18 64x64 batch 1 from host to host 120.0 -> 115.2 us, on the device 79.4 -> 76.6.
 template <typename T, int G, int U>
-__global__ __launch_bounds__(64 * kFcWaves) void pool_fc_kernel(const void *x, float *f, const void *w, const float *bias, float *z, int B, int In, int Out, int hw) {
+__global__ __launch_bounds__(64 * kFcWaves) void pool_fc_kernel(const void *x, const void *w, const float *bias, float *z, int B, int In, int Out, int hw) {
     __shared__ float part[kFcWaves][16][17];
     __shared__ __attribute__((aligned(16))) float feat[512 * G];
     constexpr int NC = 2 * G;   // most chunks of 32 k that a wave has
@@ -448,7 +448,6 @@ __global__ __launch_bounds__(64 * kFcWaves) void pool_fc_kernel(const void *x, f
         const float v = ((b2 ? a2[1] : a2[0]) + __shfl_xor(b2 ? a2[0] : a2[1], 32, 64)) * inv;
         const int k = at[i] + (b0 ? 4 : 0) + (b1 ? 2 : 0) + (b2 ? 1 : 0);
         feat[k] = v;
-        if (blockIdx.x == 0) f[k] = v;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -1190,8 +1189,7 @@ hipError_t launch_gavgpool(DType dt, const PoolArgs &a, hipStream_t s) {
 template <typename T>
 static hipError_t launch_pool_fc(const FcArgs &a, hipStream_t s) {
     const dim3 grid(blocks_for(a.Out, 16));
-    float *f = const_cast<float *>(a.f);
-#define CW_POOL_FC(G_, U_) pool_fc_kernel<T, G_, U_><<<grid, 64 * kFcWaves, 0, s>>>(a.px, f, a.w, a.bias, a.z, a.B, a.In, a.Out, a.hw)
+#define CW_POOL_FC(G_, U_) pool_fc_kernel<T, G_, U_><<<grid, 64 * kFcWaves, 0, s>>>(a.px, a.w, a.bias, a.z, a.B, a.In, a.Out, a.hw)
     const int g = pool_fc_items(a.B, a.In, a.hw);
     if (g == 1 && a.hw <= 8) CW_POOL_FC(1, 1);
     else if (g == 1) CW_POOL_FC(1, 8);

@@ -1271,7 +1271,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         }
     }
     // The global average pool inside the FC's launch.  The FC's own result goes to the IO slot, so nothing that is placed after the pool
-    // can lie over the pool's input; the pooled values are still written, for other readers.
+    // can lie over the pool's input.  Only the FC may read a global average pool (model_init), so its values are not stored.
     if (ov.fuse && !ov.keep_all && ov.tile < 0 && ov.split_k <= 0)
         for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
             Launch &lp = p.launches[i], &lf = p.launches[i + 1];

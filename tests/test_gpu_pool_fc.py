@@ -52,3 +52,24 @@ def test_pool_and_fc_in_one_launch(ctx, c, h, w, out, batch, dtype, one):   # no
     b, joined = logits(ctx, c, h, w, out, batch, dtype, False, blob, x)
     assert not apart and joined == one
     assert np.array_equal(a, b) and np.isfinite(a).all() and np.any(a != 0)
+
+
+@pytest.mark.parametrize("c,h,w,batch,dtype", [(512, 3, 5, 3, "fp16"), (1024, 2, 4, 2, "bf16"), (2048, 4, 4, 1, "fp16")])
+def test_pool_and_fc_in_one_launch_with_non_finite_maps(ctx, c, h, w, batch, dtype):   # noqa: F811
+    """Maps with NaN, infinities and large values give the logits of the two launches, NaN where they are NaN."""
+    g = np.random.default_rng(c)
+    half = torch.float16 if dtype == "fp16" else torch.bfloat16
+    shapes = [(32, 27), (c, 32), (40, c)]
+    wb = torch.cat([torch.from_numpy(g.normal(0, (128.0 if k == 27 else 2.0 / k) ** 0.5, n * k).astype(np.float32)).to(half) for n, k in shapes]).view(torch.uint8)
+    bs = torch.cat([torch.from_numpy(g.normal(0, 0.3, n).astype(np.float32)) for n, _ in shapes])
+    blob = torch.cat([wb, torch.zeros(-wb.numel() % 4, dtype=torch.uint8), bs.view(torch.uint8)]).pin_memory()
+    plain = torch.from_numpy(g.normal(0, 1, (batch, 3, 2 * h, 2 * w)).astype(np.float32))
+    # one pixel whose filter sums overflow when they are stored: infinities and, behind the 1x1, NaN in part of the map; all of a
+    # sample like that; averages of a large, finite map
+    for value, at in ((6e4 if dtype == "fp16" else 3e38, (batch - 1, 1, h, w)), (6e4 if dtype == "fp16" else 3e37, batch - 1), (30.0, batch - 1)):
+        x = plain.clone()
+        x[at] = value
+        a, apart = logits(ctx, c, h, w, 40, batch, dtype, True, blob, x.pin_memory())
+        b, joined = logits(ctx, c, h, w, 40, batch, dtype, False, blob, x.pin_memory())
+        assert joined and not apart and np.array_equal(a, b, equal_nan=True) and np.isfinite(a[:batch - 1]).all()
+        assert np.isfinite(a[batch - 1]).all() == (value == 30.0)
