@@ -3,6 +3,8 @@ swish, CONCAT written in place) on the MobileNet-, DenseNet- and Inception-style
 every layer teacher forced against the CPU oracle, logits within the per-sample tolerance."""
 import numpy as np
 import pytest
+import torch
+import torch.nn.functional as F
 
 from gpu_common import TOL, Case, rel_err_per_sample
 from oracle import network as N
@@ -183,4 +185,52 @@ def test_depthwise_3x3_at_the_line_between_its_two_forms(worker, batch):
     x = case.images(0, batch)
     worker.infer(mid, x, classes=10)
     check_every_launch(worker, case, mid, batch, x)
+    worker.ctx.unload_weights(mid)
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_depthwise_3x3_with_all_taps_together_on_non_finite_values(worker, dtype):
+    """NaN, infinities and overflow, inside and at the edges of the map: every output of the form that requests all nine taps at
+    once against 64-bit arithmetic on the inputs it had, NaN and infinite where that is."""
+    O = T.Op
+    ops = [O(T.CONV, 3, 64, 3, 3, 1, 1, 0, -1, -1), O(T.CONV, 64, 64, 3, 3, 1, 1, 0, -1, 0, 0, 64), O(T.CONV, 64, 64, 3, 3, 1, 1, 1, 0, 0, 0, 64),
+           O(T.CONV, 64, 64, 3, 3, 2, 1, 2, -1, 0, 0, 64), O(T.CONV, 64, 64, 3, 3, 2, 0, 0, -1, 1, 0, 64), O(T.CONV, 64, 256, 1, 1, 1, 0, 1, -1, 3),
+           O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 5), O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 6), O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 7)]
+    h, batch = 19, 6
+    case = Case(ops, h, seed=6, dtype=dtype, dist="normal")
+    worker.ctx.set_debug_keep(True)
+    try:
+        mid = worker.ctx.model_define(case.ops, 3, h, h, batch_sizes=(batch,), dtype=dtype)
+    finally:
+        worker.ctx.set_debug_keep(False)
+    plan = worker.ctx.plan(mid, batch)
+    assert all(l["grid_x"] <= 1024 for l in plan if l["name"].startswith("dwconv"))
+    worker.load(mid, case.blob)
+    x = case.images(0, batch).copy()
+    x[1, 0, 9, 9], x[2, 1, 0, 0], x[2, 2, h - 1, 7], x[3, 0, 5, h - 1] = np.nan, np.inf, -np.inf, np.inf
+    x[4] *= 2e4        # finite as stored, above fp16's range behind the filters
+    x[5] *= 2.0 ** -20
+    worker.infer(mid, x, classes=10)
+    shapes = T.shapes(ops, h, h)
+    got = {i: torch.from_numpy(worker.ctx.debug_read_op(mid, batch, i, (batch,) + tuple(shapes[i]))) for i in range(5)}
+    half = torch.float16 if dtype == "fp16" else torch.bfloat16
+    seen = 0
+    for i in range(1, 5):
+        o = ops[i]
+        v = F.conv2d(got[o.input_from].double(), torch.from_numpy(case.w[i]).double(), torch.from_numpy(case.b[i]).double(), o.stride, o.pad, 1, 64)
+        if o.residual_from >= 0:
+            v = v + got[o.residual_from].double()
+        relu = lambda t: torch.where(t > 0, t, torch.zeros_like(t))      # of NaN: 0, as fmaxf has it
+        v = relu(v) if o.relu == 1 else v * relu(v + 3).clamp(max=6) / 6 if o.relu == 2 else v
+        want, have = v.float().to(half).double(), got[i].double()
+        top = torch.finfo(half).max
+        edge = (v.abs() > top * (1 - 2.0 ** -9)) & (v.abs() < top * (1 + 2.0 ** -7))    # may round to the largest value or to infinity
+        assert torch.equal(want.isnan(), have.isnan())
+        assert torch.equal(want.isinf() & ~edge, have.isinf() & ~edge) and torch.equal(want[want.isinf() & ~edge], have[want.isinf() & ~edge])
+        live = want.isfinite() & have.isfinite()
+        scale = F.conv2d(got[o.input_from].double().nan_to_num(0, 0, 0).abs(), torch.from_numpy(np.abs(case.w[i])).double(), None, o.stride, o.pad, 1, 64) + 4
+        # one rounding to the storage type, which ten fp32 additions may shift by a unit
+        assert ((want - have).abs() <= (2.0 ** -10 if dtype == "fp16" else 2.0 ** -7) * want.abs() + 10 * 2.0 ** -24 * scale)[live].all(), i
+        seen += int((~want.isfinite()).sum())
+    assert seen > 1000
     worker.ctx.unload_weights(mid)

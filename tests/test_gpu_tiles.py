@@ -79,6 +79,17 @@ def test_tiles_in_parts(worker, tile, hw, dtype, batch, split_k):
     assert {l["gemm_k"] for l in small} == {256, 2304, 4608, 512}
 
 
+@pytest.mark.parametrize("tile", [17, 18, 19, 20, 21, 24, 29, 30, 31, 33, 35, 36, 37, 38, 39, 40])
+@pytest.mark.parametrize("split_k,dtype", [(5, "fp16"), (8, "bf16")])
+def test_more_splits_than_are_added_up_together(worker, tile, split_k, dtype):
+    """The waves of tiles in four and eight groups add partial sums up four splits at a time: one split in the second round, up
+    to four, and rounds that hold the wave's own sums."""
+    splits = {l["split_k"] for l in run(worker, 45, dtype, 3, tile, split_k) if l["kind"] == 1 and l["conv_tile"] == tile}
+    slices = 4608 // {17: 128, 18: 128, 19: 128, 20: 128, 21: 128, 24: 64, 36: 128, 37: 128, 38: 128}.get(tile, 256)
+    per = -(-slices // split_k)
+    assert max(splits) == -(-slices // per) > 4
+
+
 @pytest.mark.parametrize("tile", [36, 37, 38])
 def test_pair_launches_on_tiles_in_parts(worker, tile):
     """A 3x3 of stride 2 and the projection beside it in one launch, the last tile of pixels part full (3 x 6 x 6 = 108)."""
