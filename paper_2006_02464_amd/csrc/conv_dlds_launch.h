@@ -5,8 +5,9 @@
 namespace cw {
 
 #ifdef CW_STAMPS
-// A build for tune.py: workgroup b of the process's convolution launch number l leaves {start, end} in ticks of 10 ns at
-// cw_stamps[(l % kStampLaunches) * kStampGroups + b], end = its stores have been taken.
+// A build for tune.py: workgroup b of convolution launch number l since the last reset leaves {start, end} in ticks of 10 ns at
+// cw_stamps[(l % kStampLaunches) * kStampGroups + b], end = the stores of all its waves have been taken (in wave groups every wave
+// ends by itself).  Nothing before the first reset, which allocates the room.
 constexpr unsigned kStampLaunches = 256, kStampGroups = 16384;
 extern ulonglong2 *cw_stamps;
 extern unsigned cw_stamp_next;
@@ -14,10 +15,11 @@ extern unsigned cw_stamp_next;
 #define CW_STAMP_BEGIN const unsigned long long stamp_from = __builtin_amdgcn_s_memrealtime();
 #define CW_STAMP_END                                                                                            \
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                                            \
+    __syncthreads();                                                                                            \
     const unsigned stamp = blockIdx.x + conv_nb_tiles(nb) * conv_parts<BM, BN, MT>() * blockIdx.y;              \
-    if (threadIdx.x == 0 && stamp < kStampGroups)                                                               \
+    if (threadIdx.x == 0 && stamps && stamp < kStampGroups)                                                     \
         stamps[stamp] = make_ulonglong2(stamp_from, __builtin_amdgcn_s_memrealtime());
-#define CW_STAMP_PASS , cw_stamps + (size_t)(cw_stamp_next++ % kStampLaunches) * kStampGroups
+#define CW_STAMP_PASS , cw_stamps ? cw_stamps + (size_t)(cw_stamp_next++ % kStampLaunches) * kStampGroups : nullptr
 #else
 #define CW_STAMP_ARG
 #define CW_STAMP_BEGIN

@@ -3,8 +3,8 @@
 // A workgroup's K walk is bound by what its CU loads, 64 bytes a clock: a slice of 256 for a whole tile is 32 KB, for
 // a quarter half of that, and where whole tiles leave most of the CUs idle (batch 1: 56 workgroups in stage 3, 32 in stage 4)
 // the four quarters run beside each other.  The groups' accumulators, a quarter as many, are also added up sooner.
-// First workgroup's start to last store, 32x32k256g4 -> in quarters, batch 1: 3x3 of 256 channels at 14x14 5.0 -> 3.65 us, of 512
-// channels at 7x7 7.5 (K in 4 parts) -> 5.6, 1x1 2048 -> 512 at 7x7 4.5 -> 3.3, 1024 -> 256 at 14x14 3.0 -> 2.4.
+// First workgroup's start to last store, 32x32k256g4 -> in quarters, batch 1: 3x3 of 256 channels at 14x14 4.85 -> 3.39 us, of 512
+// channels at 7x7 7.53 (5.85 with K in 4 parts) -> 5.05, 1x1 2048 -> 512 at 7x7 4.56 -> 3.30, 1024 -> 256 at 14x14 3.19 -> 2.37.
 // With 64x64 tiles whose four waves each own the whole tile for a quarter of K (half the LDS reads per matrix
 // instruction) the 3x3 of stage 3 at batch 16 took 9.4 us, on 64x64 in four groups of four waves 9.2: not kept.
 #include "conv_dlds_launch.h"
