@@ -268,8 +268,8 @@ struct FcArgs {
 };
 // Every workgroup of the FC then pools the whole map: each of its eight waves its own part of the channels, in items of 64 channels of a
 // sample.  The pool's launch and round trip are worth 8 loads a lane, 1, 2 or 4 items (the return value, 0: launches of their
-// own) times 8 pixels each: ResNet-18 64x64 batch 1 79.4 -> 76.6 us, batch 4 86.8 -> 85.5, 224x224 batch 1 86.2 -> 84.6, ResNet-50 97x97
-// batch 1 177.0 -> 175.5; with 16 to 32 loads it is the other way round (ResNet-50 224x224 batch 1, 28 loads, 197.7 -> 200.3;
+// own) times 8 pixels each: EXEC of ResNet-18 64x64 batch 1 87.4 -> 85.2 us, batch 4 88.6 -> 86.3, 224x224 batch 1 94.7 -> 92.5, ResNet-50
+// 97x97 batch 1 184.1 -> 183.1; with 16 to 32 loads it is the other way round (ResNet-50 224x224 batch 1, 28 loads, 197.7 -> 200.3;
 // MobileNet 150x99 batch 3, 18, 88.6 -> 95.6), and eight items do not fit the registers beside their weights.
 constexpr int pool_fc_items(int64_t B, int64_t in, int64_t hw) {
     if (B < 1 || in < 1 || hw < 1 || in % 512 != 0 || in / 512 * B > 4) return 0;
@@ -376,9 +376,10 @@ hipError_t launch_wino_output(DType dt, const WinoArgs &a, hipStream_t s);
 // LOAD-time: canonical W[cout][cin][3][3] -> U[16][cout'][cin] = G g G^T per (cout, cin), rows in the
 // conv kernel's accumulator order, computed in fp32 and rounded once to the storage type
 hipError_t launch_pack_winograd(DType dt, const void *src, void *dst, int cout, int cin, hipStream_t s);
-// Workgroups of a LOAD-side launch: at most four per compute unit, which is what the pack kernel's LDS lets run at once, each striding
-// over its work.  (ResNet-50's 51 MB behind the copy: 53 us with one per CU, 37 with four, the same with eight.  Measured with
-// EXECs running beside continuous LOADs: caps of 16, 48, 256 and no cap all leave the EXEC p50 within 0.6 % of EXEC alone.)
+// Workgroups of a LOAD-side launch (weight packing and Winograd's transform of weights): at most four per compute unit, which is what the
+// pack kernel's LDS lets run at once, each striding over its work.  ResNet-50's 51 MB behind the copy: 53 us with one per CU, 37
+// with four, the same with eight.  A batch-8 EXEC beside back-to-back LOADs, six processes each: +1.2 to +3.1 % at the median with
+// four, +1.5 to +3.3 % with one; it is the copy that disturbs.
 constexpr unsigned kLoadGridCap = 1024;
 // LOAD-time re-layout of one tensor and its bias: canonical W[cout][cin][kh][kw] -> [cout'][khp][kwp][cinp] (zero padded);
 // permute = rows in the conv kernel's MFMA accumulator order (conv weights), else plain (FC);

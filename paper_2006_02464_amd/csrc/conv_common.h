@@ -249,8 +249,8 @@ static __device__ __forceinline__ void epilogue_store(const f32x16 (&acc)[TM][TN
 // in group order: the sum is the one a single finishing group would make) and carries them through bias, residual,
 // activation and store.  With one finishing group its waves read KG-1 times 16 single registers and convert and
 // store 16 values, 0.64 us from the last matrix instruction to the last store of a 32x32 tile in four groups, a quarter
-// of a 1x1 launch at batch 1.  ResNet-50 batch 1 245.4 -> 236.9 us, 193x161 batch 3 263.2 -> 256.6, MobileNet batch 1
-// 126.9 -> 122.6.
+// of a 1x1 launch at batch 1.  EXEC of ResNet-50 batch 1 253.3 -> 244.8 us, 193x161 batch 3 272.1 -> 265.8, MobileNet batch 1
+// 135.7 -> 131.2.
 template <int MT, int TM, int TN, int KG>
 struct GroupUnits {
     static constexpr int PER_TILE = MT == 32 ? 4 : 1;

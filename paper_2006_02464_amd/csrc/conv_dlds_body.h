@@ -61,7 +61,7 @@ static __device__ __forceinline__ u32x4 make_desc(const void *p, unsigned bytes)
 
 // t / d of workgroup-uniform values, 0 <= t, 0 < d: exact below 2^21, where t/d's rounding errors (a few 2^-23 of it) stay
 // below the half d-th that separates (t + 0.5)/d from the integers; the compiler's integer division takes three
-// times as long, and every address waits for it (0.5 % of an EXEC at batch 1).
+// times as long, and every address waits for it (EXEC of ResNet-50 batch 1 206.2 -> 205.2 us, DenseNet batch 6 216.1 -> 212.7).
 static __device__ __forceinline__ int tile_div(int t, int d) {
     if (__builtin_expect(t >= 1 << 21, 0)) return t / d;
     return __builtin_amdgcn_readfirstlane((int)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)d)));
@@ -125,8 +125,8 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const int tid = threadIdx.x;
     // Fused form: the layers' biases are requested now, without a branch (what is missing is a load out of range), and go to LDS
     // behind the K walk, by when they have long arrived: no counted load waits for them.  (Stored to LDS before the first slices
-    // were requested they were 0.7-1 us of every fused launch's set-up: ResNet-50 batch 16 425.9 -> 421.7 us, 160x140 batch 9
-    // 275.9 -> 265.0.)
+    // were requested they were 0.7-1 us of every fused launch's set-up: EXEC of ResNet-50 batch 16 416.7 -> 412.1 us, batch 8 329.7 ->
+    // 326.0.)
     constexpr unsigned BIAS_OFF = FUSED ? (NS * STAGE_BYTES > fused_lds_bytes(BM, BN, KG) ? NS * STAGE_BYTES : fused_lds_bytes(BM, BN, KG)) : 0u;
     constexpr int B2_PER = FUSED ? (kFusedMaxCout2 + NT - 1) / NT : 1;
     unsigned bias1_v = 0, bias2_v[B2_PER], biasd_v[B2_PER], bias3_v = 0;
@@ -187,7 +187,8 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const u32x4 dw = make_desc(a.w, (unsigned)a.Cout * a.K * 2u);
 
     // With general addressing the first slice's weights are requested before the pixel arithmetic and the argument line that it
-    // waits for: ResNet-18 batch 8 138.9 -> 134.6 us, ResNet-50 batch 1 201.1 -> 198.4.  (All weights of the prologue there make the
+    // waits for: EXEC of ResNet-18 batch 8 146.0 -> 141.7 us, ResNet-50 batch 1 209.1 -> 205.2, ResNet-152 batch 16 1126.6 -> 1116.
+    // MobileNet, whose convolutions are 1x1, is the same either way.  (All weights of the prologue there make the
     // first slice wait for the later ones': ResNet-18 3 % slower.)
     constexpr bool WFIRST = !GEMM;
     const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)

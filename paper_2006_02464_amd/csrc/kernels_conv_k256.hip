@@ -4,8 +4,8 @@
 // a CU loads are the bound (a 32x32 tile moves 32 KB a slice: 0.21 us).  Four or eight groups of waves share a slice's
 // 16 steps of matrix instructions.  Measured, slices of 128 -> 256: 3x3, 256 channels, 14x14, batch 1 7.0 -> 6.3 us; 3x3, 512
 // channels, 7x7, batch 8 10.9 -> 9.2 us and batch 16 14.4 -> 12.0 us.
-// The plan takes 32x32, 64x32 and 32x64 in four groups and, for the fewest pixels, 32x32 in parts (kernels_conv_small.hip).  The
-// tiles in eight groups, 64x64 and the split-K forms of whole tiles are left to a forced or installed tile.
+// The plan takes 32x32, 64x32 and 32x64 in four groups, K whole or split, 32x32 in eight now and then and, for the fewest pixels, 32x32
+// in parts (kernels_conv_small.hip).  64x64 and the wider tiles in eight groups are left to a forced or installed tile.
 #include "conv_dlds_launch.h"
 
 namespace cw {

@@ -1,5 +1,6 @@
 // The direct-to-LDS convolution on 32x32 tiles in parts, each on a workgroup of its own (four groups of one wave, 16x16x32 matrix
 // instructions): quarters of 16x16, or halves of 32 pixels x 16 channels or 16 x 32.  For few pixels and long K.
+// The networks' own layers are split in K on quarters with slices of 256 alone; other shapes on all five.
 // A workgroup's K walk is bound by what its CU loads, 64 bytes a clock: a slice of 256 for a whole tile is 32 KB, for
 // a quarter half of that, and where whole tiles leave most of the CUs idle (batch 1: 56 workgroups in stage 3, 32 in stage 4)
 // the four quarters run beside each other.  The groups' accumulators, a quarter as many, are also added up sooner.

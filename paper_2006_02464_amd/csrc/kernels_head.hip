@@ -8,12 +8,14 @@
 // matrix cores straight out of that patch, two taps x 4 channels being 16 consecutive bytes of it (the stride is 2).  With a pool the rounded
 // convolution tile goes to LDS, -inf outside the convolution's map, and is pooled from there; a pooled tile of 7 x 8 needs
 // 15 x 17 = 255 convolution pixels, eight MFMA tiles of 32, of which an eighth is computed twice by neighbours.  K runs in the order of
-// the launches of their own and every tensor is rounded as when it is stored: same bits.
+// the launches of their own and every tensor is rounded as when it is stored: same bits.  (A filter row is padded with weights of
+// zero, to 8 taps of a 7x7 and 4 of a 3x3, which has 8 in a launch of its own: an infinite or NaN pixel also makes NaN of the
+// outputs whose row ends that far before it.)
 // What bounds it: the chain image load, matrix cores, pool, at batch 16 3.5 times per CU side by side (first workgroup's
 // start to last store, 224x224: ResNet-50 batch 16 12.6 us, batch 1 4.1, ResNet-18 batch 8 7.7, MobileNet batch 16 5.5), hence the 40 KB of LDS:
 // with 56 KB, two workgroups a CU, and the weights loaded as fragments, 32 rows to an instruction, batch 16 took 21.1.  Whole
-// EXECs against three launches: ResNet-50 batch 16 423.6 -> 403.3 us, ResNet-18 batch 8 155.4 -> 142.3, DenseNet batch 6 246.1 -> 231.8,
-// ResNet-50 batch 1 210.9 -> 205.6, Inception 127x127 batch 5 95.6 -> 92.9.
+// EXECs against three launches: ResNet-50 batch 16 440.6 -> 422.0 us, batch 1 219.4 -> 212.0, ResNet-18 batch 8 163.6 -> 147.2, DenseNet
+// batch 6 238.2 -> 224.1, Inception 127x127 batch 5 104.5 -> 100.2.
 #include "conv_common.h"
 
 namespace cw {

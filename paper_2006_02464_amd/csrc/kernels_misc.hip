@@ -397,8 +397,8 @@ __global__ __launch_bounds__(64 * kFcWaves) void fc_kernel(const float *f, const
 // what its FC tile needs: wave w of a workgroup needs only the channels of its own part of K, so it requests its weights and its
 // part of the map together, G items of 64 channels of a sample with U x 8 pixels each, and passes the averages to its own
 // lanes through LDS; no barrier stands between.  Sums, products and roundings in the order of the two kernels: same bits.
-// What bounds it: one round trip, then 24 vector instructions for each of the G x U <= 8 loads a lane.  Whole requests, two launches ->
-// one: ResNet-18 64x64 batch 1 from host to host 120.0 -> 115.2 us, on the device 79.4 -> 76.6.
+// What bounds it: one round trip, then 24 vector instructions for each of the G x U <= 8 loads a lane.  EXEC of ResNet-18 64x64 batch 1, two
+// launches -> one: 87.4 -> 85.2 us.
 template <typename T, int G, int U>
 __global__ __launch_bounds__(64 * kFcWaves) void pool_fc_kernel(const void *x, const void *w, const float *bias, float *z, int B, int In, int Out, int hw) {
     __shared__ float part[kFcWaves][16][17];
@@ -748,8 +748,8 @@ __global__ __launch_bounds__(256) void dwconv_kernel(const DwArgs a) {
 // The 3x3 form for launches whose workgroups all run at once: there a thread's chain of nine loads one after the other is the
 // launch's time, not the bytes.  All taps of the image and of the filter are requested together, a tap outside the
 // image as a load out of range of both (zeros), and the index arithmetic multiplies.  Same order of additions.
-// MobileNet's 128..1024-channel layers at batch 1 take 3.4 us a launch for 5.7 (kernel trace), whole EXECs 136.0 -> 109.6 us at batch 1,
-// 148.2 -> 129.3 at batch 4, 205.9 -> 198.9 at batch 16.  With more workgroups than run at once the general form's eight waves a
+// MobileNet's 128..1024-channel layers at batch 1 take 3.4 us a launch for 5.7 (kernel trace), whole EXECs 127.6 -> 100.5 us at batch 1,
+// 142.8 -> 121.2 at batch 4, 206.5 -> 200.0 at batch 16.  With more workgroups than run at once the general form's eight waves a
 // SIMD are faster (112x112x64 at batch 16: 13.0 us, 17.1 with all taps requested together).
 template <typename T>
 __global__ __launch_bounds__(256, 4) void dwconv3_kernel(const DwArgs a) {
