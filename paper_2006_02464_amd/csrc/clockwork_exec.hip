@@ -1348,8 +1348,8 @@ int32_t cw_plan_launch_issued(cw_ctx *c, int32_t model_id, int32_t batch, int32_
     if (!m || !out) return set_err(c, CW_ERR_INVALID, "unknown model id or null pointer");
     Plan *p = get_plan(m, batch);
     if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
-    if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
-    *out = p->launches[index].issued;
+    if (index < 0 || index >= (int32_t)p->issued.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
+    *out = p->issued[index];
     return CW_OK;
 }
 

@@ -1349,13 +1349,13 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         if (l.kind != K_CONV) { l.info.conv_tile = -1; l.info.wave_groups = 1; }
         l.info.grid_x = g.x; l.info.grid_y = g.y; l.info.grid_z = g.z; l.info.block = b;
         if (l.info.split_k == 0) l.info.split_k = 1;
-        l.issued = l.info;
+        p.issued.push_back(l.info);
     }
     // What is really issued where entries are joined: the work moves to the entry that launches it, without the tensors that never
     // leave the chip then.
     for (size_t i = 0; i < p.launches.size(); ++i) {
-        Launch &l = p.launches[i];
-        cw_launch_info &d = l.issued;
+        const Launch &l = p.launches[i];
+        cw_launch_info &d = p.issued[i];
         if (l.in_head == 1 || l.in_fc) {
             d.bytes = d.flops = 0;
             d.grid_x = d.grid_y = d.grid_z = d.block = 0;

@@ -59,7 +59,6 @@ struct Launch {
     int32_t ahead_bytes = 0;
     int64_t in_bytes = 0;  // algorithmic bytes of the input tensor (counted once in a pair)
     cw_launch_info info{};
-    cw_launch_info issued{};   // what the entry really issues (cw_plan_launch_issued)
     // K_RESIDENT: the convolution layers of the run, each with partition 0's arguments (conv), its
     // tile shape (res_variant), tiles per partition and the members it waits for; `w` of the
     // resident launch itself points at the program's place in the model's weight pages.
@@ -97,6 +96,7 @@ struct Plan {
     int32_t batch = 0;
     int32_t n_counters = 0;   // arrival counters its launches use, from the start of the workspace
     std::vector<Launch> launches;
+    std::vector<cw_launch_info> issued;   // what every entry really issues (cw_plan_launch_issued)
     std::vector<Ref> op_out;  // workspace (or slot) location of every op's output
     std::vector<int32_t> op_ld;  // elements from one pixel of that output to the next (> its channels where it is a
                                  // channel range of a CONCAT result)
