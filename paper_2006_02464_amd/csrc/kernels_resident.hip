@@ -21,9 +21,9 @@
 // Flags hold epoch numbers: "done" means equal to *epoch + 1, and a one-thread launch behind the
 // run increments *epoch, so flags never need clearing.
 //
-// Measured on an MI355X (ResNet-50, 224x224, batch 16, the 52 convolutions after the max pool): 846 us
-// as one resident launch against 445 us as per-layer launches (fused and paired).  Without any
-// waiting the resident form still takes 723 us: a workgroup owns its CU alone (the kernel holds
+// Measured on an MI355X (ResNet-50, 224x224, batch 16, the 52 convolutions after the max pool): an EXEC takes 653 us with
+// them as one resident launch against 402 us as per-layer launches (fused and paired).  Waiting is the smaller part (when
+// the two took 846 and 445 us, 723 were left without any): a workgroup owns its CU alone (the kernel holds
 // every tile shape, 256 + 91 registers per lane and up to 144 KiB of LDS) and runs its tiles one
 // after the other, so nothing overlaps a tile's set-up, first loads and store drain, which is most
 // of a tile in the short-K layers of stages 1-2 (6-7 tiles per workgroup and layer); the flags cost
