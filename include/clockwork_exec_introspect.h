@@ -80,6 +80,11 @@ int32_t cw_set_debug_keep(cw_ctx *ctx, int32_t keep);
  * issue every kernel as its own launch instead; on != 0 restores the default.  Takes effect
  * for the next EXEC; graphs are recorded by LOADs issued while the setting is on. */
 int32_t cw_set_use_graphs(cw_ctx *ctx, int32_t on);
+/* A stream that waits for an EXEC of another stream (OUTPUT, or an INPUT that takes the memory of an unfinished request) first
+ * runs one wave that ends as the EXEC's last launch begins: a stream that waits any longer slows the EXEC's launches down.  The
+ * wave gives up after `us` microseconds, at most 1000000; 0: no such wave, < 0 restores the default of 50000.  The stream waits
+ * for the EXEC either way. */
+int32_t cw_set_wait_launches(cw_ctx *ctx, int32_t us);
 /* Test hook: models defined afterwards use conv tile variant `conv_tile` (0..40 =
  * 128x128, 128x64, 64x64, 64x32, 32x64, 32x32, 128x64 on 2 waves, 64x128 on 2 waves,
  * 256x64, 128x128 on 8 waves, then 128x64, 64x64, 64x32, 32x64, 32x32 with K slices of 128

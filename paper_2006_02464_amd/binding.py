@@ -115,6 +115,7 @@ SIGNATURES = {
     "cw_set_winograd": (c_int32, [c_void_p, c_int32]),
     "cw_set_resident": (c_int32, [c_void_p, c_int32]),
     "cw_set_use_graphs": (c_int32, [c_void_p, c_int32]),
+    "cw_set_wait_launches": (c_int32, [c_void_p, c_int32]),
     "cw_strerror": (c_char_p, [c_int32]),
     "cw_last_error": (c_char_p, [c_void_p]),
 }
@@ -355,6 +356,9 @@ class Context:
 
     def set_use_graphs(self, on):
         self._check(lib().cw_set_use_graphs(self._h, int(on)))
+
+    def set_wait_launches(self, us=-1):
+        self._check(lib().cw_set_wait_launches(self._h, int(us)))
 
     def set_plan_override(self, conv_tile=-1, split_k=0):
         if isinstance(conv_tile, str):

@@ -21,6 +21,9 @@ constexpr int kMaxSlots = 64;
 constexpr size_t kDefaultPageBytes = (size_t)16 << 20;  // the paper's page size (section 5.1)
 constexpr int kProfileEvents = 128;  // EXECs timed back to back between two host syncs
 
+constexpr int kDoneStride = 32;      // words from one slot's `done` word to the next: a line each
+constexpr unsigned kWaitUs = 50000;  // default of cw_set_wait_launches
+
 enum SlotState { SLOT_FREE = 0, SLOT_RELEASED, SLOT_INPUT, SLOT_EXECUTED };   // released: free once `released` is over
 
 struct Slot {
@@ -32,6 +35,9 @@ struct Slot {
     hipEvent_t exec_seen = nullptr;          // behind exec_end, with its fence, of an EXEC whose launches may raise the error word
     bool raises_error = false;               // its last EXEC was one
     uint64_t release_seq = 0;                // order of release
+    hipStream_t exec_stream = nullptr;       // of its last EXEC
+    unsigned exec_seq = 0;                   // EXECs on it so far
+    bool tells = false;                      // the last one's softmax writes exec_seq to the slot's `done` word
 };
 
 // The slot-independent middle of a plan (everything between the input cast and the FC) as one
@@ -129,6 +135,8 @@ struct cw_ctx {
     hipStream_t last_exec_stream = nullptr;
     hipEvent_t last_exec_end = nullptr;
     uint64_t release_seq = 0;
+    unsigned *done = nullptr;        // device: a word per slot
+    unsigned wait_us = kWaitUs;      // longest life of a wait_done launch, 0: none are issued
     // Set while free IO memory may still be in use by the request it was taken from: `given_on` is over once none is.
     hipEvent_t given_on = nullptr;
     bool given_on_pending = false;
@@ -184,6 +192,8 @@ Plan *get_plan(ModelRt *m, int32_t batch) {
 struct Bases {
     char *workspace = nullptr, *input = nullptr, *logits = nullptr, *probs = nullptr;
     const int32_t *pages = nullptr;  // pool page of each of the model's weight pages
+    unsigned *done = nullptr;        // the slot's word that the softmax writes `seq` to, if any
+    unsigned seq = 0;
     int32_t clear_counters = 0;      // arrival counters the first launch clears (where the last user of the workspace is not known)
 };
 
@@ -191,7 +201,10 @@ Bases bases_of(const cw_ctx *c, const ModelRt *m, const Slot *s) {
     Bases b;
     b.workspace = c->workspace;
     b.pages = m->pages.data();
-    if (s) { b.input = c->io + s->in_off; b.logits = c->io + s->logits_off; b.probs = c->io + s->probs_off; }
+    if (s) {
+        b.input = c->io + s->in_off; b.logits = c->io + s->logits_off; b.probs = c->io + s->probs_off;
+        b.done = c->done + (s - c->slots) * kDoneStride; b.seq = s->exec_seq;
+    }
     return b;
 }
 
@@ -298,6 +311,8 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
             SoftmaxArgs a = l.sm;
             a.z = reinterpret_cast<const float *>(resolve(c, m, s, l.x));
             a.p = reinterpret_cast<float *>(resolve(c, m, s, l.y));
+            a.done = s.done;
+            a.seq = s.seq;
             return launch_softmax(a, st);
         }
         case K_DWCONV: {
@@ -414,6 +429,19 @@ void free_slot(cw_ctx *c, Slot *s, bool pending = false) {
     s->release_seq = ++c->release_seq;
 }
 
+// Issued ahead of a wait of `st` for `end`, at or soon behind the end of the slot's EXEC (see wait_done_kernel).  The wait stays what
+// orders the two: where none is issued, or its launch fails, nothing is lost.
+void wait_quietly(cw_ctx *c, const Slot &s, hipEvent_t end, hipStream_t st) {
+    if (!s.tells || s.exec_stream == st || c->wait_us == 0) return;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // a capture of another thread is not disturbed by the query
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+    const bool pending = hipEventQuery(end) == hipErrorNotReady;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (pending) (void)launch_wait_done(c->done + (&s - c->slots) * kDoneStride, s.exec_seq, c->wait_us, st);
+}
+
 // From here on free IO memory may still be in use by work that `st` waits for.
 void mark_given_on(cw_ctx *c, hipStream_t st) {
     if (hipEventRecord(c->given_on, st) == hipSuccess) c->given_on_pending = true;
@@ -441,6 +469,7 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
         for (Slot &o : c->slots)
             if (o.state == SLOT_RELEASED && (!old || o.release_seq < old->release_seq)) old = &o;
         if (!old) return hipErrorNotFound;
+        wait_quietly(c, *old, old->released, st);
         const hipError_t e = hipStreamWaitEvent(st, old->released, 0);
         if (e == hipSuccess) {
             low = std::min(low, old->off);
@@ -475,6 +504,7 @@ int32_t acquire_slot(cw_ctx *c, ModelRt *m, int32_t model_id, int32_t batch, hip
     }
     if (high > 0 && (low < off || high > off + total)) mark_given_on(c, st);   // not all of it is this request's now
     s.state = SLOT_INPUT;
+    s.tells = false;
     s.model = model_id; s.batch = batch;
     s.off = off; s.bytes = total;
     s.in_off = off;
@@ -564,6 +594,8 @@ int32_t enqueue_plan(cw_ctx *c, ModelRt *m, const Plan *p, const Slot *s, hipStr
 // Records the end of an EXEC that has been enqueued on `st` and remembers where it went.
 int32_t record_exec_end(cw_ctx *c, ModelRt *m, const Plan *p, Slot *s, hipStream_t st) {
     CW_HIP(c, hipEventRecord(s->exec_end, st));
+    s->exec_stream = st;
+    s->tells = p->launches.back().kind == K_SOFTMAX;
     s->raises_error = false;
     for (const Launch &l : p->launches) s->raises_error |= l.kind == K_RESIDENT;
     if (s->raises_error) CW_HIP(c, hipEventRecord(s->exec_seen, st));
@@ -654,6 +686,12 @@ int32_t cw_create(cw_ctx **out, const cw_config *cfg) {
         cleanup();
         return CW_ERR_HIP;
     }
+    if (hipMalloc(reinterpret_cast<void **>(&p->done), kMaxSlots * kDoneStride * 4) != hipSuccess ||
+        hipMemset(p->done, 0, kMaxSlots * kDoneStride * 4) != hipSuccess) {
+        g_create_err = std::string("the slots' words: ") + hipGetErrorString(hipGetLastError());
+        cleanup();
+        return CW_ERR_NO_MEMORY;
+    }
     p->resident_capable = prop.multiProcessorCount == kResPartitions * kResGroupsPerPartition;
     if (hipHostMalloc(reinterpret_cast<void **>(&p->res_error), 64, hipHostMallocDefault) != hipSuccess) {
         g_create_err = "hipHostMalloc of the resident-launch error word failed";
@@ -713,6 +751,7 @@ int32_t cw_destroy(cw_ctx *c) {
         if (c->given_on) (void)hipEventDestroy(c->given_on);
         if (c->internal_stream) (void)hipStreamDestroy(c->internal_stream);
         if (c->res_error) (void)hipHostFree(c->res_error);
+        if (c->done) (void)hipFree(c->done);
         if (c->workspace) (void)hipFree(c->workspace);
         if (c->io) (void)hipFree(c->io);
         if (c->pool) (void)hipFree(c->pool);
@@ -1095,6 +1134,8 @@ int32_t cw_exec(cw_ctx *c, int32_t model_id, int32_t batch, int32_t slot, void *
     rc = exec_gate(c, m, s, st);
     if (rc != CW_OK) return rc;
     CW_HIP(c, hipEventRecord(s->exec_start, st));
+    s->tells = false;
+    ++s->exec_seq;
     rc = enqueue_plan(c, m, p, s, st);
     if (rc != CW_OK) return rc;
     return record_exec_end(c, m, p, s, st);
@@ -1147,6 +1188,13 @@ int32_t cw_set_use_graphs(cw_ctx *c, int32_t on) {
     return CW_OK;
 }
 
+int32_t cw_set_wait_launches(cw_ctx *c, int32_t us) {
+    if (!c) return CW_ERR_INVALID;
+    if (us > 1000000) return set_err(c, CW_ERR_INVALID, "at most a second");
+    c->wait_us = us < 0 ? kWaitUs : (unsigned)us;
+    return CW_OK;
+}
+
 int32_t cw_exec_timed_launches(cw_ctx *c, int32_t model_id, int32_t batch, int32_t slot, int32_t inner, float *launch_us,
                                void *stream) {
     ModelRt *m; Plan *p; Slot *s;
@@ -1193,6 +1241,7 @@ int32_t cw_output(cw_ctx *c, int32_t slot, float *host_probs, float *host_logits
     DeviceGuard g(c->device);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t out_b = (size_t)s.batch * m->m.classes * 4;
+    wait_quietly(c, s, s.exec_end, st);
     CW_HIP(c, hipStreamWaitEvent(st, s.exec_end, 0));
     CW_HIP(c, hipMemcpyAsync(host_probs, c->io + s.probs_off, out_b, hipMemcpyDeviceToHost, st));
     if (host_logits) CW_HIP(c, hipMemcpyAsync(host_logits, c->io + s.logits_off, out_b, hipMemcpyDeviceToHost, st));
@@ -1209,6 +1258,7 @@ int32_t cw_release(cw_ctx *c, int32_t slot) {
         // The copy into the slot or an EXEC on it may still be queued: whoever reuses the memory waits for the
         // last of them (an EXEC waits for the copy itself).
         DeviceGuard g(c->device);
+        if (s.state == SLOT_EXECUTED) wait_quietly(c, s, s.exec_end, c->internal_stream);
         CW_HIP(c, hipStreamWaitEvent(c->internal_stream, s.state == SLOT_EXECUTED ? s.exec_end : s.input_done, 0));
         CW_HIP(c, hipEventRecord(s.released, c->internal_stream));
     }

@@ -282,6 +282,8 @@ struct SoftmaxArgs {
     const float *z;
     float *p;
     int32_t B, D;
+    unsigned *done;   // gets `seq` as the launch begins (launch_wait_done), or nullptr
+    unsigned seq;
 };
 
 // Tile shapes the conv kernel is instantiated for (fixed at plan time per layer).
@@ -360,6 +362,8 @@ hipError_t launch_gavgpool(DType dt, const PoolArgs &a, hipStream_t s);
 hipError_t launch_maxpool_conv(DType dt, const PoolArgs &a, const ConvArgs &c, int bm, hipStream_t s);
 hipError_t launch_fc(DType dt, const FcArgs &a, hipStream_t s);
 hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s);
+// A launch of one wave that ends once *done has reached `seq`, or after `us` microseconds.
+hipError_t launch_wait_done(const unsigned *done, unsigned seq, unsigned us, hipStream_t s);
 hipError_t launch_dwconv(DType dt, const DwArgs &a, hipStream_t s);
 // A depthwise 3x3 convolution over c channels (no residual) and the 1x1 stride-1 convolution c -> n that reads it, in
 // one launch (channel counts of dwconv_conv_ok); cv = the 1x1's arguments (its x is not read).

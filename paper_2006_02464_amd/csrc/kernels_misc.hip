@@ -614,8 +614,13 @@ __global__ __launch_bounds__(64 * kFcsWaves) void fc_softmax_kernel(const float 
 }
 
 // ---- softmax over D values per row; one workgroup of 256 per row, wavefront reductions ---
+static __device__ __forceinline__ void softmax_begins(const SoftmaxArgs &a) {
+    if (a.done && blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(a.done, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __global__ __launch_bounds__(256) void softmax_kernel(const SoftmaxArgs a) {
     __shared__ float red[4];
+    softmax_begins(a);
     const int row = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float *z = a.z + (size_t)row * a.D;
@@ -642,8 +647,8 @@ __global__ __launch_bounds__(256) void softmax_kernel(const SoftmaxArgs a) {
 // registers, so a row is read once and every exponential computed once.  Same formula, same order of
 // every sum as softmax_kernel: the results are identical.
 template <int PER>
-__global__ __launch_bounds__(256) void softmax_rows_kernel(const float *z_in, float *p_out, int B, int D) {
-    const SoftmaxArgs a{z_in, p_out, B, D};
+__global__ __launch_bounds__(256) void softmax_rows_kernel(const float *z_in, float *p_out, int B, int D, unsigned *done, unsigned seq) {
+    const SoftmaxArgs a{z_in, p_out, B, D, done, seq};
     __shared__ float red_m[4], red_s[4];
     const int row = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -656,6 +661,7 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(const float *z_in, fl
         v[e] = j < a.D ? z[j] : -INFINITY;
         m = fmaxf(m, v[e]);
     }
+    softmax_begins(a);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     if (lane == 0) red_m[wave] = m;
@@ -1222,9 +1228,9 @@ hipError_t launch_fc(DType dt, const FcArgs &a, hipStream_t s) {
 hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s) {
     if (a.B < 1 || a.D < 1) return hipErrorInvalidValue;
     if (a.D <= 256 * 4)
-        softmax_rows_kernel<4><<<dim3(a.B), 256, 0, s>>>(a.z, a.p, a.B, a.D);
+        softmax_rows_kernel<4><<<dim3(a.B), 256, 0, s>>>(a.z, a.p, a.B, a.D, a.done, a.seq);
     else if (a.D <= 256 * 16)
-        softmax_rows_kernel<16><<<dim3(a.B), 256, 0, s>>>(a.z, a.p, a.B, a.D);
+        softmax_rows_kernel<16><<<dim3(a.B), 256, 0, s>>>(a.z, a.p, a.B, a.D, a.done, a.seq);
     else
         softmax_kernel<<<dim3(a.B), 256, 0, s>>>(a);
     return hipGetLastError();

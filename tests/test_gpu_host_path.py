@@ -88,3 +88,35 @@ def test_memory_of_a_released_input_waits_for_its_copy():
         assert np.array_equal(logits.numpy(), want)
     finally:
         wk.close()
+
+
+@pytest.mark.parametrize("us", [0, 1, -1])   # none, one that gives up long before the EXEC ends, the default
+@pytest.mark.parametrize("rooms", [1, 6])
+def test_streams_that_wait_for_an_exec(us, rooms):
+    """OUTPUT and the INPUT that takes an unfinished request's memory wait for the EXEC, whatever their wait launch does."""
+    from paper_2006_02464_amd.runner import Worker
+    case = Case(T.resnet(18), 64, seed=6, dist="uniform")
+    wk = Worker(workspace_bytes=256 << 20, io_bytes=rooms * (4 * 3 * 64 * 64 + 2 * 4096), weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = wk.ctx.model_define(case.ops, 3, 64, 64, batch_sizes=(1,))
+        wk.load(mid, case.blob)
+        x = [torch.from_numpy(np.ascontiguousarray(case.images(i, 1), dtype=np.float32)).pin_memory() for i in range(5)]
+        want = [wk.infer(mid, v.numpy())[:2] for v in x]
+        wk.ctx.set_wait_launches(us)
+        inp, exe, out = (torch.cuda.Stream() for _ in range(3))
+        with torch.cuda.stream(exe):
+            torch.cuda._sleep(2_000_000)
+        got = [(torch.empty(1, 1000, pin_memory=True), torch.empty(1, 1000, pin_memory=True)) for _ in range(80)]
+        for k, (probs, logits) in enumerate(got):
+            slot = wk.ctx.input(mid, 1, x[k % 5], inp)
+            wk.ctx.exec(mid, 1, slot, exe)
+            if k % 7 == 6:
+                wk.ctx.release(slot)   # its stream is the library's
+            else:
+                wk.ctx.output(slot, probs, logits, out)
+        torch.cuda.synchronize()
+        for k, (probs, logits) in enumerate(got):
+            if k % 7 != 6:
+                assert np.array_equal(probs.numpy(), want[k % 5][0]) and np.array_equal(logits.numpy(), want[k % 5][1]), k
+    finally:
+        wk.close()
