@@ -164,6 +164,19 @@ int32_t hip_fail(cw_ctx *c, hipError_t e, const char *what) {
         if (e__ != hipSuccess) return hip_fail(ctx, e__, #call); \
     } while (0)
 
+// The device's address of `bytes` of pinned host memory from `host` on, or nullptr: not pinned, not aligned to 16 bytes.
+char *device_view(const void *host, size_t bytes) {
+    hipPointerAttribute_t a{}, z{};
+    if (reinterpret_cast<uintptr_t>(host) % 16 != 0 || bytes == 0) return nullptr;
+    if (hipPointerGetAttributes(&a, host) != hipSuccess || hipPointerGetAttributes(&z, static_cast<const char *>(host) + bytes - 1) != hipSuccess) {
+        (void)hipGetLastError();   // memory that the runtime does not know is no error here
+        return nullptr;
+    }
+    char *first = static_cast<char *>(a.devicePointer), *last = static_cast<char *>(z.devicePointer);
+    if (a.type != hipMemoryTypeHost || z.type != hipMemoryTypeHost || !first || last != first + (bytes - 1) || reinterpret_cast<uintptr_t>(first) % 16 != 0) return nullptr;
+    return first;
+}
+
 struct DeviceGuard {
     int prev = -1;
     bool ok = false;
@@ -1243,8 +1256,13 @@ int32_t cw_output(cw_ctx *c, int32_t slot, float *host_probs, float *host_logits
     const size_t out_b = (size_t)s.batch * m->m.classes * 4;
     wait_quietly(c, s, s.exec_end, st);
     CW_HIP(c, hipStreamWaitEvent(st, s.exec_end, 0));
-    CW_HIP(c, hipMemcpyAsync(host_probs, c->io + s.probs_off, out_b, hipMemcpyDeviceToHost, st));
-    if (host_logits) CW_HIP(c, hipMemcpyAsync(host_logits, c->io + s.logits_off, out_b, hipMemcpyDeviceToHost, st));
+    char *probs = device_view(host_probs, out_b), *logits = probs && host_logits ? device_view(host_logits, out_b) : nullptr;
+    if (probs && (logits || !host_logits)) {
+        CW_HIP(c, launch_copy_out(probs, c->io + s.probs_off, logits, c->io + s.logits_off, out_b, st));
+    } else {
+        CW_HIP(c, hipMemcpyAsync(host_probs, c->io + s.probs_off, out_b, hipMemcpyDeviceToHost, st));
+        if (host_logits) CW_HIP(c, hipMemcpyAsync(host_logits, c->io + s.logits_off, out_b, hipMemcpyDeviceToHost, st));
+    }
     CW_HIP(c, hipEventRecord(s.released, st));
     free_slot(c, &s, true);
     return CW_OK;

@@ -362,6 +362,8 @@ hipError_t launch_gavgpool(DType dt, const PoolArgs &a, hipStream_t s);
 hipError_t launch_maxpool_conv(DType dt, const PoolArgs &a, const ConvArgs &c, int bm, hipStream_t s);
 hipError_t launch_fc(DType dt, const FcArgs &a, hipStream_t s);
 hipError_t launch_softmax(const SoftmaxArgs &a, hipStream_t s);
+// Copies of `bytes` (a multiple of 4) into pinned host memory, 16-byte aligned like the sources; host_logits: nullptr for none.
+hipError_t launch_copy_out(void *host_probs, const void *probs, void *host_logits, const void *logits, size_t bytes, hipStream_t s);
 // A launch of one wave that ends once *done has reached `seq`, or after `us` microseconds.
 hipError_t launch_wait_done(const unsigned *done, unsigned seq, unsigned us, hipStream_t s);
 hipError_t launch_dwconv(DType dt, const DwArgs &a, hipStream_t s);

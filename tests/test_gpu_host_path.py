@@ -120,3 +120,37 @@ def test_streams_that_wait_for_an_exec(us, rooms):
                 assert np.array_equal(probs.numpy(), want[k % 5][0]) and np.array_equal(logits.numpy(), want[k % 5][1]), k
     finally:
         wk.close()
+
+
+@pytest.mark.parametrize("batch,classes", [(1, 1), (3, 7), (1, 1000), (5, 1001), (16, 4099)])   # below 16 bytes, odd words, more than a workgroup each
+def test_results_in_any_host_memory(batch, classes):
+    """Pinned memory is written by the GPU, everything else by copies of the runtime: the same values, and nothing behind them."""
+    from paper_2006_02464_amd.runner import Worker
+    O = T.Op
+    ops = [O(T.CONV, 3, 64, 3, 3, 2, 1, 1, -1, -1), O(T.CONV, 64, 256, 1, 1, 1, 0, 1, -1, 0), O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 1),
+           O(T.FC, 256, classes, 1, 1, 1, 0, 0, -1, 2), O(T.SOFTMAX, classes, classes, 0, 0, 1, 0, 0, -1, 3)]
+    case = Case(ops, 16, seed=7, dist="uniform")
+    wk = Worker(workspace_bytes=64 << 20, io_bytes=16 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = wk.ctx.model_define(case.ops, 3, 16, 16, batch_sizes=(batch,))
+        wk.load(mid, case.blob)
+        x = torch.from_numpy(np.ascontiguousarray(case.images(0, batch), dtype=np.float32)).pin_memory()
+        n, stream, got = batch * classes, torch.cuda.Stream(), []
+        for probs_at, logits_at, pin in ((0, 0, True), (1, 0, True), (0, 2, True), (0, None, True), (0, 0, False)):
+            p, z = (torch.full((n + 8,), -5.0, pin_memory=pin) for _ in range(2))
+            slot = wk.ctx.input(mid, batch, x, stream)
+            wk.ctx.exec(mid, batch, slot, stream)
+            wk.ctx.output(slot, p[probs_at:], None if logits_at is None else z[logits_at:], stream)
+            stream.synchronize()
+            assert (p[:probs_at] == -5).all() and (p[probs_at + n:] == -5).all()
+            got.append(p[probs_at:probs_at + n].numpy().copy())
+            if logits_at is None:
+                assert (z == -5).all()
+            else:
+                assert (z[:logits_at] == -5).all() and (z[logits_at + n:] == -5).all()
+                got.append(np.exp(z[logits_at:logits_at + n].double().numpy().reshape(batch, classes)))
+                # fp32 exponentials and sums: a few units in the last place of a probability
+                np.testing.assert_allclose(got[-2].reshape(batch, classes), got[-1] / got[-1].sum(1, keepdims=True), rtol=3e-6, atol=1e-30)
+            assert np.array_equal(got[0], got[-1 if logits_at is None else -2])
+    finally:
+        wk.close()
