@@ -51,8 +51,9 @@ int32_t cw_plan_launch_ahead(cw_ctx *ctx, int32_t model_id, int32_t batch, int32
                              int32_t *workgroups, int64_t *bytes);
 /* 1 where entry `index` of the plan is no launch of its own: the input cast and, if it follows, the 3x3 stride-2 max pool,
  * whose work the first convolution's launch does (7x7 of 64 channels with the pool, 3x3 of 32 without, stride 2), and the
- * global average pool of few and small maps, which the FC's launch does; not under cw_set_fusion(0), a plan override or debug
- * retention.  0 otherwise, negative on error. */
+ * global average pool of few and small maps, which the FC's launch does, and a 1x1 convolution that the launch of the depthwise
+ * convolution behind it computes (cw_set_fusion_dw); not under cw_set_fusion(0), a plan override or debug retention.  0 otherwise,
+ * negative on error. */
 int32_t cw_plan_launch_joined(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
 /* What EXEC issues for entry `index`: the same as cw_plan_launch_info but for joined entries and those that compute them.  The
  * first have no bytes, flops, grid or block; the others have the launch's own grid and name, its tile (pixels of the stored
@@ -133,6 +134,9 @@ int32_t cw_set_fusion_pool(cw_ctx *ctx, int32_t on);
  * channels into 64 or 128 when the batch gives it enough workgroups and
  * the model has no CONCAT: the depthwise result goes through LDS to the matrix cores and is never
  * stored; cw_launch_info.op_index of that launch is the 1x1, fused_op the depthwise convolution.
+ * A 1x1 stride-1 convolution whose result the depthwise 3x3 convolution right behind it reads keeps its entry in the plan, and the
+ * depthwise convolution's launch computes both where that is predicted to be faster (small maps and batches; not under debug
+ * retention): cw_plan_launch_joined.
  * on == 0 plans them as two launches for models defined afterwards (also off with
  * cw_set_fusion(0)), on != 0 restores the default. */
 int32_t cw_set_fusion_dw(cw_ctx *ctx, int32_t on);

@@ -325,8 +325,8 @@ class Context:
         return wgs.value, nbytes.value
 
     def plan_launch_joined(self, model_id, batch, index):
-        """Whether plan entry `index` has no launch of its own: the first convolution's launch computes it (cast, max pool), or
-        the FC's (average pool)."""
+        """Whether plan entry `index` has no launch of its own: the first convolution's launch computes it (cast, max pool),
+        the FC's (average pool) or a depthwise convolution's (the 1x1 in front of it)."""
         return bool(self._check(lib().cw_plan_launch_joined(self._h, model_id, batch, index)))
 
     def plan_launch_issued(self, model_id, batch, index):

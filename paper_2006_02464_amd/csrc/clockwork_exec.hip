@@ -234,7 +234,7 @@ char *resolve(cw_ctx *c, const ModelRt *m, const Bases &b, const Ref &r) {
 
 hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, hipStream_t st) {
     const DType dt = m->m.dtype;
-    if (l.in_head == 1 || l.in_fc) return hipSuccess;   // computed by the first convolution's launch, or the FC's
+    if (l.in_head == 1 || l.in_fc || l.in_dw) return hipSuccess;   // computed by the first convolution's launch, the FC's or a depthwise convolution's
     if (l.in_head == 2) {
         HeadArgs a = l.head;
         a.x = reinterpret_cast<const float *>(resolve(c, m, s, l.head_x));
@@ -343,6 +343,15 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
             }
             a.res = resolve(c, m, s, l.res);
             a.y = resolve(c, m, s, l.y);
+            if (l.pw_fused) {
+                ConvArgs cv = l.pw;
+                cv.x = resolve(c, m, s, l.pw_x);
+                cv.w = resolve(c, m, s, l.pw_w);
+                cv.bias = reinterpret_cast<const float *>(resolve(c, m, s, l.pw_bias));
+                cv.res = resolve(c, m, s, l.pw_res);
+                cv.y = resolve(c, m, s, l.pw_y);
+                return launch_pw_dw(dt, cv, a, l.pw_y.space != SP_NONE, l.pw_tile, st);
+            }
             return launch_dwconv(dt, a, st);
         }
         case K_RESIDENT: {
@@ -1408,7 +1417,7 @@ int32_t cw_plan_launch_joined(cw_ctx *c, int32_t model_id, int32_t batch, int32_
     Plan *p = get_plan(m, batch);
     if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
     if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
-    return p->launches[index].in_head == 1 || p->launches[index].in_fc;
+    return p->launches[index].in_head == 1 || p->launches[index].in_fc || p->launches[index].in_dw;
 }
 
 int32_t cw_plan_launch_issued(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index, cw_launch_info *out) {

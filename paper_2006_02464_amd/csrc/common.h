@@ -371,6 +371,12 @@ hipError_t launch_dwconv(DType dt, const DwArgs &a, hipStream_t s);
 // one launch (channel counts of dwconv_conv_ok); cv = the 1x1's arguments (its x is not read).
 hipError_t launch_dwconv_conv(DType dt, const DwArgs &a, const ConvArgs &cv, hipStream_t s);
 bool dwconv_conv_ok(int c, int n);
+// A 1x1 stride-1 convolution (dense tensors) and the depthwise 3x3 pad-1 convolution over its result (its x is not read) in one launch;
+// keep: the 1x1's result is stored too.
+struct PwDwTile { int waves, pf, nf, rows; };   // pf x 16 pixels a wave, nf x 16 channels and `rows` rows of the depthwise result a workgroup
+bool pw_dw_pick(const ConvArgs &c, const DwArgs &d, bool keep, PwDwTile *tile, double *us);   // whether it may be worth it, and its predicted time
+dim3 pw_dw_grid(const ConvArgs &c, const DwArgs &d, const PwDwTile &t);
+hipError_t launch_pw_dw(DType dt, const ConvArgs &c, const DwArgs &d, bool keep, const PwDwTile &t, hipStream_t s);
 int dwconv_conv_bm(int c, long long M);   // output pixels per workgroup of that launch
 hipError_t launch_copy_channels(const CopyArgs &a, hipStream_t s);   // 2-byte elements, C % 8 == 0
 hipError_t launch_resident(DType dt, const ResidentArgs &a, hipStream_t s);   // + the epoch bump behind it

@@ -570,6 +570,44 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             dw_into[i] = k; dw_first[k] = i;
         }
     }
+    // 1x1 + depthwise 3x3 (the next block's): a 1x1 stride-1 convolution and the depthwise convolution right behind it that reads it.  Both
+    // keep their entries in the plan; the depthwise convolution's launch computes the two where that is predicted to be faster.
+    std::vector<int> pw_into(n_ops, -1);
+    std::vector<char> pw_kept(n_ops, 0);
+    std::vector<PwDwTile> pw_tile(n_ops);
+    if (ov.fuse && ov.fuse_dw && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
+        bool has_concat = false;
+        std::vector<int> uses(n_ops, 0);
+        for (int i = 0; i < n_ops; ++i) {
+            has_concat |= m.ops[i].op == CW_OP_CONCAT;
+            if (m.ops[i].input_from >= 0) ++uses[m.ops[i].input_from];
+            if ((m.ops[i].op == CW_OP_CONV || m.ops[i].op == CW_OP_CONCAT) && m.ops[i].residual_from >= 0) ++uses[m.ops[i].residual_from];
+        }
+        for (int i = 1; !has_concat && i + 1 < n_ops; ++i) {
+            const cw_op &oc = m.ops[i], &od = m.ops[i + 1];
+            const int k = i + 1;
+            if (oc.op != CW_OP_CONV || oc.groups > 1 || oc.kh != 1 || oc.kw != 1 || oc.stride != 1 || oc.pad != 0 || oc.input_from < 0) continue;
+            if (od.op != CW_OP_CONV || od.groups <= 1 || od.kh != 3 || od.kw != 3 || od.pad != 1 || od.input_from != i || od.residual_from >= 0) continue;
+            if (fuse_into[i] >= 0 || fused_first[i] >= 0 || in_third[i] >= 0 || in_pool[i] >= 0 || dw_first[i] >= 0 || dw_into[k] >= 0 || (m.winograd && wino_eligible(oc, i))) continue;
+            const OpShape &sm = m.shapes[i], &sd = m.shapes[k];
+            ConvArgs a{};
+            a.B = batch; a.H = a.Ho = sm.h; a.W = a.Wo = sm.w; a.Cin = oc.cin; a.Cout = oc.cout; a.kh = a.kw = a.khp = a.kwp = 1; a.stride = 1;
+            conv_set_ld(a, oc.cin, oc.cout);
+            a.M = batch * sm.h * sm.w; a.K = oc.cin; a.relu = oc.relu; a.split_k = 1;
+            const DwArgs d{nullptr, nullptr, nullptr, nullptr, nullptr, batch, sm.h, sm.w, od.cin, sd.h, sd.w, 3, 3, od.stride, 1, od.relu, od.cin, od.cin};
+            double us;
+            if (!pw_dw_pick(a, d, uses[i] > 1 || oc.residual_from >= 0, &pw_tile[i], &us)) continue;
+            // the two apart: the cost model's 1x1, and 3 us of the depthwise launch and 3.5 ns for every workgroup beyond the 196 that run
+            // within that (one more round of them is 2 us)
+            ConvTile tile;
+            int32_t split;
+            bool fixed;
+            const double conv_us = pick_conv_tile(a, false, oc.residual_from >= 0, oc.cin, false, ov, &tile, &split, &fixed);
+            const double dw_wgs = (double)batch * sd.h * sd.w * od.cin / 2048;
+            if (fixed || us >= conv_us + 3.0 + 0.0035 * std::max(0.0, dw_wgs - 196)) continue;
+            pw_into[i] = k; pw_kept[i] = uses[i] > 1;
+        }
+    }
     // Order in which the ops are planned and launched: op order, except that a convolution j which
     // reads the same tensor as an earlier convolution i and depends on nothing after i (a ResNet
     // block's projection shortcut, i = the block's first 1x1) moves to right behind i, where the two
@@ -582,11 +620,11 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             for (int i = 1; i < n_ops; ++i) {
                 const cw_op &a = m.ops[i];
                 if (a.op != CW_OP_CONV || a.groups > 1 || a.input_from < 0 || a.cin % 64 != 0 || fuse_into[i] >= 0 || fused_first[i] >= 0 || moved[i]) continue;
-                if (in_third[i] >= 0 || in_pool[i] >= 0 || dw_first[i] >= 0) continue;
+                if (in_third[i] >= 0 || in_pool[i] >= 0 || dw_first[i] >= 0 || pw_into[i] >= 0) continue;
                 if (m.winograd && wino_eligible(a, i)) continue;
                 for (int j = i + 1; j < n_ops && j <= i + 3; ++j) {
                     const cw_op &b = m.ops[j];
-                    if (b.op != CW_OP_CONV || b.groups > 1 || b.input_from != a.input_from || fuse_into[j] >= 0 || fused_first[j] >= 0 || moved[j] || in_third[j] >= 0 || in_pool[j] >= 0 || dw_first[j] >= 0) continue;
+                    if (b.op != CW_OP_CONV || b.groups > 1 || b.input_from != a.input_from || fuse_into[j] >= 0 || fused_first[j] >= 0 || moved[j] || in_third[j] >= 0 || in_pool[j] >= 0 || dw_first[j] >= 0 || pw_into[j] >= 0) continue;
                     if (b.residual_from >= i || (m.winograd && wino_eligible(b, j))) continue;
                     partner[i] = j; moved[j] = 1;
                     break;
@@ -605,7 +643,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     // fused launch reads its inputs when that launch runs.
     std::vector<int> last_use(n_ops, -1);
     for (int i = 0; i < n_ops; ++i) {
-        const int at = pos[fuse_into[i] >= 0 ? fuse_into[i] : (in_third[i] >= 0 ? in_third[i] : (in_pool[i] >= 0 ? in_pool[i] : (dw_into[i] >= 0 ? dw_into[i] : i)))];
+        const int at = pos[fuse_into[i] >= 0 ? fuse_into[i] : (in_third[i] >= 0 ? in_third[i] : (in_pool[i] >= 0 ? in_pool[i] : (dw_into[i] >= 0 ? dw_into[i] : (pw_into[i] >= 0 ? pw_into[i] : i))))];
         if (m.ops[i].input_from >= 0) last_use[m.ops[i].input_from] = std::max(last_use[m.ops[i].input_from], at);
         if ((m.ops[i].op == CW_OP_CONV || m.ops[i].op == CW_OP_CONCAT) && m.ops[i].residual_from >= 0)
             last_use[m.ops[i].residual_from] = std::max(last_use[m.ops[i].residual_from], at);
@@ -1282,10 +1320,20 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             lf.pool_x = lp.x;
             lf.fc.hw = lp.pool.H * lp.pool.W;
         }
+    for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
+        Launch &lc = p.launches[i], &ld = p.launches[i + 1];
+        if (lc.kind != K_CONV || lc.pair_op >= 0 || lc.fused_bm > 0 || pw_into[lc.op_index] < 0 || ld.kind != K_DWCONV || ld.dw_fused || ld.op_index != pw_into[lc.op_index]) continue;
+        lc.in_dw = true;
+        ld.pw_fused = true;
+        ld.pw_tile = pw_tile[lc.op_index];
+        ld.pw = lc.conv;
+        ld.pw_x = lc.x; ld.pw_w = lc.w; ld.pw_bias = lc.bias; ld.pw_res = lc.res;
+        if (pw_kept[lc.op_index]) ld.pw_y = lc.y;
+    }
     // Weights are read ahead by the nearest of the four launches before the one that uses them which has CUs to spare.
     {
         auto host = [&](const Launch &l) {
-            if (l.kind != K_CONV || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
+            if (l.kind != K_CONV || l.in_dw || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
             if (!conv_uses_dlds(l.conv, false) || l.ahead_bytes > 0) return false;
             const TileDim d = conv_tile_dim(l.tile);
             return (int64_t)((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn) * d.parts() <= kPrefetchMaxTiles;
@@ -1356,7 +1404,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     for (size_t i = 0; i < p.launches.size(); ++i) {
         const Launch &l = p.launches[i];
         cw_launch_info &d = p.issued[i];
-        if (l.in_head == 1 || l.in_fc) {
+        if (l.in_head == 1 || l.in_fc || l.in_dw) {
             d.bytes = d.flops = 0;
             d.grid_x = d.grid_y = d.grid_z = d.block = 0;
         } else if (l.in_head == 2) {
@@ -1373,6 +1421,14 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 d.flops += p.launches[i + 1].info.flops;
                 d.bytes += (int64_t)h.n1 * h.cout * esz + h.n1 * 4 + out * h.n1 * (int64_t)esz;
             }
+        } else if (l.pw_fused) {
+            const int64_t between = (int64_t)l.pw.M * l.pw.Cout * (int64_t)esz;
+            const dim3 g = pw_dw_grid(l.pw, l.dw, l.pw_tile);
+            d.grid_x = (int32_t)g.x; d.grid_y = d.grid_z = 1; d.block = 64 * l.pw_tile.waves;
+            d.flops += p.launches[i - 1].info.flops;
+            d.bytes += p.launches[i - 1].info.bytes - between * (l.pw_y.space == SP_NONE ? 2 : 1);   // not read, and stored where something else reads it
+            d.gemm_m = l.pw.M; d.gemm_n = l.pw.Cout; d.gemm_k = l.pw.K;
+            snprintf(d.name, sizeof d.name, "%s+%s", p.launches[i - 1].info.name, l.info.name);
         } else if (l.kind == K_FC && l.fc.hw > 0) {
             d.bytes += (int64_t)batch * l.fc.hw * l.fc.In * esz - (int64_t)batch * l.fc.In * 4;   // the map, and no pooled values
             snprintf(d.name, sizeof d.name, "%s+%s", p.launches[i - 1].info.name, l.info.name);

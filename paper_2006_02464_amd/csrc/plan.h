@@ -67,6 +67,12 @@ struct Launch {
     // issues it, 1 = the others, which then issue nothing.
     int32_t in_head = 0;
     HeadArgs head{};
+    // A 1x1 convolution (in_dw) that the launch of the depthwise convolution behind it computes (pw_fused: pw = its arguments,
+    // pw_x ... pw_y its tensors; pw_y is none where no other op reads it).
+    bool in_dw = false, pw_fused = false;
+    PwDwTile pw_tile{};
+    ConvArgs pw{};
+    Ref pw_x, pw_w, pw_bias, pw_res, pw_y;
     bool in_fc = false;    // a global average pool that the FC's launch right behind it computes
     Ref pool_x;            // that FC: the pool's input
     Ref head_x, head_y, head_w1, head_bias1, head_y1;

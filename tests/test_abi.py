@@ -426,6 +426,33 @@ def test_depthwise_with_the_1x1_behind_it(ctx):
         ctx.set_fusion_dw(1)
 
 
+def test_1x1_with_the_depthwise_behind_it(ctx):
+    """The two keep their entries; the depthwise one issues both, with their work, where its launch is small."""
+    from oracle import topology as T
+    ops = [tuple(o) for o in T.mobilenet()]
+    m = ctx.model_define(ops, 3, 224, 224)
+    for b, n in ((1, 9), (2, 7), (16, 0)):
+        plan = ctx.plan(m, b)
+        joined = [i for i, l in enumerate(plan) if ctx.plan_launch_joined(m, b, i) and l["kind"] == 1 and l["op_index"] > 0]
+        assert len(joined) == n
+        for i in joined:
+            pw, dw, both = plan[i], plan[i + 1], ctx.plan_launch_issued(m, b, i + 1)
+            k = ops[pw["op_index"]]
+            assert dw["kind"] == 7 and dw["fused_op"] < 0 and dw["op_index"] == pw["op_index"] + 1 and ops[dw["op_index"]][9] == pw["op_index"]
+            assert both["flops"] == pw["flops"] + dw["flops"] and both["name"] == pw["name"] + "+" + dw["name"] and both["grid_x"] <= 256
+            between = 2 * pw["gemm_m"] * k[2]
+            kept = any(o[0] == 0 and o[8] == pw["op_index"] for o in ops)
+            assert both["bytes"] == pw["bytes"] + dw["bytes"] - between * (1 if kept else 2)
+            assert ctx.plan_launch_issued(m, b, i)["flops"] == 0
+    for off in ("set_fusion_dw", "set_fusion"):
+        getattr(ctx, off)(0)
+        try:
+            m2 = ctx.model_define(ops, 3, 224, 224)
+            assert not [l for i, l in enumerate(ctx.plan(m2, 1)) if ctx.plan_launch_joined(m2, 1, i) and l["kind"] == 1 and l["op_index"] > 0]
+        finally:
+            getattr(ctx, off)(1)
+
+
 def test_weight_pages():
     """The weight pool is paged (paper section 5.1): page counts per model, the limits, the free count."""
     c = cw.Context(device=-1, weight_pool_bytes=1 << 30)          # default page: 16 MiB

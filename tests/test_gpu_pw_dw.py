@@ -1,0 +1,55 @@
+"""A 1x1 convolution inside the launch of the depthwise 3x3 convolution behind it, against the oracle and the two launches."""
+import numpy as np
+import pytest
+
+from oracle import network as N
+from oracle import topology as T
+from workload import gen
+
+pytestmark = pytest.mark.gpu
+O = T.Op
+HSWISH = 2
+
+
+def net(k, n, stride, act, shortcut):
+    """stem -> 1x1 to k channels -> [1x1 k -> n -> depthwise] -> 1x1 to 256 (and the 1x1's result onto n channels more) -> head."""
+    ops = [O(T.CONV, 3, 32, 3, 3, 2, 1, 1, -1, -1), O(T.CONV, 32, k, 1, 1, 1, 0, 1, -1, 0)]
+    ops.append(O(T.CONV, k, n, 1, 1, 1, 0, act, 1 if shortcut else -1, 1))
+    ops.append(O(T.CONV, n, n, 3, 3, stride, 1, act, -1, 2, 0, n))
+    if shortcut and stride == 1:   # another reader of the 1x1's result: it is stored too
+        ops.append(O(T.CONV, n, n, 1, 1, 1, 0, act, 2, 3))
+    ops.append(O(T.CONV, n, 256, 1, 1, 1, 0, 1, -1, len(ops) - 1))
+    ops += [O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, len(ops) - 1), O(T.FC, 256, 11, 1, 1, 1, 0, 0, -1, len(ops)), O(T.SOFTMAX, 11, 11, 0, 0, 1, 0, 0, -1, len(ops) + 1)]
+    return ops
+
+
+@pytest.mark.parametrize("h,w,k,n,stride,batch,act,shortcut,dtype", [
+    (14, 14, 256, 512, 1, 1, 1, False, "fp16"), (14, 14, 512, 512, 1, 1, HSWISH, True, "fp16"), (14, 14, 512, 512, 2, 2, HSWISH, False, "bf16"),
+    (7, 7, 512, 1024, 1, 2, HSWISH, False, "fp16"), (28, 28, 128, 256, 1, 1, 1, False, "bf16"), (28, 28, 256, 256, 2, 1, 1, False, "fp16"),
+    (56, 56, 64, 128, 1, 1, 1, False, "fp16"), (57, 41, 64, 128, 2, 1, 0, False, "fp16"), (61, 60, 32, 64, 2, 1, 1, False, "fp16"),
+    (15, 13, 256, 256, 1, 3, 1, True, "bf16"), (1, 1, 128, 64, 1, 3, 1, False, "fp16"), (1, 17, 128, 128, 2, 1, 1, True, "fp16"),
+    (17, 1, 128, 32, 1, 2, 1, False, "fp16"), (2, 9, 384, 96, 1, 2, 1, False, "fp16"), (5, 3, 64, 32, 2, 1, 1, False, "fp16")])
+def test_1x1_inside_the_depthwise_launch(h, w, k, n, stride, batch, act, shortcut, dtype):
+    from paper_2006_02464_amd.runner import Worker
+    ops = net(k, n, stride, act, shortcut)
+    wts, biases = gen.model_tensors(T.weight_shapes(ops), 9, dtype)
+    x = gen.images(9, 0, batch, 3, 2 * h, 2 * w, "uniform", dtype)
+    ref = N.forward(ops, wts, biases, x, prec="f32")["logits"]
+    wk = Worker(workspace_bytes=128 << 20, io_bytes=16 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        got = []
+        for on in (1, 0):
+            wk.ctx.set_fusion_dw(on)
+            mid = wk.ctx.model_define(ops, 3, 2 * h, 2 * w, batch_sizes=(batch,), dtype=dtype)
+            plan = wk.ctx.plan(mid, batch)
+            at = [i for i, l in enumerate(plan) if l["op_index"] == 2][0]
+            assert wk.ctx.plan_launch_joined(mid, batch, at) == bool(on)
+            wk.load(mid, gen.pack_blob(wts, biases, dtype))
+            got.append(wk.infer(mid, x, classes=11)[1])
+        # six or seven roundings to the storage type on the way, each at most half a unit in the last place of a value
+        tol = 7 * (2.0 ** -11 if dtype == "fp16" else 2.0 ** -8)
+        for z in got:
+            assert np.abs(z - ref).max() <= tol * np.abs(ref).max()
+        assert np.abs(got[0] - got[1]).max() <= tol * np.abs(ref).max()
+    finally:
+        wk.close()
