@@ -146,8 +146,12 @@ struct DwArgs {
     int32_t B, H, W, C, Ho, Wo, kh, kw, stride, pad, act, ldx, ldy;
     FastDiv c8_div, wo_div, ho_div;   // of the 3x3 form (set by the launch code)
 };
-// The 3x3 form of the kernel holds 4 waves a SIMD: up to as many workgroups as run at once it takes the launch.
-constexpr unsigned kDwOneRound = 1024;
+// One output pixel a thread, taps one after the other; 3x3: all taps together; 3x3 stride 1: two pixels a thread.
+enum DwForm { DW_ANY, DW_TAPS, DW_PAIRS };
+constexpr unsigned kDwPairsFrom = 512;    // above so many workgroups of one pixel a thread
+constexpr unsigned kDwPairThreads = 128;  // workgroup of the pairs
+DwForm dw_form(const DwArgs &a);
+dim3 dw_grid(const DwArgs &a);
 
 // Winograd F(2x2, 3x3) for a 3x3 stride-1 pad-1 convolution.  Output pixels are cut into 2x2 tiles,
 // th x tw per image (th = ceil(Ho/2), tw = ceil(Wo/2)), tiles = B*th*tw.  The input transform writes

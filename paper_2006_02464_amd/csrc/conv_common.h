@@ -203,6 +203,27 @@ static __device__ __forceinline__ void epilogue_load(EpiOperands<TM, TN> &e, con
     }
 }
 
+// Values through the activation and one rounding.  The choice is one branch of the wave around all N: both activations and a choice
+// for every value are 8 instructions each.
+template <typename T, int N, typename V>
+static __device__ __forceinline__ V activate_as(const float (&v)[N], int act) {
+    static_assert(sizeof(V) == N * sizeof(T), "");
+    T o[N];
+    if (act == ACT_HSWISH) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) o[e] = (T)(v[e] * fminf(fmaxf(v[e] + 3.f, 0.f), 6.f) * (1.f / 6.f));
+    } else if (act == ACT_RELU) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) o[e] = (T)fmaxf(v[e], 0.f);
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; ++e) o[e] = (T)v[e];
+    }
+    return *reinterpret_cast<const V *>(o);
+}
+template <typename T> static __device__ __forceinline__ u32x4 activate(const float (&v)[8], int act) { return activate_as<T, 8, u32x4>(v, act); }
+template <typename T> static __device__ __forceinline__ u32x2 activate(const float (&v)[4], int act) { return activate_as<T, 4, u32x2>(v, act); }
+
 // + bias, + residual, activation, one round-to-nearest-even to the storage type, 16-byte stores.
 // The activation code is uniform, so the hard-swish arithmetic sits behind a scalar branch and the
 // ReLU / identity form runs the instructions it always ran.

@@ -697,12 +697,6 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(const float *z_in, fl
 // 16-byte pieces, and the taps' overlap between neighbouring pixels is served by the caches.
 // Weights are [kh][kw][C] in the storage type; fp32 accumulation; + bias, + residual, activation,
 // one round-to-nearest-even; x and y may be channel ranges of wider tensors (ldx, ldy).
-static __device__ __forceinline__ float dw_act(float v, int act) {
-    const float r = fmaxf(v, 0.f);
-    const float h = v * fminf(fmaxf(v + 3.f, 0.f), 6.f) * (1.f / 6.f);
-    return act == ACT_RELU ? r : (act == ACT_HSWISH ? h : v);
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void dwconv_kernel(const DwArgs a) {
     const unsigned c8 = (unsigned)a.C / 8u;
@@ -745,18 +739,15 @@ __global__ __launch_bounds__(256) void dwconv_kernel(const DwArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] += (float)re[e];
     }
-    T out[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) out[e] = (T)dw_act(acc[e], a.act);
-    *reinterpret_cast<uint4 *>(static_cast<T *>(a.y) + (size_t)m * a.ldy + cg * 8u) = *reinterpret_cast<const uint4 *>(out);
+    *reinterpret_cast<u32x4 *>(static_cast<T *>(a.y) + (size_t)m * a.ldy + cg * 8u) = activate<T>(acc, a.act);
 }
 
-// The 3x3 form for launches whose workgroups all run at once: there a thread's chain of nine loads one after the other is the
-// launch's time, not the bytes.  All taps of the image and of the filter are requested together, a tap outside the
-// image as a load out of range of both (zeros), and the index arithmetic multiplies.  Same order of additions.
-// MobileNet's 128..1024-channel layers at batch 1 take 3.4 us a launch for 5.7 (kernel trace), whole EXECs 127.6 -> 100.5 us at batch 1,
-// 142.8 -> 121.2 at batch 4, 206.5 -> 200.0 at batch 16.  With more workgroups than run at once the general form's eight waves a
-// SIMD are faster (112x112x64 at batch 16: 13.0 us, 17.1 with all taps requested together).
+// The 3x3 form: a thread's chain of nine loads one after the other is the time of a small launch, and the instructions around them
+// are that of a large one.  All taps of the image and of the filter are requested together, a tap outside the
+// image as a load out of range of both (zeros), and the index arithmetic multiplies.  Same order of additions.  Graph replay, in fp16, against
+// the general form: 14x14x512 at batch 1 2.4 us for 3.7, 112x112x64 to 56x56 at batch 16 7.2 for 8.3 (bf16 7.7 for 10.0), 56x56x128 at batch 16 10.9 for 12.3.
+// A SIMD starts about 525 instructions a microsecond, and an 8-channel result is 72 multiply-adds among 200; with both activations computed for every
+// value and one of them chosen it was 273 (112x112x64 at batch 16 9.2 us, then through the general form).
 template <typename T>
 __global__ __launch_bounds__(256, 4) void dwconv3_kernel(const DwArgs a) {
     const unsigned c8 = (unsigned)a.C / 8u;
@@ -791,10 +782,77 @@ __global__ __launch_bounds__(256, 4) void dwconv3_kernel(const DwArgs a) {
         for (int e = 0; e < 8; ++e) acc[e] += (float)xe[e] * (float)we[e];
     }
     const T *re = reinterpret_cast<const T *>(&rv);
-    T out[8];
+    if (a.res)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) out[e] = (T)dw_act(a.res ? acc[e] + (float)re[e] : acc[e], a.act);
-    *reinterpret_cast<uint4 *>(static_cast<T *>(a.y) + (size_t)m * a.ldy + cg * 8u) = *reinterpret_cast<const uint4 *>(out);
+        for (int e = 0; e < 8; ++e) acc[e] += (float)re[e];
+    *reinterpret_cast<u32x4 *>(static_cast<T *>(a.y) + (size_t)m * a.ldy + cg * 8u) = activate<T>(acc, a.act);
+}
+
+// The 3x3 stride-1 form of larger launches, where the vector memory path (64 bytes a clock on a compute unit: 18 loads of 16 bytes a
+// lane for a result of 16) and the instructions for masks and addresses are the time: two neighbouring pixels of a row a thread, 12 loads of pixels and
+// 9 of the filter for two results.  Graph replay at batch 16, fp16 and bf16, against one pixel a thread and against the general form that took these
+// launches: 56x56x128 8.6 and 9.2 us (10.9 and 11.0, 12.5 and 14.0), 28x28x256 6.0 and 6.4 (7.0 and 7.1, 7.4 and 8.6), 14x14x512 3.9 and 4.3 (4.4 and 4.5).
+// Four pixels a thread, or two rows of two, gain nothing more at 56x56 (9.1 us) and lose below.  128 threads: workgroups of 256 are 8.7 and 9.3 us at 56x56.
+template <typename T>
+__global__ __launch_bounds__(kDwPairThreads) void dwconv3_pair_kernel(const DwArgs a) {
+    const unsigned c8 = (unsigned)a.C / 8u, pairs = ((unsigned)a.Wo + 1u) / 2u;
+    const unsigned i = xcd_block(blockIdx.x, gridDim.x) * kDwPairThreads + threadIdx.x;
+    if (i >= (unsigned)a.B * a.Ho * pairs * c8) return;
+    const unsigned u = fast_div(i, a.c8_div), cg = i - u * c8;
+    const unsigned t = fast_div(u, a.wo_div), q = (u - t * pairs) * 2u, n = fast_div(t, a.ho_div);
+    const int ih0 = (int)(t - n * (unsigned)a.Ho) - a.pad, iw0 = (int)q - a.pad;
+    const unsigned pixel = (unsigned)a.ldx * 2u, row = (unsigned)a.W * pixel;
+    const unsigned base = ((n * a.H + (unsigned)ih0) * a.W + (unsigned)iw0) * pixel + cg * 16u;   // modulo 2^32 where that pixel is outside
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (((unsigned)a.B * a.H * a.W - 1u) * a.ldx + (unsigned)a.C) * 2u);
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.w, 9u * a.C * 2u), rb = make_rsrc(a.bias, a.C * 4u);
+    typedef typename Mfma<T>::v8 v8;
+    bool row_in[3], col_in[4];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) row_in[r] = (unsigned)(ih0 + r) < (unsigned)a.H;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) col_in[k] = (unsigned)(iw0 + k) < (unsigned)a.W;
+    u32x4 xv[3][4], wv[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) wv[k] = __builtin_amdgcn_raw_buffer_load_b128(rw, cg * 16u + (unsigned)k * (unsigned)a.C * 2u, 0, 0);
+    const u32x4 b0 = __builtin_amdgcn_raw_buffer_load_b128(rb, cg * 32u, 0, 0), b1 = __builtin_amdgcn_raw_buffer_load_b128(rb, cg * 32u + 16u, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xv[r][k] = __builtin_amdgcn_raw_buffer_load_b128(rx, row_in[r] && col_in[k] ? base + r * row + k * pixel : kOob, 0, 0);
+    float acc[2][8];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[j][e] = __uint_as_float(e < 4 ? b0[e & 3] : b1[e & 3]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        if (row_in[r]) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (!col_in[k]) continue;   // a tap outside the image adds nothing, also where it is infinite
+                const v8 v = __builtin_bit_cast(v8, xv[r][k]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (k - j < 0 || k - j > 2) continue;
+                    const v8 f = __builtin_bit_cast(v8, wv[r * 3 + k - j]);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[j][e] += (float)v[e] * (float)f[e];
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);   // the next row's pixels are waited for behind this row's products
+    }
+    const unsigned m = t * (unsigned)a.Wo + q;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (q + j >= (unsigned)a.Wo) break;
+        if (a.res) {
+            const v8 v = *reinterpret_cast<const v8 *>(static_cast<const T *>(a.res) + (size_t)(m + j) * a.C + cg * 8u);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[j][e] += (float)v[e];
+        }
+        *reinterpret_cast<u32x4 *>(static_cast<T *>(a.y) + (size_t)(m + j) * a.ldy + cg * 8u) = activate<T>(acc[j], a.act);
+    }
 }
 
 // ---- depthwise 3x3 convolution and the 1x1 convolution that reads it, in one launch --------
@@ -868,10 +926,7 @@ __global__ __launch_bounds__(256) void dwconv_conv1x1_kernel(const DwArgs a, con
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] = ok[j][k] ? acc[e] + (float)xe[e] * (float)we[e] : acc[e];
         }
-        T out[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = (T)dw_act(acc[e], a.act);
-        *reinterpret_cast<uint4 *>(sX + swz<C>((int)((tid + j * 256u) / CG), (int)cg)) = *reinterpret_cast<const uint4 *>(out);
+        *reinterpret_cast<u32x4 *>(sX + swz<C>((int)((tid + j * 256u) / CG), (int)cg)) = activate<T>(acc, a.act);
     }
     __syncthreads();
     f32x16 accm[TM][TN];
@@ -1033,10 +1088,7 @@ __global__ __launch_bounds__(256) void wino_output_kernel(const WinoArgs a) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[k] += (float)re[k];
             }
-            T out[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) out[k] = (T)dw_act(v[k], a.act);
-            *reinterpret_cast<uint4 *>(Y + at) = *reinterpret_cast<const uint4 *>(out);
+            *reinterpret_cast<u32x4 *>(Y + at) = activate<T>(v, a.act);
         }
 }
 
@@ -1255,6 +1307,21 @@ hipError_t launch_nhwc_to_nchw_f32(DType dt, const void *src, float *dst, int B,
     return hipGetLastError();
 }
 
+// 3x3 filters: all nine taps together; two pixels a thread where a launch of one pixel a thread has more than two workgroups on a
+// compute unit (56x56x128 stride 1 at batch 3 and 5, 588 and 980 workgroups: 3.65 us for 3.74, 4.51 for 5.05; 28x28x256 at
+// batch 4 and 5, 392 and 490: 3.36 for 3.11, 3.41 for 3.17) and where the rows are not so narrow that the pairs' empty halves take the gain back.
+DwForm dw_form(const DwArgs &a) {
+    if (a.kh != 3 || a.kw != 3 || (int64_t)a.B * a.H * a.W * a.ldx >= (1ll << 30) || (int64_t)a.B * a.Ho * a.Wo * a.C >= (1ll << 30)) return DW_ANY;   // offsets below kOob
+    const int64_t wgs = ((int64_t)a.B * a.Ho * a.Wo * (a.C / 8) + 255) / 256;
+    if (a.stride == 1 && wgs > kDwPairsFrom && (a.Wo + 1) / 2 * 3 < a.Wo * 2) return DW_PAIRS;
+    return DW_TAPS;
+}
+
+dim3 dw_grid(const DwArgs &a) {
+    if (dw_form(a) == DW_PAIRS) return dim3(blocks_for((size_t)a.B * a.Ho * ((a.Wo + 1) / 2) * (a.C / 8), kDwPairThreads));
+    return dim3(blocks_for((size_t)a.B * a.Ho * a.Wo * (a.C / 8), 256));
+}
+
 hipError_t launch_dwconv(DType dt, const DwArgs &a, hipStream_t s) {
     // shapes the kernel's indexing relies on, checked here so that a bad launch is an error
     if (a.C < 8 || a.C % 8 != 0 || a.ldx < a.C || a.ldy < a.C || a.ldx % 8 != 0 || a.ldy % 8 != 0) return hipErrorInvalidValue;
@@ -1263,15 +1330,17 @@ hipError_t launch_dwconv(DType dt, const DwArgs &a, hipStream_t s) {
     if (!a.x || !a.w || !a.bias || !a.y) return hipErrorInvalidValue;
     const size_t total = (size_t)a.B * a.Ho * a.Wo * (a.C / 8);
     if (total >= (1ull << 31) || (size_t)a.B * a.H * a.W * a.ldx >= (1ull << 31) || (size_t)a.B * a.Ho * a.Wo * a.ldy >= (1ull << 31)) return hipErrorInvalidValue;
-    if (a.kh == 3 && a.kw == 3 && blocks_for(total, 256) <= kDwOneRound && (size_t)a.B * a.H * a.W * a.ldx < (1ull << 30)) {
+    const DwForm form = dw_form(a);
+    if (form != DW_ANY) {
         DwArgs b = a;
         b.c8_div = make_fast_div((uint32_t)a.C / 8);
-        b.wo_div = make_fast_div((uint32_t)a.Wo);
+        b.wo_div = make_fast_div(form == DW_PAIRS ? ((uint32_t)a.Wo + 1) / 2 : (uint32_t)a.Wo);
         b.ho_div = make_fast_div((uint32_t)a.Ho);
-        CW_DISPATCH(dt, dwconv3_kernel, dim3(blocks_for(total, 256)), 256, s, b);
+        if (form == DW_PAIRS) CW_DISPATCH(dt, dwconv3_pair_kernel, dw_grid(a), kDwPairThreads, s, b);
+        else CW_DISPATCH(dt, dwconv3_kernel, dw_grid(a), 256, s, b);
         return hipGetLastError();
     }
-    CW_DISPATCH(dt, dwconv_kernel, dim3(blocks_for(total, 256)), 256, s, a);
+    CW_DISPATCH(dt, dwconv_kernel, dw_grid(a), 256, s, a);
     return hipGetLastError();
 }
 

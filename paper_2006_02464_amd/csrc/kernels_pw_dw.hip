@@ -28,12 +28,6 @@ struct alignas(64) PwDwRest {
     int32_t B, Wo;
 };
 
-static __device__ __forceinline__ float pw_dw_act(float v, int act) {
-    const float r = fmaxf(v, 0.f);
-    const float h = v * fminf(fmaxf(v + 3.f, 0.f), 6.f) * (1.f / 6.f);
-    return act == ACT_RELU ? r : (act == ACT_HSWISH ? h : v);
-}
-
 // LDS: weights of the 1x1 [BN][K] | taps [9][BN] | bias of the depthwise convolution [BN] | 16 zero bytes | result of the 1x1 [pixels][BN + 8]
 constexpr unsigned pw_dw_pitch(int nf) { return 16 * nf * 2 + 16; }   // bytes of a pixel: 16 consecutive ones start on different banks
 static unsigned pw_dw_lds(const PwDwTile &t, int K, int pixels) {
@@ -143,10 +137,10 @@ __global__ __launch_bounds__(64 * WAVES) void pw_dw_kernel(const void *x, const 
         for (int j = 0; j < NF; ++j) {
             const float *b = reinterpret_cast<const float *>(&bv[j]);
             const T *r = reinterpret_cast<const T *>(&rv[f][j]);
-            T out[4];
+            float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) out[e] = (T)pw_dw_act(acc[f][j][e] + b[e] + (float)r[e], a.act);
-            if (m < P) *reinterpret_cast<u32x2 *>(cw_dyn_lds + o_y + (unsigned)m * PITCH + (nl - n0 + 16 * j) * 2u) = *reinterpret_cast<const u32x2 *>(out);
+            for (int e = 0; e < 4; ++e) v[e] = acc[f][j][e] + b[e] + (float)r[e];
+            if (m < P) *reinterpret_cast<u32x2 *>(cw_dyn_lds + o_y + (unsigned)m * PITCH + (nl - n0 + 16 * j) * 2u) = activate<T>(v, a.act);
         }
     }
     wait_lds_and_barrier();
@@ -173,10 +167,7 @@ __global__ __launch_bounds__(64 * WAVES) void pw_dw_kernel(const void *x, const 
 #pragma unroll
             for (int e = 0; e < 8; ++e) s[e] += (float)v[e] * (float)f[e];
         }
-        T out[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = (T)pw_dw_act(s[e], a.act_d);
-        *reinterpret_cast<u32x4 *>(static_cast<T *>(a.d) + ((size_t)(n * Ho + r0 + orow) * a.Wo + ocol) * N + n0 + c * 8) = *reinterpret_cast<const u32x4 *>(out);
+        *reinterpret_cast<u32x4 *>(static_cast<T *>(a.d) + ((size_t)(n * Ho + r0 + orow) * a.Wo + ocol) * N + n0 + c * 8) = activate<T>(s, a.act_d);
     }
     if (a.y) {   // the rows of the 1x1's result that this strip owns
         const int ya = r0 * stride, yb = strip + 1 == strips ? H : r1 * stride;

@@ -1380,8 +1380,8 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                     const int bm = dwconv_conv_bm(l.dw.C, M);
                     g = dim3((unsigned)((M + bm - 1) / bm));
                 }
-                else g = dim3((unsigned)(((size_t)l.dw.B * l.dw.Ho * l.dw.Wo * (l.dw.C / 8) + 255) / 256));
-                b = 256;
+                else g = dw_grid(l.dw);
+                b = !l.dw_fused && dw_form(l.dw) == DW_PAIRS ? kDwPairThreads : 256;
                 break;
             case K_COPY_CHANNELS: g = dim3((unsigned)(((size_t)l.copy.pixels * (l.copy.C / 8) + 255) / 256)); b = 256; break;
             case K_RESIDENT: g = dim3(kResPartitions * kResGroupsPerPartition); b = 256; break;

@@ -10,6 +10,7 @@ from gpu_common import TOL, Case, rel_err_per_sample
 from oracle import network as N
 from oracle import topology as T
 from test_gpu_parity_full import _head, check_every_launch
+from workload import gen
 
 pytestmark = pytest.mark.gpu
 
@@ -170,7 +171,7 @@ def test_depthwise_shapes_off_the_mobilenet_path(worker):
 
 @pytest.mark.parametrize("batch", [32, 33])
 def test_depthwise_3x3_at_the_line_between_its_two_forms(worker, batch):
-    """32x32x64 at batch 32 is 1024 workgroups, which all run at once (all taps requested together), at batch 33 more (tap after tap)."""
+    """32x32x64 at batch 32 is 1024 workgroups of one pixel a thread, which all run at once, at batch 33 more."""
     O = T.Op
     ops = [O(T.CONV, 3, 64, 3, 3, 1, 1, 1, -1, -1), O(T.CONV, 64, 64, 3, 3, 1, 1, 1, 0, 0, 0, 64), O(T.CONV, 64, 256, 1, 1, 2, 0, 1, -1, 1),
            O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 2), O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 3), O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 4)]
@@ -233,4 +234,53 @@ def test_depthwise_3x3_with_all_taps_together_on_non_finite_values(worker, dtype
         assert ((want - have).abs() <= (2.0 ** -10 if dtype == "fp16" else 2.0 ** -7) * want.abs() + 10 * 2.0 ** -24 * scale)[live].all(), i
         seen += int((~want.isfinite()).sum())
     assert seen > 1000
+    worker.ctx.unload_weights(mid)
+
+
+@pytest.mark.parametrize("dtype,h,batch", [("fp16", 35, 8), ("bf16", 34, 9), ("fp16", 33, 9)])
+def test_depthwise_3x3_in_pairs_of_pixels(worker, dtype, h, batch):
+    """Stride 1 above 512 workgroups of one pixel a thread, two pixels a thread: odd and even rows, pad 0 to 2, every activation, a residual;
+    NaN and infinities in the maps, and infinite taps, which add nothing where they are outside the image."""
+    O = T.Op
+    dw = lambda pad, act, res, src: O(T.CONV, 128, 128, 3, 3, 1, pad, act, res, src, 0, 128)
+    ops = [O(T.CONV, 3, 128, 3, 3, 1, 1, 0, -1, -1), dw(1, 0, -1, 0), dw(1, 1, 0, 1), dw(0, 2, -1, 2), dw(2, 2, -1, 1),
+           O(T.CONV, 128, 256, 1, 1, 1, 0, 1, -1, 4), O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 5), O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 6), O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 7)]
+    case = Case(ops, h, seed=9, dtype=dtype, dist="normal")
+    case.w[1][5, 0, 0, 0], case.w[1][70, 0, 2, 2] = np.inf, -np.inf
+    case.blob = gen.pack_blob(case.w, case.b, dtype)
+    half = torch.float16 if dtype == "fp16" else torch.bfloat16
+    worker.ctx.set_debug_keep(True)
+    try:
+        mid = worker.ctx.model_define(case.ops, 3, h, h, batch_sizes=(batch,), dtype=dtype)
+    finally:
+        worker.ctx.set_debug_keep(False)
+    plan = [l for l in worker.ctx.plan(mid, batch) if l["name"].startswith("dwconv")]
+    shapes = T.shapes(ops, h, h)
+    assert [(l["grid_x"], l["block"]) for l in plan] == [((batch * shapes[i][1] * ((shapes[i][2] + 1) // 2) * 16 + 127) // 128, 128) for i in range(1, 5)]
+    worker.load(mid, case.blob)
+    x = case.images(0, batch).copy()
+    x[1, 0, 9, 9], x[2, 1, 0, 0], x[2, 2, h - 1, 7], x[3, 0, 5, h - 1] = np.nan, np.inf, -np.inf, np.inf
+    x[4] *= 2e4        # finite as stored, above fp16's range behind the filters
+    worker.infer(mid, x, classes=10)
+    got = {i: torch.from_numpy(worker.ctx.debug_read_op(mid, batch, i, (batch,) + tuple(shapes[i]))) for i in range(5)}
+    relu = lambda t: torch.where(t > 0, t, torch.zeros_like(t))      # of NaN: 0, as fmaxf has it
+    for i in range(1, 5):
+        o = ops[i]
+        src, w = got[o.input_from].double(), torch.from_numpy(case.w[i]).double()
+        v = F.conv2d(src, w.nan_to_num(0, 1, -1), torch.from_numpy(case.b[i]).double(), o.stride, o.pad, 1, 128)
+        if i == 1:   # the infinite taps, of which the product above had one of the same sign
+            v[:, 5, 1:, 1:] += src[:, 5, :-1, :-1] * np.inf
+            v[:, 70, :-1, :-1] -= src[:, 70, 1:, 1:] * np.inf
+        if o.residual_from >= 0:
+            v = v + got[o.residual_from].double()
+        v = relu(v) if o.relu == 1 else v * relu(v + 3).clamp(max=6) / 6 if o.relu == 2 else v
+        want, have = v.float().to(half).double(), got[i].double()
+        top = torch.finfo(half).max
+        edge = (v.abs() > top * (1 - 2.0 ** -9)) & (v.abs() < top * (1 + 2.0 ** -7))    # may round to the largest value or to infinity
+        assert torch.equal(want.isnan(), have.isnan()), i
+        assert torch.equal(want[want.isinf() & ~edge], have[want.isinf() & ~edge]), i
+        live = want.isfinite() & have.isfinite()
+        scale = F.conv2d(src.nan_to_num(0, 0, 0).abs(), w.nan_to_num(0, 0, 0).abs(), None, o.stride, o.pad, 1, 128) + 4
+        # one rounding to the storage type, which ten fp32 additions may shift by a unit
+        assert ((want - have).abs() <= (2.0 ** -10 if dtype == "fp16" else 2.0 ** -7) * want.abs() + 10 * 2.0 ** -24 * scale)[live].all(), i
     worker.ctx.unload_weights(mid)
