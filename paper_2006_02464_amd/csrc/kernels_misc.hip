@@ -891,25 +891,21 @@ __global__ __launch_bounds__(256) void dwconv_conv1x1_kernel(const DwArgs a, con
     for (int k = 0; k < 9; ++k) fw[k] = *reinterpret_cast<const uint4 *>(static_cast<const T *>(a.w) + k * C + cg * 8u);
     const float4 b0 = *reinterpret_cast<const float4 *>(a.bias + cg * 8u);
     const float4 b1 = *reinterpret_cast<const float4 *>(a.bias + cg * 8u + 4u);
-    uint4 raw[PIECES][9];
-    bool ok[PIECES][9];
+    const unsigned pixel = (unsigned)a.ldx * 2u, row = (unsigned)a.W * pixel;
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (((unsigned)a.B * a.H * a.W - 1u) * a.ldx + (unsigned)a.C) * 2u);
+    u32x4 raw[PIECES][9];
+    bool row_in[PIECES][3], col_in[PIECES][3];
 #pragma unroll
     for (int j = 0; j < PIECES; ++j) {
         const unsigned m = min(m0 + (tid + j * 256u) / CG, M - 1u);   // rows beyond M: a valid pixel, never stored
-        unsigned t = m / (unsigned)a.Wo;
-        const int q = (int)(m - t * (unsigned)a.Wo);
-        const unsigned n = t / (unsigned)a.Ho;
-        const int p = (int)(t - n * (unsigned)a.Ho);
-        const T *xg = static_cast<const T *>(a.x) + cg * 8u;
+        const unsigned t = fast_div(m, a.wo_div), n = fast_div(t, a.ho_div);
+        const int ih0 = (int)(t - n * (unsigned)a.Ho) * a.stride - a.pad, iw0 = (int)(m - t * (unsigned)a.Wo) * a.stride - a.pad;
+        const unsigned base = ((n * a.H + (unsigned)ih0) * a.W + (unsigned)iw0) * pixel + cg * 16u;   // modulo 2^32 where that pixel is outside
 #pragma unroll
-        for (int r = 0; r < 3; ++r)
+        for (int k = 0; k < 3; ++k) { row_in[j][k] = (unsigned)(ih0 + k) < (unsigned)a.H; col_in[j][k] = (unsigned)(iw0 + k) < (unsigned)a.W; }
 #pragma unroll
-            for (int s2 = 0; s2 < 3; ++s2) {
-                const int ih = p * a.stride - a.pad + r, iw = q * a.stride - a.pad + s2;
-                ok[j][r * 3 + s2] = (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-                const unsigned ihc = (unsigned)min(max(ih, 0), a.H - 1), iwc = (unsigned)min(max(iw, 0), a.W - 1);
-                raw[j][r * 3 + s2] = *reinterpret_cast<const uint4 *>(xg + ((n * (unsigned)a.H + ihc) * (unsigned)a.W + iwc) * (unsigned)a.ldx);
-            }
+        for (int k = 0; k < 9; ++k)
+            raw[j][k] = __builtin_amdgcn_raw_buffer_load_b128(rx, row_in[j][k / 3] && col_in[j][k % 3] ? base + (unsigned)(k / 3) * row + (unsigned)(k % 3) * pixel : kOob, 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < WPIECES; ++j) {
@@ -921,10 +917,10 @@ __global__ __launch_bounds__(256) void dwconv_conv1x1_kernel(const DwArgs a, con
         float acc[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            const T *xe = reinterpret_cast<const T *>(&raw[j][k]);
-            const T *we = reinterpret_cast<const T *>(&fw[k]);
+            if (!(row_in[j][k / 3] && col_in[j][k % 3])) continue;   // a tap outside the image adds nothing, also where it is infinite
+            const v8 v = __builtin_bit_cast(v8, raw[j][k]), f = __builtin_bit_cast(v8, fw[k]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] = ok[j][k] ? acc[e] + (float)xe[e] * (float)we[e] : acc[e];
+            for (int e = 0; e < 8; ++e) acc[e] += (float)v[e] * (float)f[e];
         }
         *reinterpret_cast<u32x4 *>(sX + swz<C>((int)((tid + j * 256u) / CG), (int)cg)) = activate<T>(acc, a.act);
     }
@@ -1216,10 +1212,13 @@ hipError_t launch_dwconv_conv(DType dt, const DwArgs &a, const ConvArgs &c, hipS
     if (c.Cin != a.C || c.K != a.C || (size_t)c.M != M || !c.w || !c.bias || !c.y || conv_ldy(c) < c.Cout) return hipErrorInvalidValue;
     const int bm = dwconv_conv_bm(a.C, (long long)M);
     const dim3 grid((unsigned)((M + bm - 1) / bm));
+    DwArgs b = a;
+    b.wo_div = make_fast_div((uint32_t)a.Wo);
+    b.ho_div = make_fast_div((uint32_t)a.Ho);
 #define CW_DWPW(C_, N_, BM_)                                                                      \
     do {                                                                                          \
-        if (dt == DT_F16) dwconv_conv1x1_kernel<f16, C_, N_, BM_><<<grid, 256, 0, s>>>(a, c);     \
-        else dwconv_conv1x1_kernel<bf16, C_, N_, BM_><<<grid, 256, 0, s>>>(a, c);                 \
+        if (dt == DT_F16) dwconv_conv1x1_kernel<f16, C_, N_, BM_><<<grid, 256, 0, s>>>(b, c);     \
+        else dwconv_conv1x1_kernel<bf16, C_, N_, BM_><<<grid, 256, 0, s>>>(b, c);                 \
     } while (0)
 #define CW_DWPW_N(C_, BM_)                          \
     do {                                            \
