@@ -313,9 +313,9 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
             a.bias = reinterpret_cast<const float *>(resolve(c, m, s, l.bias));
             a.z = reinterpret_cast<float *>(resolve(c, m, s, l.y));
             if (a.hw > 0) a.px = resolve(c, m, s, l.pool_x);
+            a.partial = reinterpret_cast<float *>(resolve(c, m, s, l.partial));
             if (l.probs.space == SP_SLOT_PROBS) {
                 a.p = reinterpret_cast<float *>(resolve(c, m, s, l.probs));
-                a.partial = reinterpret_cast<float *>(resolve(c, m, s, l.partial));
                 a.counters = reinterpret_cast<int32_t *>(resolve(c, m, s, l.counters));
             }
             return launch_fc(dt, a, st);
@@ -324,6 +324,8 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
             SoftmaxArgs a = l.sm;
             a.z = reinterpret_cast<const float *>(resolve(c, m, s, l.x));
             a.p = reinterpret_cast<float *>(resolve(c, m, s, l.y));
+            a.partial = reinterpret_cast<const float *>(resolve(c, m, s, l.partial));
+            a.bias = reinterpret_cast<const float *>(resolve(c, m, s, l.bias));
             a.done = s.done;
             a.seq = s.seq;
             return launch_softmax(a, st);

@@ -263,7 +263,7 @@ struct FcArgs {
     // workgroups per 16 outputs, which meet through `partial` and arrival counters like the
     // convolution's split-K; the workgroup that finishes the last 16 outputs computes p = softmax(z).
     float *p;           // [B][Out] probabilities, or nullptr: logits only (the unfused kernel)
-    float *partial;     // [split_k][16][Out] fp32 (split_k > 1)
+    float *partial;     // [split_k][16][Out] fp32 (split_k > 1); without p: [kFcWaves][B][Out rounded up to 16], z is left to the softmax
     int32_t *counters;  // ceil(Out/16) + 1 arrival counters, zero between launches
     int32_t split_k;    // 1, 2 or 4; In % (128 * split_k) == 0
     // The global average pool in the FC's launch (px != nullptr): no f, the averages stay in LDS.
@@ -282,12 +282,23 @@ constexpr int pool_fc_items(int64_t B, int64_t in, int64_t hw) {
 }
 constexpr int kFcSoftmaxMaxBatch = 16, kFcSoftmaxMaxOut = 1024;
 
+// The FC's parts of K, each a sum of its own: by the waves of a workgroup, or (fc_in_parts) by workgroups, for the softmax to add up.  Up to 1024
+// features, where the weights' way to the chip is the smaller part: whole EXECs of ResNet-18 batch 8 133.9 -> 132.6 us, DenseNet batch 6 206.7 -> 204.7, Inception batch 5
+// 92.7 -> 91.2; with 2048 from eight samples on, ResNet-50 batch 16 421.1 -> 419.3 (batch 4 267.5 -> 268.3, batch 1 204.4 -> 205.9: the launch is 1.7 us
+// shorter, the softmax, which fetches the parts from other XCDs' L2s, 0.7 us longer).
+constexpr int kFcWaves = 8, kFcPartsMaxOut = 1024;
+constexpr bool fc_in_parts(int64_t B, int64_t in, int64_t out) {
+    return out <= kFcPartsMaxOut && in % (32 * kFcWaves) == 0 && (in <= 1024 || (B >= 8 && in <= 4096)) && (B + 15) / 16 * ((out + 15) / 16) <= 256;
+}
+
 struct SoftmaxArgs {
     const float *z;
     float *p;
     int32_t B, D;
     unsigned *done;   // gets `seq` as the launch begins (launch_wait_done), or nullptr
     unsigned seq;
+    const float *partial;   // the FC's parts instead of z, which is then written (FcArgs::partial), or nullptr
+    const float *bias;
 };
 
 // Tile shapes the conv kernel is instantiated for (fixed at plan time per layer).

@@ -698,6 +698,14 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         return off;
     };
 
+    // Whether the FC's launch is to take the global average pool before it (see below).
+    auto pool_in_fc = [&](int i) {
+        const int src = m.ops[i].input_from;
+        if (!ov.fuse || ov.keep_all || ov.tile >= 0 || ov.split_k > 0 || src < 0 || m.ops[src].op != CW_OP_GAVGPOOL || m.ops[src].input_from < 0) return false;
+        const OpShape &map = m.shapes[m.ops[src].input_from];
+        return pool_fc_items(batch, m.ops[i].cin, (int64_t)map.h * map.w) > 0;
+    };
+
     // Where op i's output goes: a region of its own, or its channel range of the CONCAT tensor
     // that hosts it (allocated when its first member is planned).
     auto place_output = [&](int i, size_t dense_bytes) {
@@ -1109,6 +1117,17 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                     l.counters = Ref{SP_WORKSPACE, 0};
                     l.probs = Ref{SP_SLOT_PROBS, 0};
                     l.info.split_k = l.fc.split_k;
+                } else if (fc_in_parts(batch, o.cin, o.cout) && !pool_in_fc(i)) {
+                    // in space that is free by now, or not at all: the workspace of a model does not grow by it
+                    const size_t bytes = (size_t)kFcWaves * batch * ((o.cout + 15) & ~15) * 4;
+                    RangeAllocator trial = arena;
+                    size_t off;
+                    if (trial.alloc(bytes, &off) && trial.high_water() == arena.high_water()) {
+                        partial_bytes = bytes;
+                        partial_off = ws_alloc(bytes);
+                        l.partial = Ref{SP_WORKSPACE, partial_off};
+                        l.y = Ref{};   // the softmax writes the logits: this launch knows no slot
+                    }
                 }
                 p.launches.push_back(l);
                 break;
@@ -1129,6 +1148,14 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 l.sm.B = batch; l.sm.D = o.cout;
                 l.x = src; l.y = p.op_out[i];
                 l.info.bytes = 2 * (int64_t)batch * o.cout * 4;
+                if (!p.launches.empty() && p.launches.back().kind == K_FC && p.launches.back().partial.space != SP_NONE) {
+                    Launch &lf = p.launches.back();
+                    l.partial = lf.partial;   // freed, but nothing is placed between the FC and this
+                    l.bias = lf.bias;
+                    const int64_t parts = (int64_t)kFcWaves * batch * ((o.cout + 15) & ~15) * 4;
+                    lf.info.bytes += parts - (int64_t)batch * o.cout * 4;
+                    l.info.bytes += parts;
+                }
                 snprintf(l.info.name, sizeof l.info.name, "softmax");
                 p.launches.push_back(l);
                 break;
@@ -1313,7 +1340,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     if (ov.fuse && !ov.keep_all && ov.tile < 0 && ov.split_k <= 0)
         for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
             Launch &lp = p.launches[i], &lf = p.launches[i + 1];
-            if (lp.kind != K_GAVGPOOL || lf.kind != K_FC || lf.probs.space == SP_SLOT_PROBS || lf.y.space != SP_SLOT_LOGITS) continue;
+            if (lp.kind != K_GAVGPOOL || lf.kind != K_FC || lf.probs.space == SP_SLOT_PROBS || lf.partial.space != SP_NONE || lf.y.space != SP_SLOT_LOGITS) continue;
             if (lf.x.space != lp.y.space || lf.x.offset != lp.y.offset || lf.fc.In != lp.pool.C || lf.fc.B != lp.pool.B) continue;
             if (!pool_fc_items(lf.fc.B, lf.fc.In, (int64_t)lp.pool.H * lp.pool.W)) continue;
             lp.in_fc = true;
@@ -1371,6 +1398,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             case K_GAVGPOOL: g = dim3((unsigned)(l.pool.B * (l.pool.C / 64))); b = l.pool.H * l.pool.W >= kGapWideFrom ? 1024 : 64; break;
             case K_FC:
                 if (l.probs.space == SP_SLOT_PROBS) { g = dim3((l.fc.Out + 15) / 16, l.fc.split_k); b = 256; }
+                else if (l.partial.space != SP_NONE) { g = dim3((l.fc.Out + 15) / 16, (l.fc.B + 15) / 16, kFcWaves); b = 64; }
                 else { g = dim3((l.fc.Out + 15) / 16, (l.fc.B + 15) / 16); b = 512; }
                 break;
             case K_SOFTMAX: g = dim3(l.sm.B); b = 256; break;

@@ -73,3 +73,29 @@ def test_pool_and_fc_in_one_launch_with_non_finite_maps(ctx, c, h, w, batch, dty
         b, joined = logits(ctx, c, h, w, 40, batch, dtype, False, blob, x.pin_memory())
         assert joined and not apart and np.array_equal(a, b, equal_nan=True) and np.isfinite(a[:batch - 1]).all()
         assert np.isfinite(a[batch - 1]).all() == (value == 30.0)
+
+
+# one to ten chunks of 32 features a wave, part of a tile of outputs and of samples, a second tile of samples; and 2048 features with few samples, apart as they were
+@pytest.mark.parametrize("c,out,batch,dtype,parts", [
+    (256, 1000, 5, "fp16", True), (768, 17, 1, "bf16", True), (1024, 1024, 17, "fp16", True), (2048, 1000, 8, "bf16", True), (2560, 40, 16, "fp16", True), (2048, 1000, 7, "fp16", False),
+])
+def test_fc_in_parts_for_the_softmax(ctx, c, out, batch, dtype, parts):   # noqa: F811
+    """The FC's eight parts of K added up by the softmax against the sum inside the FC's launch, in the same order: same bits."""
+    g = np.random.default_rng(c + out)
+    half = torch.float16 if dtype == "fp16" else torch.bfloat16
+    shapes = [(32, 27), (c, 32), (out, c)]
+    wb = torch.cat([torch.from_numpy(g.normal(0, (2.0 / k) ** 0.5, n * k).astype(np.float32)).to(half) for n, k in shapes]).view(torch.uint8)
+    bs = torch.cat([torch.from_numpy(g.normal(0, 0.3, n).astype(np.float32)) for n, _ in shapes])
+    blob = torch.cat([wb, torch.zeros(-wb.numel() % 4, dtype=torch.uint8), bs.view(torch.uint8)]).pin_memory()
+    x = torch.from_numpy(g.normal(0, 1, (batch, 3, 18, 18)).astype(np.float32)).pin_memory()
+    x[0, 0, 4, 4] = float("inf")
+    a, _ = logits(ctx, c, 9, 9, out, batch, dtype, True, blob, x)
+    fc = []
+    define = ctx.model_define
+    ctx.model_define = lambda *args, **kw: fc.append(define(*args, **kw)) or fc[0]
+    try:
+        b, joined = logits(ctx, c, 9, 9, out, batch, dtype, False, blob, x)
+    finally:
+        del ctx.model_define
+    assert not joined and [l["grid_z"] for l in ctx.plan(fc[0], batch) if l["name"] == "fc"] == [8 if parts else 1]
+    assert np.array_equal(a, b, equal_nan=True) and np.isfinite(a[1:]).all() and not np.isfinite(a[0]).all()
