@@ -51,9 +51,10 @@ int32_t cw_plan_launch_ahead(cw_ctx *ctx, int32_t model_id, int32_t batch, int32
                              int32_t *workgroups, int64_t *bytes);
 /* 1 where entry `index` of the plan is no launch of its own: the input cast and, if it follows, the 3x3 stride-2 max pool,
  * whose work the first convolution's launch does (7x7 of 64 channels with the pool, 3x3 of 32 without, stride 2), and the
- * global average pool of few and small maps, which the FC's launch does, and a 1x1 convolution that the launch of the depthwise
- * convolution behind it computes (cw_set_fusion_dw); not under cw_set_fusion(0), a plan override or debug retention.  0 otherwise,
- * negative on error. */
+ * global average pool of few and small maps, which the FC's launch does, a 1x1 convolution that the launch of the depthwise
+ * convolution behind it computes (cw_set_fusion_dw), and a 1x1 convolution to 128 channels that the launch of the 3x3 to 32 behind it, its only
+ * reader, computes (a densely connected layer, where that is predicted to be faster); not under cw_set_fusion(0), a plan override or debug
+ * retention.  0 otherwise, negative on error. */
 int32_t cw_plan_launch_joined(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
 /* What EXEC issues for entry `index`: the same as cw_plan_launch_info but for joined entries and those that compute them.  The
  * first have no bytes, flops, grid or block; the others have the launch's own grid and name, its tile (pixels of the stored

@@ -234,7 +234,7 @@ char *resolve(cw_ctx *c, const ModelRt *m, const Bases &b, const Ref &r) {
 
 hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, hipStream_t st) {
     const DType dt = m->m.dtype;
-    if (l.in_head == 1 || l.in_fc || l.in_dw) return hipSuccess;   // computed by the first convolution's launch, the FC's or a depthwise convolution's
+    if (l.in_head == 1 || l.in_fc || l.in_next) return hipSuccess;   // computed by the first convolution's launch, the FC's or the next convolution's
     if (l.in_head == 2) {
         HeadArgs a = l.head;
         a.x = reinterpret_cast<const float *>(resolve(c, m, s, l.head_x));
@@ -285,6 +285,13 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
                 a0.res = resolve(c, m, s, l.res0);
                 a0.y = resolve(c, m, s, l.y0);
                 return launch_conv_pair(dt, l.tile, a0, a, st);
+            }
+            if (l.dense_fused) {
+                ConvArgs a1 = l.pw;
+                a1.x = resolve(c, m, s, l.pw_x);
+                a1.w = resolve(c, m, s, l.pw_w);
+                a1.bias = reinterpret_cast<const float *>(resolve(c, m, s, l.pw_bias));
+                return launch_dense_layer(dt, a1, a, l.dense_tile, st);
             }
             if (l.ahead_bytes > 0) {
                 a.w2 = resolve(c, m, s, l.ahead);
@@ -1419,7 +1426,7 @@ int32_t cw_plan_launch_joined(cw_ctx *c, int32_t model_id, int32_t batch, int32_
     Plan *p = get_plan(m, batch);
     if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
     if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
-    return p->launches[index].in_head == 1 || p->launches[index].in_fc || p->launches[index].in_dw;
+    return p->launches[index].in_head == 1 || p->launches[index].in_fc || p->launches[index].in_next;
 }
 
 int32_t cw_plan_launch_issued(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index, cw_launch_info *out) {

@@ -386,6 +386,12 @@ hipError_t launch_dwconv(DType dt, const DwArgs &a, hipStream_t s);
 // one launch (channel counts of dwconv_conv_ok); cv = the 1x1's arguments (its x is not read).
 hipError_t launch_dwconv_conv(DType dt, const DwArgs &a, const ConvArgs &cv, hipStream_t s);
 bool dwconv_conv_ok(int c, int n);
+// A 1x1 convolution to 128 channels and the 3x3 pad-1 convolution to 32 over its result (its x is not read), as in a densely connected block, in one launch;
+// the 1x1's result is not stored.
+struct DenseTile { int th, tw; };   // rows and columns of the 3x3's result that a workgroup computes
+bool dense_pick(const ConvArgs &c1, const ConvArgs &c2, DenseTile *best, double *us);   // the tile predicted to be fastest and its time; false: not for this kernel
+hipError_t launch_dense_layer(DType dt, const ConvArgs &c1, const ConvArgs &c2, const DenseTile &t, hipStream_t s);
+dim3 dense_grid(const ConvArgs &c1, const DenseTile &t);
 // A 1x1 stride-1 convolution (dense tensors) and the depthwise 3x3 pad-1 convolution over its result (its x is not read) in one launch;
 // keep: the 1x1's result is stored too.
 struct PwDwTile { int waves, pf, nf, rows; };   // pf x 16 pixels a wave, nf x 16 channels and `rows` rows of the depthwise result a workgroup

@@ -608,6 +608,42 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             pw_into[i] = k; pw_kept[i] = uses[i] > 1;
         }
     }
+    // A densely connected layer: a 1x1 convolution to 128 channels and the 3x3 to 32 right behind it, its only reader.  Entries as above.
+    std::vector<DenseTile> dense_tile(n_ops);
+    if (ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
+        std::vector<int> uses(n_ops, 0);
+        for (int i = 0; i < n_ops; ++i) {
+            if (m.ops[i].input_from >= 0) ++uses[m.ops[i].input_from];
+            if ((m.ops[i].op == CW_OP_CONV || m.ops[i].op == CW_OP_CONCAT) && m.ops[i].residual_from >= 0) ++uses[m.ops[i].residual_from];
+        }
+        for (int i = 1; i + 1 < n_ops; ++i) {
+            const int k = i + 1;
+            const cw_op &o1 = m.ops[i], &o2 = m.ops[k];
+            if (o1.op != CW_OP_CONV || o1.groups > 1 || o1.kh != 1 || o1.kw != 1 || o1.stride != 1 || o1.pad != 0 || o1.cin % 32 != 0 || o1.input_from < 0 || o1.residual_from >= 0 || uses[i] != 1) continue;
+            if (o2.op != CW_OP_CONV || o2.groups > 1 || o2.kh != 3 || o2.kw != 3 || o2.stride != 1 || o2.pad != 1 || o2.input_from != i || o2.residual_from >= 0) continue;
+            if (fuse_into[i] >= 0 || fused_first[i] >= 0 || in_third[i] >= 0 || in_pool[i] >= 0 || fuse_into[k] >= 0 || fused_first[k] >= 0 || in_third[k] >= 0 || (m.winograd && (wino_eligible(o1, i) || wino_eligible(o2, k)))) continue;
+            const OpShape &sh = m.shapes[i];
+            ConvArgs a{}, c{};
+            a.B = batch; a.H = a.Ho = sh.h; a.W = a.Wo = sh.w; a.Cin = o1.cin; a.Cout = o1.cout; a.kh = a.kw = a.khp = a.kwp = 1; a.stride = 1;
+            conv_set_ld(a, o1.cin, o1.cout);
+            a.M = batch * sh.h * sh.w; a.K = o1.cin; a.relu = o1.relu; a.split_k = 1;
+            c = a;
+            c.Cin = o2.cin; c.Cout = o2.cout; c.kh = c.kw = c.khp = c.kwp = 3; c.K = 9 * o2.cin; c.relu = o2.relu;
+            conv_set_pad(c, 1, o2.kh == o2.kw ? 1 : o2.pad_w);
+            conv_set_ld(c, o2.cin, o2.cout);
+            double us;
+            if (!dense_pick(a, c, &dense_tile[i], &us)) continue;
+            ConvTile tile;
+            int32_t split;
+            bool fixed1, fixed2;
+            const double apart = pick_conv_tile(a, false, false, o1.cin, false, ov, &tile, &split, &fixed1) + pick_conv_tile(c, false, false, 9 * (int64_t)o2.cin, false, ov, &tile, &split, &fixed2);
+            // The cost model's launches apart are 10 to 17 % longer than graph replay has them.  Whole EXECs of DenseNet, all apart and as decided here, 224x224
+            // batch 1, 6, 8, 16: 149.0 -> 138.8 us, 207.0 -> 176.9, 207.8 -> 196.1, 301.3 -> 289.5; 199x155 batch 9 204.2 -> 174.3, 200x180 batch 13 (more than one
+            // round of tiles everywhere) 215.6 -> 216.0, with every layer in one launch 227.
+            if (fixed1 || fixed2 || us >= 0.85 * apart - 0.2) continue;
+            pw_into[i] = k;
+        }
+    }
     // Order in which the ops are planned and launched: op order, except that a convolution j which
     // reads the same tensor as an earlier convolution i and depends on nothing after i (a ResNet
     // block's projection shortcut, i = the block's first 1x1) moves to right behind i, where the two
@@ -1349,10 +1385,16 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         }
     for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
         Launch &lc = p.launches[i], &ld = p.launches[i + 1];
-        if (lc.kind != K_CONV || lc.pair_op >= 0 || lc.fused_bm > 0 || pw_into[lc.op_index] < 0 || ld.kind != K_DWCONV || ld.dw_fused || ld.op_index != pw_into[lc.op_index]) continue;
-        lc.in_dw = true;
-        ld.pw_fused = true;
-        ld.pw_tile = pw_tile[lc.op_index];
+        if (lc.kind != K_CONV || lc.pair_op >= 0 || lc.fused_bm > 0 || pw_into[lc.op_index] < 0 || ld.op_index != pw_into[lc.op_index]) continue;
+        if (ld.kind == K_CONV ? ld.pair_op >= 0 || ld.fused_bm > 0 || ld.stem : ld.kind != K_DWCONV || ld.dw_fused) continue;
+        lc.in_next = true;
+        if (ld.kind == K_CONV) {
+            ld.dense_fused = true;
+            ld.dense_tile = dense_tile[lc.op_index];
+        } else {
+            ld.pw_fused = true;
+            ld.pw_tile = pw_tile[lc.op_index];
+        }
         ld.pw = lc.conv;
         ld.pw_x = lc.x; ld.pw_w = lc.w; ld.pw_bias = lc.bias; ld.pw_res = lc.res;
         if (pw_kept[lc.op_index]) ld.pw_y = lc.y;
@@ -1360,7 +1402,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     // Weights are read ahead by the nearest of the four launches before the one that uses them which has CUs to spare.
     {
         auto host = [&](const Launch &l) {
-            if (l.kind != K_CONV || l.in_dw || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
+            if (l.kind != K_CONV || l.in_next || l.dense_fused || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
             if (!conv_uses_dlds(l.conv, false) || l.ahead_bytes > 0) return false;
             const TileDim d = conv_tile_dim(l.tile);
             return (int64_t)((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn) * d.parts() <= kPrefetchMaxTiles;
@@ -1432,7 +1474,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     for (size_t i = 0; i < p.launches.size(); ++i) {
         const Launch &l = p.launches[i];
         cw_launch_info &d = p.issued[i];
-        if (l.in_head == 1 || l.in_fc || l.in_dw) {
+        if (l.in_head == 1 || l.in_fc || l.in_next) {
             d.bytes = d.flops = 0;
             d.grid_x = d.grid_y = d.grid_z = d.block = 0;
         } else if (l.in_head == 2) {
@@ -1449,6 +1491,14 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                 d.flops += p.launches[i + 1].info.flops;
                 d.bytes += (int64_t)h.n1 * h.cout * esz + h.n1 * 4 + out * h.n1 * (int64_t)esz;
             }
+        } else if (l.dense_fused) {
+            const dim3 g = dense_grid(l.pw, l.dense_tile);
+            d.grid_x = (int32_t)g.x; d.grid_y = d.grid_z = 1; d.block = 256;
+            d.tile_m = l.dense_tile.th * l.dense_tile.tw; d.tile_n = l.conv.Cout; d.tile_k = 0; d.conv_tile = -1; d.split_k = d.wave_groups = 1;
+            d.flops += p.launches[i - 1].info.flops;
+            d.bytes += p.launches[i - 1].info.bytes - 2 * (int64_t)l.pw.M * l.pw.Cout * (int64_t)esz;   // what is between stays on the chip
+            if (l.conv.split_k > 1) d.bytes -= 2 * (int64_t)l.conv.split_k * l.conv.M * l.conv.Cout * 4;
+            snprintf(d.name, sizeof d.name, "%s+conv3x3_s1", p.launches[i - 1].info.name);
         } else if (l.pw_fused) {
             const int64_t between = (int64_t)l.pw.M * l.pw.Cout * (int64_t)esz;
             const dim3 g = pw_dw_grid(l.pw, l.dw, l.pw_tile);

@@ -67,10 +67,11 @@ struct Launch {
     // issues it, 1 = the others, which then issue nothing.
     int32_t in_head = 0;
     HeadArgs head{};
-    // A 1x1 convolution (in_dw) that the launch of the depthwise convolution behind it computes (pw_fused: pw = its arguments,
-    // pw_x ... pw_y its tensors; pw_y is none where no other op reads it).
-    bool in_dw = false, pw_fused = false;
+    // A 1x1 convolution (in_next) that the launch of the convolution behind it computes: a depthwise one (pw_fused) or the 3x3 of a densely
+    // connected layer (dense_fused).  pw = its arguments, pw_x ... pw_y its tensors; pw_y is none where no other op reads it.
+    bool in_next = false, pw_fused = false, dense_fused = false;
     PwDwTile pw_tile{};
+    DenseTile dense_tile{};
     ConvArgs pw{};
     Ref pw_x, pw_w, pw_bias, pw_res, pw_y;
     bool in_fc = false;    // a global average pool that the FC's launch right behind it computes

@@ -453,6 +453,28 @@ def test_1x1_with_the_depthwise_behind_it(ctx):
             getattr(ctx, off)(1)
 
 
+def test_densely_connected_layer_in_one_launch(ctx):
+    """The 1x1 and the 3x3 keep their entries; the 3x3's launch does the work of both, without the tensor between."""
+    from oracle import topology as T
+    ops = [tuple(o) for o in T.dense_net()]
+    m = ctx.model_define(ops, 3, 224, 224)
+    for b, n in ((1, 15), (4, 17)):
+        plan = ctx.plan(m, b)
+        joined = [i for i, l in enumerate(plan) if ctx.plan_launch_joined(m, b, i) and l["kind"] == 1 and l["op_index"] > 0]
+        assert len(joined) == n
+        for i in joined:
+            a, c, both = plan[i], plan[i + 1], ctx.plan_launch_issued(m, b, i + 1)
+            assert c["op_index"] == a["op_index"] + 1 and ops[c["op_index"]][9] == a["op_index"] and a["gemm_n"] == 128 and c["gemm_n"] == 32
+            assert both["flops"] == a["flops"] + c["flops"] and both["name"] == a["name"] + "+conv3x3_s1" and both["split_k"] == 1
+            assert both["grid_x"] * both["tile_m"] >= a["gemm_m"] and both["bytes"] < a["bytes"] + c["bytes"] - 4 * 128 * a["gemm_m"] + 1
+    ctx.set_fusion(0)
+    try:
+        m2 = ctx.model_define(ops, 3, 224, 224)
+        assert not [l for i, l in enumerate(ctx.plan(m2, 1)) if ctx.plan_launch_joined(m2, 1, i)]
+    finally:
+        ctx.set_fusion(1)
+
+
 def test_weight_pages():
     """The weight pool is paged (paper section 5.1): page counts per model, the limits, the free count."""
     c = cw.Context(device=-1, weight_pool_bytes=1 << 30)          # default page: 16 MiB
