@@ -22,6 +22,7 @@ constexpr size_t kDefaultPageBytes = (size_t)16 << 20;  // the paper's page size
 constexpr int kProfileEvents = 128;  // EXECs timed back to back between two host syncs
 
 constexpr int kDoneStride = 32;      // words from one slot's `done` word to the next: a line each
+constexpr size_t kWordBytes = (size_t)kMaxSlots * kDoneStride * 4;
 constexpr unsigned kWaitUs = 50000;  // default of cw_set_wait_launches
 
 enum SlotState { SLOT_FREE = 0, SLOT_RELEASED, SLOT_INPUT, SLOT_EXECUTED };   // released: free once `released` is over
@@ -135,7 +136,8 @@ struct cw_ctx {
     hipStream_t last_exec_stream = nullptr;
     hipEvent_t last_exec_end = nullptr;
     uint64_t release_seq = 0;
-    unsigned *done = nullptr;        // device: a word per slot
+    char *words = nullptr;           // device: kWordBytes for the slots' words, the workspace behind them
+    unsigned *done = nullptr;        // a word per slot
     unsigned wait_us = kWaitUs;      // longest life of a wait_done launch, 0: none are issued
     // Set while free IO memory may still be in use by the request it was taken from: `given_on` is over once none is.
     hipEvent_t given_on = nullptr;
@@ -699,15 +701,17 @@ int32_t cw_create(cw_ctx **out, const cw_config *cfg) {
     auto dmalloc = [&](char **ptr, size_t bytes) {
         return bytes == 0 ? hipSuccess : hipMalloc(reinterpret_cast<void **>(ptr), bytes);
     };
-    if (dmalloc(&p->workspace, cfg->workspace_bytes) != hipSuccess || dmalloc(&p->io, cfg->io_bytes) != hipSuccess ||
+    if (dmalloc(&p->words, kWordBytes + cfg->workspace_bytes) != hipSuccess || dmalloc(&p->io, cfg->io_bytes) != hipSuccess ||
         dmalloc(&p->pool, cfg->weight_pool_bytes) != hipSuccess ||
         dmalloc(&p->staging, cfg->load_staging_bytes) != hipSuccess) {
         g_create_err = std::string("hipMalloc of the pools: ") + hipGetErrorString(hipGetLastError());
         cleanup();
         return CW_ERR_NO_MEMORY;
     }
+    p->done = reinterpret_cast<unsigned *>(p->words);
+    p->workspace = p->words + kWordBytes;
     // split-K arrival counters must start at zero; every launch leaves them at zero again
-    if (cfg->workspace_bytes < kCounterBytes + kResidentBytes || hipMemset(p->workspace, 0, kCounterBytes + kResidentBytes) != hipSuccess) {
+    if (cfg->workspace_bytes < kCounterBytes + kResidentBytes || hipMemset(p->words, 0, kWordBytes + kCounterBytes + kResidentBytes) != hipSuccess) {
         g_create_err = "workspace smaller than its header (split-K counters, resident-launch flags), or hipMemset failed";
         cleanup();
         return CW_ERR_NO_MEMORY;
@@ -716,12 +720,6 @@ int32_t cw_create(cw_ctx **out, const cw_config *cfg) {
         g_create_err = std::string("hipGetSymbolAddress of the static arena: ") + hipGetErrorString(ce);
         cleanup();
         return CW_ERR_HIP;
-    }
-    if (hipMalloc(reinterpret_cast<void **>(&p->done), kMaxSlots * kDoneStride * 4) != hipSuccess ||
-        hipMemset(p->done, 0, kMaxSlots * kDoneStride * 4) != hipSuccess) {
-        g_create_err = std::string("the slots' words: ") + hipGetErrorString(hipGetLastError());
-        cleanup();
-        return CW_ERR_NO_MEMORY;
     }
     p->resident_capable = prop.multiProcessorCount == kResPartitions * kResGroupsPerPartition;
     if (hipHostMalloc(reinterpret_cast<void **>(&p->res_error), 64, hipHostMallocDefault) != hipSuccess) {
@@ -782,8 +780,7 @@ int32_t cw_destroy(cw_ctx *c) {
         if (c->given_on) (void)hipEventDestroy(c->given_on);
         if (c->internal_stream) (void)hipStreamDestroy(c->internal_stream);
         if (c->res_error) (void)hipHostFree(c->res_error);
-        if (c->done) (void)hipFree(c->done);
-        if (c->workspace) (void)hipFree(c->workspace);
+        if (c->words) (void)hipFree(c->words);
         if (c->io) (void)hipFree(c->io);
         if (c->pool) (void)hipFree(c->pool);
         if (c->staging) (void)hipFree(c->staging);
