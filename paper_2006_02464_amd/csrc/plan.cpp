@@ -1162,8 +1162,10 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                         partial_bytes = bytes;
                         partial_off = ws_alloc(bytes);
                         l.partial = Ref{SP_WORKSPACE, partial_off};
-                        l.y = Ref{};   // the softmax writes the logits: this launch knows no slot
+                    } else if (ov.keep_all && res_mode == 0 && bytes <= cast_bytes) {
+                        l.partial = Ref{SP_WORKSPACE, cast_off};   // retention keeps every op's tensor, the cast images are none
                     }
+                    if (l.partial.space != SP_NONE) l.y = Ref{};   // the softmax writes the logits: this launch knows no slot
                 }
                 p.launches.push_back(l);
                 break;

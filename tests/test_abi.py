@@ -102,6 +102,21 @@ def test_debug_keep_uses_more_workspace(ctx):
     assert ctx.model_workspace_bytes(k, 16) > ctx.model_workspace_bytes(m, 16)
 
 
+@pytest.mark.parametrize("depth, hw, batch", [(18, 224, 8), (50, 224, 8), (50, 224, 16)])
+def test_debug_keep_leaves_the_head_of_the_network_as_it_is(ctx, depth, hw, batch):
+    """The FC in parts takes space that is free by then; a retained plan frees none and has the cast images' for it."""
+    ops = ctx.model_get_ops(ctx.model_define_resnet(depth, hw, hw))
+    plain = ctx.model_define(ops, 3, hw, hw, batch_sizes=(batch,))
+    ctx.set_debug_keep(True)
+    try:
+        kept = ctx.model_define(ops, 3, hw, hw, batch_sizes=(batch,))
+    finally:
+        ctx.set_debug_keep(False)
+    key = lambda m: [(l["name"], l["bytes"], l["grid_x"], l["grid_y"], l["grid_z"], l["block"]) for l in ctx.plan(m, batch)[-2:]]
+    assert key(kept) == key(plain)
+    assert key(plain)[0][4:] == (8, 64)
+
+
 def test_plan_override_reaches_every_tile(ctx):
     for name, idx in cw.CONV_TILES.items():
         ctx.set_plan_override(idx, 2)
