@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libclockwork_exec.so")
 STAMPED_LIB = os.path.join(HERE, "libclockwork_exec_stamps.so")
-SOURCES = ["clockwork_exec.hip", "plan.cpp", "kernels_conv.hip", "kernels_conv_dlds.hip", "kernels_conv_f16.hip", "kernels_conv_bf16.hip", "kernels_conv_small.hip", "kernels_conv_k256.hip", "kernels_conv_tail.hip", "kernels_resident.hip", "kernels_misc.hip", "kernels_head.hip", "kernels_load.hip", "kernels_io.hip", "kernels_pw_dw.hip", "kernels_dense.hip", "worker.hip"]
+SOURCES = ["clockwork_exec.hip", "plan.cpp", "kernels_conv.hip", "kernels_conv_dlds.hip", "kernels_conv_f16.hip", "kernels_conv_bf16.hip", "kernels_conv_small.hip", "kernels_conv_k256.hip", "kernels_conv_tail.hip", "kernels_resident.hip", "kernels_misc.hip", "kernels_head.hip", "kernels_load.hip", "kernels_io.hip", "kernels_pw_dw.hip", "kernels_dense.hip", "kernels_tail.hip", "worker.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-fno-gpu-rdc",

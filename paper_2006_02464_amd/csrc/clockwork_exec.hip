@@ -236,7 +236,7 @@ char *resolve(cw_ctx *c, const ModelRt *m, const Bases &b, const Ref &r) {
 
 hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, hipStream_t st) {
     const DType dt = m->m.dtype;
-    if (l.in_head == 1 || l.in_fc || l.in_next) return hipSuccess;   // computed by the first convolution's launch, the FC's or the next convolution's
+    if (l.in_head == 1 || l.in_fc || l.in_next || l.in_tail) return hipSuccess;   // computed by the first convolution's launch, the FC's or a later convolution's
     if (l.in_head == 2) {
         HeadArgs a = l.head;
         a.x = reinterpret_cast<const float *>(resolve(c, m, s, l.head_x));
@@ -294,6 +294,24 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
                 a1.w = resolve(c, m, s, l.pw_w);
                 a1.bias = reinterpret_cast<const float *>(resolve(c, m, s, l.pw_bias));
                 return launch_dense_layer(dt, a1, a, l.dense_tile, st);
+            }
+            if (l.tail > 0) {
+                TailArgs t{};
+                t.M = l.pw.M; t.H = l.pw.H; t.W = l.pw.W; t.act1 = l.pw.relu;
+                t.x = resolve(c, m, s, l.pw_x);
+                t.w1 = resolve(c, m, s, l.pw_w);
+                t.bias1 = reinterpret_cast<const float *>(resolve(c, m, s, l.pw_bias));
+                if (l.tail == 2) {
+                    t.w2 = a.w; t.bias2 = a.bias; t.res = a.res; t.y = a.y; t.act2 = a.relu;
+                } else {
+                    t.w2 = resolve(c, m, s, l.w2);
+                    t.bias2 = reinterpret_cast<const float *>(resolve(c, m, s, l.bias2));
+                    t.res = resolve(c, m, s, l.pw_res);
+                    t.y = resolve(c, m, s, l.pw_y);
+                    t.act2 = l.conv0.relu;
+                    t.w3 = a.w; t.bias3 = a.bias; t.y3 = a.y; t.act3 = a.relu;
+                }
+                return launch_tail(dt, t, st);
             }
             if (l.ahead_bytes > 0) {
                 a.w2 = resolve(c, m, s, l.ahead);
@@ -1424,6 +1442,16 @@ int32_t cw_plan_launch_joined(cw_ctx *c, int32_t model_id, int32_t batch, int32_
     if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
     if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
     return p->launches[index].in_head == 1 || p->launches[index].in_fc || p->launches[index].in_next;
+}
+
+int32_t cw_plan_launch_tail(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index) {
+    if (!c) return CW_ERR_INVALID;
+    ModelRt *m = get_model(c, model_id);
+    if (!m) return set_err(c, CW_ERR_INVALID, "unknown model id");
+    Plan *p = get_plan(m, batch);
+    if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
+    if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
+    return p->launches[index].in_tail ? 1 : p->launches[index].tail;
 }
 
 int32_t cw_plan_launch_issued(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index, cw_launch_info *out) {

@@ -392,6 +392,18 @@ struct DenseTile { int th, tw; };   // rows and columns of the 3x3's result that
 bool dense_pick(const ConvArgs &c1, const ConvArgs &c2, DenseTile *best, double *us);   // the tile predicted to be fastest and its time; false: not for this kernel
 hipError_t launch_dense_layer(DType dt, const ConvArgs &c1, const ConvArgs &c2, const DenseTile &t, hipStream_t s);
 dim3 dense_grid(const ConvArgs &c1, const DenseTile &t);
+// A 3x3 stride-1 pad-1 convolution 64 -> 64, the 1x1 to 256 over its result with a residual and (w3) the 1x1 back to 64 over that, dense tensors, in one launch;
+// the 3x3's result is not stored.
+struct TailArgs {
+    const void *x, *w1, *w2, *res, *w3;
+    const float *bias1, *bias2, *bias3;
+    void *y, *y3;
+    int32_t M, H, W, act1, act2, act3;
+    FastDiv w_div, h_div;   // filled in by the launcher
+};
+bool tail_shape_ok(int64_t M, int32_t H, int32_t W);
+int tail_bm(int64_t M);   // pixels a workgroup
+hipError_t launch_tail(DType dt, const TailArgs &a, hipStream_t s);
 // A 1x1 stride-1 convolution (dense tensors) and the depthwise 3x3 pad-1 convolution over its result (its x is not read) in one launch;
 // keep: the 1x1's result is stored too.
 struct PwDwTile { int waves, pf, nf, rows; };   // pf x 16 pixels a wave, nf x 16 channels and `rows` rows of the depthwise result a workgroup

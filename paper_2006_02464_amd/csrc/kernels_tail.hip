@@ -1,0 +1,236 @@
+// The tail of a narrow bottleneck over few pixels in one launch: a 3x3 convolution 64 -> 64, the 1x1 to 256 with its residual and, where that is the
+// result's only reader as an input, the 1x1 back to 64 of the block behind it.
+// What bounds it: what a CU has to fetch, 72 KB + 32 KB (+ 32 KB) of weights, at about 50 bytes a clock; the matrix instructions are a tenth of that.
+// So all of it is requested at the start, in the order in which it is needed, and nothing waits for more than its own part:
+// - 16 or 32 pixels a workgroup, so that these few pixels still are a workgroup a CU; with 136 KB of weights in LDS there is room for one.
+// - A wave has 16 of the 64 channels of the first and the third layer and 64 of the 256, and fetches their weights itself: only pixels and what a layer
+//   hands to the next pass a barrier.
+// - With 32 pixels the third layer's weights come into the place of the wave's own of the first, once it has read them.
+// Back to back, 56x56 at batch 1 and 49x41 at batch 3 (3136 and 6027 pixels): three layers 9.3 -> 5.7 us and 10.7 -> 7.0, two layers 6.6 -> 4.6 and 7.5 -> 6.1. The 64-pixel form of the
+// convolution kernel, which walks the layers in chunks with two barriers each, takes 10.0 and 8.6 at 6272 pixels.
+#include "conv_dlds_body.h"
+
+namespace cw {
+
+constexpr int kTailC = 64, kTailWide = 256, kTailTaps = 9;
+
+template <int F>   // 16-pixel groups of a workgroup
+struct TailLds {
+    static constexpr unsigned W1 = 0, XS = 4 * 18432, W2 = XS + F * 18432, W3 = F == 1 ? W2 + 32768 : 0, P = (F == 1 ? W3 : W2) + 32768;
+    static constexpr unsigned P_PITCH = kTailC * 2 + 16, Q_PITCH = kTailWide * 2 + 16;   // 16 consecutive pixels start on different banks
+    static constexpr unsigned Q = XS;          // over the first layer's pixels
+    static constexpr unsigned BIAS = P + 16 * F * P_PITCH, BYTES = BIAS + 3 * 1024;
+    static_assert(16 * F * Q_PITCH <= F * 18432 && BYTES <= 160 * 1024, "");
+};
+
+template <typename T, int F, bool THIRD>
+__global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
+    typedef MfmaTile<T, 16> MF;
+    typedef typename Mfma<T>::v8 v8;
+    typedef TailLds<F> L;
+    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)cw_dyn_lds;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lrow = lane & 15, lhalf = lane >> 4;
+    const unsigned row8 = lane >> 3, c8 = lane & 7;   // of a piece of 8 rows x 128 bytes; chunk c of row r lies at c ^ (r / 2) % 8
+    const int m0 = xcd_tile_id(blockIdx.x, gridDim.x) * 16 * F;
+    const u32x4 dx = make_desc(a.x, (unsigned)a.M * (kTailC * 2u)), dw1 = make_desc(a.w1, kTailC * kTailTaps * kTailC * 2u), dw2 = make_desc(a.w2, kTailWide * kTailC * 2u);
+    const u32x4 dw3 = make_desc(THIRD ? a.w3 : a.w2, kTailC * kTailWide * 2u);
+    const unsigned key_l = row8 >> 1;   // (r / 2) % 8 of row 8h + row8: key_l + 4h
+    const unsigned cs[2] = {(c8 ^ key_l) << 4, (c8 ^ (key_l + 4)) << 4};
+    auto load_w1 = [&](int tap) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            load_to_lds(dw1, row8 * (kTailTaps * kTailC * 2u) + cs[h], (unsigned)(wave * 16 + h * 8) * (kTailTaps * kTailC * 2u) + (unsigned)tap * (kTailC * 2u),
+                        lds_base + L::W1 + (unsigned)wave * 18432u + (unsigned)(tap * 2 + h) * 1024u);
+    };
+    load_w1(0);
+    __builtin_amdgcn_sched_barrier(0);
+    // A wave's pieces of the pixels: always the same 8 of the workgroup's, of taps 0 and 2 or 1 of a filter row (16 pixels), or of all three (32)
+    const int xp = F == 1 ? wave & 1 : wave;
+    const int pm = m0 + xp * 8 + (int)row8;
+    const unsigned x_cs = cs[xp & 1];
+    const unsigned pt = fast_div((unsigned)min(pm, a.M - 1), a.w_div), pn = fast_div(pt, a.h_div);
+    const int pj = min(pm, a.M - 1) - (int)pt * a.W, pi = (int)(pt - pn * (unsigned)a.H);
+    const bool p_in = pm < a.M;
+    auto load_x = [&](int r, int s) {
+        const bool in = p_in && (unsigned)(pi + r - 1) < (unsigned)a.H && (unsigned)(pj + s - 1) < (unsigned)a.W;
+        load_to_lds(dx, in ? (unsigned)(pm + (r - 1) * a.W + s - 1) * (kTailC * 2u) + x_cs : kOob, 0u, lds_base + L::XS + (unsigned)((r * 3 + s) * 2 * F + xp) * 1024u);
+    };
+    auto load_x_row = [&](int r) {
+        if constexpr (F == 2) { load_x(r, 0); load_x(r, 1); load_x(r, 2); }
+        else if (wave < 2) { load_x(r, 0); load_x(r, 2); }   // uniform
+        else load_x(r, 1);
+    };
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        load_x_row(r);
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            if (r + s > 0) load_w1(r * 3 + s);
+    }
+    {   // biases: wave 0 the first layer's, wave 1 the second's, the others the third's (twice the same bytes to the same place)
+        const u32x4 db = make_desc(wave == 0 ? a.bias1 : wave == 1 || !THIRD ? a.bias2 : a.bias3, wave == 0 || (wave > 1 && THIRD) ? kTailC * 4u : kTailWide * 4u);
+        load_to_lds(db, (unsigned)lane * 16u, 0u, lds_base + L::BIAS + (unsigned)min(wave, 2) * 1024u);
+    }
+    // the residual: 4 channels of each of a lane's four 16-channel tiles
+    const unsigned nl = 8 * (lhalf & 1) + 4 * (lhalf >> 1);   // the channel of a lane's first row (packed weights)
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.res, (unsigned)a.M * (kTailWide * 2u)), ry = make_rsrc(a.y, (unsigned)a.M * (kTailWide * 2u));
+    unsigned y_off[F];
+    u32x2 res[F][4];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+        const int m = m0 + f * 16 + lrow;
+        y_off[f] = m < a.M ? (unsigned)m * (kTailWide * 2u) + (unsigned)(wave * 64 + nl) * 2u : kOob;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) res[f][j] = __builtin_amdgcn_raw_buffer_load_b64(rr, y_off[f], j * 32, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        load_to_lds(dw2, row8 * (kTailC * 2u) + cs[q & 1], (unsigned)(wave * 64 + q * 8) * (kTailC * 2u), lds_base + L::W2 + (unsigned)(wave * 8 + q) * 1024u);
+    auto load_w3 = [&] {
+#pragma unroll
+        for (int q = 0; q < 8; ++q)   // 64 of the 256 channels, half of the rows
+            load_to_lds(dw3, row8 * (kTailWide * 2u) + cs[q & 1], (unsigned)(wave * 16 + (q & 1) * 8) * (kTailWide * 2u) + (unsigned)(q >> 1) * 128u,
+                        lds_base + L::W3 + (unsigned)wave * (F == 1 ? 8192u : 18432u) + (unsigned)q * 1024u);
+    };
+    if (THIRD && F == 1) load_w3();
+    // Loads behind the last of filter row r
+    constexpr int N3 = THIRD ? 8 : 0, AFTER = 1 + 4 * F + 8 + (F == 1 ? N3 : 0);
+    typename MF::acc acc[F][2];
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) acc[f][k] = typename MF::acc{0.f, 0.f, 0.f, 0.f};
+    const unsigned key = (lrow >> 1) & 7, rd = (unsigned)lrow * 128u;
+    const unsigned ck[2] = {((unsigned)lhalf ^ key) << 4, ((unsigned)(4 + lhalf) ^ key) << 4};
+    auto row = [&](int r) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int tap = r * 3 + s;
+                const v8 fw = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W1 + (unsigned)wave * 18432u + tap * 2048u + rd + ck[k]);
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    const v8 fx = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::XS + (unsigned)(tap * F + f) * 2048u + rd + ck[k]);
+                    acc[f][k] = MF::mma(fw, fx, acc[f][k]);
+                }
+            }
+    };
+    // (16 pixels: waves 0 and 1 have one load of pixels a filter row more)
+    if (F == 2) wait_lds_loads_and_barrier<AFTER + 2 * 9>();
+    else if (wave < 2) wait_lds_loads_and_barrier<AFTER + 2 * 8>();
+    else wait_lds_loads_and_barrier<AFTER + 2 * 7>();
+    row(0);
+    if (F == 2) wait_lds_loads_and_barrier<AFTER + 9>();
+    else if (wave < 2) wait_lds_loads_and_barrier<AFTER + 8>();
+    else wait_lds_loads_and_barrier<AFTER + 7>();
+    row(1);
+    wait_lds_loads_and_barrier<AFTER - 1>();   // the biases too
+    row(2);
+    // first layer's result: 4 channels of a pixel, rounded as when it is stored
+    {
+        const typename MF::acc b = *reinterpret_cast<const typename MF::acc *>(cw_dyn_lds + L::BIAS + (wave * 16 + nl) * 4u);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[f][0][e] + acc[f][1][e] + b[e];
+            *reinterpret_cast<u32x2 *>(cw_dyn_lds + L::P + (unsigned)(f * 16 + lrow) * L::P_PITCH + (wave * 16 + nl) * 2u) = activate<T>(v, a.act1);
+        }
+    }
+    if (THIRD && F == 2) {
+        // this wave's reads of its first weights have returned (their products are in the sums just stored)
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+        load_w3();
+    }
+    wait_lds_loads_and_barrier<N3>();   // the second layer's weights (and the residual); everyone's part of the first layer's result
+    {
+        v8 fp[F][2];
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) fp[f][k] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::P + (unsigned)(f * 16 + lrow) * L::P_PITCH + (unsigned)(k * 4 + lhalf) * 16u);
+        typename MF::acc s[F][4], b[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            b[j] = *reinterpret_cast<const typename MF::acc *>(cw_dyn_lds + L::BIAS + 1024u + (wave * 64 + j * 16 + nl) * 4u);
+            v8 fw[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) fw[k] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W2 + (unsigned)wave * 8192u + j * 2048u + rd + ck[k]);
+#pragma unroll
+            for (int f = 0; f < F; ++f) s[f][j] = MF::mma(fw[0], fp[f][0], typename MF::acc{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+            for (int f = 0; f < F; ++f) s[f][j] = MF::mma(fw[1], fp[f][1], s[f][j]);
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const T *r = reinterpret_cast<const T *>(&res[f][j]);
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = s[f][j][e] + b[j][e] + (float)r[e];
+                const u32x2 o = activate<T>(v, a.act2);
+                __builtin_amdgcn_raw_buffer_store_b64(o, ry, y_off[f], j * 32, 0);
+                if (THIRD) *reinterpret_cast<u32x2 *>(cw_dyn_lds + L::Q + (unsigned)(f * 16 + lrow) * L::Q_PITCH + (unsigned)(wave * 64 + j * 16 + nl) * 2u) = o;
+            }
+    }
+    if constexpr (THIRD) {
+        wait_lds_loads_and_barrier<4 * F>();   // older than the stores are the third layer's weights; everyone's part of the second's result
+        const typename MF::acc b = *reinterpret_cast<const typename MF::acc *>(cw_dyn_lds + L::BIAS + 2048u + (wave * 16 + nl) * 4u);
+        typename MF::acc s[F][2];
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) s[f][k] = typename MF::acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const v8 fw = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W3 + (unsigned)wave * (F == 1 ? 8192u : 18432u) + (k >> 1) * 2048u + rd + ck[k & 1]);
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const v8 fq = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::Q + (unsigned)(f * 16 + lrow) * L::Q_PITCH + (unsigned)(k * 4 + lhalf) * 16u);
+                s[f][k & 1] = MF::mma(fw, fq, s[f][k & 1]);
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = s[f][0][e] + s[f][1][e] + b[e];
+            const int m = m0 + f * 16 + lrow;
+            if (m < a.M) *reinterpret_cast<u32x2 *>(static_cast<char *>(a.y3) + (size_t)m * (kTailC * 2) + (wave * 16 + nl) * 2u) = activate<T>(v, a.act3);
+        }
+    }
+}
+
+int tail_bm(int64_t M) { return M <= 16 * 256 ? 16 : 32; }
+
+// Up to a round of 32 pixels a workgroup.  From 96 tiles of 64 pixels on the plan has the convolution kernel's own form, so that this one sees less.
+bool tail_shape_ok(int64_t M, int32_t H, int32_t W) { return M >= 1 && M <= 32 * 256 && H >= 1 && W >= 1 && M % ((int64_t)H * W) == 0; }
+
+template <typename T, int F, bool THIRD>
+static hipError_t launch_one(const TailArgs &a, hipStream_t s) {
+    auto k = tail_kernel<T, F, THIRD>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)TailLds<F>::BYTES);
+    if (attr != hipSuccess) return attr;
+    k<<<(unsigned)((a.M + 16 * F - 1) / (16 * F)), 256, TailLds<F>::BYTES, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_tail(DType dt, const TailArgs &a_in, hipStream_t s) {
+    TailArgs a = a_in;
+    if (!tail_shape_ok(a.M, a.H, a.W) || !a.x || !a.w1 || !a.bias1 || !a.w2 || !a.bias2 || !a.res || !a.y) return hipErrorInvalidValue;
+    if (a.w3 && (!a.bias3 || !a.y3)) return hipErrorInvalidValue;
+    a.w_div = make_fast_div((uint32_t)a.W);
+    a.h_div = make_fast_div((uint32_t)a.H);
+#define CW_TAIL(T_, F_) (a.w3 ? launch_one<T_, F_, true>(a, s) : launch_one<T_, F_, false>(a, s))
+    if (tail_bm(a.M) == 16) return dt == DT_F16 ? CW_TAIL(f16, 1) : CW_TAIL(bf16, 1);
+    return dt == DT_F16 ? CW_TAIL(f16, 2) : CW_TAIL(bf16, 2);
+#undef CW_TAIL
+}
+
+}  // namespace cw

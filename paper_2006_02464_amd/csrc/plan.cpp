@@ -644,6 +644,37 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             pw_into[i] = k;
         }
     }
+    // The tail of a narrow bottleneck over too few pixels for the convolution kernel's fused form: a 3x3 64 -> 64, the 1x1 to 256 behind it, its only reader, with a
+    // residual, and the next block's 1x1 back to 64, the only one to read that as its input.  tail_into[i] = the op whose launch computes op i.
+    // Always: it is faster from a few dozen pixels on (whole EXECs by graph replay, apart and as decided here, ResNet-50 64x64 batch 1 186.8 -> 178.6 us, 130x97 200.1 -> 189.8,
+    // 224x224 216.9 -> 206.2, 150x150 batch 2 215.2 -> 206.4, 193x161 batch 3 253.9 -> 243.6, 100x100 batch 7 248.7 -> 239.2).
+    std::vector<int> tail_into(n_ops, -1);
+    if (ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0 && !m.winograd) {
+        std::vector<int> uses(n_ops, 0), in_readers(n_ops, 0);
+        bool has_concat = false;
+        for (int i = 0; i < n_ops; ++i) {
+            has_concat |= m.ops[i].op == CW_OP_CONCAT;   // whose members may be channel ranges of wider tensors
+            if (m.ops[i].input_from >= 0) { ++uses[m.ops[i].input_from]; ++in_readers[m.ops[i].input_from]; }
+            if (m.ops[i].op == CW_OP_CONV && m.ops[i].residual_from >= 0) ++uses[m.ops[i].residual_from];
+        }
+        auto plain = [&](int i, int k, int cin, int cout) {
+            const cw_op &o = m.ops[i];
+            return o.op == CW_OP_CONV && o.groups <= 1 && o.kh == k && o.kw == k && o.stride == 1 && o.pad == k / 2 && o.cin == cin && o.cout == cout && o.input_from >= 0 &&
+                   fuse_into[i] < 0 && fused_first[i] < 0 && in_third[i] < 0 && in_pool[i] < 0 && pw_into[i] < 0;
+        };
+        for (int i = 1; !has_concat && i + 1 < n_ops; ++i) {
+            if (!plain(i, 3, 64, 64) || m.ops[i].residual_from >= 0 || uses[i] != 1) continue;
+            const OpShape &sh = m.shapes[i];
+            if (!tail_shape_ok((int64_t)batch * sh.h * sh.w, sh.h, sh.w)) continue;
+            int j = -1;
+            for (int t = i + 1; t <= i + 2 && t < n_ops; ++t)
+                if (m.ops[t].op == CW_OP_CONV && m.ops[t].input_from == i) j = t;
+            if (j < 0 || !plain(j, 1, 64, 256) || m.ops[j].residual_from < 0 || m.ops[j].residual_from == i) continue;
+            tail_into[i] = j;
+            const int k = j + 1;
+            if (k < n_ops && plain(k, 1, 256, 64) && m.ops[k].input_from == j && m.ops[k].residual_from < 0 && in_readers[j] == 1) tail_into[j] = k;
+        }
+    }
     // Order in which the ops are planned and launched: op order, except that a convolution j which
     // reads the same tensor as an earlier convolution i and depends on nothing after i (a ResNet
     // block's projection shortcut, i = the block's first 1x1) moves to right behind i, where the two
@@ -678,8 +709,9 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     // Time (position in `order`) of the last read of every op's output.  An op computed inside a
     // fused launch reads its inputs when that launch runs.
     std::vector<int> last_use(n_ops, -1);
+    auto tail_end = [&](int i) { while (tail_into[i] >= 0) i = tail_into[i]; return i; };
     for (int i = 0; i < n_ops; ++i) {
-        const int at = pos[fuse_into[i] >= 0 ? fuse_into[i] : (in_third[i] >= 0 ? in_third[i] : (in_pool[i] >= 0 ? in_pool[i] : (dw_into[i] >= 0 ? dw_into[i] : (pw_into[i] >= 0 ? pw_into[i] : i))))];
+        const int at = pos[fuse_into[i] >= 0 ? fuse_into[i] : (in_third[i] >= 0 ? in_third[i] : (in_pool[i] >= 0 ? in_pool[i] : (dw_into[i] >= 0 ? dw_into[i] : (pw_into[i] >= 0 ? pw_into[i] : tail_end(i)))))];
         if (m.ops[i].input_from >= 0) last_use[m.ops[i].input_from] = std::max(last_use[m.ops[i].input_from], at);
         if ((m.ops[i].op == CW_OP_CONV || m.ops[i].op == CW_OP_CONCAT) && m.ops[i].residual_from >= 0)
             last_use[m.ops[i].residual_from] = std::max(last_use[m.ops[i].residual_from], at);
@@ -1401,10 +1433,28 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         ld.pw_x = lc.x; ld.pw_w = lc.w; ld.pw_bias = lc.bias; ld.pw_res = lc.res;
         if (pw_kept[lc.op_index]) ld.pw_y = lc.y;
     }
+    for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
+        auto alone = [&](const Launch &l) { return l.kind == K_CONV && l.pair_op < 0 && l.fused_bm <= 0 && !l.stem && !l.in_next && !l.in_tail && !l.dense_fused && l.tail == 0 && l.conv.nz <= 1; };
+        Launch &l1 = p.launches[i], &l2 = p.launches[i + 1];
+        if (tail_into[l1.op_index] < 0 || tail_into[l1.op_index] != l2.op_index || !alone(l1) || !alone(l2)) continue;
+        if (m.ops[l1.op_index].kh != 3 || conv_ldx(l1.conv) != 64 || conv_ldy(l2.conv) != 256) continue;
+        const bool third = i + 2 < p.launches.size() && tail_into[l2.op_index] >= 0 && tail_into[l2.op_index] == p.launches[i + 2].op_index && alone(p.launches[i + 2]) &&
+                           conv_ldy(p.launches[i + 2].conv) == 64;
+        Launch &lt = p.launches[i + (third ? 2 : 1)];
+        l1.in_tail = true;
+        lt.tail = third ? 3 : 2;
+        lt.pw = l1.conv;
+        lt.pw_x = l1.x; lt.pw_w = l1.w; lt.pw_bias = l1.bias;
+        if (third) {
+            l2.in_tail = true;
+            lt.conv0 = l2.conv;
+            lt.w2 = l2.w; lt.bias2 = l2.bias; lt.pw_res = l2.res; lt.pw_y = l2.y;
+        }
+    }
     // Weights are read ahead by the nearest of the four launches before the one that uses them which has CUs to spare.
     {
         auto host = [&](const Launch &l) {
-            if (l.kind != K_CONV || l.in_next || l.dense_fused || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
+            if (l.kind != K_CONV || l.in_next || l.in_tail || l.dense_fused || l.tail > 0 || l.stem || l.fused_bm > 0 || l.pair_op >= 0 || l.conv.nz > 1 || l.conv.split_k != 1) return false;
             if (!conv_uses_dlds(l.conv, false) || l.ahead_bytes > 0) return false;
             const TileDim d = conv_tile_dim(l.tile);
             return (int64_t)((l.conv.M + d.bm - 1) / d.bm) * ((l.conv.Cout + d.bn - 1) / d.bn) * d.parts() <= kPrefetchMaxTiles;

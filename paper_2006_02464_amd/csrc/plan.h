@@ -70,6 +70,10 @@ struct Launch {
     // A 1x1 convolution (in_next) that the launch of the convolution behind it computes: a depthwise one (pw_fused) or the 3x3 of a densely
     // connected layer (dense_fused).  pw = its arguments, pw_x ... pw_y its tensors; pw_y is none where no other op reads it.
     bool in_next = false, pw_fused = false, dense_fused = false;
+    // The tail of a narrow bottleneck: the last of its two or three entries issues all (tail = their number), the others are in_tail.  pw, pw_x, pw_w and pw_bias are
+    // the 3x3's, and of three layers conv0, w2, bias2, pw_res and pw_y the second's.
+    int32_t tail = 0;
+    bool in_tail = false;
     PwDwTile pw_tile{};
     DenseTile dense_tile{};
     ConvArgs pw{};

@@ -490,6 +490,24 @@ def test_densely_connected_layer_in_one_launch(ctx):
         ctx.set_fusion(1)
 
 
+def test_tail_of_a_narrow_bottleneck_in_one_launch(ctx):
+    """ResNet-50's first stage at batch 1: 3x3, 1x1 and the next block's 1x1 share a launch, except for the last block, whose next 1x1 is as wide as it reads."""
+    m = ctx.model_define_resnet(50, 224, 224)
+    tail = lambda m, b: [ctx.plan_launch_tail(m, b, i) for i in range(ctx.plan_num_launches(m, b))]
+    assert [t for t in tail(m, 1) if t] == [1, 1, 3, 1, 1, 3, 1, 2] and not any(tail(m, 16))
+    for i, t in enumerate(tail(m, 1)):
+        if t > 1:
+            k = [ctx.plan_launch_info(m, 1, j)["gemm_k"] for j in range(i - t + 1, i + 1)]
+            assert k == [576, 64, 256][:t]
+    for on, off in ((lambda: ctx.set_fusion(0), lambda: ctx.set_fusion(1)), (lambda: ctx.set_debug_keep(True), lambda: ctx.set_debug_keep(False)),
+                    (lambda: ctx.set_plan_override(2, 0), lambda: ctx.set_plan_override(-1, 0))):
+        on()
+        try:
+            assert not any(tail(ctx.model_define_resnet(50, 224, 224), 1))
+        finally:
+            off()
+
+
 def test_weight_pages():
     """The weight pool is paged (paper section 5.1): page counts per model, the limits, the free count."""
     c = cw.Context(device=-1, weight_pool_bytes=1 << 30)          # default page: 16 MiB

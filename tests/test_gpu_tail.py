@@ -1,0 +1,54 @@
+"""The tail of a narrow bottleneck over few pixels, 3x3 64 -> 64, 1x1 to 256 with a residual and the next block's 1x1 back, in one launch, against the oracle and the
+launches apart."""
+import numpy as np
+import pytest
+
+from oracle import network as N
+from oracle import topology as T
+from workload import gen
+
+pytestmark = pytest.mark.gpu
+O = T.Op
+RELU, HSWISH = 1, 2
+
+
+def net(act1, act2, act3):
+    """stem -> 1x1 to 256 -> two bottlenecks (256 -> 64, 3x3, 64 -> 256 plus the block's input) -> head."""
+    ops = [O(T.CONV, 3, 32, 3, 3, 2, 1, RELU, -1, -1), O(T.CONV, 32, 256, 1, 1, 1, 0, RELU, -1, 0)]
+    last = 1
+    for _ in range(2):
+        ops += [O(T.CONV, 256, 64, 1, 1, 1, 0, act3, -1, last), O(T.CONV, 64, 64, 3, 3, 1, 1, act1, -1, last + 1), O(T.CONV, 64, 256, 1, 1, 1, 0, act2, last, last + 2)]
+        last += 3
+    return ops + [O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, last), O(T.FC, 256, 11, 1, 1, 1, 0, 0, -1, last + 1), O(T.SOFTMAX, 11, 11, 0, 0, 1, 0, 0, -1, last + 2)]
+
+
+# One and two groups of 16 pixels a workgroup at the edge between them and at the largest that is not the 64-pixel form's, tiles that end within an image or
+# a group, maps of a pixel, a row and a column, every activation
+@pytest.mark.parametrize("h,w,batch,act1,act2,act3,dtype", [
+    (56, 56, 1, RELU, RELU, RELU, "fp16"), (64, 64, 1, RELU, RELU, RELU, "bf16"), (4097, 1, 1, RELU, 0, RELU, "fp16"), (49, 41, 3, RELU, RELU, HSWISH, "bf16"),
+    (55, 55, 2, HSWISH, RELU, 0, "fp16"), (1, 1, 1, RELU, RELU, RELU, "fp16"), (1, 19, 3, 0, RELU, RELU, "fp16"), (37, 1, 2, RELU, HSWISH, RELU, "bf16"),
+    (3, 5, 7, RELU, RELU, RELU, "fp16"), (7, 9, 1, RELU, RELU, RELU, "bf16"), (13, 17, 16, RELU, RELU, RELU, "fp16"), (33, 31, 5, RELU, RELU, RELU, "fp16")])
+def test_tail_of_a_narrow_bottleneck_in_one_launch(h, w, batch, act1, act2, act3, dtype):
+    from paper_2006_02464_amd.runner import Worker
+    ops = net(act1, act2, act3)
+    wts, biases = gen.model_tensors(T.weight_shapes(ops), 9, dtype)
+    x = gen.images(9, 0, batch, 3, 2 * h, 2 * w, "uniform", dtype)
+    ref = N.forward(ops, wts, biases, x, prec="f32")["logits"]
+    wk = Worker(workspace_bytes=512 << 20, io_bytes=64 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        got = []
+        for on in (1, 0):
+            wk.ctx.set_fusion(on)
+            mid = wk.ctx.model_define(ops, 3, 2 * h, 2 * w, batch_sizes=(batch,), dtype=dtype)
+            tail = {l["op_index"]: wk.ctx.plan_launch_tail(mid, batch, i) for i, l in enumerate(wk.ctx.plan(mid, batch)) if l["kind"] == 1}
+            assert [tail[k] for k in range(2, 8)] == ([0, 1, 1, 3, 1, 2] if on else [0] * 6)
+            wk.load(mid, gen.pack_blob(wts, biases, dtype))
+            got.append(wk.infer(mid, x, classes=11)[1])
+        # seven roundings to the storage type on the way, each at most half a unit in the last place of a value
+        tol = 8 * (2.0 ** -11 if dtype == "fp16" else 2.0 ** -8)
+        for z in got:
+            assert np.abs(z - ref).max() <= tol * np.abs(ref).max()
+        assert np.abs(got[0] - got[1]).max() <= tol * np.abs(ref).max()
+    finally:
+        wk.ctx.set_fusion(1)
+        wk.close()
