@@ -277,6 +277,14 @@ hipError_t issue(cw_ctx *c, const ModelRt *m, const Bases &s, const Launch &l, h
                 a.w3 = resolve(c, m, s, l.w3);
                 a.bias3 = reinterpret_cast<const float *>(resolve(c, m, s, l.bias3));
                 a.y3 = resolve(c, m, s, l.y3);
+                if (l.walk) {
+                    TailArgs t{};
+                    t.M = a.M; t.H = a.H; t.W = a.W; t.act1 = a.relu; t.act2 = a.relu2; t.act3 = a.relu3;
+                    t.x = a.x; t.w1 = a.w; t.bias1 = a.bias; t.w2 = a.w2; t.bias2 = a.bias2; t.res = a.res; t.y = a.y;
+                    t.x2 = a.x2; t.wd = a.wd; t.biasd = a.biasd;
+                    t.w3 = a.w3; t.bias3 = a.bias3; t.y3 = a.y3;
+                    return launch_tail_walk(dt, t, st);
+                }
                 return launch_conv_fused(dt, l.fused_bm, l.fused_kg, a, st);
             }
             if (l.pair_op >= 0) {

@@ -400,10 +400,18 @@ struct TailArgs {
     void *y, *y3;
     int32_t M, H, W, act1, act2, act3;
     FastDiv w_div, h_div;   // filled in by the launcher
+    int32_t tiles;          // as these; launch_tail_walk
+    const void *x2, *wd;    // launch_tail_walk: a projection from 64 channels instead of the residual, or nullptr
+    const float *biasd;
 };
 bool tail_shape_ok(int64_t M, int32_t H, int32_t W);
 int tail_bm(int64_t M);   // pixels a workgroup
 hipError_t launch_tail(DType dt, const TailArgs &a, hipStream_t s);
+// The same for many pixels.
+constexpr int kTailWalkThreads = 512;
+bool tail_walk_ok(int64_t M, int32_t H, int32_t W);
+int tail_walk_bm(int64_t M);
+hipError_t launch_tail_walk(DType dt, const TailArgs &a, hipStream_t s);
 // A 1x1 stride-1 convolution (dense tensors) and the depthwise 3x3 pad-1 convolution over its result (its x is not read) in one launch;
 // keep: the 1x1's result is stored too.
 struct PwDwTile { int waves, pf, nf, rows; };   // pf x 16 pixels a wave, nf x 16 channels and `rows` rows of the depthwise result a workgroup

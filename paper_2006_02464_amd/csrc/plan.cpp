@@ -774,6 +774,16 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         return pool_fc_items(batch, m.ops[i].cin, (int64_t)map.h * map.w) > 0;
     };
 
+    // Whether a fused launch of ops f and i is that of the narrow bottleneck.  From four tiles of 32 pixels a workgroup on memory bounds both forms: 25088 pixels, two
+    // layers 11.2 us in either, three 13.0 and 13.2; with the projection, which the other form walks through one buffer, 12.9 and 14.2, and at 50176 pixels 19.2 and 20.8
+    // by itself, but whole EXECs of ResNet-152 are no faster.
+    auto walks = [&](int f, int i) {
+        const cw_op &o1 = m.ops[f];
+        const int64_t M = (int64_t)batch * m.shapes[f].h * m.shapes[f].w;
+        return ov.fuse == 1 && o1.kh == 3 && o1.kw == 3 && o1.stride == 1 && o1.pad == 1 && o1.cin == 64 && o1.cout == 64 && m.ops[i].cout == 256 &&
+               tail_walk_ok(M, m.shapes[f].h, m.shapes[f].w) && tail_walk_bm(M) <= (proj_of[i] >= 0 ? 4 : 3) * 32;
+    };
+
     // Where op i's output goes: a region of its own, or its channel range of the CONCAT tensor
     // that hosts it (allocated when its first member is planned).
     auto place_output = [&](int i, size_t dense_bytes) {
@@ -846,6 +856,8 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                     l.op_index = i;
                     l.fused_bm = fused_bm[i];
                     l.fused_kg = fused_kg[i];
+                    l.walk = walks(f, i);
+                    if (l.walk) l.fused_bm = tail_walk_bm((int64_t)batch * s1.h * s1.w);
                     ConvArgs &a = l.conv;
                     a.B = batch; a.H = sin.h; a.W = sin.w; a.Cin = o1.cin; a.Ho = s1.h; a.Wo = s1.w; a.Cout = o1.cout;
                     a.kh = o1.kh; a.kw = o1.kw; a.kwp = o1.kw; a.khp = o1.kh; a.stride = o1.stride;
@@ -1479,7 +1491,10 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         int b = 0;
         switch (l.kind) {
             case K_CONV:
-                if (l.fused_bm > 0) conv_fused_grid(l.fused_bm, l.fused_kg, l.conv, &g, &b);
+                if (l.fused_bm > 0) {
+                    conv_fused_grid(l.fused_bm, l.fused_kg, l.conv, &g, &b);
+                    if (l.walk) b = kTailWalkThreads;
+                }
                 else if (l.pair_op >= 0) conv_pair_grid(l.tile, l.conv0, l.conv, &g, &b);
                 else conv_grid(l.tile, l.conv, &g, &b);
                 break;

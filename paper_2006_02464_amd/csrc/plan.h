@@ -29,6 +29,7 @@ struct Launch {
     bool tile_fixed = false;  // its tile comes from the installed table or was forced
     int32_t fused_bm = 0;  // > 0: this convolution and the 1x1 one after it in one launch (pixels per workgroup)
     int32_t fused_kg = 1;  // wave groups of that launch (1 or 2)
+    bool walk = false;     // that launch is launch_tail_walk's
     // Shape fields are final; pointer fields are filled from the Refs at EXEC time.
     ConvArgs conv{};
     CastArgs cast{};

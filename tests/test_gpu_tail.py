@@ -52,3 +52,47 @@ def test_tail_of_a_narrow_bottleneck_in_one_launch(h, w, batch, act1, act2, act3
     finally:
         wk.ctx.set_fusion(1)
         wk.close()
+
+
+def net_with_projection(act1, act3):
+    """stem -> 1x1 to 64 -> a block whose shortcut is a 1x1 64 -> 256 -> a block with its input as the shortcut -> head."""
+    ops = [O(T.CONV, 3, 32, 3, 3, 2, 1, RELU, -1, -1), O(T.CONV, 32, 64, 1, 1, 1, 0, RELU, -1, 0),
+           O(T.CONV, 64, 64, 1, 1, 1, 0, RELU, -1, 1), O(T.CONV, 64, 64, 3, 3, 1, 1, act1, -1, 2), O(T.CONV, 64, 256, 1, 1, 1, 0, 0, -1, 1), O(T.CONV, 64, 256, 1, 1, 1, 0, RELU, 4, 3),
+           O(T.CONV, 256, 64, 1, 1, 1, 0, act3, -1, 5), O(T.CONV, 64, 64, 3, 3, 1, 1, RELU, -1, 6), O(T.CONV, 64, 256, 1, 1, 1, 0, RELU, 5, 7)]
+    return ops + [O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 8), O(T.FC, 256, 11, 1, 1, 1, 0, 0, -1, 9), O(T.SOFTMAX, 11, 11, 0, 0, 1, 0, 0, -1, 10)]
+
+
+# One to four tiles of 32 pixels a workgroup (and more, for the other fused form), the last workgroup with all of them, some, and one of a single pixel; maps of a row and a column
+@pytest.mark.parametrize("h,w,batch,act1,act3,third,dtype", [
+    (79, 77, 1, RELU, RELU, 1, "fp16"), (64, 64, 2, RELU, 0, 1, "bf16"), (8193, 1, 1, RELU, RELU, 1, "fp16"), (1, 6145, 2, 0, RELU, 0, "fp16"), (128, 129, 1, RELU, RELU, 1, "bf16"),
+    (56, 56, 16, RELU, RELU, 1, "fp16"), (56, 56, 4, 0, 0, 0, "bf16"), (97, 97, 3, RELU, RELU, 1, "fp16"), (90, 91, 4, RELU, 0, 0, "bf16"), (113, 97, 6, RELU, RELU, 1, "fp16"), (41, 49, 13, RELU, RELU, 1, "bf16")])
+def test_tail_of_a_narrow_bottleneck_walks_many_pixels(h, w, batch, act1, act3, third, dtype):
+    from paper_2006_02464_amd.runner import Worker
+    ops = net_with_projection(act1, act3)
+    wts, biases = gen.model_tensors(T.weight_shapes(ops), 9, dtype)
+    x = gen.images(9, 0, batch, 3, 2 * h, 2 * w, "uniform", dtype)
+    ref = N.forward(ops, wts, biases, x, prec="f32")["logits"]
+    wk = Worker(workspace_bytes=512 << 20, io_bytes=128 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        wk.ctx.set_fusion_third(third)
+        got = []
+        for on in (1, 0):
+            wk.ctx.set_fusion(on)
+            mid = wk.ctx.model_define(ops, 3, 2 * h, 2 * w, batch_sizes=(batch,), dtype=dtype)
+            fused = [l for l in wk.ctx.plan(mid, batch) if l["fused_op"] >= 0 and l["kind"] == 1]
+            assert [(l["op_index"], l["proj_op"], l["next_op"]) for l in fused] == ([(5, 4, 6 if third else -1), (8, -1, -1)] if on else [])
+            tiles = -(-h * w * batch // (32 * 256))
+            walk = [l for l in fused if l["tile_m"] == 32 * tiles and l["block"] == 512]
+            assert len(walk) == (on and (tiles <= 4) + (tiles <= 3)) and all(l["proj_op"] == 4 for l in walk[:1])   # with the projection up to four tiles
+            assert all(l["grid_x"] <= 256 for l in walk)
+            wk.load(mid, gen.pack_blob(wts, biases, dtype))
+            got.append(wk.infer(mid, x, classes=11)[1])
+        # nine roundings to the storage type on the way, each at most half a unit in the last place of a value
+        tol = 8 * (2.0 ** -11 if dtype == "fp16" else 2.0 ** -8)
+        for z in got:
+            assert np.abs(z - ref).max() <= tol * np.abs(ref).max()
+        assert np.abs(got[0] - got[1]).max() <= tol * np.abs(ref).max()
+    finally:
+        wk.ctx.set_fusion(1)
+        wk.ctx.set_fusion_third(1)
+        wk.close()
