@@ -912,6 +912,14 @@ int32_t cw_model_define(cw_ctx *c, const cw_op *ops, int32_t n_ops, int32_t in_c
         Plan p;
         rc = plan_build(m->m, batch_sizes[i], c->ov, &p, &err);
         if (rc != CW_OK) return set_err(c, rc, err);
+        // A launch that computes several entries keeps the first one's input until the last: where only that is too much, they stay apart.
+        auto fits = [&](size_t bytes) { return (bytes <= c->cfg.workspace_bytes || c->device < 0) + (bytes <= kStaticScratchBytes); };
+        if (fits(p.workspace_bytes) < 2) {
+            PlanOverride apart = c->ov;
+            apart.join = false;
+            Plan q;
+            if (plan_build(m->m, batch_sizes[i], apart, &q, &err) == CW_OK && fits(q.workspace_bytes) > fits(p.workspace_bytes)) p = std::move(q);
+        }
         if (p.workspace_bytes > c->cfg.workspace_bytes && c->device >= 0)
             return set_err(c, CW_ERR_NO_MEMORY, "plan needs more workspace than the context has");
         m->m.plans.push_back(std::move(p));

@@ -575,7 +575,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     std::vector<int> pw_into(n_ops, -1);
     std::vector<char> pw_kept(n_ops, 0);
     std::vector<PwDwTile> pw_tile(n_ops);
-    if (ov.fuse && ov.fuse_dw && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
+    if (ov.join && ov.fuse && ov.fuse_dw && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
         bool has_concat = false;
         std::vector<int> uses(n_ops, 0);
         for (int i = 0; i < n_ops; ++i) {
@@ -610,7 +610,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     }
     // A densely connected layer: a 1x1 convolution to 128 channels and the 3x3 to 32 right behind it, its only reader.  Entries as above.
     std::vector<DenseTile> dense_tile(n_ops);
-    if (ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
+    if (ov.join && ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
         std::vector<int> uses(n_ops, 0);
         for (int i = 0; i < n_ops; ++i) {
             if (m.ops[i].input_from >= 0) ++uses[m.ops[i].input_from];
@@ -649,7 +649,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     // Always: it is faster from a few dozen pixels on (whole EXECs by graph replay, apart and as decided here, ResNet-50 64x64 batch 1 186.8 -> 178.6 us, 130x97 200.1 -> 189.8,
     // 224x224 216.9 -> 206.2, 150x150 batch 2 215.2 -> 206.4, 193x161 batch 3 253.9 -> 243.6, 100x100 batch 7 248.7 -> 239.2).
     std::vector<int> tail_into(n_ops, -1);
-    if (ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0 && !m.winograd) {
+    if (ov.join && ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0 && !m.winograd) {
         std::vector<int> uses(n_ops, 0), in_readers(n_ops, 0);
         bool has_concat = false;
         for (int i = 0; i < n_ops; ++i) {

@@ -125,6 +125,7 @@ struct PlanOverride {
     int32_t tile = -1;     // ConvTile or -1 = automatic
     int32_t split_k = 0;   // 0 = automatic
     bool keep_all = false; // no workspace reuse (debug read-back)
+    bool join = true;      // launches that compute convolutions of earlier entries, whose inputs then live longer
     int32_t fuse = 1;      // two-layer launches: 0 = none, 1 = yes, 2 = yes but never with two wave groups
     bool pair = true;      // two convolutions over one tensor as one launch
     bool winograd = false; // 3x3 stride-1 pad-1 convolutions through Winograd F(2x2, 3x3)

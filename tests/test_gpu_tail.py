@@ -96,3 +96,21 @@ def test_tail_of_a_narrow_bottleneck_walks_many_pixels(h, w, batch, act1, act3, 
         wk.ctx.set_fusion(1)
         wk.ctx.set_fusion_third(1)
         wk.close()
+
+
+def test_layers_stay_apart_where_the_workspace_has_no_room_for_their_joint_launch():
+    """The launch keeps the 3x3's input until its last layer is done; a workspace that only has what the launches apart need gets those."""
+    import paper_2006_02464_amd as cw
+    ops = net(RELU, RELU, RELU)
+    tails = lambda c, m: [c.plan_launch_tail(m, 3, i) for i in range(c.plan_num_launches(m, 3))]
+    sizes = dict(io_bytes=16 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=16 << 20)
+    need = []
+    for room in (64 << 20, None, None):
+        c = cw.Context(workspace_bytes=room or need[-1] - (len(need) - 1) * 256, **sizes)
+        try:
+            m = c.model_define(ops, 3, 80, 72, batch_sizes=(3,))
+            assert any(tails(c, m)) == (len(need) < 2)
+            need.append(c.model_workspace_bytes(m, 3))
+        finally:
+            c.destroy()
+    assert need[0] == need[1] > need[2]
