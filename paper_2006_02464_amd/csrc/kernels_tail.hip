@@ -6,7 +6,8 @@
 // - A wave has 16 of the 64 channels of the first and the third layer and 64 of the 256, and fetches their weights itself: only pixels and what a layer
 //   hands to the next pass a barrier.
 // - With 32 pixels the third layer's weights come into the place of the wave's own of the first, once it has read them.
-// Back to back, 56x56 at batch 1 and 49x41 at batch 3 (3136 and 6027 pixels): three layers 9.3 -> 5.7 us and 10.7 -> 7.0, two layers 6.6 -> 4.6 and 7.5 -> 6.1. The 64-pixel form of the
+// Back to back, 56x56 at batch 1 and 49x41 at batch 3 (3136 and 6027 pixels): three layers 9.3 -> 5.0 us and 10.7 -> 6.2, two layers 6.6 -> 4.3 and 7.5 -> 5.7 (with LDS
+// reads left to the compiler and a branch per activation 5.6, 7.0, 4.6 and 6.2). The 64-pixel form of the
 // convolution kernel, which walks the layers in chunks with two barriers each, takes 10.0 and 8.6 at 6272 pixels.
 #include "conv_dlds_body.h"
 
@@ -22,6 +23,22 @@ struct TailLds {
     static constexpr unsigned BIAS = P + 16 * F * P_PITCH, BYTES = BIAS + 3 * 1024;
     static_assert(16 * F * Q_PITCH <= F * 18432 && BYTES <= 160 * 1024, "");
 };
+
+// Without a branch: with one around every four values a tile was a chain of small blocks.
+template <typename T>
+static __device__ __forceinline__ u32x2 relu_or_none(const float (&v)[4], int act) {
+    T o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (T)(act ? fmaxf(v[e], 0.f) : v[e]);
+    return *reinterpret_cast<const u32x2 *>(o);
+}
+
+// The same for every activation, one branch around all of `body`, which gets the activation.
+template <typename T, typename F>
+static __device__ __forceinline__ void with_activation(int act, F body) {
+    if (act == ACT_HSWISH) body([](const float (&v)[4]) { return activate<T>(v, ACT_HSWISH); });
+    else body([act](const float (&v)[4]) { return relu_or_none<T>(v, act); });
+}
 
 template <typename T, int F, bool THIRD>
 __global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
@@ -106,19 +123,20 @@ __global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
         for (int k = 0; k < 2; ++k) acc[f][k] = typename MF::acc{0.f, 0.f, 0.f, 0.f};
     const unsigned key = (lrow >> 1) & 7, rd = (unsigned)lrow * 128u;
     const unsigned ck[2] = {((unsigned)lhalf ^ key) << 4, ((unsigned)(4 + lhalf) ^ key) << 4};
-    auto row = [&](int r) {
+    auto row = [&](int r) {   // all reads, then the products: left to the compiler two or three are in flight
+        v8 fw[6], fx[6][F];
 #pragma unroll
-        for (int s = 0; s < 3; ++s)
+        for (int q = 0; q < 6; ++q) {
+            const int tap = r * 3 + (q >> 1);
+            fw[q] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W1 + (unsigned)wave * 18432u + tap * 2048u + rd + ck[q & 1]);
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int tap = r * 3 + s;
-                const v8 fw = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W1 + (unsigned)wave * 18432u + tap * 2048u + rd + ck[k]);
+            for (int f = 0; f < F; ++f) fx[q][f] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::XS + (unsigned)(tap * F + f) * 2048u + rd + ck[q & 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    const v8 fx = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::XS + (unsigned)(tap * F + f) * 2048u + rd + ck[k]);
-                    acc[f][k] = MF::mma(fw, fx, acc[f][k]);
-                }
-            }
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int f = 0; f < F; ++f) acc[f][q & 1] = MF::mma(fw[q], fx[q][f], acc[f][q & 1]);
     };
     // (16 pixels: waves 0 and 1 have one load of pixels a filter row more)
     if (F == 2) wait_lds_loads_and_barrier<AFTER + 2 * 9>();
@@ -132,16 +150,16 @@ __global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
     wait_lds_loads_and_barrier<AFTER - 1>();   // the biases too
     row(2);
     // first layer's result: 4 channels of a pixel, rounded as when it is stored
-    {
+    with_activation<T>(a.act1, [&](auto activation) {
         const typename MF::acc b = *reinterpret_cast<const typename MF::acc *>(cw_dyn_lds + L::BIAS + (wave * 16 + nl) * 4u);
 #pragma unroll
         for (int f = 0; f < F; ++f) {
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = acc[f][0][e] + acc[f][1][e] + b[e];
-            *reinterpret_cast<u32x2 *>(cw_dyn_lds + L::P + (unsigned)(f * 16 + lrow) * L::P_PITCH + (wave * 16 + nl) * 2u) = activate<T>(v, a.act1);
+            *reinterpret_cast<u32x2 *>(cw_dyn_lds + L::P + (unsigned)(f * 16 + lrow) * L::P_PITCH + (wave * 16 + nl) * 2u) = activation(v);
         }
-    }
+    });
     if (THIRD && F == 2) {
         // this wave's reads of its first weights have returned (their products are in the sums just stored)
         asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
@@ -155,29 +173,35 @@ __global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
 #pragma unroll
             for (int k = 0; k < 2; ++k) fp[f][k] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::P + (unsigned)(f * 16 + lrow) * L::P_PITCH + (unsigned)(k * 4 + lhalf) * 16u);
         typename MF::acc s[F][4], b[4];
+        v8 fw[4][2];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            b[j] = *reinterpret_cast<const typename MF::acc *>(cw_dyn_lds + L::BIAS + 1024u + (wave * 64 + j * 16 + nl) * 4u);
-            v8 fw[2];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) fw[k] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W2 + (unsigned)wave * 8192u + j * 2048u + rd + ck[k]);
-#pragma unroll
-            for (int f = 0; f < F; ++f) s[f][j] = MF::mma(fw[0], fp[f][0], typename MF::acc{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-            for (int f = 0; f < F; ++f) s[f][j] = MF::mma(fw[1], fp[f][1], s[f][j]);
+            for (int k = 0; k < 2; ++k) fw[j][k] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W2 + (unsigned)wave * 8192u + j * 2048u + rd + ck[k]);
         }
 #pragma unroll
-        for (int f = 0; f < F; ++f)
+        for (int j = 0; j < 4; ++j) b[j] = *reinterpret_cast<const typename MF::acc *>(cw_dyn_lds + L::BIAS + 1024u + (wave * 64 + j * 16 + nl) * 4u);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const T *r = reinterpret_cast<const T *>(&res[f][j]);
-                float v[4];
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = s[f][j][e] + b[j][e] + (float)r[e];
-                const u32x2 o = activate<T>(v, a.act2);
-                __builtin_amdgcn_raw_buffer_store_b64(o, ry, y_off[f], j * 32, 0);
-                if (THIRD) *reinterpret_cast<u32x2 *>(cw_dyn_lds + L::Q + (unsigned)(f * 16 + lrow) * L::Q_PITCH + (unsigned)(wave * 64 + j * 16 + nl) * 2u) = o;
-            }
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int f = 0; f < F; ++f) s[f][j] = MF::mma(fw[j][k], fp[f][k], k == 0 ? typename MF::acc{0.f, 0.f, 0.f, 0.f} : s[f][j]);
+        with_activation<T>(a.act2, [&](auto activation) {
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const T *r = reinterpret_cast<const T *>(&res[f][j]);
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = s[f][j][e] + b[j][e] + (float)r[e];
+                    const u32x2 o = activation(v);
+                    __builtin_amdgcn_raw_buffer_store_b64(o, ry, y_off[f], j * 32, 0);
+                    if (THIRD) *reinterpret_cast<u32x2 *>(cw_dyn_lds + L::Q + (unsigned)(f * 16 + lrow) * L::Q_PITCH + (unsigned)(wave * 64 + j * 16 + nl) * 2u) = o;
+                }
+        });
     }
     if constexpr (THIRD) {
         wait_lds_loads_and_barrier<4 * F>();   // older than the stores are the third layer's weights; everyone's part of the second's result
@@ -187,23 +211,28 @@ __global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
         for (int f = 0; f < F; ++f)
 #pragma unroll
             for (int k = 0; k < 2; ++k) s[f][k] = typename MF::acc{0.f, 0.f, 0.f, 0.f};
+        v8 fw[8], fq[8][F];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const v8 fw = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W3 + (unsigned)wave * (F == 1 ? 8192u : 18432u) + (k >> 1) * 2048u + rd + ck[k & 1]);
+            fw[k] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::W3 + (unsigned)wave * (F == 1 ? 8192u : 18432u) + (k >> 1) * 2048u + rd + ck[k & 1]);
+#pragma unroll
+            for (int f = 0; f < F; ++f) fq[k][f] = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::Q + (unsigned)(f * 16 + lrow) * L::Q_PITCH + (unsigned)(k * 4 + lhalf) * 16u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int f = 0; f < F; ++f) s[f][k & 1] = MF::mma(fw[k], fq[k][f], s[f][k & 1]);
+        with_activation<T>(a.act3, [&](auto activation) {
 #pragma unroll
             for (int f = 0; f < F; ++f) {
-                const v8 fq = *reinterpret_cast<const v8 *>(cw_dyn_lds + L::Q + (unsigned)(f * 16 + lrow) * L::Q_PITCH + (unsigned)(k * 4 + lhalf) * 16u);
-                s[f][k & 1] = MF::mma(fw, fq, s[f][k & 1]);
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = s[f][0][e] + s[f][1][e] + b[e];
+                const int m = m0 + f * 16 + lrow;
+                if (m < a.M) *reinterpret_cast<u32x2 *>(static_cast<char *>(a.y3) + (size_t)m * (kTailC * 2) + (wave * 16 + nl) * 2u) = activation(v);
             }
-        }
-#pragma unroll
-        for (int f = 0; f < F; ++f) {
-            float v[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = s[f][0][e] + s[f][1][e] + b[e];
-            const int m = m0 + f * 16 + lrow;
-            if (m < a.M) *reinterpret_cast<u32x2 *>(static_cast<char *>(a.y3) + (size_t)m * (kTailC * 2) + (wave * 16 + nl) * 2u) = activate<T>(v, a.act3);
-        }
+        });
     }
 }
 
@@ -214,15 +243,6 @@ __global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
 // the chip, where a large copy reaches 4.7.  One wave a SIMD instead of two 2.6 us a tile, with the reads of LDS left to the compiler 3.6.
 // Against the convolution kernel's fused form, back to back, with projection and third layer / with the third / alone: 6272 pixels 10.5 -> 6.2 us / 9.9 -> 6.2 / 8.6 -> 5.4,
 // 12544 11.0 -> 8.5 / 10.4 -> 8.5 / 9.0 -> 7.3, 25088 14.2 -> 12.9 / 13.2 -> 13.0 / 11.2 -> 11.2, 50176 in bf16 20.8 -> 19.2 / 19.4 -> 19.5 / 16.5 -> 17.0.
-
-// Without a branch: with one around every four values a tile was a chain of small blocks.
-template <typename T>
-static __device__ __forceinline__ u32x2 relu_or_none(const float (&v)[4], int act) {
-    T o[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = (T)(act ? fmaxf(v[e], 0.f) : v[e]);
-    return *reinterpret_cast<const u32x2 *>(o);
-}
 
 template <bool PROJ>
 struct WalkLds {
