@@ -117,6 +117,7 @@ SIGNATURES = {
     "cw_set_resident": (c_int32, [c_void_p, c_int32]),
     "cw_set_use_graphs": (c_int32, [c_void_p, c_int32]),
     "cw_set_wait_launches": (c_int32, [c_void_p, c_int32]),
+    "cw_output_by_launch": (c_int32, [c_void_p, c_void_p, c_size_t]),
     "cw_strerror": (c_char_p, [c_int32]),
     "cw_last_error": (c_char_p, [c_void_p]),
 }
@@ -364,6 +365,10 @@ class Context:
 
     def set_wait_launches(self, us=-1):
         self._check(lib().cw_set_wait_launches(self._h, int(us)))
+
+    def output_by_launch(self, host, nbytes):
+        """Whether OUTPUT writes `nbytes` at the address `host` by a launch, not by a copy of the runtime."""
+        return bool(self._check(lib().cw_output_by_launch(self._h, host, nbytes)))
 
     def set_plan_override(self, conv_tile=-1, split_k=0):
         if isinstance(conv_tile, str):

@@ -166,17 +166,21 @@ int32_t hip_fail(cw_ctx *c, hipError_t e, const char *what) {
         if (e__ != hipSuccess) return hip_fail(ctx, e__, #call); \
     } while (0)
 
-// The device's address of `bytes` of pinned host memory from `host` on, or nullptr: not pinned, not aligned to 16 bytes.
+// The device's address of `bytes` of pinned host memory from `host` on, or nullptr: not pinned, not all in one allocation (where the device's
+// addresses are the host's, first and last byte may lie in two with unmapped pages between), not aligned to 16 bytes.
 char *device_view(const void *host, size_t bytes) {
-    hipPointerAttribute_t a{}, z{};
+    hipPointerAttribute_t a{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
     if (reinterpret_cast<uintptr_t>(host) % 16 != 0 || bytes == 0) return nullptr;
-    if (hipPointerGetAttributes(&a, host) != hipSuccess || hipPointerGetAttributes(&z, static_cast<const char *>(host) + bytes - 1) != hipSuccess) {
+    if (hipPointerGetAttributes(&a, host) != hipSuccess || a.type != hipMemoryTypeHost || !a.devicePointer ||
+        hipMemGetAddressRange(&base, &size, static_cast<hipDeviceptr_t>(a.devicePointer)) != hipSuccess) {
         (void)hipGetLastError();   // memory that the runtime does not know is no error here
         return nullptr;
     }
-    char *first = static_cast<char *>(a.devicePointer), *last = static_cast<char *>(z.devicePointer);
-    if (a.type != hipMemoryTypeHost || z.type != hipMemoryTypeHost || !first || last != first + (bytes - 1) || reinterpret_cast<uintptr_t>(first) % 16 != 0) return nullptr;
-    return first;
+    const uintptr_t first = reinterpret_cast<uintptr_t>(a.devicePointer), from = reinterpret_cast<uintptr_t>(base);
+    if (first % 16 != 0 || first < from || first - from > size || bytes > size - (first - from)) return nullptr;
+    return static_cast<char *>(a.devicePointer);
 }
 
 struct DeviceGuard {
@@ -1315,6 +1319,13 @@ int32_t cw_output(cw_ctx *c, int32_t slot, float *host_probs, float *host_logits
     CW_HIP(c, hipEventRecord(s.released, st));
     free_slot(c, &s, true);
     return CW_OK;
+}
+
+int32_t cw_output_by_launch(cw_ctx *c, const void *host, size_t bytes) {
+    if (!c) return CW_ERR_INVALID;
+    if (c->device < 0) return set_err(c, CW_ERR_INVALID, "planning-only context has no device");
+    DeviceGuard g(c->device);
+    return device_view(host, bytes) != nullptr;
 }
 
 int32_t cw_release(cw_ctx *c, int32_t slot) {

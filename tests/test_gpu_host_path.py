@@ -154,3 +154,22 @@ def test_results_in_any_host_memory(batch, classes):
             assert np.array_equal(got[0], got[-1 if logits_at is None else -2])
     finally:
         wk.close()
+
+
+def test_output_by_launch_only_within_one_allocation():
+    """Two ends in pinned memory do not make a result of what lies between them."""
+    import paper_2006_02464_amd as cw
+    c = cw.Context(workspace_bytes=64 << 20, io_bytes=16 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        size = 1 << 20
+        pinned = [torch.empty(size, dtype=torch.uint8, pin_memory=True) for _ in range(3)]
+        pageable = torch.empty(size + 16, dtype=torch.uint8)
+        at = sorted(t.data_ptr() for t in pinned)
+        for a in at:
+            assert c.output_by_launch(a, size) and c.output_by_launch(a + size - 16, 16) and c.output_by_launch(a + 16, 4)
+            assert not c.output_by_launch(a + size - 16, 20 + size) and not c.output_by_launch(a + 4, 16) and not c.output_by_launch(a, 0)
+        for a, b in zip(at, at[1:]):
+            assert not c.output_by_launch(a, b - a + size) and not c.output_by_launch(a + size - 16, b - a - size + 32)
+        assert not c.output_by_launch((pageable.data_ptr() + 15) & ~15, 16)
+    finally:
+        c.destroy()
