@@ -92,8 +92,8 @@ int32_t cw_set_use_graphs(cw_ctx *ctx, int32_t on);
  * wave gives up after `us` microseconds, at most 1000000; 0: no such wave, < 0 restores the default of 50000.  The stream waits
  * for the EXEC either way. */
 int32_t cw_set_wait_launches(cw_ctx *ctx, int32_t us);
-/* 1 where OUTPUT writes a result of `bytes` at `host` by a launch of its own: pinned memory of one allocation, 16-byte aligned; 0 where it is
- * left to a copy of the runtime.  Touches no memory.  Negative on error. */
+/* 1 where OUTPUT writes a result of `bytes` at `host` by a launch of its own: pinned memory of one allocation, 16-byte aligned, below 2 GiB; 0
+ * where it is left to a copy of the runtime.  Touches no memory.  Negative on error. */
 int32_t cw_output_by_launch(cw_ctx *ctx, const void *host, size_t bytes);
 /* Test hook: models defined afterwards use conv tile variant `conv_tile` (0..40 =
  * 128x128, 128x64, 64x64, 64x32, 32x64, 32x32, 128x64 on 2 waves, 64x128 on 2 waves,

@@ -167,12 +167,13 @@ int32_t hip_fail(cw_ctx *c, hipError_t e, const char *what) {
     } while (0)
 
 // The device's address of `bytes` of pinned host memory from `host` on, or nullptr: not pinned, not all in one allocation (where the device's
-// addresses are the host's, first and last byte may lie in two with unmapped pages between), not aligned to 16 bytes.
+// addresses are the host's, first and last byte may lie in two with unmapped pages between), not aligned to 16 bytes, more than copy_out_kernel's
+// 32-bit offsets reach.
 char *device_view(const void *host, size_t bytes) {
     hipPointerAttribute_t a{};
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
-    if (reinterpret_cast<uintptr_t>(host) % 16 != 0 || bytes == 0) return nullptr;
+    if (reinterpret_cast<uintptr_t>(host) % 16 != 0 || bytes == 0 || bytes >= (1ull << 31)) return nullptr;
     if (hipPointerGetAttributes(&a, host) != hipSuccess || a.type != hipMemoryTypeHost || !a.devicePointer ||
         hipMemGetAddressRange(&base, &size, static_cast<hipDeviceptr_t>(a.devicePointer)) != hipSuccess) {
         (void)hipGetLastError();   // memory that the runtime does not know is no error here

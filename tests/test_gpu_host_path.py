@@ -173,3 +173,14 @@ def test_output_by_launch_only_within_one_allocation():
         assert not c.output_by_launch((pageable.data_ptr() + 15) & ~15, 16)
     finally:
         c.destroy()
+
+
+def test_results_of_2_gib_are_left_to_the_runtime():
+    """The launch's offsets end below 2 GiB; a larger result goes through the copy that takes any size."""
+    import paper_2006_02464_amd as cw
+    c = cw.Context(workspace_bytes=64 << 20, io_bytes=16 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        pinned = torch.empty(1 << 31, dtype=torch.uint8, pin_memory=True)
+        assert c.output_by_launch(pinned.data_ptr(), (1 << 31) - 16) and not c.output_by_launch(pinned.data_ptr(), 1 << 31)
+    finally:
+        c.destroy()
