@@ -1310,7 +1310,10 @@ int32_t cw_output(cw_ctx *c, int32_t slot, float *host_probs, float *host_logits
     const size_t out_b = (size_t)s.batch * m->m.classes * 4;
     wait_quietly(c, s, s.exec_end, st);
     CW_HIP(c, hipStreamWaitEvent(st, s.exec_end, 0));
-    char *probs = device_view(host_probs, out_b), *logits = probs && host_logits ? device_view(host_logits, out_b) : nullptr;
+    // The launch writes both at once: where they share bytes the logits stay, which only copies one behind the other see to.
+    const uintptr_t at_p = reinterpret_cast<uintptr_t>(host_probs), at_z = reinterpret_cast<uintptr_t>(host_logits);
+    const bool apart = !host_logits || (at_p > at_z ? at_p - at_z : at_z - at_p) >= out_b;
+    char *probs = apart ? device_view(host_probs, out_b) : nullptr, *logits = probs && host_logits ? device_view(host_logits, out_b) : nullptr;
     if (probs && (logits || !host_logits)) {
         CW_HIP(c, launch_copy_out(probs, c->io + s.probs_off, logits, c->io + s.logits_off, out_b, st));
     } else {

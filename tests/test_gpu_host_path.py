@@ -156,6 +156,29 @@ def test_results_in_any_host_memory(batch, classes):
         wk.close()
 
 
+@pytest.mark.parametrize("ahead", [0, 1000, 15 * 1000])   # of the 16 x 1000 probabilities the logits take all, all but a row, a row
+def test_results_that_share_pinned_memory(ahead):
+    """The logits are written behind the probabilities."""
+    from paper_2006_02464_amd.runner import Worker
+    case, batch = Case(T.resnet(18), 64, seed=6, dist="uniform"), 16
+    wk = Worker(workspace_bytes=256 << 20, io_bytes=16 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = wk.ctx.model_define(case.ops, 3, 64, 64, batch_sizes=(batch,))
+        wk.load(mid, case.blob)
+        x = torch.from_numpy(np.ascontiguousarray(case.images(0, batch), dtype=np.float32)).pin_memory()
+        probs, logits = (v.reshape(-1) for v in wk.infer(mid, x.numpy())[:2])
+        stream = torch.cuda.Stream()
+        for k in range(20):
+            both = torch.full((2 * batch * 1000,), -5.0, pin_memory=True)
+            slot = wk.ctx.input(mid, batch, x, stream)
+            wk.ctx.exec(mid, batch, slot, stream)
+            wk.ctx.output(slot, both, both[ahead:], stream)
+            stream.synchronize()
+            assert np.array_equal(both[:ahead].numpy(), probs[:ahead]) and np.array_equal(both[ahead:ahead + batch * 1000].numpy(), logits), k
+    finally:
+        wk.close()
+
+
 def test_output_by_launch_only_within_one_allocation():
     """Two ends in pinned memory do not make a result of what lies between them."""
     import paper_2006_02464_amd as cw
