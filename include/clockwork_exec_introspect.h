@@ -124,8 +124,8 @@ int32_t cw_set_plan_override(cw_ctx *ctx, int32_t conv_tile, int32_t split_k);
  * other values: CW_ERR_INVALID.  Under debug retention the first layer's tensor of such a launch is
  * the one tensor that cannot be read back (it is never stored). */
 int32_t cw_set_fusion(cw_ctx *ctx, int32_t on);
-/* A fused launch (see above) may also compute the 1x1 stride-1 convolution that reads its output:
- * the next bottleneck's reduce, whose input then never comes back from memory.  on == 0 plans that
+/* A fused launch (see above), or that of a narrow bottleneck's tail (cw_plan_launch_tail), may also compute the 1x1 stride-1
+ * convolution that reads its output: the next bottleneck's reduce, whose input then never comes back from memory.  on == 0 plans that
  * convolution as a launch of its own for models defined afterwards; on == 2 does so only where
  * the fused launch also computes a projection shortcut; on == 1 restores the default; other
  * values: CW_ERR_INVALID. */

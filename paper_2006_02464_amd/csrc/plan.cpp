@@ -672,7 +672,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             if (j < 0 || !plain(j, 1, 64, 256) || m.ops[j].residual_from < 0 || m.ops[j].residual_from == i) continue;
             tail_into[i] = j;
             const int k = j + 1;
-            if (k < n_ops && plain(k, 1, 256, 64) && m.ops[k].input_from == j && m.ops[k].residual_from < 0 && in_readers[j] == 1) tail_into[j] = k;
+            if (ov.fuse_third && k < n_ops && plain(k, 1, 256, 64) && m.ops[k].input_from == j && m.ops[k].residual_from < 0 && in_readers[j] == 1) tail_into[j] = k;
         }
     }
     // Order in which the ops are planned and launched: op order, except that a convolution j which

@@ -508,6 +508,17 @@ def test_tail_of_a_narrow_bottleneck_in_one_launch(ctx):
             off()
 
 
+def test_tail_of_a_narrow_bottleneck_obeys_the_third_layers_setting(ctx):
+    """cw_set_fusion_third(0): the next block's 1x1 is a launch of its own, also behind a tail."""
+    tail = lambda: [t for m in (ctx.model_define_resnet(50, 224, 224),) for t in (ctx.plan_launch_tail(m, 1, i) for i in range(ctx.plan_num_launches(m, 1))) if t]
+    for third, want in ((0, [1, 2, 1, 2, 1, 2]), (2, [1, 1, 3, 1, 1, 3, 1, 2]), (1, [1, 1, 3, 1, 1, 3, 1, 2])):
+        ctx.set_fusion_third(third)
+        try:
+            assert tail() == want
+        finally:
+            ctx.set_fusion_third(1)
+
+
 def test_weight_pages():
     """The weight pool is paged (paper section 5.1): page counts per model, the limits, the free count."""
     c = cw.Context(device=-1, weight_pool_bytes=1 << 30)          # default page: 16 MiB
