@@ -358,19 +358,25 @@ static bool split_ok(const ConvArgs &a, bool stem, ConvTile tile, int32_t split)
     return (slices + per - 1) / per == split && tiles * conv_counters_per_tile(tile) * 4 <= (int64_t)kCounterBytes && (int64_t)a.M * a.Cout * 4 < (1ll << 31);
 }
 
+// The installed table's row for a convolution, or nullptr.
+static const TunedShape *table_row(const PlanOverride &ov, int64_t M, int32_t N, int64_t K, int32_t kh, int32_t stride) {
+    for (const TunedShape &t : ov.table)
+        if (t.M == M && t.N == N && t.K == K && t.kh == kh && t.stride == stride && t.tile >= 0 && t.tile < N_CONV_TILES) return &t;
+    return nullptr;
+}
+
 // The cheapest tile and split-K of a convolution; a row of the installed table or a forced tile comes first.  A pure function
 // of the convolution's shape and of `one_group`: no tile whose wave groups share a slice's products.
 static double pick_conv_tile(const ConvArgs &a, bool stem, bool res, int64_t real_k, bool one_group, const PlanOverride &ov, ConvTile *tile,
                              int32_t *split, bool *fixed) {
     *fixed = ov.tile >= 0 || ov.split_k > 0;
     if (!*fixed)
-        for (const TunedShape &t : ov.table)
-            if (t.M == a.M && t.N == a.Cout && t.K == real_k && t.kh == a.kh && t.stride == a.stride && t.tile >= 0 && t.tile < N_CONV_TILES) {
-                *tile = (ConvTile)t.tile;
-                *split = std::max(1, t.split_k);
-                *fixed = true;
-                return 0;
-            }
+        if (const TunedShape *t = table_row(ov, a.M, a.Cout, real_k, a.kh, a.stride)) {
+            *tile = (ConvTile)t->tile;
+            *split = std::max(1, t->split_k);
+            *fixed = true;
+            return 0;
+        }
     const int cls = cost_class(a, stem);
     const ConvArgs *as[1] = {&a};
     double best = 1e30;
@@ -659,7 +665,8 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         }
         auto plain = [&](int i, int k, int cin, int cout) {
             const cw_op &o = m.ops[i];
-            return o.op == CW_OP_CONV && o.groups <= 1 && o.kh == k && o.kw == k && o.stride == 1 && o.pad == k / 2 && o.cin == cin && o.cout == cout && o.input_from >= 0 &&
+            const bool as_said = table_row(ov, (int64_t)batch * m.shapes[i].h * m.shapes[i].w, cout, (int64_t)k * k * cin, k, 1);   // a launch of its own, on that tile
+            return o.op == CW_OP_CONV && o.groups <= 1 && o.kh == k && o.kw == k && o.stride == 1 && o.pad == k / 2 && o.cin == cin && o.cout == cout && o.input_from >= 0 && !as_said &&
                    fuse_into[i] < 0 && fused_first[i] < 0 && in_third[i] < 0 && in_pool[i] < 0 && pw_into[i] < 0;
         };
         for (int i = 1; !has_concat && i + 1 < n_ops; ++i) {

@@ -519,6 +519,22 @@ def test_tail_of_a_narrow_bottleneck_obeys_the_third_layers_setting(ctx):
             ctx.set_fusion_third(1)
 
 
+def test_tail_of_a_narrow_bottleneck_leaves_the_plan_tables_rows_their_launches(ctx):
+    """A convolution with a row of the table runs on that row's tile; what is left of the tail still shares a launch."""
+    px = 56 * 56
+    rows = [(px, 64, 576, 3, 1, 3, 1), (px, 256, 64, 1, 1, 2, 1), (px, 64, 256, 1, 1, 4, 1)]
+    all_apart, no_third = [], [1, 2, 1, 2, 1, 2]
+    for row, want in zip(rows, (all_apart, all_apart, no_third)):
+        ctx.set_plan_table([row])
+        try:
+            m = ctx.model_define_resnet(50, 224, 224)
+        finally:
+            ctx.set_plan_table([])
+        assert [t for t in (ctx.plan_launch_tail(m, 1, i) for i in range(ctx.plan_num_launches(m, 1))) if t] == want
+        tiles = [l["conv_tile"] for i, l in enumerate(ctx.plan(m, 1)) if (l["gemm_m"], l["gemm_n"], l["gemm_k"]) == row[:3] and l["kind"] == 1 and l["pair_op"] < 0 and not ctx.plan_launch_tail(m, 1, i)]
+        assert tiles and set(tiles) == {row[5]}
+
+
 def test_weight_pages():
     """The weight pool is paged (paper section 5.1): page counts per model, the limits, the free count."""
     c = cw.Context(device=-1, weight_pool_bytes=1 << 30)          # default page: 16 MiB
