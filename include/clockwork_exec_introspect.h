@@ -52,9 +52,9 @@ int32_t cw_plan_launch_ahead(cw_ctx *ctx, int32_t model_id, int32_t batch, int32
 /* 1 where entry `index` of the plan is no launch of its own: the input cast and, if it follows, the 3x3 stride-2 max pool,
  * whose work the first convolution's launch does (7x7 of 64 channels with the pool, 3x3 of 32 without, stride 2), and the
  * global average pool of few and small maps, which the FC's launch does, a 1x1 convolution that the launch of the depthwise
- * convolution behind it computes (cw_set_fusion_dw), and a 1x1 convolution to 128 channels that the launch of the 3x3 to 32 behind it, its only
- * reader, computes (a densely connected layer, where that is predicted to be faster); not under cw_set_fusion(0), a plan override or debug
- * retention.  0 otherwise, negative on error.  (cw_plan_launch_tail tells of further entries that share a launch.) */
+ * convolution behind it computes (cw_set_fusion_dw), a 1x1 convolution to 128 channels that the launch of the 3x3 to 32 behind it, its only
+ * reader, computes (a densely connected layer, where that is predicted to be faster), and the first layers of a narrow bottleneck's tail
+ * (cw_plan_launch_tail); not under cw_set_fusion(0), a plan override or debug retention.  0 otherwise, negative on error. */
 int32_t cw_plan_launch_joined(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
 /* What EXEC issues for entry `index`: the same as cw_plan_launch_info but for joined entries and those that compute them.  The
  * first have no bytes, flops, grid or block; the others have the launch's own grid and name, its tile (pixels of the stored
@@ -62,9 +62,8 @@ int32_t cw_plan_launch_joined(cw_ctx *ctx, int32_t model_id, int32_t batch, int3
  * over a plan's entries are those of an EXEC. */
 int32_t cw_plan_launch_issued(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index, cw_launch_info *out);
 /* The tail of a narrow bottleneck over few pixels, its 3x3 64 -> 64, the 1x1 to 256 with a residual and, where that is the result's only reader as an
- * input, the 1x1 back to 64, is one launch: 2 or 3 (layers) for its last entry, which launches it, 1 for the others, 0 for every other entry, negative on
- * error.  cw_plan_launch_joined and cw_plan_launch_issued have these entries as they are apart, cw_exec_timed_launches the launch's time at the last.  Not under
- * cw_set_fusion(0), a plan override or debug retention. */
+ * input, the 1x1 back to 64 (cw_set_fusion_third), is one launch: 2 or 3 (layers) for its last entry, which launches it, 1 for the others, 0 for every other
+ * entry, negative on error.  Layers with a row of the plan table stay apart. */
 int32_t cw_plan_launch_tail(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
 /* Runs EXEC like cw_exec but times every launch of the plan with its own pair of
  * events, issuing it `inner` (>= 1) times back to back between them (a launch is

@@ -328,7 +328,8 @@ class Context:
 
     def plan_launch_joined(self, model_id, batch, index):
         """Whether plan entry `index` has no launch of its own: the first convolution's launch computes it (cast, max pool),
-        the FC's (average pool) or a depthwise convolution's (the 1x1 in front of it)."""
+        the FC's (average pool), a depthwise convolution's (the 1x1 in front of it), a 3x3's (the 1x1 of a densely connected
+        layer) or that of a bottleneck tail's last layer."""
         return bool(self._check(lib().cw_plan_launch_joined(self._h, model_id, batch, index)))
 
     def plan_launch_tail(self, model_id, batch, index):

@@ -1472,7 +1472,8 @@ int32_t cw_plan_launch_joined(cw_ctx *c, int32_t model_id, int32_t batch, int32_
     Plan *p = get_plan(m, batch);
     if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
     if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
-    return p->launches[index].in_head == 1 || p->launches[index].in_fc || p->launches[index].in_next;
+    const Launch &l = p->launches[index];
+    return l.in_head == 1 || l.in_fc || l.in_next || l.in_tail;
 }
 
 int32_t cw_plan_launch_tail(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index) {

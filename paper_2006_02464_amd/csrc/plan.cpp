@@ -1545,10 +1545,13 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     }
     // What is really issued where entries are joined: the work moves to the entry that launches it, without the tensors that never
     // leave the chip then.
+    // An entry's bytes and name without the split of its K, which a launch that computes it with others does not have.
+    auto whole_bytes = [&](const Launch &l) { return l.info.bytes - (l.conv.split_k > 1 ? 2 * (int64_t)l.conv.split_k * l.conv.M * l.conv.Cout * 4 : 0); };
+    auto whole_name = [&](const Launch &l) { return std::string(l.info.name, strcspn(l.info.name, "_")) + "_s" + std::to_string(l.conv.stride); };
     for (size_t i = 0; i < p.launches.size(); ++i) {
         const Launch &l = p.launches[i];
         cw_launch_info &d = p.issued[i];
-        if (l.in_head == 1 || l.in_fc || l.in_next) {
+        if (l.in_head == 1 || l.in_fc || l.in_next || l.in_tail) {
             d.bytes = d.flops = 0;
             d.grid_x = d.grid_y = d.grid_z = d.block = 0;
         } else if (l.in_head == 2) {
@@ -1570,17 +1573,27 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
             d.grid_x = (int32_t)g.x; d.grid_y = d.grid_z = 1; d.block = 256;
             d.tile_m = l.dense_tile.th * l.dense_tile.tw; d.tile_n = l.conv.Cout; d.tile_k = 0; d.conv_tile = -1; d.split_k = d.wave_groups = 1;
             d.flops += p.launches[i - 1].info.flops;
-            d.bytes += p.launches[i - 1].info.bytes - 2 * (int64_t)l.pw.M * l.pw.Cout * (int64_t)esz;   // what is between stays on the chip
-            if (l.conv.split_k > 1) d.bytes -= 2 * (int64_t)l.conv.split_k * l.conv.M * l.conv.Cout * 4;
-            snprintf(d.name, sizeof d.name, "%s+conv3x3_s1", p.launches[i - 1].info.name);
+            d.bytes = whole_bytes(p.launches[i - 1]) + whole_bytes(l) - 2 * (int64_t)l.pw.M * l.pw.Cout * (int64_t)esz;   // what is between stays on the chip
+            snprintf(d.name, sizeof d.name, "%s+conv3x3_s1", whole_name(p.launches[i - 1]).c_str());
+        } else if (l.tail > 0) {
+            const Launch &l1 = p.launches[i + 1 - l.tail];
+            const int64_t M = l1.conv.M;
+            d.flops = d.bytes = 0;
+            for (size_t k = i + 1 - l.tail; k <= i; ++k) { d.flops += p.launches[k].info.flops; d.bytes += whole_bytes(p.launches[k]); }
+            // the 3x3's result is neither stored nor read, the 1x1's to 256 stored but not read
+            d.bytes -= 2 * M * l1.conv.Cout * (int64_t)esz + (l.tail == 3 ? M * l.conv0.Cout * (int64_t)esz : 0);
+            d.grid_x = (int32_t)((M + tail_bm(M) - 1) / tail_bm(M)); d.grid_y = d.grid_z = 1; d.block = 256;
+            d.gemm_m = (int32_t)M; d.gemm_n = l1.conv.Cout; d.gemm_k = l1.conv.K;
+            d.tile_m = tail_bm(M); d.tile_n = l.conv.Cout; d.tile_k = 0; d.conv_tile = -1; d.split_k = d.wave_groups = 1;
+            snprintf(d.name, sizeof d.name, "%s+1x1%s", whole_name(l1).c_str(), l.tail == 3 ? "+1x1" : "");
         } else if (l.pw_fused) {
             const int64_t between = (int64_t)l.pw.M * l.pw.Cout * (int64_t)esz;
             const dim3 g = pw_dw_grid(l.pw, l.dw, l.pw_tile);
             d.grid_x = (int32_t)g.x; d.grid_y = d.grid_z = 1; d.block = 64 * l.pw_tile.waves;
             d.flops += p.launches[i - 1].info.flops;
-            d.bytes += p.launches[i - 1].info.bytes - between * (l.pw_y.space == SP_NONE ? 2 : 1);   // not read, and stored where something else reads it
+            d.bytes += whole_bytes(p.launches[i - 1]) - between * (l.pw_y.space == SP_NONE ? 2 : 1);   // not read, and stored where something else reads it
             d.gemm_m = l.pw.M; d.gemm_n = l.pw.Cout; d.gemm_k = l.pw.K;
-            snprintf(d.name, sizeof d.name, "%s+%s", p.launches[i - 1].info.name, l.info.name);
+            snprintf(d.name, sizeof d.name, "%s+%s", whole_name(p.launches[i - 1]).c_str(), l.info.name);
         } else if (l.kind == K_FC && l.fc.hw > 0) {
             d.bytes += (int64_t)batch * l.fc.hw * l.fc.In * esz - (int64_t)batch * l.fc.In * 4;   // the map, and no pooled values
             snprintf(d.name, sizeof d.name, "%s+%s", p.launches[i - 1].info.name, l.info.name);

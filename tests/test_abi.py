@@ -355,7 +355,8 @@ def test_entries_joined_into_the_first_convolutions_launch(ctx):
         m = define()
         return [i for i in range(ctx.plan_num_launches(m, 1)) if ctx.plan_launch_joined(m, 1, i)]
     r50 = lambda: ctx.model_define_resnet(50, 224, 224)
-    assert joined(r50) == [0, 2] and joined(lambda: ctx.model_define_resnet(18, 64, 64)) == [0, 2, 19]   # and the average pool of 4 pixels
+    # with the first layers of stage 1's tails, and the average pool of 4 pixels
+    assert joined(r50) == [0, 2, 4, 5, 7, 8, 10] and joined(lambda: ctx.model_define_resnet(18, 64, 64)) == [0, 2, 19]
     for on, off in ((lambda: ctx.set_fusion(0), lambda: ctx.set_fusion(1)), (lambda: ctx.set_debug_keep(True), lambda: ctx.set_debug_keep(False)),
                     (lambda: ctx.set_plan_override(2, 0), lambda: ctx.set_plan_override(-1, 0)), (lambda: ctx.set_plan_override(-1, 2), lambda: ctx.set_plan_override(-1, 0))):
         on()
@@ -384,7 +385,8 @@ def test_issued_launches_hold_the_work_of_joined_entries(ctx, batch):
     for i in gone:
         l = ctx.plan_launch_issued(m, batch, i)
         assert (l["bytes"], l["flops"], l["grid_x"], l["block"]) == (0, 0, 0, 0)
-    assert gone == [0, 2]
+    tail = [ctx.plan_launch_tail(m, batch, i) for i in range(len(plan))]
+    assert gone == [0, 2] + [i for i, t in enumerate(tail) if t == 1] and len(issued) == len(plan) - (7 if batch == 1 else 2)
     assert sum(l["flops"] for l in issued.values()) == 2 * batch * T.mac_count(T.resnet(50), 224, 224)
     px = batch * 56 * 56
     head = issued[1]
@@ -393,9 +395,20 @@ def test_issued_launches_hold_the_work_of_joined_entries(ctx, batch):
     assert head["flops"] == 2 * batch * 112 * 112 * 64 * 147 + (2 * px * 64 * 64 if batch > 1 else 0)
     assert head["name"] == "cast+stem7x7_s2+maxpool3x3_s2" + ("+1x1" if batch > 1 else "")
     assert (head["grid_x"], head["block"], head["conv_tile"]) == (batch * (8 if batch > 1 else 19) * 7, 256, -1)   # 7 x 8 or 3 x 8 pooled pixels
-    assert sum(l["bytes"] for l in plan) - sum(l["bytes"] for l in issued.values()) == sum(plan[i]["bytes"] for i in range(3)) - head["bytes"] > 0
+    unread = 0     # what stage 1's tails, the one launch of up to three layers each, neither store nor read again
+    for i, t in enumerate(tail):
+        if t < 2:
+            continue
+        l, parts = issued[i], [plan[k]["split_k"] for k in range(i - t + 1, i + 1)]
+        assert parts == [1] * t
+        assert l["flops"] == 2 * px * (576 * 64 + 64 * 256 + (256 * 64 if t == 3 else 0))
+        assert l["bytes"] == px * 2 * (64 + 256 + 256 + (64 if t == 3 else 0)) + 2 * (576 * 64 + 64 * 256 + (256 * 64 if t == 3 else 0)) + 4 * (64 + 256 + (64 if t == 3 else 0))
+        assert (l["name"], l["grid_x"], l["block"], l["tile_m"], l["tile_n"], l["conv_tile"]) == ("conv3x3_s1+1x1" + ("+1x1" if t == 3 else ""), px // 16, 256, 16, 64 if t == 3 else 256, -1)
+        assert (l["gemm_m"], l["gemm_n"], l["gemm_k"], l["op_index"]) == (px, 64, 576, plan[i]["op_index"])
+        unread += px * 2 * (2 * 64 + (256 if t == 3 else 0))
+    assert sum(l["bytes"] for l in plan) - sum(l["bytes"] for l in issued.values()) == sum(plan[i]["bytes"] for i in range(3)) - head["bytes"] + unread > 0
     for i, l in issued.items():
-        assert i == 1 or l == plan[i]
+        assert i == 1 or tail[i] > 1 or l == plan[i]
 
 
 def test_issued_launch_of_the_average_pool_and_the_fc(ctx):
