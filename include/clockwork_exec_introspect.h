@@ -54,7 +54,8 @@ int32_t cw_plan_launch_ahead(cw_ctx *ctx, int32_t model_id, int32_t batch, int32
  * global average pool of few and small maps, which the FC's launch does, a 1x1 convolution that the launch of the depthwise
  * convolution behind it computes (cw_set_fusion_dw), a 1x1 convolution to 128 channels that the launch of the 3x3 to 32 behind it, its only
  * reader, computes (a densely connected layer, where that is predicted to be faster), and the first layers of a narrow bottleneck's tail
- * (cw_plan_launch_tail); not under cw_set_fusion(0), a plan override or debug retention.  0 otherwise, negative on error. */
+ * (cw_plan_launch_tail); not under cw_set_fusion(0), a plan override or debug retention (but
+ * see cw_set_debug_keep_joined).  0 otherwise, negative on error. */
 int32_t cw_plan_launch_joined(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
 /* What EXEC issues for entry `index`: the same as cw_plan_launch_info but for joined entries and those that compute them.  The
  * first have no bytes, flops, grid or block; the others have the launch's own grid and name, its tile (pixels of the stored
@@ -81,6 +82,10 @@ int32_t cw_debug_read_op(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t o
 /* When keep != 0, plans built afterwards give every op output its own workspace
  * region (no reuse) so cw_debug_read_op can read them.  Costs workspace only. */
 int32_t cw_set_debug_keep(cw_ctx *ctx, int32_t keep);
+/* on != 0: debug retention leaves the launches that compute several convolutions (a 1x1 with the depthwise convolution behind it, a densely
+ * connected layer, a narrow bottleneck's tail) as they are without it, for models defined afterwards; what they do not store cannot be read
+ * back.  on == 0, the default: under retention these layers are launches of their own. */
+int32_t cw_set_debug_keep_joined(cw_ctx *ctx, int32_t on);
 /* EXEC normally replays, for the slot-independent middle of a plan, a HIP graph recorded at
  * LOAD (fewer, cheaper submissions; identical kernels and arguments).  on == 0 makes EXEC
  * issue every kernel as its own launch instead; on != 0 restores the default.  Takes effect

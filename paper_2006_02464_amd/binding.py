@@ -104,6 +104,7 @@ SIGNATURES = {
     "cw_exec_timed_launches": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_int32, c_void_p, c_void_p]),
     "cw_debug_read_op": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_void_p, c_size_t]),
     "cw_set_debug_keep": (c_int32, [c_void_p, c_int32]),
+    "cw_set_debug_keep_joined": (c_int32, [c_void_p, c_int32]),
     "cw_set_plan_override": (c_int32, [c_void_p, c_int32, c_int32]),
     "cw_set_plan_table": (c_int32, [c_void_p, c_void_p, c_int32]),
     "cw_set_fusion": (c_int32, [c_void_p, c_int32]),
@@ -358,8 +359,10 @@ class Context:
         self._check(lib().cw_debug_read_op(self._h, model_id, batch, op_index, _ptr(out), out.size))
         return out
 
-    def set_debug_keep(self, keep):
+    def set_debug_keep(self, keep, joined=False):
+        """joined: the launches that compute several convolutions stay as they are without retention."""
         self._check(lib().cw_set_debug_keep(self._h, int(keep)))
+        self._check(lib().cw_set_debug_keep_joined(self._h, int(joined)))
 
     def set_use_graphs(self, on):
         self._check(lib().cw_set_use_graphs(self._h, int(on)))

@@ -826,6 +826,12 @@ int32_t cw_set_debug_keep(cw_ctx *c, int32_t keep) {
     return CW_OK;
 }
 
+int32_t cw_set_debug_keep_joined(cw_ctx *c, int32_t on) {
+    if (!c) return CW_ERR_INVALID;
+    c->ov.keep_joined = on != 0;
+    return CW_OK;
+}
+
 int32_t cw_set_plan_override(cw_ctx *c, int32_t conv_tile, int32_t split_k) {
     if (!c) return CW_ERR_INVALID;
     if (conv_tile >= (int32_t)N_CONV_TILES || split_k < 0) return set_err(c, CW_ERR_INVALID, "bad override");

@@ -581,7 +581,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     std::vector<int> pw_into(n_ops, -1);
     std::vector<char> pw_kept(n_ops, 0);
     std::vector<PwDwTile> pw_tile(n_ops);
-    if (ov.join && ov.fuse && ov.fuse_dw && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
+    if (ov.join && ov.fuse && ov.fuse_dw && (!ov.keep_all || ov.keep_joined) && !resident && ov.tile < 0 && ov.split_k <= 0) {
         bool has_concat = false;
         std::vector<int> uses(n_ops, 0);
         for (int i = 0; i < n_ops; ++i) {
@@ -616,7 +616,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     }
     // A densely connected layer: a 1x1 convolution to 128 channels and the 3x3 to 32 right behind it, its only reader.  Entries as above.
     std::vector<DenseTile> dense_tile(n_ops);
-    if (ov.join && ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0) {
+    if (ov.join && ov.fuse && (!ov.keep_all || ov.keep_joined) && !resident && ov.tile < 0 && ov.split_k <= 0) {
         std::vector<int> uses(n_ops, 0);
         for (int i = 0; i < n_ops; ++i) {
             if (m.ops[i].input_from >= 0) ++uses[m.ops[i].input_from];
@@ -655,7 +655,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
     // Always: it is faster from a few dozen pixels on (whole EXECs by graph replay, apart and as decided here, ResNet-50 64x64 batch 1 186.8 -> 178.6 us, 130x97 200.1 -> 189.8,
     // 224x224 216.9 -> 206.2, 150x150 batch 2 215.2 -> 206.4, 193x161 batch 3 253.9 -> 243.6, 100x100 batch 7 248.7 -> 239.2).
     std::vector<int> tail_into(n_ops, -1);
-    if (ov.join && ov.fuse && !ov.keep_all && !resident && ov.tile < 0 && ov.split_k <= 0 && !m.winograd) {
+    if (ov.join && ov.fuse && (!ov.keep_all || ov.keep_joined) && !resident && ov.tile < 0 && ov.split_k <= 0 && !m.winograd) {
         std::vector<int> uses(n_ops, 0), in_readers(n_ops, 0);
         bool has_concat = false;
         for (int i = 0; i < n_ops; ++i) {
@@ -1451,6 +1451,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         ld.pw = lc.conv;
         ld.pw_x = lc.x; ld.pw_w = lc.w; ld.pw_bias = lc.bias; ld.pw_res = lc.res;
         if (pw_kept[lc.op_index]) ld.pw_y = lc.y;
+        else p.op_out[lc.op_index] = Ref{};   // never stored
     }
     for (size_t i = 0; i + 1 < p.launches.size(); ++i) {
         auto alone = [&](const Launch &l) { return l.kind == K_CONV && l.pair_op < 0 && l.fused_bm <= 0 && !l.stem && !l.in_next && !l.in_tail && !l.dense_fused && l.tail == 0 && l.conv.nz <= 1; };
@@ -1461,6 +1462,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
                            conv_ldy(p.launches[i + 2].conv) == 64;
         Launch &lt = p.launches[i + (third ? 2 : 1)];
         l1.in_tail = true;
+        p.op_out[l1.op_index] = Ref{};   // never stored
         lt.tail = third ? 3 : 2;
         lt.pw = l1.conv;
         lt.pw_x = l1.x; lt.pw_w = l1.w; lt.pw_bias = l1.bias;

@@ -125,6 +125,7 @@ struct PlanOverride {
     int32_t tile = -1;     // ConvTile or -1 = automatic
     int32_t split_k = 0;   // 0 = automatic
     bool keep_all = false; // no workspace reuse (debug read-back)
+    bool keep_joined = false;  // with keep_all: launches that compute several convolutions stay as they are without it
     bool join = true;      // launches that compute convolutions of earlier entries, whose inputs then live longer
     int32_t fuse = 1;      // two-layer launches: 0 = none, 1 = yes, 2 = yes but never with two wave groups
     bool pair = true;      // two convolutions over one tensor as one launch

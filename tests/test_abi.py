@@ -548,6 +548,19 @@ def test_tail_of_a_narrow_bottleneck_leaves_the_plan_tables_rows_their_launches(
         assert tiles and set(tiles) == {row[5]}
 
 
+def test_debug_retention_can_leave_joint_launches_as_they_are(ctx):
+    for ops in (T.resnet(50), T.mobilenet(), T.dense_net()):
+        define = lambda: ctx.model_define([tuple(o) for o in ops], 3, 224, 224, batch_sizes=(1,))
+        joined = lambda m: [i for i, l in enumerate(ctx.plan(m, 1)) if ctx.plan_launch_joined(m, 1, i) and l["kind"] == 1 and l["op_index"] > 0]
+        plain = joined(define())
+        for keep_joined, want in ((False, []), (True, plain)):
+            ctx.set_debug_keep(True, joined=keep_joined)
+            try:
+                assert joined(define()) == want and plain
+            finally:
+                ctx.set_debug_keep(False)
+
+
 def test_weight_pages():
     """The weight pool is paged (paper section 5.1): page counts per model, the limits, the free count."""
     c = cw.Context(device=-1, weight_pool_bytes=1 << 30)          # default page: 16 MiB

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+from gpu_common import check_layers, define_retained, with_infinities
 from oracle import network as N
 from oracle import topology as T
 from workload import gen
@@ -51,6 +52,36 @@ def test_densely_connected_layer_in_one_launch(h, w, k, batch, act1, act2, conca
         for z in got:
             assert np.abs(z - ref).max() <= tol * np.abs(ref).max()
         assert np.abs(got[0] - got[1]).max() <= tol * np.abs(ref).max()
+        wk.ctx.set_fusion(1)   # every stored element
+        mid = define_retained(wk.ctx, ops, 2 * h, 2 * w, batch, dtype)
+        wk.load(mid, gen.pack_blob(wts, biases, dtype))
+        wk.infer(mid, x, classes=11)
+        check_layers(wk.ctx, ops, wts, biases, mid, batch, x, dtype, unstored=(2, 5) if concat else (2,))
     finally:
         wk.ctx.set_fusion(1)
+        wk.close()
+
+
+@pytest.mark.parametrize("h,w,k,batch,act,dtype", [(15, 13, 96, 3, 0, "fp16"), (28, 28, 256, 6, HSWISH, "bf16"), (13, 29, 160, 3, RELU, "fp16")])
+def test_densely_connected_layer_on_non_finite_values(h, w, k, batch, act, dtype):
+    """NaN and infinities in the images, inside and at the edges of the map, and then infinite weights: the same elements are NaN or infinite as in the oracle."""
+    from paper_2006_02464_amd.runner import Worker
+    ops = [o._replace(relu=0) if o.op == T.CONV and (i < 2 or act == 0) else o for i, o in enumerate(net(k, act, act, True))]   # (ReLU of NaN is 0)
+    wts, biases = gen.model_tensors(T.weight_shapes(ops), 9, dtype)
+    x = gen.images(9, 0, batch, 3, 2 * h, 2 * w, "uniform", dtype).copy()
+    x[0, 0, h, w], x[1, 1, 0, 0], x[1, 2, 2 * h - 1, w], x[2, 0, h // 2, 2 * w - 1] = np.nan, np.inf, -np.inf, np.inf
+    wk = Worker(workspace_bytes=512 << 20, io_bytes=64 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = define_retained(wk.ctx, ops, 2 * h, 2 * w, batch, dtype)
+        wk.load(mid, gen.pack_blob(wts, biases, dtype))
+        wk.infer(mid, x, classes=11)
+        # (the first convolution's filter rows are padded with weights of zero, which an infinite pixel beside the filter makes NaN)
+        assert check_layers(wk.ctx, ops, wts, biases, mid, batch, x, dtype, (2, 5), given=(0,)) > (0 if act == RELU else 500) - 1
+        wts = with_infinities(ops, wts, {3: (7, 5, 0, 0), 5: (100, 40, 0, 0), 6: (9, 3, 2, 2)})
+        x = gen.images(4, 0, batch, 3, 2 * h, 2 * w, "uniform", dtype)
+        wk.ctx.unload_weights(mid)
+        wk.load(mid, gen.pack_blob(wts, biases, dtype))
+        wk.infer(mid, x, classes=11)
+        assert check_layers(wk.ctx, ops, wts, biases, mid, batch, x, dtype, (2, 5)) > 0
+    finally:
         wk.close()

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+from gpu_common import check_layers, define_retained, with_infinities
 from oracle import network as N
 from oracle import topology as T
 from workload import gen
@@ -51,5 +52,36 @@ def test_1x1_inside_the_depthwise_launch(h, w, k, n, stride, batch, act, shortcu
         for z in got:
             assert np.abs(z - ref).max() <= tol * np.abs(ref).max()
         assert np.abs(got[0] - got[1]).max() <= tol * np.abs(ref).max()
+        wk.ctx.set_fusion_dw(1)   # every stored element
+        mid = define_retained(wk.ctx, ops, 2 * h, 2 * w, batch, dtype)
+        wk.load(mid, gen.pack_blob(wts, biases, dtype))
+        wk.infer(mid, x, classes=11)
+        check_layers(wk.ctx, ops, wts, biases, mid, batch, x, dtype, unstored=() if shortcut and stride == 1 else (2,))
+    finally:
+        wk.close()
+
+
+@pytest.mark.parametrize("h,w,k,n,stride,batch,act,shortcut,dtype", [(15, 13, 256, 256, 1, 3, HSWISH, True, "bf16"), (14, 14, 128, 64, 2, 3, 0, False, "fp16"), (14, 14, 128, 64, 1, 3, 1, False, "fp16")])
+def test_1x1_inside_the_depthwise_launch_on_non_finite_values(h, w, k, n, stride, batch, act, shortcut, dtype):
+    """NaN and infinities in the images, inside and at the edges of the map, and then infinite weights: the same elements are NaN or infinite as in the oracle."""
+    from paper_2006_02464_amd.runner import Worker
+    ops = [o._replace(relu=0) if o.op == T.CONV and (i < 2 or act == 0) else o for i, o in enumerate(net(k, n, stride, act, shortcut))]   # (ReLU of NaN is 0)
+    wts, biases = gen.model_tensors(T.weight_shapes(ops), 9, dtype)
+    x = gen.images(9, 0, batch, 3, 2 * h, 2 * w, "uniform", dtype).copy()
+    x[0, 0, h, w], x[1, 1, 0, 0], x[1, 2, 2 * h - 1, w], x[2, 0, h // 2, 2 * w - 1] = np.nan, np.inf, -np.inf, np.inf
+    unstored = () if shortcut and stride == 1 else (2,)
+    wk = Worker(workspace_bytes=128 << 20, io_bytes=16 << 20, weight_pool_bytes=64 << 20, load_staging_bytes=64 << 20)
+    try:
+        mid = define_retained(wk.ctx, ops, 2 * h, 2 * w, batch, dtype)
+        wk.load(mid, gen.pack_blob(wts, biases, dtype))
+        wk.infer(mid, x, classes=11)
+        # (the first convolution's filter rows are padded with weights of zero, which an infinite pixel beside the filter makes NaN)
+        assert check_layers(wk.ctx, ops, wts, biases, mid, batch, x, dtype, unstored, given=(0,)) > (0 if act == 1 else 500) - 1
+        wts = with_infinities(ops, wts, {2: (30, 40, 0, 0), 3: (7, 0, 0, 0)})
+        x = gen.images(4, 0, batch, 3, 2 * h, 2 * w, "uniform", dtype)
+        wk.ctx.unload_weights(mid)
+        wk.load(mid, gen.pack_blob(wts, biases, dtype))
+        wk.infer(mid, x, classes=11)
+        assert check_layers(wk.ctx, ops, wts, biases, mid, batch, x, dtype, unstored) > 0
     finally:
         wk.close()
