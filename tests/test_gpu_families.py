@@ -169,19 +169,21 @@ def test_depthwise_shapes_off_the_mobilenet_path(worker):
         ctx.unload_weights(mid)
 
 
-@pytest.mark.parametrize("batch", [32, 33])
-def test_depthwise_3x3_at_the_line_between_its_two_forms(worker, batch):
-    """32x32x64 at batch 32 is 1024 workgroups of one pixel a thread, which all run at once, at batch 33 more."""
+@pytest.mark.parametrize("h,batch,wgs", [(32, 16, 512), (20, 41, 513)])
+def test_depthwise_3x3_at_the_line_between_its_two_forms(worker, h, batch, wgs):
+    """Up to 512 workgroups of one pixel a thread the launch has them, above two pixels a thread in workgroups of half the size."""
     O = T.Op
     ops = [O(T.CONV, 3, 64, 3, 3, 1, 1, 1, -1, -1), O(T.CONV, 64, 64, 3, 3, 1, 1, 1, 0, 0, 0, 64), O(T.CONV, 64, 256, 1, 1, 2, 0, 1, -1, 1),
            O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 2), O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 3), O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 4)]
-    case = Case(ops, 32, seed=5, dtype="fp16", dist="normal")
+    case = Case(ops, h, seed=5, dtype="fp16", dist="normal")
     worker.ctx.set_debug_keep(True)
     try:
-        mid = worker.ctx.model_define(case.ops, 3, 32, 32, batch_sizes=(batch,), dtype="fp16")
+        mid = worker.ctx.model_define(case.ops, 3, h, h, batch_sizes=(batch,), dtype="fp16")
     finally:
         worker.ctx.set_debug_keep(False)
-    assert [l["grid_x"] for l in worker.ctx.plan(mid, batch) if l["name"].startswith("dwconv")] == [32 * batch]
+    pairs = wgs > 512
+    assert (batch * h * h * 8 + 255) // 256 == wgs
+    assert [(l["grid_x"], l["block"]) for l in worker.ctx.plan(mid, batch) if l["name"].startswith("dwconv")] == [((batch * h * (h // 2) * 8 + 127) // 128, 128) if pairs else (wgs, 256)]
     worker.load(mid, case.blob)
     x = case.images(0, batch)
     worker.infer(mid, x, classes=10)
