@@ -283,9 +283,9 @@ constexpr int pool_fc_items(int64_t B, int64_t in, int64_t hw) {
 constexpr int kFcSoftmaxMaxBatch = 16, kFcSoftmaxMaxOut = 1024;
 
 // The FC's parts of K, each a sum of its own: by the waves of a workgroup, or (fc_in_parts) by workgroups, for the softmax to add up.  Up to 1024
-// features, where the weights' way to the chip is the smaller part: whole EXECs of ResNet-18 batch 8 133.9 -> 132.6 us, DenseNet batch 6 206.7 -> 204.7, Inception batch 5
-// 92.7 -> 91.2; with 2048 from eight samples on, ResNet-50 batch 16 421.1 -> 419.3 (batch 4 267.5 -> 268.3, batch 1 204.4 -> 205.9: the launch is 1.7 us
-// shorter, the softmax, which fetches the parts from other XCDs' L2s, 0.7 us longer).
+// features, where the weights' way to the chip is the smaller part: whole EXECs by graph replay, of which two processes of one side differ by up to 0.6 %, DenseNet batch 6
+// 206.7 -> 204.7 us, Inception batch 5 92.7 -> 91.2, ResNet-18 batch 8 133.9 -> 132.6; with 2048 from eight samples on, ResNet-50 batch 16 421.1 -> 419.3, no more than that
+// difference (batch 4 267.5 -> 268.3, batch 1 204.4 -> 205.9: the launch is 1.7 us shorter, the softmax, which fetches the parts from other XCDs' L2s, 0.7 us longer).
 constexpr int kFcWaves = 8, kFcPartsMaxOut = 1024;
 constexpr bool fc_in_parts(int64_t B, int64_t in, int64_t out) {
     return out <= kFcPartsMaxOut && in % (32 * kFcWaves) == 0 && (in <= 1024 || (B >= 8 && in <= 4096)) && (B + 15) / 16 * ((out + 15) / 16) <= 256;

@@ -2,8 +2,9 @@
 // As two launches the tensor between them, 128 channels for the 32 that stay, goes to memory and back, and at DenseNet's sizes each launch is its fixed
 // time and one wait for operands (28x28, batch 6: 2.8 to 4.3 us and 4.3 for 0.3 and 0.2 us of matrix instructions).  Here a workgroup computes a tile of the
 // result: the 1x1 over the tile and a border of one pixel, rounded as when it is stored, into LDS, and the 3x3 from there.
-// What bounds it: what a CU has to fetch, 256 bytes x K of the 1x1's weights, 72 KB of the 3x3's and the pixels, at about 35 bytes a clock, then
-// two contractions one behind the other with one wave a SIMD.  What made it faster than the two launches:
+// What bounds it: what a CU has to fetch, 256 bytes x K of the 1x1's weights, 72 KB of the 3x3's and the pixels, then
+// two contractions one behind the other with one wave a SIMD.  By counters at batch 6 a wave lives 12.0k to 16.9k clocks at 28x28 and waits 35 to 40 % of them; a stage of 64
+// channels of K is 800 clocks for 26 KB (33 bytes a clock of the 58 to 64 that the load path sustains), 1800 at 56x56 with twice the pixels a wave.  What made it faster than the two launches:
 // - All operands go to LDS by direct loads whose neighbouring lanes read neighbouring bytes.  A load into the registers of an
 //   MFMA operand has its 16 lowest lanes in 16 rows and takes 41 clocks a KB for 14 (28x28, K 256, batch 6 6.4 -> 5.7 us; K 480 8.9 -> 7.0).
 // - A wave reads its own quarter of the 3x3's weights, 32 of the 128 channels, into registers once; the four partial sums meet in LDS.

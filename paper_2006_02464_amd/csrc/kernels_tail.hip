@@ -1,6 +1,7 @@
 // The tail of a narrow bottleneck over few pixels in one launch: a 3x3 convolution 64 -> 64, the 1x1 to 256 with its residual and, where that is the
 // result's only reader as an input, the 1x1 back to 64 of the block behind it.
-// What bounds it: what a CU has to fetch, 72 KB + 32 KB (+ 32 KB) of weights, at about 50 bytes a clock; the matrix instructions are a tenth of that.
+// What bounds it: a chain of latencies around what a CU has to fetch, 72 KB + 32 KB (+ 32 KB) of weights.  By counters (three layers, 3136 pixels) a wave lives 11.2k clocks, in
+// which 152 KB come from L2, waits 46 % of them and has a matrix instruction in the pipe for 5 %.
 // So all of it is requested at the start, in the order in which it is needed, and nothing waits for more than its own part:
 // - 16 or 32 pixels a workgroup, so that these few pixels still are a workgroup a CU; with 136 KB of weights in LDS there is room for one.
 // - A wave has 16 of the 64 channels of the first and the third layer and 64 of the 256, and fetches their weights itself: only pixels and what a layer
@@ -239,8 +240,9 @@ __global__ __launch_bounds__(256) void tail_kernel(const TailArgs a) {
 // The same for many pixels, also with the projection shortcut of a stage's first block (x2, 64 channels, instead of a residual).  Workgroups of the form for few pixels, in
 // several rounds, would fetch the weights again each time; here a wave holds its own in registers, 104 to 168 of the 256 that it has, and the workgroup, one
 // a CU, walks its range of pixels 32 at a time: four waves by channels for each half of the 32.  The next tile's pixels and residual are on their way meanwhile.
-// What bounds it: up to three tiles the start (5.7 us with the first tile), then memory: a tile reads 20 KB and stores 20, at 2.1 us a tile 4.9 TB/s over
-// the chip, where a large copy reaches 4.7.  One wave a SIMD instead of two 2.6 us a tile, with the reads of LDS left to the compiler 3.6.
+// What bounds it: up to three tiles the start, 5.0 to 6.0 us with the first tile; each further one takes 1.8 to 3.0 us for 5.6 (projection) to 8.0 MB over the chip, 2.2 to
+// 3.9 TB/s where a large copy reaches 4.7, and a wave waits 42 to 47 % of its life (kernel trace and counters at one to four tiles on 196 CUs).  Where two waves a SIMD took
+// 2.1 us a tile, one took 2.6, and two with the reads of LDS left to the compiler 3.6.
 // Against the convolution kernel's fused form, back to back, with projection and third layer / with the third / alone: 6272 pixels 10.5 -> 6.2 us / 9.9 -> 6.2 / 8.6 -> 5.4,
 // 12544 11.0 -> 8.5 / 10.4 -> 8.5 / 9.0 -> 7.3, 25088 14.2 -> 12.9 / 13.2 -> 13.0 / 11.2 -> 11.2, 50176 in bf16 20.8 -> 19.2 / 19.4 -> 19.5 / 16.5 -> 17.0.
 

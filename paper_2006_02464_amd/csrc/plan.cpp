@@ -781,7 +781,7 @@ int32_t plan_build(const Model &m, int32_t batch, const PlanOverride &ov, Plan *
         return pool_fc_items(batch, m.ops[i].cin, (int64_t)map.h * map.w) > 0;
     };
 
-    // Whether a fused launch of ops f and i is that of the narrow bottleneck.  From four tiles of 32 pixels a workgroup on memory bounds both forms: 25088 pixels, two
+    // Whether a fused launch of ops f and i is that of the narrow bottleneck.  From four tiles of 32 pixels a workgroup on both forms take the same time: 25088 pixels, two
     // layers 11.2 us in either, three 13.0 and 13.2; with the projection, which the other form walks through one buffer, 12.9 and 14.2, and at 50176 pixels 19.2 and 20.8
     // by itself, but whole EXECs of ResNet-152 are no faster.
     auto walks = [&](int f, int i) {

@@ -9,7 +9,7 @@ from oracle import network as N
 from oracle import topology as T
 from workload import gen
 
-TOL = 2e-2   # max |z_gpu - z_ref| / max |z_ref| per sample (spec tolerance)
+TOL = 2e-2   # max |z_gpu - z_ref| / max |z_ref| per sample
 
 
 class Case:
