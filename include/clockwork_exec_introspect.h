@@ -28,7 +28,8 @@ typedef struct {
     int32_t proj_op;       /* -1, or the projection-shortcut op this launch computes as well */
     int32_t pair_op;       /* -1, or a second, independent convolution over the same input computed by this launch */
     int32_t kind;          /* internal kernel family id */
-    int32_t grid_x, grid_y, grid_z, block;   /* without the workgroups that read ahead: cw_plan_launch_ahead */
+    int32_t grid_x, grid_y, grid_z, block;   /* without the workgroups that read ahead (cw_plan_launch_ahead); of a convolution the threads
+                                                that multiply, beside which tiles of one or two wave groups have 256 that only load */
     int32_t tile_m, tile_n, tile_k, split_k; /* conv: pixels x channels per workgroup, K slice */
     int32_t conv_tile;     /* conv: the tile variant in cw_set_plan_override's numbering; -1 for a fused pair and for other kinds */
     int32_t wave_groups;   /* conv: groups of waves that split every K slice (1 = none) */

@@ -1,6 +1,6 @@
 // Entry point and launch of one convolution on the direct-to-LDS kernel, for the files that instantiate it.
 #pragma once
-#include "conv_dlds_body.h"
+#include "conv_loader_body.h"
 
 namespace cw {
 
@@ -90,9 +90,19 @@ struct ConvRest<MODE, false, true> : ConvArgs {   // the fused form reads all of
     __device__ __forceinline__ void unpack(ConvArgs &a) const { a = *this; }
 };
 
+template <int WARPS_M, int WARPS_N, int KG, int MODE, bool FUSED>
+constexpr int conv_threads() { return 64 * (WARPS_M * WARPS_N * KG + (conv_has_loaders(MODE, FUSED, KG) ? kLoaderWaves : 0)); }
+
+// The tile on the body that is the form's.
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED, int KG, int MT>
+static __device__ __forceinline__ void conv_body(const ConvArgs &a, const int bid, const int nb, const unsigned magic) {
+    if constexpr (conv_has_loaders(MODE, FUSED, KG)) conv_loader_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, KG, MT>(a, bid, nb, magic);
+    else conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, bid, nb);
+}
+
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, int MT = 32>
-__global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
-                                                                                 int M, int K, int cout_ldy, int cin_ldx, int nb, int relu,
+__global__ __launch_bounds__((conv_threads<WARPS_M, WARPS_N, KG, MODE, FUSED>())) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
+                                                                                 int M, int K, int cout_ldy, int cin_ldx, unsigned nb_relu, unsigned magic,
                                                                                  const ConvRest<MODE, SPLITK, FUSED> rest CW_STAMP_ARG) {
     CW_STAMP_BEGIN
     // The ten leading arguments (14 dwords, all the user SGPRs there are beside the argument
@@ -100,13 +110,15 @@ __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(
     // they are in SGPRs when a wave starts and the first address arithmetic does not wait for a
     // load of the argument block.  Everything else is read from `rest` when it is needed.
     // Cout and Cin carry the pixel pitches of y and x in their upper halves, so that the 1x1 form
-    // still needs nothing beyond the preloaded scalars for its addressing.
+    // still needs nothing beyond the preloaded scalars for its addressing, and the tile count the activation in its top two bits (in
+    // the argument block, a load of it stays in flight across the K walk, and every LDS read there then waits for all of them).
+    const int nb = (int)(nb_relu & 0x3fffffffu);
     ConvArgs a;
     a.x = x; a.w = w; a.res = res; a.y = y;
     a.M = M; a.K = K;
     rest.unpack(a);
     a.x = x; a.w = w; a.res = res; a.y = y;
-    a.M = M; a.K = K; a.Cout = cout_ldy & 0xffff; a.Cin = cin_ldx & 0xffff; a.nb = nb; a.relu = relu;
+    a.M = M; a.K = K; a.Cout = cout_ldy & 0xffff; a.Cin = cin_ldx & 0xffff; a.nb = nb; a.relu = (int)(nb_relu >> 30);
     a.ld = (int)(((unsigned)cin_ldx >> 16) | ((unsigned)cout_ldy & 0xffff0000u));
     if constexpr (MODE == MODE_GEMM && !SPLITK && !FUSED && MT == 32) {
         // batched form: one GEMM per blockIdx.z, operands advanced by the strides in the last argument line
@@ -117,10 +129,10 @@ __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(
         }
     }
     if constexpr (FUSED || SPLITK || MODE == MODE_STEM) {
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, blockIdx.x, nb);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, MT>(a, blockIdx.x, nb, magic);
         CW_STAMP_END
     } else if (__builtin_expect((int)blockIdx.x < conv_nb_tiles(nb) * conv_parts<BM, BN, MT>(), 1)) {
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, blockIdx.x, nb);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, MT>(a, blockIdx.x, nb, magic);
         CW_STAMP_END
     } else {   // a workgroup that reads ahead (its code behind the convolution's, which most launches find cold)
         const int wgs = conv_nb_tiles(nb) * conv_parts<BM, BN, MT>();
@@ -138,6 +150,8 @@ __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_kernel(
     }
 }
 
+static inline uint32_t conv_pack_relu(const ConvArgs &a) { return (uint32_t)a.nb | (uint32_t)a.relu << 30; }   // panel_log2 <= 3: bits 28 and 29
+
 // A tile numbering in 2^p panels needs the channel tiles to divide evenly, and the tile count must
 // leave the bits above kPanelShift free.
 static bool conv_panel_ok(const ConvArgs &a, int bn, unsigned tiles) {
@@ -153,9 +167,11 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     a.nb = conv_pack_nb((int)grid.x, a.panel_log2);
     if (MODE == MODE_TAIL ? a.nz > 1 : a.K % BK != 0 && MODE != MODE_STEM) return hipErrorInvalidValue;
     if (!SPLITK && a.ktiles_per_split != (MODE == MODE_STEM ? (a.kh + 1) / 2 : (a.K + BK - 1) / BK)) return hipErrorInvalidValue;  // the kernel walks the whole K
+    if (SPLITK && (long long)(a.split_k - 1) * a.ktiles_per_split >= (MODE == MODE_STEM ? (a.kh + 1) / 2 : (a.K + BK - 1) / BK)) return hipErrorInvalidValue;   // no split is empty
     if (a.nz > 1 && (MT != 32 || MODE != MODE_GEMM || SPLITK || a.bias || a.res || grid.z != (unsigned)a.nz)) return hipErrorInvalidValue;
     constexpr unsigned PARTS = conv_parts<BM, BN, MT>();
     if (a.nz <= 1 && grid.z != PARTS) return hipErrorInvalidValue;
+    const unsigned grid_tiles = grid.x * PARTS;
     if (PARTS > 1) grid = dim3(grid.x * PARTS, grid.y, 1);   // the workgroups that read ahead come behind all the parts
     ConvRest<MODE, SPLITK, false> rest;
     rest.pack(a);
@@ -170,8 +186,10 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
     // at the end needs its own room)
     if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && a.nz <= 1) grid.x += conv_prefetch_wgs(a.Cout2);
-    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG >= 4 ? KG : KG - 1) * BM * BN * 4);
-    kern<<<grid, block, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, rest CW_STAMP_PASS);
+    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG > 1 ? KG : 0) * BM * BN * 4);
+    if (block != 64 * WARPS_M * WARPS_N * KG) return hipErrorInvalidValue;
+    const uint32_t magic = conv_tile_magic(grid_tiles, (unsigned)(a.Cout + BN - 1) / BN);
+    kern<<<grid, conv_threads<WARPS_M, WARPS_N, KG, MODE, false>(), used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), conv_pack_relu(a), magic, rest CW_STAMP_PASS);
     return hipGetLastError();
 }
 

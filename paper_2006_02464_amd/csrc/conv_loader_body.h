@@ -1,0 +1,303 @@
+// The direct-to-LDS convolution with waves that only load: the per-tile body of the per-layer launches (conv_dlds_launch.h) and of
+// the pair launches (kernels_conv_dlds.hip).
+//
+// Same GEMM view, weight layout, LDS stages and swizzle, MFMA roles, K order and epilogues as conv_dlds_body.h, and the same sums
+// bit for bit.  What differs is who does what.  A wave issues its instructions in order, and one that both multiplies and loads pays
+// for each in turn: per 16-k step of a 64x64 tile on four waves 32 clocks of matrix core, about 13 for each operand read and 35-40 for
+// a load to LDS, whose issue waits for the CU's address path (16 clocks a load, shared by the four SIMDs), 890 clocks a slice of 128
+// where the load path needs 512 and the matrix cores 256.  Here kLoaderWaves further waves, one a SIMD, issue all of them, and the
+// others only read and multiply:
+// - a slice costs what is longer of the two, not the sum;
+// - the set-up of the addresses (0.25 us, 0.5 with general addressing) is the loaders' alone; beside it the others request bias
+//   and residual, which used to be requested before the last slice;
+// - with no loads of their own to count, the multiplying waves read a slice's first operands while they multiply the last ones of
+//   the slice before: one barrier a slice, behind its last operand read, says both that the next slice has arrived and that this one's
+//   stage may be loaded again.
+// Single launches, back to back, weights of 24 layers in turn, before -> now: 3x3 of 256 channels at 14x14 batch 16 10.1 -> 9.0 us (64x64,
+// slices of 128), 1x1 1024 -> 256 there 6.1 -> 5.4, 3x3 of 128 channels at 28x28 batch 8 6.7 -> 5.9, 1x1 128 -> 512 there at batch 1
+// 3.15 -> 2.81.  Whole EXECs: ResNet-152 batch 16 1175 -> 1145 us, ResNet-18 batch 8 132.6 -> 128.1, ResNet-50 batch 16 418.6 -> 411.4,
+// Inception 127x127 batch 5 115.5 -> 110.4.  Two loaders are as fast for 1x1 and 0.1-0.9 us slower for 3x3, one is slower everywhere; a
+// higher wave priority for them, or operands requested behind the first slice, cost 1-2 %.
+#pragma once
+#include "conv_dlds_body.h"
+
+namespace cw {
+
+constexpr int kLoaderWaves = 4;
+// Forms that have them: tiles of one or two wave groups.  Four groups put a multiplying wave of every group on a SIMD already, and with one step
+// a slice and group the loaders' own chain from barrier to barrier is the longer one: ResNet-18 64x64 batch 1 97.1 us without, 101.4 with
+// them (its 32x32 tiles on slices of 64 4.0 -> 4.6 us a launch), ResNet-50 batch 1 187 and 189.
+constexpr bool conv_has_loaders(int mode, bool fused, int kg) { return mode != MODE_STEM && !fused && kg <= 2; }
+
+// tile / tiles_n by a reciprocal from the host; 0: none (one channel tile, or too many tiles for it to be exact).
+inline uint32_t conv_tile_magic(unsigned tiles, unsigned tiles_n) {
+    return tiles_n > 1 && (unsigned long long)tiles * tiles_n < (1ull << 32) ? (uint32_t)((1ull << 32) / tiles_n) + 1u : 0u;
+}
+
+template <typename V>
+static __device__ __forceinline__ V lds_read(unsigned at) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) V *>((size_t)at);
+}
+
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, int KG, int MT>
+static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const int bid, const int nb_packed, const unsigned magic) {
+    constexpr int PARTS = MT == 16 ? (32 / BM) * (32 / BN) : 1, ROUND = MT == 16 ? 32 : BM;
+    const int nb = conv_nb_tiles(nb_packed) * PARTS, panel = conv_nb_panel(nb_packed);
+    static_assert(MODE == MODE_CONV || MODE == MODE_GEMM || MODE == MODE_TAIL, "");
+    typedef MfmaTile<T, MT> MF;
+    typedef typename MF::acc acc_t;
+    typedef typename Mfma<T>::v8 v8;
+    static_assert(MT == 32 || KG >= 4, "16x16 MFMA tiles: in wave groups");
+    static_assert((BK / MF::K) % KG == 0, "K groups: whole steps per group");
+    constexpr bool GEMM = MODE != MODE_CONV;
+    constexpr int CW = WARPS_M * WARPS_N * KG, NT = 64 * kLoaderWaves;
+    constexpr int WM = BM / WARPS_M, WN = BN / WARPS_N, TM = WM / MT, TN = WN / MT;
+    constexpr int CPR = BK / 8, RSTEP = NT / CPR;   // 16-byte chunks per LDS row; rows the loaders fetch together
+    static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/threads mismatch");
+    constexpr int X_PER = BM * CPR / NT, W_PER = BN * CPR / NT, LOADS = X_PER + W_PER;   // load instructions per loading thread per slice
+    constexpr unsigned STAGE = (BM + BN) * BK * 2u;
+    static_assert(NS >= 2 && NS <= 4 && (NS - 2) * LOADS < 64, "ring of 2..4 stages");
+    const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)cw_dyn_lds;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per = nb >> 3, rem = nb & 7, xcd = bid & 7;
+    const int tile_id = xcd * per + min(xcd, rem) + (bid >> 3);   // xcd_tile_id without branches
+    const int tiles_n = (a.Cout + BN - 1) / BN;
+    int tile_m, tile_n;
+    if (panel == 0) {   // uniform
+        tile_m = magic ? (int)__umulhi((unsigned)tile_id, magic) : tile_div(tile_id, tiles_n);
+        tile_n = tile_id - tile_m * tiles_n;
+    } else {   // panel after panel of tiles_n >> panel channel tiles, row by row inside a panel
+        const int pw = tiles_n >> panel;
+        const int pp = (a.M + ROUND - 1) / ROUND * (ROUND / BM) * pw;
+        const int p = tile_id / pp, r = tile_id - p * pp;
+        tile_m = r / pw;
+        tile_n = p * pw + (r - tile_m * pw);
+    }
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    if (MT == 16 && m0 >= a.M) return;   // the lower part of the last pixels' tile
+    const int ktiles = MODE == MODE_TAIL ? (a.K + BK - 1) / BK : a.K / BK;
+    const int kt0 = SPLITK ? blockIdx.y * a.ktiles_per_split : 0;
+    const int nsteps = (SPLITK ? min(ktiles, kt0 + a.ktiles_per_split) : ktiles) - kt0;   // at least one (checked by the launcher)
+    // Barriers: both kinds of waves meet at (general addressing) 1 behind the rows' arithmetic, 1 + nsteps around the slices, 1 in
+    // the wave groups' exchange and 2 in splitk_exchange.
+    constexpr bool ROWS_SHARED = MODE == MODE_CONV && X_PER > 1;
+
+    if (wave >= CW) {
+        // ---- the loading waves.  Piece j of a slice is LDS position lt + j*NT of the operand's [rows][CPR chunks] stage: row lt/CPR +
+        // j*RSTEP, chunk position lt%CPR, holding logical chunk lt%CPR ^ key(row).
+        const int lt = tid - CW * 64, lw = wave - CW;
+        const unsigned row = (unsigned)lt / CPR, pc = (unsigned)lt % CPR;
+        unsigned chunk[2];   // the key is the same for every other step of RSTEP rows
+#pragma unroll
+        for (int q = 0; q < 2; ++q) chunk[q] = pc ^ (unsigned)swz_key<BK>((int)row + q * RSTEP);
+        const unsigned ldx2 = (unsigned)conv_ldx(a) * 2u, k2 = (unsigned)a.K * 2u;
+        // Rows past M (1x1) or Cout begin at or past the buffers' ends, where loads return zeros.
+        const u32x4 dw = make_desc(a.w, (unsigned)a.Cout * k2);
+        unsigned w_off[W_PER];
+        const unsigned w_row0 = (unsigned)n0 * k2 + row * k2;
+#pragma unroll
+        for (int j = 0; j < W_PER; ++j) w_off[j] = w_row0 + (unsigned)(j * RSTEP) * k2 + (chunk[j & 1] << 4);
+        const unsigned dst0 = lds_base + (unsigned)lw * 1024u;
+        const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)
+        auto beyond = [&](int j) { return MODE == MODE_TAIL && (int)chunk[j & 1] * 8 >= k_last; };   // piece j is not in the last slice
+        unsigned kb = (unsigned)kt0 * (BK * 2u);   // byte offset of the next slice within a weight row
+        bool part = false;                         // it is the last, part of a slice (MODE_TAIL)
+        auto load_w = [&](int j, unsigned stage_at) { load_to_lds(dw, part && beyond(j) ? kOob : w_off[j], kb, stage_at + BM * BK * 2u + j * (NT * 16u)); };
+        // with general addressing the first slice's weights need none of the pixel arithmetic
+        if constexpr (!GEMM) {
+#pragma unroll
+            for (int j = 0; j < W_PER; ++j) load_w(j, dst0);
+        }
+        // The activation buffer is described from the top-left tap's offset before its start, so that centre offset (per thread) + tap and
+        // channel offset (uniform) is never negative.  x may be the first Cin channels of a wider tensor.
+        const int pad_h = GEMM ? 0 : conv_pad_h(a), pad_w = GEMM ? 0 : conv_pad_w(a);
+        const unsigned x_bytes = ((GEMM ? (unsigned)a.M : (unsigned)a.B * a.H * a.W) - 1u) * ldx2 + (unsigned)a.Cin * 2u;
+        const unsigned x_shift = GEMM ? 0u : (unsigned)(pad_h * a.W + pad_w) * ldx2;
+        const u32x4 dx = make_desc(static_cast<const char *>(a.x) - x_shift, x_bytes + x_shift);
+        unsigned x_off[X_PER], x_mask[X_PER];   // byte offset at the filter's centre pixel; the taps inside the image (bit r*kw+s)
+        if constexpr (GEMM) {
+            const unsigned x_row0 = (unsigned)m0 * ldx2 + row * ldx2;
+#pragma unroll
+            for (int j = 0; j < X_PER; ++j) x_off[j] = x_row0 + (unsigned)(j * RSTEP) * ldx2 + (chunk[j & 1] << 4);
+        } else {
+            auto pixel_row = [&](unsigned m) {
+                const unsigned t = fast_div(m, a.wo_div), n = fast_div(t, a.ho_div);
+                const int iwc = (int)(m - t * (unsigned)a.Wo) * a.stride, ihc = (int)(t - n * (unsigned)a.Ho) * a.stride;
+                const int r_lo = max(0, pad_h - ihc), r_hi = min(a.kh, a.H + pad_h - ihc);
+                const int s_lo = max(0, pad_w - iwc), s_hi = min(a.kw, a.W + pad_w - iwc);
+                // in-range columns s_lo..s_hi-1 replicated into every in-range filter row r_lo..r_hi-1: a multiplication by the
+                // rows' unit bits (no carries: cols < 2^kw)
+                unsigned row_units = 0;   // bit r*kw for every filter row r
+                for (int r = 0; r < a.kh; ++r) row_units |= 1u << (r * a.kw);
+                const unsigned cols = ((1u << s_hi) - 1u) & ~((1u << s_lo) - 1u);
+                const unsigned rows = row_units & (unsigned)((1ull << (r_hi * a.kw)) - 1ull) & ~((1u << (r_lo * a.kw)) - 1u);
+                return u32x2{(unsigned)((n * a.H + ihc) * a.W + iwc) * ldx2, m < (unsigned)a.M ? cols * rows : 0u};
+            };
+            if constexpr (!ROWS_SHARED) {
+                const u32x2 ri = pixel_row((unsigned)m0 + row);
+                x_off[0] = ri.x + (chunk[0] << 4);
+                x_mask[0] = ri.y;
+            } else {
+                // once per tile row, by thread `row`, and through LDS to the threads that load the row's chunks
+                __shared__ u32x2 s_row[BM];
+                static_assert(NT >= BM, "one thread per tile row");
+                if (lt < BM) s_row[lt] = pixel_row((unsigned)(m0 + lt));
+                wait_lds_and_barrier();
+#pragma unroll
+                for (int j = 0; j < X_PER; ++j) {
+                    const u32x2 ri = s_row[row + j * RSTEP];
+                    x_off[j] = ri.x + (chunk[j & 1] << 4);
+                    x_mask[j] = ri.y;
+                }
+            }
+        }
+        // (r, s, c0) of the next slice: k0 = kt*BK = (r*kw + s)*Cin + c0
+        int fr = 0, fs = 0, fc0 = 0;
+        if (SPLITK && !GEMM) {
+            const int rs = kt0 * BK / a.Cin;
+            fc0 = kt0 * BK - rs * a.Cin;
+            fr = rs / a.kw;
+            fs = rs - fr * a.kw;
+        }
+        unsigned soff = GEMM ? kb : ((unsigned)(fr * a.W + fs) * (unsigned)conv_ldx(a) + (unsigned)fc0) * 2u, tbit = GEMM ? 1u : 1u << (fr * a.kw + fs);
+        int kt = 0;   // slices issued
+        auto issue = [&](unsigned stage, bool with_w) {
+            const unsigned at = dst0 + stage * STAGE;
+            if (MODE == MODE_TAIL) part = kt0 + kt == ktiles - 1;
+#pragma unroll
+            for (int j = 0; j < X_PER; ++j)
+                load_to_lds(dx, (GEMM ? part && beyond(j) : (x_mask[j] & tbit) == 0u) ? kOob : x_off[j], soff, at + j * (NT * 16u));
+            if (with_w) {
+#pragma unroll
+                for (int j = 0; j < W_PER; ++j) load_w(j, at);
+            }
+            ++kt;
+            kb += BK * 2u;
+            if constexpr (GEMM) {
+                soff = kb;
+            } else {
+                fc0 += BK;
+                if (fc0 == a.Cin) {
+                    fc0 = 0;
+                    if (++fs == a.kw) { fs = 0; ++fr; }
+                }
+                soff = ((unsigned)(fr * a.W + fs) * (unsigned)conv_ldx(a) + (unsigned)fc0) * 2u;
+                tbit = 1u << (fr * a.kw + fs);
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < NS - 1; ++u)
+            if (u < nsteps) issue(u, GEMM || u > 0);
+        // Slice i has arrived when at most the loads of the slices behind it are outstanding.  Behind barrier i the stage of slice i - 1
+        // (no one's for i = 0) is free for slice i + NS - 1.
+        unsigned fill = NS - 1;
+        int i = 0;
+        for (; i + NS - 1 < nsteps; ++i) {
+            wait_loads_and_barrier<(NS - 2) * LOADS>();
+            issue(fill, true);
+            fill = fill + 1 == NS ? 0 : fill + 1;
+        }
+        if (NS >= 4 && i + 2 < nsteps) { wait_loads_and_barrier<2 * LOADS>(); ++i; }
+        if (NS >= 3 && i + 1 < nsteps) { wait_loads_and_barrier<LOADS>(); ++i; }
+        wait_loads_and_barrier<0>();
+        wait_lds_and_barrier();   // the last slice is read
+        if constexpr (KG > 1) wait_lds_and_barrier();
+        if constexpr (SPLITK && KG == 1) { wait_lds_and_barrier(); wait_lds_and_barrier(); }
+        return;
+    }
+
+    // ---- the multiplying waves
+    const int kg = wave / (WARPS_M * WARPS_N), wq = wave - kg * (WARPS_M * WARPS_N);
+    const int wm0 = (wq / WARPS_N) * WM, wn0 = (wq % WARPS_N) * WN;
+    const int lrow = lane & (MT - 1), lhalf = lane / MT;
+    const EpiPos pos{m0, n0, wm0, wn0, lrow, lhalf};
+    EpiOperands<TM, TN> eo;
+    GroupOperands<MT, TM, TN, KG> go;
+    if constexpr (!SPLITK) {
+        if constexpr (KG > 1) group_epilogue_load<MT, TM, TN, KG>(go, a, pos, kg);
+        else epilogue_load<TM, TN>(eo, a, pos);
+    }
+    acc_t acc[TM][TN];  // [pixel tile][channel tile]; MFMA rows = channels, columns = pixels
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < MF::REGS; ++e) acc[i][j][e] = 0.f;
+    // Operands are read LA of the wave's steps ahead, four matrix instructions of 64x64 wave tiles or three steps of smaller ones.
+    constexpr int KK = BK / MF::K / KG;   // steps of a slice that are this wave's: kg, kg + KG, ...
+    constexpr int DEPTH0 = TM * TN >= 4 ? 2 : 4, DEPTH = KK >= DEPTH0 ? DEPTH0 : KK > 1 ? KK : 2, LA = DEPTH - 1;
+    static_assert(KK == 1 || KK % DEPTH == 0, "");
+    // The key is the same for all of a wave's tiles: MT rows are whole periods of it.
+    const unsigned xkey = (unsigned)swz_key<BK>(wm0 + lrow), wkey = (unsigned)swz_key<BK>(wn0 + lrow);
+    const unsigned xo = lds_base + (unsigned)(wm0 + lrow) * (BK * 2u), wo = lds_base + (unsigned)(BM + wn0 + lrow) * (BK * 2u);
+    unsigned xc[KK], wc[KK];
+#pragma unroll
+    for (int t = 0; t < KK; ++t) {
+        const unsigned c = (unsigned)((kg + t * KG) * (MF::K / 8) + lhalf);
+        xc[t] = xo + ((c ^ xkey) << 4);
+        wc[t] = wo + ((c ^ wkey) << 4);
+    }
+    v8 fx[DEPTH][TM], fw[DEPTH][TN];
+    auto fetch = [&](unsigned stage, int t, v8 (&qx)[TM], v8 (&qw)[TN]) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) qx[i] = lds_read<v8>(xc[t] + stage * STAGE + i * (MT * BK * 2u));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) qw[j] = lds_read<v8>(wc[t] + stage * STAGE + j * (MT * BK * 2u));
+    };
+    if constexpr (ROWS_SHARED) wait_lds_and_barrier();
+    wait_lds_and_barrier();   // the first slice is there
+#pragma unroll
+    for (int t = 0; t < LA && t < KK; ++t) fetch(0, t, fx[t], fw[t]);
+    unsigned stage = 0;
+    for (int kt = 0; kt < nsteps; ++kt) {
+        const unsigned next = stage + 1 == NS ? 0 : stage + 1;
+#pragma unroll
+        for (int t = 0; t < KK; ++t) {
+            if (t + LA < KK) {
+                fetch(stage, t + LA, fx[(t + LA) % DEPTH], fw[(t + LA) % DEPTH]);
+            } else {
+                // the slice's last operands are in registers: its stage is free, the next slice is there
+                if (t + LA == KK) wait_lds_and_barrier();
+                if (kt + 1 < nsteps) fetch(next, t + LA - KK, fx[(t + LA) % DEPTH], fw[(t + LA) % DEPTH]);
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fw[t % DEPTH][j], fx[t % DEPTH][i], acc[i][j]);
+            if constexpr (KK == 1) {   // one step a slice, read one ahead
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fx[0][i] = fx[1][i];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) fw[0][j] = fw[1][j];
+            }
+        }
+        stage = next;
+    }
+    // Every wave is behind the last slice's barrier: the ring is free.
+    if constexpr (KG > 1) {
+        static_assert(KG * BM * BN * 4 <= NS * (int)STAGE, "K-group exchange does not fit the ring");
+        float *xch = reinterpret_cast<float *>(cw_dyn_lds);
+        group_exchange_write<MT, TM, TN, KG, WARPS_M * WARPS_N>(acc, xch, kg, wq, lane);
+        wait_lds_and_barrier();
+        typedef GroupUnits<MT, TM, TN, KG> G;
+        if (kg * G::UPG >= G::UNITS) return;   // more groups than units
+        float4 sum[G::UPG];
+        group_sum<MT, TM, TN, KG, WARPS_M * WARPS_N>(xch, sum, kg, wq, lane);
+        if constexpr (SPLITK) {
+            group_epilogue_load<MT, TM, TN, KG>(go, a, pos, kg);   // here behind the partial sums' way out
+            if (!group_splitk<MT, TM, TN, KG>(a, pos, sum, kg, lane, a.counters + tile_id * CW + wave)) return;
+        }
+        group_epilogue_store<T, MT, TM, TN, KG>(sum, go, a, pos, kg);
+    } else {
+        if constexpr (SPLITK) {
+            if (!splitk_exchange<TM, TN>(acc, a, pos, tile_id)) return;
+            epilogue_load<TM, TN>(eo, a, pos);
+        }
+        epilogue_store<T, TM, TN>(acc, eo, a, pos);
+    }
+}
+
+}  // namespace cw

@@ -13,15 +13,15 @@ namespace cw {
 struct alignas(64) ConvLines { unsigned long long v[16]; };   // of each its first two argument lines, which hold all it reads
 static_assert(offsetof(ConvArgs, khp) == sizeof(ConvLines), "argument lines");
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int KG, int MT>
-__global__ __launch_bounds__(64 * WARPS_M * WARPS_N * KG) void conv_dlds_pair_kernel(const ConvLines l0, const ConvLines l1) {
+__global__ __launch_bounds__((conv_threads<WARPS_M, WARPS_N, KG, MODE_CONV, false>())) void conv_dlds_pair_kernel(const ConvLines l0, const ConvLines l1) {
     ConvArgs a0, a1;
     __builtin_memcpy(&a0, &l0, sizeof l0);
     __builtin_memcpy(&a1, &l1, sizeof l1);
     const int nb0 = conv_nb_tiles(a0.nb) * conv_parts<BM, BN, MT>();
     if ((int)blockIdx.x < nb0)
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, false, MT>(a0, blockIdx.x, a0.nb);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, MT>(a0, blockIdx.x, a0.nb, 0u);
     else
-        conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, false, MT>(a1, blockIdx.x - nb0, a1.nb);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, MT>(a1, blockIdx.x - nb0, a1.nb, 0u);
 }
 
 template <typename T, int BM, int BN, int MODE, int KG>
@@ -41,7 +41,7 @@ static hipError_t launch_fused_one(const ConvArgs &a_in, hipStream_t s) {
     if (a.w3 && BN / (2 * KG) < 32) return hipErrorInvalidValue;   // the third layer needs whole 32-channel tiles per wave
     ConvRest<MODE, false, true> rest;
     rest.pack(a);
-    kern<<<dim3((a.M + BM - 1) / BM, 1, 1), 256 * KG, need, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), a.nb, a.relu, rest CW_STAMP_PASS);
+    kern<<<dim3((a.M + BM - 1) / BM, 1, 1), 256 * KG, need, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), conv_pack_relu(a), 0u, rest CW_STAMP_PASS);
     return hipGetLastError();
 }
 
@@ -98,7 +98,7 @@ static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, 
     auto kern = conv_dlds_pair_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, KG, MT>;
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
     if (attr != hipSuccess) return attr;
-    const size_t used = std::max((size_t)std::min(NS, std::max(a0.ktiles_per_split, a1.ktiles_per_split)) * stage_bytes, (size_t)(KG >= 4 ? KG : KG - 1) * BM * BN * 4);
+    const size_t used = std::max((size_t)std::min(NS, std::max(a0.ktiles_per_split, a1.ktiles_per_split)) * stage_bytes, (size_t)(KG > 1 ? KG : 0) * BM * BN * 4);
     constexpr int TM = MT == 16 ? 32 : BM, TN = MT == 16 ? 32 : BN;
     const unsigned nb0 = ((a0.M + TM - 1) / TM) * ((a0.Cout + TN - 1) / TN), nb1 = ((a1.M + TM - 1) / TM) * ((a1.Cout + TN - 1) / TN);
     if (!conv_panel_ok(a0, TN, nb0) || !conv_panel_ok(a1, TN, nb1)) return hipErrorInvalidValue;
@@ -107,7 +107,7 @@ static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, 
     ConvLines l0, l1;
     memcpy(&l0, &a0, sizeof l0);
     memcpy(&l1, &a1, sizeof l1);
-    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), 64 * WARPS_M * WARPS_N * KG, used, s>>>(l0, l1);
+    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), conv_threads<WARPS_M, WARPS_N, KG, MODE_CONV, false>(), used, s>>>(l0, l1);
     return hipGetLastError();
 }
 
