@@ -226,10 +226,12 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < MF::REGS; ++e) acc[i][j][e] = 0.f;
-    // Operands are read LA of the wave's steps ahead, four matrix instructions of 64x64 wave tiles or three steps of smaller ones.
-    constexpr int KK = BK / MF::K / KG;   // steps of a slice that are this wave's: kg, kg + KG, ...
-    constexpr int DEPTH0 = TM * TN >= 4 ? 2 : 4, DEPTH = KK >= DEPTH0 ? DEPTH0 : KK > 1 ? KK : 2, LA = DEPTH - 1;
-    static_assert(KK == 1 || KK % DEPTH == 0, "");
+    // A slice is multiplied in two halves.  While the first is, the second's operands are read, and behind the barrier, while the second is,
+    // those of the next slice's first half: every read has half a slice of matrix instructions to arrive in.  The order is pinned: left to the
+    // compiler a step waited for the reads just issued for a later one, 9.25 against 9.10 us for 3x3 of 256 channels at 14x14 batch 16, 7.88 and
+    // 7.65 of 64 at 56x56 batch 8, 1x1 1024 -> 512 at 14x14 batch 16 (slices of 64) 9.8 and 9.4; two wave groups the same either way.
+    constexpr int KK = BK / MF::K / KG, HK = KK / 2;   // steps of a slice that are this wave's: kg, kg + KG, ...
+    static_assert(KK % 2 == 0, "halves of whole steps");
     // The key is the same for all of a wave's tiles: MT rows are whole periods of it.
     const unsigned xkey = (unsigned)swz_key<BK>(wm0 + lrow), wkey = (unsigned)swz_key<BK>(wn0 + lrow);
     const unsigned xo = lds_base + (unsigned)(wm0 + lrow) * (BK * 2u), wo = lds_base + (unsigned)(BM + wn0 + lrow) * (BK * 2u);
@@ -240,38 +242,38 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
         xc[t] = xo + ((c ^ xkey) << 4);
         wc[t] = wo + ((c ^ wkey) << 4);
     }
-    v8 fx[DEPTH][TM], fw[DEPTH][TN];
-    auto fetch = [&](unsigned stage, int t, v8 (&qx)[TM], v8 (&qw)[TN]) {
+    v8 fx[KK][TM], fw[KK][TN];
+    auto fetch = [&](unsigned stage, int t) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) qx[i] = lds_read<v8>(xc[t] + stage * STAGE + i * (MT * BK * 2u));
+        for (int i = 0; i < TM; ++i) fx[t][i] = lds_read<v8>(xc[t] + stage * STAGE + i * (MT * BK * 2u));
 #pragma unroll
-        for (int j = 0; j < TN; ++j) qw[j] = lds_read<v8>(wc[t] + stage * STAGE + j * (MT * BK * 2u));
+        for (int j = 0; j < TN; ++j) fw[t][j] = lds_read<v8>(wc[t] + stage * STAGE + j * (MT * BK * 2u));
     };
     if constexpr (ROWS_SHARED) wait_lds_and_barrier();
     wait_lds_and_barrier();   // the first slice is there
 #pragma unroll
-    for (int t = 0; t < LA && t < KK; ++t) fetch(0, t, fx[t], fw[t]);
+    for (int t = 0; t < HK; ++t) {
+        fetch(0, t);
+        __builtin_amdgcn_sched_barrier(0);   // in this order: the loop's waits count the reads behind a step's
+    }
     unsigned stage = 0;
     for (int kt = 0; kt < nsteps; ++kt) {
-        const unsigned next = stage + 1 == NS ? 0 : stage + 1;
+        const bool more = kt + 1 < nsteps;   // behind the last slice its first half is read again: no branch, whose two sides would wait for all reads
+        const unsigned next = !more ? stage : stage + 1 == NS ? 0 : stage + 1;
 #pragma unroll
-        for (int t = 0; t < KK; ++t) {
-            if (t + LA < KK) {
-                fetch(stage, t + LA, fx[(t + LA) % DEPTH], fw[(t + LA) % DEPTH]);
-            } else {
-                // the slice's last operands are in registers: its stage is free, the next slice is there
-                if (t + LA == KK) wait_lds_and_barrier();
-                if (kt + 1 < nsteps) fetch(next, t + LA - KK, fx[(t + LA) % DEPTH], fw[(t + LA) % DEPTH]);
-            }
+        for (int h = 0; h < 2; ++h) {
+            if (h == 1) wait_lds_and_barrier();   // the slice's last operands are in registers: its stage is free, the next slice is there
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int t = 0; t < HK; ++t) {
+                // two steps' reads with one step's instructions, so that the half ends with none just issued
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fw[t % DEPTH][j], fx[t % DEPTH][i], acc[i][j]);
-            if constexpr (KK == 1) {   // one step a slice, read one ahead
+                for (int u = 2 * t; u < 2 * t + 2 && u < HK; ++u) fetch(h ? next : stage, h ? u : HK + u);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < TM; ++i) fx[0][i] = fx[1][i];
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) fw[0][j] = fw[1][j];
+                    for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fw[h * HK + t][j], fx[h * HK + t][i], acc[i][j]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         stage = next;
