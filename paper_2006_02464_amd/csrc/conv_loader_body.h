@@ -15,8 +15,8 @@
 //   stage may be loaded again.
 // Single launches, back to back, weights of 24 layers in turn, before -> now: 3x3 of 256 channels at 14x14 batch 16 10.1 -> 9.0 us (64x64,
 // slices of 128), 1x1 1024 -> 256 there 6.1 -> 5.4, 3x3 of 128 channels at 28x28 batch 8 6.7 -> 5.9, 1x1 128 -> 512 there at batch 1
-// 3.15 -> 2.81.  Whole EXECs: ResNet-152 batch 16 1175 -> 1145 us, ResNet-18 batch 8 132.6 -> 128.1, ResNet-50 batch 16 418.6 -> 411.4,
-// Inception 127x127 batch 5 115.5 -> 110.4.  Two loaders are as fast for 1x1 and 0.1-0.9 us slower for 3x3, one is slower everywhere; a
+// 3.15 -> 2.81.  Whole EXECs: ResNet-152 batch 16 1161 -> 1120 us, ResNet-18 batch 8 132.2 -> 126.9, ResNet-50 batch 16 397.2 -> 391.4,
+// Inception 127x127 batch 5 114.2 -> 109.9.  Two loaders are as fast for 1x1 and 0.1-0.9 us slower for 3x3, one is slower everywhere; a
 // higher wave priority for them, or operands requested behind the first slice, cost 1-2 %.
 #pragma once
 #include "conv_dlds_body.h"

@@ -124,3 +124,31 @@ def test_chosen_tiles_at_ragged_sizes(worker, hw, batch):
             o = OPS[l["op_index"]]
             assert (o[1] % l["tile_k"] == 0 or (o[3] == 1 and l["tile_k"] == 64)) and l["tile_n"] <= max(32, l["gemm_n"])
             assert l["grid_x"] == -(-l["gemm_m"] // l["tile_m"]) * -(-l["gemm_n"] // l["tile_n"])
+
+
+# Tiles of one and two wave groups, whose loads are issued by waves of their own: one to four channel slices of a filter's tap, 3x3 and 5x5 filters, strides,
+# 1x1 whose K is one, two and several slices (fewer than the ring has stages, and more), Cout beside a tile's width, residuals, K whole and split inside and between taps.
+LOADER_TILES = {"128x64": 1, "64x64": 2, "64x32": 3, "32x32": 5, "256x64": 8, "128x128w8": 9, "128x64k128": 10, "64x64k128": 11, "128x64k128g2": 15, "64x64k128g2": 16, "64x64g2": 23}
+LOADER_OPS = [
+    O(T.CONV, 3, 64, 7, 7, 2, 3, 1, -1, -1),
+    O(T.CONV, 64, 128, 3, 3, 1, 1, 1, -1, 0),
+    O(T.CONV, 128, 256, 3, 3, 1, 1, 1, -1, 1),
+    O(T.CONV, 256, 256, 5, 5, 1, 2, 1, -1, 2),
+    O(T.CONV, 256, 256, 3, 3, 1, 1, 0, 2, 3),
+    O(T.CONV, 256, 128, 3, 3, 1, 1, 1, -1, 4),
+    O(T.CONV, 128, 512, 3, 3, 2, 1, 1, -1, 5),
+    O(T.CONV, 512, 384, 3, 3, 1, 1, 1, -1, 6),
+    O(T.CONV, 384, 96, 3, 3, 1, 1, 1, -1, 7),
+    O(T.CONV, 96, 256, 1, 1, 1, 0, 1, -1, 8),
+    O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 9),
+    O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 10),
+    O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 11),
+]
+
+
+@pytest.mark.parametrize("name", sorted(LOADER_TILES))
+@pytest.mark.parametrize("hw,batch,split_k,dtype", [(45, 2, 1, "fp16"), (27, 1, 3, "bf16"), (4, 1, 1, "fp16")])
+def test_tiles_with_loading_waves(worker, name, hw, batch, split_k, dtype):
+    if split_k > 1 and name in ("256x64", "128x128w8"):
+        split_k = 1
+    run(worker, hw, dtype, batch, LOADER_TILES[name], split_k, LOADER_OPS)
