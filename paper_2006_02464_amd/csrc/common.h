@@ -323,8 +323,8 @@ struct TileDim {
     int parts() const { return (bm / pm) * (bn / pn); }
 };
 TileDim conv_tile_dim(ConvTile t);
-// Split-K arrival counters of an output tile: one, or one per multiplying wave where wave groups finish the tile together.
-inline int conv_counters_per_tile(ConvTile t) { const TileDim d = conv_tile_dim(t); return d.kg > 1 ? d.parts() * (d.threads / 64) : 1; }
+// Split-K arrival counters of an output tile: one, or one per wave where the wave groups finish the tile together.
+inline int conv_counters_per_tile(ConvTile t) { const TileDim d = conv_tile_dim(t); return d.kg >= 4 ? d.parts() * (d.threads / 64) : 1; }
 // The same tile with K slices of 64 (for shapes a k128 tile cannot take).
 ConvTile conv_tile_k64(ConvTile t);
 // The same tile with one group of waves (split-K needs that).

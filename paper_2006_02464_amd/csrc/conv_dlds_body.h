@@ -1,7 +1,7 @@
 // Implicit-GEMM convolution on gfx950 MFMA whose K slices travel global -> LDS directly: the
-// per-tile body of tiles in four and more wave groups, the first convolution's form and the fused form (kernels_conv_dlds.hip) and of the
-// resident multi-layer kernel (kernels_resident.hip); the other forms of the per-layer kernels have waves that only load
-// (conv_loader_body.h).
+// per-tile body, shared by the per-layer kernels (kernels_conv_dlds.hip) and the resident
+// multi-layer kernel (kernels_resident.hip).  Many tiles of one and two wave groups have a second body whose loads are issued by waves
+// of their own (conv_loader_body.h).
 //
 // Same GEMM view, weight layout, LDS swizzle, MFMA roles and epilogue as the register-staged
 // kernel (kernels_conv.hip), for Cin % 64 == 0 (K slices of 64, or of 128 when Cin % 128 == 0
@@ -103,8 +103,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     typedef MfmaTile<T, MT> MF;
     typedef typename MF::acc acc_t;
     static_assert(MT == 32 || (KG >= 4 && !FUSED && MODE != MODE_STEM), "16x16 MFMA tiles: plain form in wave groups");
-    static_assert(KG == 1 || ((BK / MF::K) % KG == 0 && (FUSED ? KG == 2 : KG >= 4)), "K groups: whole steps per group");
-    static_assert(MODE != MODE_TAIL, "conv_loader_body's");
+    static_assert(KG == 1 || ((BK / MF::K) % KG == 0 && (!FUSED || KG == 2)), "K groups: whole steps per group");
     static_assert(!FUSED || (!SPLITK && MODE != MODE_STEM && (BN == 64 || BN == 128)), "fused form: whole first layer in one tile");
     constexpr int NT = 64 * WARPS_M * WARPS_N * KG;
     constexpr int WM = BM / WARPS_M, WN = BN / WARPS_N;
@@ -169,9 +168,9 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     if (MT == 16 && m0 >= a.M) return;   // the lower part of the last pixels' tile
 
-    constexpr bool GEMM = MODE == MODE_GEMM;
+    constexpr bool GEMM = MODE == MODE_GEMM || MODE == MODE_TAIL;
     // a first convolution's filter rows beyond kh are padding
-    const int ktiles = MODE == MODE_STEM ? (a.kh + 1) / 2 : a.K / BK;
+    const int ktiles = MODE == MODE_STEM ? (a.kh + 1) / 2 : MODE == MODE_TAIL ? (a.K + BK - 1) / BK : a.K / BK;
     const int kt0 = SPLITK ? blockIdx.y * a.ktiles_per_split : 0;
     const int kt1 = SPLITK ? min(ktiles, kt0 + a.ktiles_per_split) : ktiles;  // no split: the whole K
     const int nsteps = kt1 - kt0;
@@ -193,7 +192,8 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     // MobileNet, whose convolutions are 1x1, is the same either way.  (All weights of the prologue there make the
     // first slice wait for the later ones': ResNet-18 3 % slower.)
     constexpr bool WFIRST = !GEMM;
-    unsigned w_off[W_PER];
+    const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)
+    unsigned w_off[W_PER], w_last = 0;   // bit j of w_last: piece j is also in the last slice (MODE_TAIL)
 #pragma unroll
     for (int j = 0; j < W_PER; ++j) {
         const int cid = tid + j * NT;
@@ -201,6 +201,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         const int c = (cid % CPR) ^ swz_key<BK>(row);
         const int n = n0 + row;
         w_off[j] = n < a.Cout ? ((unsigned)n * a.K + c * 8) * 2u : kOob;
+        if (MODE == MODE_TAIL && c * 8 < k_last) w_last |= 1u << j;
     }
     if constexpr (WFIRST) {
         if (nsteps > 0) {   // uniform
@@ -223,7 +224,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
             const int c = (cid % CPR) ^ swz_key<BK>(row);
             const unsigned m = m0 + row;
             x_voff[j] = m * ldx * 2u + c * 16u;
-            x_mask[j] = m < (unsigned)a.M ? 1u : 0u;
+            x_mask[j] = m < (unsigned)a.M ? (MODE == MODE_TAIL && c * 8 < k_last ? 3u : 1u) : 0u;   // bit 1: also in the last slice
         }
     } else {
         // The pixel arithmetic (two divisions and the tap mask) is done once per tile row, by
@@ -295,7 +296,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         is_soff = GEMM                ? (unsigned)fc0 * 2u
                   : MODE == MODE_STEM ? (unsigned)kt * (2u * a.W * 8u)
                                       : ((unsigned)(fr * a.W + fs) * ldx + (unsigned)fc0) * 2u;
-        is_tbit = MODE == MODE_CONV ? (1u << (fr * a.kw + fs)) : 1u;
+        is_tbit = MODE == MODE_CONV ? (1u << (fr * a.kw + fs)) : MODE == MODE_TAIL && kt == ktiles - 1 ? 2u : 1u;
         is_dst = lds_base + (unsigned)stage * STAGE_BYTES + (unsigned)wave * 1024u;
         is_kb = (unsigned)kt * (BK * 2u);
     };
@@ -303,7 +304,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         if (idx < X_PER)
             load_to_lds(dx, (x_mask[idx] & is_tbit) ? x_voff[idx] : kOob, is_soff, is_dst + idx * (NT * 16));
         else
-            load_to_lds(dw, w_off[idx - X_PER], is_kb, is_dst + BM * BK * 2 + (idx - X_PER) * (NT * 16));
+            load_to_lds(dw, MODE == MODE_TAIL && is_tbit == 2u && !(w_last >> (idx - X_PER) & 1u) ? kOob : w_off[idx - X_PER], is_kb, is_dst + BM * BK * 2 + (idx - X_PER) * (NT * 16));
     };
     auto issue_end = [&]() {
         fc0 += BK;
@@ -368,7 +369,8 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     };
 
     const EpiPos pos{m0, n0, wm0, wn0, lrow, lhalf};
-    // Wave groups finish the tile together.
+    // Four and eight groups finish the tile together.  Two (128x64, 64x64) keep one finishing group, which moves half as
+    // much through LDS.
     constexpr bool SHARED = KG >= 4 && !FUSED;
     EpiOperands<TM, TN> eo;
     GroupOperands<MT, TM, TN, KG> go;
@@ -437,6 +439,35 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         group_epilogue_store<T, MT, TM, TN, KG>(sum, go, a, pos, kg);
         return;
     } else {
+    if constexpr (KG > 1 && !FUSED) {
+        // Groups 1.. hand their accumulators to group 0 through LDS (the ring is free once every
+        // wave has passed the barrier); group 0 adds them in group order and goes on alone.
+        static_assert((KG - 1) * BM * BN * 4 <= NS * (int)STAGE_BYTES, "K-group exchange does not fit the ring");
+        float *xch = reinterpret_cast<float *>(cw_dyn_lds);
+        wait_lds_loads_and_barrier<0>();
+        if (kg > 0) {
+            float *dst = xch + ((kg - 1) * (WARPS_M * WARPS_N) + wq) * (TM * TN * 16 * 64) + lane;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) dst[((i * TN + j) * 16 + e) * 64] = acc[i][j][e];
+        }
+        wait_lds_loads_and_barrier<0>();
+        if (kg > 0) return;
+#pragma unroll
+        for (int g = 1; g < KG; ++g) {
+            const float *src = xch + ((g - 1) * (WARPS_M * WARPS_N) + wq) * (TM * TN * 16 * 64) + lane;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] += src[((i * TN + j) * 16 + e) * 64];
+        }
+    }
+
     if constexpr (FUSED) {
         // ---- second layer: y[m][:] = act2(res[m][:] + bias2 + W2 * p[m][:]),  p = act(acc + bias) ----
         // BN == Cout: the tile holds every channel of its BM pixels, so the 1x1 convolution that

@@ -90,20 +90,20 @@ struct ConvRest<MODE, false, true> : ConvArgs {   // the fused form reads all of
     __device__ __forceinline__ void unpack(ConvArgs &a) const { a = *this; }
 };
 
-template <int BM, int BN, int WARPS_M, int WARPS_N, int KG, int MODE, bool FUSED>
+template <int BM, int BN, int WARPS_M, int WARPS_N, int KG, int MODE, bool SPLITK, bool FUSED>
 constexpr int conv_threads() {
-    return 64 * (WARPS_M * WARPS_N * KG + (conv_has_loaders(MODE, FUSED, BM, BN, WARPS_M * WARPS_N * KG, KG) ? kLoaderWaves : 0));
+    return 64 * (WARPS_M * WARPS_N * KG + (conv_has_loaders(MODE, SPLITK, FUSED, BM, BN, WARPS_M * WARPS_N * KG, KG) ? kLoaderWaves : 0));
 }
 
 // The tile on the body that is the form's.
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED, int KG, int MT>
 static __device__ __forceinline__ void conv_body(const ConvArgs &a, const int bid, const int nb, const unsigned magic) {
-    if constexpr (conv_has_loaders(MODE, FUSED, BM, BN, WARPS_M * WARPS_N * KG, KG)) conv_loader_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, KG, MT>(a, bid, nb, magic);
+    if constexpr (conv_has_loaders(MODE, SPLITK, FUSED, BM, BN, WARPS_M * WARPS_N * KG, KG)) conv_loader_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, KG, MT>(a, bid, nb, magic);
     else conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, bid, nb);
 }
 
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, int MT = 32>
-__global__ __launch_bounds__((conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE, FUSED>())) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
+__global__ __launch_bounds__((conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE, SPLITK, FUSED>())) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
                                                                                  int M, int K, int cout_ldy, int cin_ldx, unsigned nb_relu, unsigned magic,
                                                                                  const ConvRest<MODE, SPLITK, FUSED> rest CW_STAMP_ARG) {
     CW_STAMP_BEGIN
@@ -169,7 +169,6 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     a.nb = conv_pack_nb((int)grid.x, a.panel_log2);
     if (MODE == MODE_TAIL ? a.nz > 1 : a.K % BK != 0 && MODE != MODE_STEM) return hipErrorInvalidValue;
     if (!SPLITK && a.ktiles_per_split != (MODE == MODE_STEM ? (a.kh + 1) / 2 : (a.K + BK - 1) / BK)) return hipErrorInvalidValue;  // the kernel walks the whole K
-    if (SPLITK && (long long)(a.split_k - 1) * a.ktiles_per_split >= (MODE == MODE_STEM ? (a.kh + 1) / 2 : (a.K + BK - 1) / BK)) return hipErrorInvalidValue;   // no split is empty
     if (a.nz > 1 && (MT != 32 || MODE != MODE_GEMM || SPLITK || a.bias || a.res || grid.z != (unsigned)a.nz)) return hipErrorInvalidValue;
     constexpr unsigned PARTS = conv_parts<BM, BN, MT>();
     if (a.nz <= 1 && grid.z != PARTS) return hipErrorInvalidValue;
@@ -188,10 +187,12 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
     // at the end needs its own room)
     if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && a.nz <= 1) grid.x += conv_prefetch_wgs(a.Cout2);
-    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG > 1 ? KG : 0) * BM * BN * 4);
+    constexpr int THREADS = conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE, SPLITK, false>();
+    constexpr int KX = KG > 1 && (KG >= 4 || THREADS > 64 * WARPS_M * WARPS_N * KG) ? KG : KG - 1;   // groups whose sums pass through LDS
+    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)KX * BM * BN * 4);
     if (block != 64 * WARPS_M * WARPS_N * KG) return hipErrorInvalidValue;
     const uint32_t magic = conv_tile_magic(grid_tiles, (unsigned)(a.Cout + BN - 1) / BN);
-    kern<<<grid, conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE, false>(), used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), conv_pack_relu(a), magic, rest CW_STAMP_PASS);
+    kern<<<grid, THREADS, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), conv_pack_relu(a), magic, rest CW_STAMP_PASS);
     return hipGetLastError();
 }
 

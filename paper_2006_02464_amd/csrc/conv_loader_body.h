@@ -31,8 +31,10 @@ constexpr int kLoaderWaves = 4;
 // residual for each.  On eight multiplying waves (three a SIMD then) waves of 64x64 do not fit, nor do waves of 128x64 and 64x128 anywhere: they spilled in the
 // loop over the slices, 256x128 and 128x256 on eight waves 29.1 -> 32.9 us for 1x7 of 256 channels at 56x56 batch 8 and 9.8 -> 15.2 for 1x1 256 -> 128 there
 // at batch 16, 256x256 3-10 times as slow.
-constexpr bool conv_has_loaders(int mode, bool fused, int bm, int bn, int waves, int kg) {
-    return mode != MODE_STEM && !fused && kg <= 2 && 48 * (bm * bn * kg / (waves * 1024)) + 16 <= 512 / ((waves + kLoaderWaves + 3) / 4);
+// Not with split K: in two and four splits launches took 0.73-2.1 times the time, by tile (80-97 shapes each) 0.87-1.07 in the median and 1.3 for 1x1 on
+// 32x32 with slices of 128; and a ticket a wave, which two groups that finish a tile together draw, takes eight times the arrival counters.
+constexpr bool conv_has_loaders(int mode, bool splitk, bool fused, int bm, int bn, int waves, int kg) {
+    return mode != MODE_STEM && !splitk && !fused && kg <= 2 && 48 * (bm * bn * kg / (waves * 1024)) + 16 <= 512 / ((waves + kLoaderWaves + 3) / 4);
 }
 
 // tile / tiles_n by a reciprocal from the host; 0: none (one channel tile, or too many tiles for it to be exact).
@@ -45,7 +47,7 @@ static __device__ __forceinline__ V lds_read(unsigned at) {
     return *reinterpret_cast<const __attribute__((address_space(3))) V *>((size_t)at);
 }
 
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, int KG, int MT>
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, int KG, int MT>
 static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const int bid, const int nb_packed, const unsigned magic) {
     constexpr int PARTS = MT == 16 ? (32 / BM) * (32 / BN) : 1, ROUND = MT == 16 ? 32 : BM;
     const int nb = conv_nb_tiles(nb_packed) * PARTS, panel = conv_nb_panel(nb_packed);
@@ -83,11 +85,9 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     if (MT == 16 && m0 >= a.M) return;   // the lower part of the last pixels' tile
-    const int ktiles = MODE == MODE_TAIL ? (a.K + BK - 1) / BK : a.K / BK;
-    const int kt0 = SPLITK ? blockIdx.y * a.ktiles_per_split : 0;
-    const int nsteps = (SPLITK ? min(ktiles, kt0 + a.ktiles_per_split) : ktiles) - kt0;   // at least one (checked by the launcher)
-    // Barriers: both kinds of waves meet at (general addressing) 1 behind the rows' arithmetic, 1 + nsteps around the slices, 1 in
-    // the wave groups' exchange and 2 in splitk_exchange.
+    const int nsteps = MODE == MODE_TAIL ? (a.K + BK - 1) / BK : a.K / BK;   // at least one
+    // Barriers: both kinds of waves meet at (general addressing) 1 behind the rows' arithmetic, 1 + nsteps around the slices and 1 in
+    // the wave groups' exchange.
     constexpr bool ROWS_SHARED = MODE == MODE_CONV && X_PER > 1;
 
     if (wave >= CW) {
@@ -106,10 +106,10 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
 #pragma unroll
         for (int j = 0; j < W_PER; ++j) w_off[j] = w_row0 + (unsigned)(j * RSTEP) * k2 + (chunk[j & 1] << 4);
         const unsigned dst0 = lds_base + (unsigned)lw * 1024u;
-        const int k_last = a.K - (ktiles - 1) * BK;   // K elements of the last slice (MODE_TAIL)
+        const int k_last = a.K - (nsteps - 1) * BK;   // K elements of the last slice (MODE_TAIL)
         auto beyond = [&](int j) { return MODE == MODE_TAIL && (int)chunk[j & 1] * 8 >= k_last; };   // piece j is not in the last slice
-        unsigned kb = (unsigned)kt0 * (BK * 2u);   // byte offset of the next slice within a weight row
-        bool part = false;                         // it is the last, part of a slice (MODE_TAIL)
+        unsigned kb = 0;   // byte offset of the next slice within a weight row
+        bool part = false; // it is the last, part of a slice (MODE_TAIL)
         auto load_w = [&](int j, unsigned stage_at) { load_to_lds(dw, part && beyond(j) ? kOob : w_off[j], kb, stage_at + BM * BK * 2u + j * (NT * 16u)); };
         // with general addressing the first slice's weights need none of the pixel arithmetic
         if constexpr (!GEMM) {
@@ -161,17 +161,11 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
         }
         // (r, s, c0) of the next slice: k0 = kt*BK = (r*kw + s)*Cin + c0
         int fr = 0, fs = 0, fc0 = 0;
-        if (SPLITK && !GEMM) {
-            const int rs = kt0 * BK / a.Cin;
-            fc0 = kt0 * BK - rs * a.Cin;
-            fr = rs / a.kw;
-            fs = rs - fr * a.kw;
-        }
-        unsigned soff = GEMM ? kb : ((unsigned)(fr * a.W + fs) * (unsigned)conv_ldx(a) + (unsigned)fc0) * 2u, tbit = GEMM ? 1u : 1u << (fr * a.kw + fs);
+        unsigned soff = 0, tbit = 1u;
         int kt = 0;   // slices issued
         auto issue = [&](unsigned stage, bool with_w) {
             const unsigned at = dst0 + stage * STAGE;
-            if (MODE == MODE_TAIL) part = kt0 + kt == ktiles - 1;
+            if (MODE == MODE_TAIL) part = kt == nsteps - 1;
 #pragma unroll
             for (int j = 0; j < X_PER; ++j)
                 load_to_lds(dx, (GEMM ? part && beyond(j) : (x_mask[j] & tbit) == 0u) ? kOob : x_off[j], soff, at + j * (NT * 16u));
@@ -210,7 +204,6 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
         wait_loads_and_barrier<0>();
         wait_lds_and_barrier();   // the last slice is read
         if constexpr (KG > 1) wait_lds_and_barrier();
-        if constexpr (SPLITK && KG == 1) { wait_lds_and_barrier(); wait_lds_and_barrier(); }
         return;
     }
 
@@ -221,10 +214,8 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
     const EpiPos pos{m0, n0, wm0, wn0, lrow, lhalf};
     EpiOperands<TM, TN> eo;
     GroupOperands<MT, TM, TN, KG> go;
-    if constexpr (!SPLITK) {
-        if constexpr (KG > 1) group_epilogue_load<MT, TM, TN, KG>(go, a, pos, kg);
-        else epilogue_load<TM, TN>(eo, a, pos);
-    }
+    if constexpr (KG > 1) group_epilogue_load<MT, TM, TN, KG>(go, a, pos, kg);
+    else epilogue_load<TM, TN>(eo, a, pos);
     acc_t acc[TM][TN];  // [pixel tile][channel tile]; MFMA rows = channels, columns = pixels
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -294,16 +285,8 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
         if (kg * G::UPG >= G::UNITS) return;   // more groups than units
         float4 sum[G::UPG];
         group_sum<MT, TM, TN, KG, WARPS_M * WARPS_N>(xch, sum, kg, wq, lane);
-        if constexpr (SPLITK) {
-            group_epilogue_load<MT, TM, TN, KG>(go, a, pos, kg);   // here behind the partial sums' way out
-            if (!group_splitk<MT, TM, TN, KG>(a, pos, sum, kg, lane, a.counters + tile_id * CW + wave)) return;
-        }
         group_epilogue_store<T, MT, TM, TN, KG>(sum, go, a, pos, kg);
     } else {
-        if constexpr (SPLITK) {
-            if (!splitk_exchange<TM, TN>(acc, a, pos, tile_id)) return;
-            epilogue_load<TM, TN>(eo, a, pos);
-        }
         epilogue_store<T, TM, TN>(acc, eo, a, pos);
     }
 }

@@ -13,7 +13,7 @@ namespace cw {
 struct alignas(64) ConvLines { unsigned long long v[16]; };   // of each its first two argument lines, which hold all it reads
 static_assert(offsetof(ConvArgs, khp) == sizeof(ConvLines), "argument lines");
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int KG, int MT>
-__global__ __launch_bounds__((conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE_CONV, false>())) void conv_dlds_pair_kernel(const ConvLines l0, const ConvLines l1) {
+__global__ __launch_bounds__((conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE_CONV, false, false>())) void conv_dlds_pair_kernel(const ConvLines l0, const ConvLines l1) {
     ConvArgs a0, a1;
     __builtin_memcpy(&a0, &l0, sizeof l0);
     __builtin_memcpy(&a1, &l1, sizeof l1);
@@ -107,7 +107,7 @@ static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, 
     ConvLines l0, l1;
     memcpy(&l0, &a0, sizeof l0);
     memcpy(&l1, &a1, sizeof l1);
-    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE_CONV, false>(), used, s>>>(l0, l1);
+    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE_CONV, false, false>(), used, s>>>(l0, l1);
     return hipGetLastError();
 }
 

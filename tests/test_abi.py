@@ -117,6 +117,21 @@ def test_debug_keep_leaves_the_head_of_the_network_as_it_is(ctx, depth, hw, batc
     assert key(plain)[0][4:] == (8, 64)
 
 
+@pytest.mark.parametrize("name", ["128x64k128g2", "64x64k128g2", "128x64g2", "64x64g2"])
+def test_two_wave_groups_draw_one_ticket_a_tile(ctx, name):
+    """A forced split and one of the plan table hold up to 65536 tiles, as many as there are arrival counters."""
+    ops = [T.Op(T.CONV, 3, 128, 7, 7, 2, 3, 1, -1, -1), T.Op(T.CONV, 128, 512, 3, 3, 1, 1, 1, -1, 0), T.Op(T.GAVGPOOL, 512, 512, 0, 0, 1, 0, 0, -1, 1),
+           T.Op(T.FC, 512, 10, 1, 1, 1, 0, 0, -1, 2), T.Op(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 3)]
+    for table in (False, True):
+        if table:
+            ctx.set_plan_table([(16 * 112 * 112, 512, 1152, 3, 1, cw.CONV_TILES[name], 2)])
+        else:
+            ctx.set_plan_override(cw.CONV_TILES[name], 2)
+        l, = [l for l in ctx.plan(ctx.model_define(ops, 3, 224, 224, batch_sizes=(16,)), 16) if l["op_index"] == 1]
+        ctx.set_plan_override(-1, 0)
+        assert (l["conv_tile"], l["split_k"]) == (cw.CONV_TILES[name], 2) and 8192 < l["grid_x"] <= 65536
+
+
 def test_plan_override_reaches_every_tile(ctx):
     for name, idx in cw.CONV_TILES.items():
         ctx.set_plan_override(idx, 2)
