@@ -28,8 +28,8 @@ typedef struct {
     int32_t proj_op;       /* -1, or the projection-shortcut op this launch computes as well */
     int32_t pair_op;       /* -1, or a second, independent convolution over the same input computed by this launch */
     int32_t kind;          /* internal kernel family id */
-    int32_t grid_x, grid_y, grid_z, block;   /* without the workgroups that read ahead (cw_plan_launch_ahead); of a convolution the threads
-                                                that multiply, beside which tiles of one or two wave groups have 256 that only load */
+    int32_t grid_x, grid_y, grid_z, block;   /* without the workgroups that read ahead (cw_plan_launch_ahead) and the threads of a
+                                                workgroup that only load (cw_plan_launch_loaders) */
     int32_t tile_m, tile_n, tile_k, split_k; /* conv: pixels x channels per workgroup, K slice */
     int32_t conv_tile;     /* conv: the tile variant in cw_set_plan_override's numbering; -1 for a fused pair and for other kinds */
     int32_t wave_groups;   /* conv: groups of waves that split every K slice (1 = none) */
@@ -67,6 +67,10 @@ int32_t cw_plan_launch_issued(cw_ctx *ctx, int32_t model_id, int32_t batch, int3
  * input, the 1x1 back to 64 (cw_set_fusion_third), is one launch: 2 or 3 (layers) for its last entry, which launches it, 1 for the others, 0 for every other
  * entry, negative on error.  Layers with a row of the plan table stay apart. */
 int32_t cw_plan_launch_tail(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
+/* Entry `index` as a launch of its own: the threads of a workgroup that only load, beside cw_launch_info.block that multiply; 0 where
+ * all do both (convolutions over split K or in four and more wave groups, the first convolution's form, the fused form, the
+ * register-staged kernel, tiles whose registers leave no room) and for other launches.  Negative on error. */
+int32_t cw_plan_launch_loaders(cw_ctx *ctx, int32_t model_id, int32_t batch, int32_t index);
 /* Runs EXEC like cw_exec but times every launch of the plan with its own pair of
  * events, issuing it `inner` (>= 1) times back to back between them (a launch is
  * idempotent); launch_us [host] receives cw_plan_num_launches() averages, each

@@ -100,6 +100,7 @@ SIGNATURES = {
     "cw_plan_launch_ahead": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(c_int32), POINTER(c_int64)]),
     "cw_plan_launch_joined": (c_int32, [c_void_p, c_int32, c_int32, c_int32]),
     "cw_plan_launch_tail": (c_int32, [c_void_p, c_int32, c_int32, c_int32]),
+    "cw_plan_launch_loaders": (c_int32, [c_void_p, c_int32, c_int32, c_int32]),
     "cw_plan_launch_issued": (c_int32, [c_void_p, c_int32, c_int32, c_int32, POINTER(cw_launch_info)]),
     "cw_exec_timed_launches": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_int32, c_void_p, c_void_p]),
     "cw_debug_read_op": (c_int32, [c_void_p, c_int32, c_int32, c_int32, c_void_p, c_size_t]),
@@ -336,6 +337,10 @@ class Context:
     def plan_launch_tail(self, model_id, batch, index):
         """Layers of the bottleneck tail that entry `index` launches (2 or 3), 1 for one that a later entry's launch computes, 0 for any other."""
         return self._check(lib().cw_plan_launch_tail(self._h, model_id, batch, index))
+
+    def plan_launch_loaders(self, model_id, batch, index):
+        """Threads of a workgroup of entry `index`, as a launch of its own, that only load (beside its `block`)."""
+        return self._check(lib().cw_plan_launch_loaders(self._h, model_id, batch, index))
 
     def plan_launch_issued(self, model_id, batch, index):
         """What EXEC issues for plan entry `index`: the work of joined entries stands with the entry that launches it."""

@@ -1492,6 +1492,18 @@ int32_t cw_plan_launch_tail(cw_ctx *c, int32_t model_id, int32_t batch, int32_t 
     return p->launches[index].in_tail ? 1 : p->launches[index].tail;
 }
 
+int32_t cw_plan_launch_loaders(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index) {
+    if (!c) return CW_ERR_INVALID;
+    ModelRt *m = get_model(c, model_id);
+    if (!m) return set_err(c, CW_ERR_INVALID, "unknown model id");
+    Plan *p = get_plan(m, batch);
+    if (!p) return set_err(c, CW_ERR_BAD_BATCH, "no plan for this batch size");
+    if (index < 0 || index >= (int32_t)p->launches.size()) return set_err(c, CW_ERR_INVALID, "launch index out of range");
+    const Launch &l = p->launches[index];
+    if (l.kind != K_CONV || l.fused_bm > 0) return 0;
+    return conv_loader_threads(l.tile, l.stem, l.conv, l.pair_op >= 0 ? &l.conv0 : nullptr);
+}
+
 int32_t cw_plan_launch_issued(cw_ctx *c, int32_t model_id, int32_t batch, int32_t index, cw_launch_info *out) {
     ModelRt *m = get_model(c, model_id);
     if (!m || !out) return set_err(c, CW_ERR_INVALID, "unknown model id or null pointer");

@@ -318,7 +318,7 @@ enum ConvTile : int32_t {
     T32x32k128g4q, T32x32k128g4n, T32x32k128g4m, T32x32k256g4q, T32x32k256g4n, N_CONV_TILES
 };
 struct TileDim {
-    int bm, bn, threads, bk, kg;   // threads: of the waves that multiply; those that only load (conv_loader_body.h) come on top
+    int bm, bn, threads, bk, kg;   // threads: of the waves that multiply; those that only load (conv_loader_threads) come on top
     int pm = bm, pn = bn;   // what one workgroup computes of it
     int parts() const { return (bm / pm) * (bn / pn); }
 };
@@ -339,6 +339,9 @@ bool conv_uses_dlds(const ConvArgs &a, bool stem);
 
 // Tiles in parts (kernels_conv_small.hip): a launch has grid.x * grid.z workgroups, grid.z = parts of a tile.
 inline bool conv_tile_small(ConvTile t) { return t >= T32x32k128g4q && t < N_CONV_TILES; }
+
+// Threads of a convolution launch (of a pair with a1) that only load, beside conv_grid's; 0 where its waves load for themselves.
+int conv_loader_threads(ConvTile tile, bool stem, const ConvArgs &a, const ConvArgs *a1 = nullptr);
 
 // Launchers (kernels_*.hip).  All only enqueue; they return the launch's error state.
 hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hipStream_t s);

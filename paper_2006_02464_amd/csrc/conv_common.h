@@ -15,6 +15,21 @@ constexpr unsigned kOob = 0x80000000u;  // byte offset beyond any buffer (buffer
 // MODE_TAIL: MODE_GEMM whose K ends in part of a slice (a form of its own: the masks cost the plain one 1.5 %)
 enum ConvMode : int { MODE_CONV = 0, MODE_GEMM = 1, MODE_STEM = 2, MODE_TAIL = 3 };
 
+// Waves of a workgroup that only load (conv_loader_body.h).
+constexpr int kLoaderWaves = 4;
+// Forms that have them: tiles of one or two wave groups whose waves' registers fit beside the loaders'.  Four groups put a multiplying wave of every
+// group on a SIMD already, and with one step a slice and group the loaders' own chain from barrier to barrier is the longer one: ResNet-18 64x64 batch 1
+// 97.1 us without, 101.4 with them (its 32x32 tiles on slices of 64 4.0 -> 4.6 us a launch), ResNet-50 batch 1 187 and 189.
+// Registers: a wave's 512 a lane and SIMD are shared with the loaders, and a tile of MFMA tiles of 32x32 takes 16 accumulators, about 24 of operands and 8 of
+// residual for each.  On eight multiplying waves (three a SIMD then) waves of 64x64 do not fit, nor do waves of 128x64 and 64x128 anywhere: they spilled in the
+// loop over the slices, 256x128 and 128x256 on eight waves 29.1 -> 32.9 us for 1x7 of 256 channels at 56x56 batch 8 and 9.8 -> 15.2 for 1x1 256 -> 128 there
+// at batch 16, 256x256 3-10 times as slow.
+// Not with split K: in two and four splits launches took 0.73-2.1 times the time, by tile (80-97 shapes each) 0.87-1.07 in the median and 1.3 for 1x1 on
+// 32x32 with slices of 128; and a ticket a wave, which two groups that finish a tile together draw, takes eight times the arrival counters.
+constexpr bool conv_has_loaders(int mode, bool splitk, bool fused, int bm, int bn, int waves, int kg) {
+    return mode != MODE_STEM && !splitk && !fused && kg <= 2 && 48 * (bm * bn * kg / (waves * 1024)) + 16 <= 512 / ((waves + kLoaderWaves + 3) / 4);
+}
+
 // n / d for a divisor prepared on the host (round-up multiplier; exact for every 32-bit n).
 static __device__ __forceinline__ unsigned fast_div(unsigned n, const FastDiv &d) {
     const unsigned t = __umulhi(d.magic, n);

@@ -415,6 +415,17 @@ void conv_grid(ConvTile tile, const ConvArgs &a, dim3 *grid, int *block) {
     *block = d.threads;
 }
 
+static int conv_mode(const ConvArgs &a, bool stem, int bk) {
+    return stem ? MODE_STEM : !conv_is_gemm(a, stem) ? MODE_CONV : a.K % bk ? MODE_TAIL : MODE_GEMM;
+}
+
+int conv_loader_threads(ConvTile tile, bool stem, const ConvArgs &a, const ConvArgs *a1) {
+    if (!conv_uses_dlds(a, stem)) return 0;
+    const TileDim d = conv_tile_dim(tile);
+    const int mode = a1 ? MODE_CONV : conv_mode(a, stem, conv_bk(a, stem, tile));   // a pair: general addressing
+    return conv_has_loaders(mode, a.split_k > 1, false, d.bm, d.bn, d.threads / 64, d.kg) ? 64 * kLoaderWaves : 0;
+}
+
 template <typename T, int BK, int MODE, bool SPLITK>
 static hipError_t launch_conv_t(ConvTile tile, const ConvArgs &a, hipStream_t s) {
     dim3 grid;
@@ -466,8 +477,7 @@ hipError_t launch_conv(DType dt, ConvTile tile, bool stem, const ConvArgs &a, hi
     if ((long long)a.M * (a.partial ? a.Cout * 4ll : conv_ldy(a) * 2ll) >= (1ll << 31) || (long long)a.M * conv_ldy(a) * 2 >= (1ll << 31) || (long long)a.Cout * a.K * 2 >= (1ll << 31))
         return hipErrorInvalidValue;
     // What the direct-to-LDS kernel does not take stays on the register-staged kernel of this file.
-    if (stem && stem_is_dlds(a)) return launch_conv_dlds(dt, tile, bk, MODE_STEM, a, s);
-    if (!stem && conv_uses_dlds(a, false)) return launch_conv_dlds(dt, tile, bk, !gemm ? MODE_CONV : a.K % bk ? MODE_TAIL : MODE_GEMM, a, s);
+    if (conv_uses_dlds(a, stem)) return launch_conv_dlds(dt, tile, bk, conv_mode(a, stem, bk), a, s);
     if (a.split_k > 1) return dt == DT_F16 ? launch_conv_dt<f16, true>(tile, stem, a, s) : launch_conv_dt<bf16, true>(tile, stem, a, s);
     return dt == DT_F16 ? launch_conv_dt<f16, false>(tile, stem, a, s) : launch_conv_dt<bf16, false>(tile, stem, a, s);
 }

@@ -5,6 +5,7 @@ import struct
 import msgpack
 
 import paper_2006_02464_amd as cw
+from oracle import topology as T
 from paper_2006_02464_amd import build
 
 BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
@@ -52,3 +53,37 @@ def test_convolution_tiles_need_no_scratch():
     assert len(scratch) >= 14 and {(256, 128), (128, 256), (256, 256), (64, 64)} <= set(scratch)
     assert [t for t, b in scratch.items() if max(b) > 0] == [(256, 256)]
     assert max(scratch[256, 256]) <= 640   # bytes a lane
+
+
+OPS = [T.Op(T.CONV, 3, 64, 7, 7, 2, 3, 1, -1, -1), T.Op(T.CONV, 64, 512, 3, 3, 1, 1, 1, -1, 0), T.Op(T.CONV, 512, 512, 1, 1, 1, 0, 1, -1, 1),
+       T.Op(T.CONV, 512, 96, 1, 1, 1, 0, 1, -1, 2), T.Op(T.CONV, 96, 512, 1, 1, 1, 0, 1, -1, 3), T.Op(T.CONV, 512, 512, 3, 3, 1, 1, 1, -1, 4),
+       T.Op(T.GAVGPOOL, 512, 512, 0, 0, 1, 0, 0, -1, 5), T.Op(T.FC, 512, 10, 1, 1, 1, 0, 0, -1, 6), T.Op(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 7)]
+
+
+def test_workgroups_have_the_threads_that_the_plan_tells():
+    """block + cw_plan_launch_loaders of every plain form, whole and split K, as its kernel was compiled for."""
+    form = re.compile(r"conv_dlds_kernelIDF16_Li(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi\d+ELi(\d+)ELb([01])ELb0ELi(\d+)ELi(16|32)E")
+    compiled = {}
+    for name, k in kernels(build.LIB).items():
+        m = form.search(name)
+        if m:
+            bm, bn, wm, wn, bk, mode, split, kg, mt = (int(v) for v in m.groups())
+            compiled.setdefault((bm, bn, 64 * wm * wn * kg, bk, mode, split, kg), set()).add(k[".max_flat_workgroup_size"])
+    ctx = cw.Context(device=-1)
+    seen = set()
+    try:
+        for name, tile in cw.CONV_TILES.items():
+            for split in (1, 2):
+                ctx.set_plan_override(tile, split)
+                mid = ctx.model_define(OPS, 3, 32, 32, batch_sizes=(1,), dtype="fp16")
+                for i, l in enumerate(ctx.plan(mid, 1)):
+                    if l["kind"] != 1 or l["grid_z"] > 1:   # tiles in parts: a part's sizes are not reported
+                        continue
+                    o = OPS[l["op_index"]]
+                    mode = 2 if l["op_index"] == 0 else 0 if o.kh > 1 else 1 if o.cin % l["tile_k"] == 0 else 3
+                    threads = l["block"] + ctx.plan_launch_loaders(mid, 1, i)
+                    assert threads in compiled[l["tile_m"], l["tile_n"], l["block"], l["tile_k"], mode, int(l["split_k"] > 1), l["wave_groups"]], (name, l)
+                    seen.add((threads > l["block"], mode, l["split_k"] > 1))
+    finally:
+        ctx.destroy()
+    assert {k for k in seen if k[0]} == {(True, m, False) for m in (0, 1, 3)} and {(False, m, True) for m in range(4)} <= seen
