@@ -27,7 +27,19 @@ constexpr int kLoaderWaves = 4;
 // Not with split K: in two and four splits launches took 0.73-2.1 times the time, by tile (80-97 shapes each) 0.87-1.07 in the median and 1.3 for 1x1 on
 // 32x32 with slices of 128; and a ticket a wave, which two groups that finish a tile together draw, takes eight times the arrival counters.
 constexpr bool conv_has_loaders(int mode, bool splitk, bool fused, int bm, int bn, int waves, int kg) {
-    return mode != MODE_STEM && !splitk && !fused && kg <= 2 && 48 * (bm * bn * kg / (waves * 1024)) + 16 <= 512 / ((waves + kLoaderWaves + 3) / 4);
+    return mode != MODE_STEM && !splitk && !fused && kg <= 2 && 48 * (bm * bn * kg / (waves * 1024)) + 16 <= 512 / ((waves + kLoaderWaves + 3) / 4) &&
+           !(mode == MODE_GEMM && bm * bn * kg >= waves * 4096);   // 1x1 in waves of 64x64: 1.04 times the time in the median of 340 launches
+}
+// The launches of such a form that are issued with them: those whose workgroups are on the CUs all at once.  Loaders take workgroups' places: with them
+// two fit a CU, one of eight multiplying waves or of a larger tile, where up to five of the same tile would.  Behind that a workgroup's set-up and epilogue
+// stand alone: 1x1 64 -> 256 at 56x56 batch 16 13.2 -> 17.3 us on 64x64, 32 -> 64 at 112x112 10.7 -> 27.8 on 32x32, 128 -> 512 at 28x28 9.9 -> 11.7 on
+// 64x64 with slices of 128, 7x1 of 256 channels at 56x56 66 -> 78 on 128x64 in two groups; except that four multiplying waves gain from K = 256 on
+// (64x64 0.85-0.97 of the time, 128x64 0.93-1.0), larger tiles only with general addressing.  One slice on a CU of its own has nothing to overlap and
+// pays for the longer start: 128x128 on eight waves 4.1 -> 4.4.  Over 7900 pairs of shape and tile inside EXECs, whole K, launches under this rule take 0.74-1.0
+// times the time in the mean by tile and form and 1.08 at most (128x128 three of 1.1-1.2, 1x1 of stride 2 on less than a fifth of the CUs).
+constexpr bool conv_loads_apart(int mode, int bm, int bn, int bk, int waves, int K, long long workgroups) {
+    const bool two = waves < 8 && bm * bn * bk <= waves * 131072;
+    return workgroups <= (two ? 512 : 256) ? two || K > bk : waves == 4 && K >= 256 && (two || mode == MODE_CONV);
 }
 
 // n / d for a divisor prepared on the host (round-up multiplier; exact for every 32-bit n).

@@ -90,20 +90,18 @@ struct ConvRest<MODE, false, true> : ConvArgs {   // the fused form reads all of
     __device__ __forceinline__ void unpack(ConvArgs &a) const { a = *this; }
 };
 
-template <int BM, int BN, int WARPS_M, int WARPS_N, int KG, int MODE, bool SPLITK, bool FUSED>
-constexpr int conv_threads() {
-    return 64 * (WARPS_M * WARPS_N * KG + (conv_has_loaders(MODE, SPLITK, FUSED, BM, BN, WARPS_M * WARPS_N * KG, KG) ? kLoaderWaves : 0));
-}
+template <int WARPS_M, int WARPS_N, int KG, bool LOADERS>
+constexpr int conv_threads() { return 64 * (WARPS_M * WARPS_N * KG + (LOADERS ? kLoaderWaves : 0)); }
 
 // The tile on the body that is the form's.
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED, int KG, int MT>
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED, int KG, int MT, bool LOADERS>
 static __device__ __forceinline__ void conv_body(const ConvArgs &a, const int bid, const int nb, const unsigned magic) {
-    if constexpr (conv_has_loaders(MODE, SPLITK, FUSED, BM, BN, WARPS_M * WARPS_N * KG, KG)) conv_loader_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, KG, MT>(a, bid, nb, magic);
+    if constexpr (LOADERS) conv_loader_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, KG, MT>(a, bid, nb, magic);
     else conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, bid, nb);
 }
 
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, int MT = 32>
-__global__ __launch_bounds__((conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE, SPLITK, FUSED>())) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED = false, int KG = 1, int MT = 32, bool LOADERS = false>
+__global__ __launch_bounds__((conv_threads<WARPS_M, WARPS_N, KG, LOADERS>())) void conv_dlds_kernel(const void *x, const void *w, const void *res, void *y,
                                                                                  int M, int K, int cout_ldy, int cin_ldx, unsigned nb_relu, unsigned magic,
                                                                                  const ConvRest<MODE, SPLITK, FUSED> rest CW_STAMP_ARG) {
     CW_STAMP_BEGIN
@@ -131,10 +129,10 @@ __global__ __launch_bounds__((conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE, S
         }
     }
     if constexpr (FUSED || SPLITK || MODE == MODE_STEM) {
-        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, MT>(a, blockIdx.x, nb, magic);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, MT, LOADERS>(a, blockIdx.x, nb, magic);
         CW_STAMP_END
     } else if (__builtin_expect((int)blockIdx.x < conv_nb_tiles(nb) * conv_parts<BM, BN, MT>(), 1)) {
-        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, MT>(a, blockIdx.x, nb, magic);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, MT, LOADERS>(a, blockIdx.x, nb, magic);
         CW_STAMP_END
     } else {   // a workgroup that reads ahead (its code behind the convolution's, which most launches find cold)
         const int wgs = conv_nb_tiles(nb) * conv_parts<BM, BN, MT>();
@@ -162,6 +160,27 @@ static bool conv_panel_ok(const ConvArgs &a, int bn, unsigned tiles) {
     return a.panel_log2 == 0 || tiles_n % (1 << a.panel_log2) == 0;
 }
 
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int MODE, bool SPLITK, int KG, int MT, bool LOADERS>
+static hipError_t launch_form(dim3 grid, const ConvArgs &a, hipStream_t s) {
+    ConvRest<MODE, SPLITK, false> rest;
+    rest.pack(a);
+    constexpr int NS = RingDepth<BM, BN, BK>::value;
+    constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
+    static_assert(NS * stage_bytes <= 160 * 1024, "ring does not fit the LDS");
+    auto kern = conv_dlds_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, false, KG, MT, LOADERS>;
+    // More than 64 KiB of LDS per workgroup has to be requested once per kernel; done on first
+    // use (under LOAD's graph recording or the first plain EXEC), never per launch afterwards.
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
+    if (attr != hipSuccess) return attr;
+    const uint32_t magic = conv_tile_magic(grid.x, (unsigned)(a.Cout + BN - 1) / BN);
+    // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
+    // at the end needs its own room)
+    if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && a.nz <= 1) grid.x += conv_prefetch_wgs(a.Cout2);
+    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)(KG >= 4 || LOADERS ? KG : KG - 1) * BM * BN * 4);
+    kern<<<grid, conv_threads<WARPS_M, WARPS_N, KG, LOADERS>(), used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), conv_pack_relu(a), magic, rest CW_STAMP_PASS);
+    return hipGetLastError();
+}
+
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int MODE, bool SPLITK, int KG = 1, int MT = 32>
 static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStream_t s) {
     ConvArgs a = a_in;
@@ -172,28 +191,14 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     if (a.nz > 1 && (MT != 32 || MODE != MODE_GEMM || SPLITK || a.bias || a.res || grid.z != (unsigned)a.nz)) return hipErrorInvalidValue;
     constexpr unsigned PARTS = conv_parts<BM, BN, MT>();
     if (a.nz <= 1 && grid.z != PARTS) return hipErrorInvalidValue;
-    const unsigned grid_tiles = grid.x * PARTS;
+    constexpr int WAVES = WARPS_M * WARPS_N * KG;
+    if (block != 64 * WAVES) return hipErrorInvalidValue;
     if (PARTS > 1) grid = dim3(grid.x * PARTS, grid.y, 1);   // the workgroups that read ahead come behind all the parts
-    ConvRest<MODE, SPLITK, false> rest;
-    rest.pack(a);
-    constexpr int NS = RingDepth<BM, BN, BK>::value;
-    constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
-    static_assert(NS * stage_bytes <= 160 * 1024, "ring does not fit the LDS");
-    auto kern = conv_dlds_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, false, KG, MT>;
-    // More than 64 KiB of LDS per workgroup has to be requested once per kernel; done on first
-    // use (under LOAD's graph recording or the first plain EXEC), never per launch afterwards.
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
-    if (attr != hipSuccess) return attr;
-    // a K walk shorter than the ring only ever touches its first stages (the wave groups' exchange
-    // at the end needs its own room)
-    if (!SPLITK && MODE != MODE_STEM && a.Cout2 > 0 && a.w2 && a.nz <= 1) grid.x += conv_prefetch_wgs(a.Cout2);
-    constexpr int THREADS = conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE, SPLITK, false>();
-    constexpr int KX = KG > 1 && (KG >= 4 || THREADS > 64 * WARPS_M * WARPS_N * KG) ? KG : KG - 1;   // groups whose sums pass through LDS
-    const size_t used = std::max((size_t)std::min(NS, a.ktiles_per_split) * stage_bytes, (size_t)KX * BM * BN * 4);
-    if (block != 64 * WARPS_M * WARPS_N * KG) return hipErrorInvalidValue;
-    const uint32_t magic = conv_tile_magic(grid_tiles, (unsigned)(a.Cout + BN - 1) / BN);
-    kern<<<grid, THREADS, used, s>>>(a.x, a.w, a.res, a.y, a.M, a.K, a.Cout | (conv_ldy(a) << 16), a.Cin | (conv_ldx(a) << 16), conv_pack_relu(a), magic, rest CW_STAMP_PASS);
-    return hipGetLastError();
+    if constexpr (conv_has_loaders(MODE, SPLITK, false, BM, BN, WAVES, KG)) {
+        if (conv_loads_apart(MODE, BM, BN, BK, WAVES, a.K, (long long)grid.x * grid.z))
+            return launch_form<T, BM, BN, WARPS_M, WARPS_N, BK, MODE, SPLITK, KG, MT, true>(grid, a, s);
+    }
+    return launch_form<T, BM, BN, WARPS_M, WARPS_N, BK, MODE, SPLITK, KG, MT, false>(grid, a, s);
 }
 
 }  // namespace cw

@@ -12,16 +12,16 @@ namespace cw {
 // one set-up latency and one tail instead of two.
 struct alignas(64) ConvLines { unsigned long long v[16]; };   // of each its first two argument lines, which hold all it reads
 static_assert(offsetof(ConvArgs, khp) == sizeof(ConvLines), "argument lines");
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int KG, int MT>
-__global__ __launch_bounds__((conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE_CONV, false, false>())) void conv_dlds_pair_kernel(const ConvLines l0, const ConvLines l1) {
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int KG, int MT, bool LOADERS>
+__global__ __launch_bounds__((conv_threads<WARPS_M, WARPS_N, KG, LOADERS>())) void conv_dlds_pair_kernel(const ConvLines l0, const ConvLines l1) {
     ConvArgs a0, a1;
     __builtin_memcpy(&a0, &l0, sizeof l0);
     __builtin_memcpy(&a1, &l1, sizeof l1);
     const int nb0 = conv_nb_tiles(a0.nb) * conv_parts<BM, BN, MT>();
     if ((int)blockIdx.x < nb0)
-        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, MT>(a0, blockIdx.x, a0.nb, 0u);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, MT, LOADERS>(a0, blockIdx.x, a0.nb, 0u);
     else
-        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, MT>(a1, blockIdx.x - nb0, a1.nb, 0u);
+        conv_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE_CONV, false, false, KG, MT, LOADERS>(a1, blockIdx.x - nb0, a1.nb, 0u);
 }
 
 template <typename T, int BM, int BN, int MODE, int KG>
@@ -90,25 +90,34 @@ hipError_t launch_conv_fused(DType dt, int bm, int kg, const ConvArgs &a, hipStr
 #undef CW_FUSED_T
 }
 
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int KG, int MT, bool LOADERS>
+static hipError_t launch_pair_form(const ConvArgs &a0, const ConvArgs &a1, unsigned nb0, unsigned nb1, hipStream_t s) {
+    constexpr int NS = RingDepth<BM, BN, BK>::value;
+    constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
+    auto kern = conv_dlds_pair_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, KG, MT, LOADERS>;
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
+    if (attr != hipSuccess) return attr;
+    const size_t used = std::max((size_t)std::min(NS, std::max(a0.ktiles_per_split, a1.ktiles_per_split)) * stage_bytes, (size_t)(KG >= 4 || LOADERS ? KG : KG - 1) * BM * BN * 4);
+    ConvLines l0, l1;
+    memcpy(&l0, &a0, sizeof l0);
+    memcpy(&l1, &a1, sizeof l1);
+    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), conv_threads<WARPS_M, WARPS_N, KG, LOADERS>(), used, s>>>(l0, l1);
+    return hipGetLastError();
+}
+
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int KG, int MT = 32>
 static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, hipStream_t s) {
     ConvArgs a0 = a0_in, a1 = a1_in;
-    constexpr int NS = RingDepth<BM, BN, BK>::value;
-    constexpr size_t stage_bytes = (size_t)(BM + BN) * BK * 2;
-    auto kern = conv_dlds_pair_kernel<T, BM, BN, WARPS_M, WARPS_N, BK, NS, KG, MT>;
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(NS * stage_bytes));
-    if (attr != hipSuccess) return attr;
-    const size_t used = std::max((size_t)std::min(NS, std::max(a0.ktiles_per_split, a1.ktiles_per_split)) * stage_bytes, (size_t)(KG > 1 ? KG : 0) * BM * BN * 4);
-    constexpr int TM = MT == 16 ? 32 : BM, TN = MT == 16 ? 32 : BN;
+    constexpr int TM = MT == 16 ? 32 : BM, TN = MT == 16 ? 32 : BN, WAVES = WARPS_M * WARPS_N * KG;
     const unsigned nb0 = ((a0.M + TM - 1) / TM) * ((a0.Cout + TN - 1) / TN), nb1 = ((a1.M + TM - 1) / TM) * ((a1.Cout + TN - 1) / TN);
     if (!conv_panel_ok(a0, TN, nb0) || !conv_panel_ok(a1, TN, nb1)) return hipErrorInvalidValue;
     a0.nb = conv_pack_nb((int)nb0, a0.panel_log2);
     a1.nb = conv_pack_nb((int)nb1, a1.panel_log2);
-    ConvLines l0, l1;
-    memcpy(&l0, &a0, sizeof l0);
-    memcpy(&l1, &a1, sizeof l1);
-    kern<<<dim3((nb0 + nb1) * conv_parts<BM, BN, MT>(), 1, 1), conv_threads<BM, BN, WARPS_M, WARPS_N, KG, MODE_CONV, false, false>(), used, s>>>(l0, l1);
-    return hipGetLastError();
+    if constexpr (conv_has_loaders(MODE_CONV, false, false, BM, BN, WAVES, KG)) {
+        if (conv_loads_apart(MODE_CONV, BM, BN, BK, WAVES, std::max(a0.K, a1.K), (long long)nb0 + nb1))
+            return launch_pair_form<T, BM, BN, WARPS_M, WARPS_N, BK, KG, MT, true>(a0, a1, nb0, nb1, s);
+    }
+    return launch_pair_form<T, BM, BN, WARPS_M, WARPS_N, BK, KG, MT, false>(a0, a1, nb0, nb1, s);
 }
 
 bool conv_pair_tile_ok(ConvTile tile) {

@@ -132,6 +132,28 @@ def test_two_wave_groups_draw_one_ticket_a_tile(ctx, name):
         assert (l["conv_tile"], l["split_k"]) == (cw.CONV_TILES[name], 2) and 8192 < l["grid_x"] <= 65536
 
 
+# (tile, batch, image side, input channels, output channels, filter, loading threads): a tile's workgroups at 512 and above, at 256 and above, from K = 256 on, one slice
+@pytest.mark.parametrize("tile, batch, hw, cin, cout, k, loaders", [
+    ("64x64", 2, 256, 64, 64, 1, 256), ("64x64", 2, 258, 64, 64, 1, 0), ("64x64", 2, 258, 192, 64, 1, 0), ("64x64", 2, 258, 256, 64, 1, 256), ("64x64", 2, 258, 64, 64, 3, 256),
+    ("64x64", 2, 258, 160, 64, 1, 0), ("64x64", 2, 258, 288, 64, 1, 256), ("32x32", 1, 256, 64, 32, 3, 256), ("32x32", 1, 258, 64, 32, 3, 0), ("64x32", 2, 256, 64, 32, 1, 256),
+    ("64x32", 2, 258, 256, 32, 1, 0), ("32x64k128", 1, 256, 128, 64, 3, 256), ("32x64k128", 1, 258, 128, 64, 3, 0), ("128x64k128", 2, 256, 128, 64, 1, 0),
+    ("128x64k128", 2, 256, 256, 64, 1, 256), ("128x64k128", 2, 258, 256, 64, 1, 0), ("128x64k128", 2, 258, 128, 64, 3, 256), ("128x64g2", 2, 256, 256, 64, 3, 256),
+    ("128x64g2", 2, 258, 256, 64, 3, 0), ("64x64g2", 1, 256, 128, 64, 1, 256), ("64x64g2", 1, 258, 128, 64, 1, 0), ("128x128w8", 2, 256, 64, 128, 1, 0), ("128x128w8", 2, 256, 128, 128, 1, 256),
+    ("128x128w8", 2, 258, 128, 128, 1, 0), ("128x128", 1, 128, 64, 128, 3, 256), ("128x128", 1, 128, 256, 128, 1, 0), ("128x128", 1, 128, 96, 128, 1, 256),
+    ("256x128w8", 1, 128, 128, 128, 3, 0), ("128x256w8", 1, 128, 128, 256, 3, 0), ("256x128", 1, 128, 128, 128, 3, 0), ("32x32k128g4", 1, 128, 128, 32, 3, 0)])
+def test_launches_that_have_loading_waves(ctx, tile, batch, hw, cin, cout, k, loaders):
+    ops = [T.Op(T.CONV, 3, cin, 7, 7, 2, 3, 1, -1, -1), T.Op(T.CONV, cin, cout, k, k, 1, k // 2, 1, -1, 0), T.Op(T.CONV, cout, 256, 1, 1, 2, 0, 1, -1, 1),
+           T.Op(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 2), T.Op(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 3), T.Op(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 4)]
+    ctx.set_plan_override(cw.CONV_TILES[tile], 1)
+    try:
+        mid = ctx.model_define(ops, 3, hw, hw, batch_sizes=(batch,))
+    finally:
+        ctx.set_plan_override(-1, 0)
+    plan = ctx.plan(mid, batch)
+    i, = [i for i, l in enumerate(plan) if l["op_index"] == 1]
+    assert plan[i]["conv_tile"] == cw.CONV_TILES[tile] and ctx.plan_launch_loaders(mid, batch, i) == loaders
+
+
 def test_plan_override_reaches_every_tile(ctx):
     for name, idx in cw.CONV_TILES.items():
         ctx.set_plan_override(idx, 2)

@@ -43,7 +43,7 @@ def run(worker, hw, dtype, batch, tile=-1, split_k=0, ops=OPS):
     finally:
         worker.ctx.set_plan_override(-1, 0)
         worker.ctx.set_debug_keep(False)
-    plan = worker.ctx.plan(mid, batch)
+    plan = [dict(l, loaders=worker.ctx.plan_launch_loaders(mid, batch, i)) for i, l in enumerate(worker.ctx.plan(mid, batch))]
     worker.load(mid, case.blob)
     x = case.images(0, batch)
     probs, logits, _ = worker.infer(mid, x, classes=10)
@@ -152,3 +152,28 @@ def test_tiles_with_loading_waves(worker, name, hw, batch, split_k, dtype):
     if split_k > 1 and name in ("256x64", "128x128w8"):
         split_k = 1
     run(worker, hw, dtype, batch, LOADER_TILES[name], split_k, LOADER_OPS)
+
+
+# 182 x 182 pixels of 64 to 128 channels, 91 x 91 of 256 and 46 x 46 of 128 and 256: 17 to 4144 workgroups, K from half a slice to 36
+BOTH_OPS = [
+    O(T.CONV, 3, 64, 7, 7, 2, 3, 1, -1, -1),
+    O(T.CONV, 64, 96, 3, 3, 1, 1, 1, -1, 0),
+    O(T.CONV, 96, 64, 1, 1, 1, 0, 1, 0, 1),
+    O(T.CONV, 64, 128, 1, 1, 1, 0, 1, -1, 2),
+    O(T.CONV, 128, 128, 1, 1, 1, 0, 1, 3, 3),
+    O(T.CONV, 128, 256, 1, 1, 2, 0, 0, -1, 4),
+    O(T.CONV, 256, 128, 3, 3, 2, 1, 1, -1, 5),
+    O(T.CONV, 128, 256, 1, 1, 1, 0, 1, -1, 6),
+    O(T.GAVGPOOL, 256, 256, 0, 0, 1, 0, 0, -1, 7),
+    O(T.FC, 256, 10, 1, 1, 1, 0, 0, -1, 8),
+    O(T.SOFTMAX, 10, 10, 0, 0, 1, 0, 0, -1, 9),
+]
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("tile, loaders", [(0, {1, 5, 6}), (1, {1, 2, 5, 6, 7}), (2, {1, 6, 7}), (3, {6, 7}), (4, {6, 7}), (5, {6}), (9, {5, 6, 7}),
+                                           (10, {1, 2, 6}), (11, {1, 6, 7}), (12, {6, 7}), (13, {6, 7}), (14, {6}), (15, {2, 6}), (16, {6}), (22, {2, 6, 7}), (23, {6, 7})])
+def test_layers_with_and_without_loading_waves(worker, tile, loaders, dtype):
+    """One network whose layers are issued both ways on every tile."""
+    plan = run(worker, 363, dtype, 1, tile, 1, BOTH_OPS)
+    assert {l["op_index"] for l in plan if l["kind"] == 1 and l["loaders"]} == loaders
