@@ -131,7 +131,9 @@ constexpr int kPrefetchMinBytes = 256 * 1024;   // of a smaller tensor every wor
 constexpr int kPrefetchMaxTiles = 512;   // two a CU, most of which run at once; behind more, the reads would come late
 constexpr int kPrefetchLines = 256;      // per workgroup: a CU has only so many misses in flight (one workgroup per 4096 made ResNet-152 4 % slower)
 constexpr int kPrefetchPerThread = 4;    // reads a thread has in flight
-inline int conv_prefetch_wgs(int lines) { return lines < 64 * kPrefetchLines ? (lines + kPrefetchLines - 1) / kPrefetchLines : 64; }
+constexpr int conv_prefetch_wgs(int lines) { return lines < 64 * kPrefetchLines ? (lines + kPrefetchLines - 1) / kPrefetchLines : 64; }
+// Threads of a workgroup that read; the others would take the lines of further workgroups, several times as many a CU.
+constexpr int conv_prefetch_threads(int threads) { return threads < kPrefetchLines ? threads : kPrefetchLines; }
 constexpr int kMaxChannels = 32768;  // channel counts and pitches travel in 16 bits
 
 // Maps of at least this many pixels are averaged by the 16-wave kernel (one wave per 64 channels below).

@@ -136,10 +136,11 @@ __global__ __launch_bounds__((conv_threads<WARPS_M, WARPS_N, KG, LOADERS>())) vo
         CW_STAMP_END
     } else {   // a workgroup that reads ahead (its code behind the convolution's, which most launches find cold)
         const int wgs = conv_nb_tiles(nb) * conv_parts<BM, BN, MT>();
-        const int first = (int)blockIdx.x - wgs, nt = ((int)gridDim.x - wgs) * (int)blockDim.x;
-        const int lines = rest.Cout2;
+        constexpr int readers = conv_prefetch_threads(conv_threads<WARPS_M, WARPS_N, KG, LOADERS>());
+        if ((int)threadIdx.x >= readers) return;
+        const int nt = ((int)gridDim.x - wgs) * readers, lines = rest.Cout2;
         const char *p = static_cast<const char *>(rest.w2);
-        for (int i = first * (int)blockDim.x + (int)threadIdx.x; i < lines; i += nt * kPrefetchPerThread) {
+        for (int i = ((int)blockIdx.x - wgs) * readers + (int)threadIdx.x; i < lines; i += nt * kPrefetchPerThread) {
             unsigned v[kPrefetchPerThread];
 #pragma unroll
             for (int u = 0; u < kPrefetchPerThread; ++u)

@@ -1,6 +1,7 @@
 """What the compiler gave the convolution kernels, from the metadata of the built library's own code objects."""
 import re
 import struct
+import subprocess
 
 import msgpack
 
@@ -87,3 +88,34 @@ def test_workgroups_have_the_threads_that_the_plan_tells():
     finally:
         ctx.destroy()
     assert {k for k in seen if k[0]} == {(True, m, False) for m in (0, 1, 3)} and {(False, m, True) for m in range(4)} <= seen
+
+
+READ_AHEAD = r"""
+#include "common.h"
+using namespace cw;
+// Lines that workgroup `wg` of a launch's `wgs` reads: thread t from wg * readers + t on, every wgs * readers.
+constexpr int lines_of(int wg, int wgs, int readers, int lines) {
+    int n = 0;
+    for (int i = wg * readers; i < lines; i += wgs * readers) n += lines - i < readers ? lines - i : readers;
+    return n;
+}
+constexpr bool even(int lines, int threads) {
+    const int wgs = conv_prefetch_wgs(lines), readers = conv_prefetch_threads(threads), each = (lines + wgs - 1) / wgs;
+    int all = 0;
+    for (int wg = 0; wg < wgs; ++wg) {
+        const int n = lines_of(wg, wgs, readers, lines);
+        if (n > (each + kPrefetchLines - 1) / kPrefetchLines * kPrefetchLines) return false;
+        all += n;
+    }
+    return all == lines && readers <= threads;
+}
+constexpr bool even_for(int threads) { return even(2048, threads) && even(9216, threads) && even(9217, threads) && even(16384, threads) && even(18432, threads) && even(36864, threads); }
+static_assert(even_for(64) && even_for(128) && even_for(256) && even_for(320) && even_for(384) && even_for(512) && even_for(768) && even_for(1024), "");
+"""
+
+
+def test_reading_ahead_is_spread_over_its_workgroups(tmp_path):
+    """However many threads a workgroup has, those that read ahead take 256 lines each (more where 64 of them are too few)."""
+    src = tmp_path / "read_ahead.hip"
+    src.write_text(READ_AHEAD)
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-fsyntax-only", "-I", build.CSRC, str(src)], check=True)
