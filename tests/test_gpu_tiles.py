@@ -126,9 +126,10 @@ def test_chosen_tiles_at_ragged_sizes(worker, hw, batch):
             assert l["grid_x"] == -(-l["gemm_m"] // l["tile_m"]) * -(-l["gemm_n"] // l["tile_n"])
 
 
-# Tiles of one and two wave groups, whose loads are issued by waves of their own: one to four channel slices of a filter's tap, 3x3 and 5x5 filters, strides,
+# Tiles of one and two wave groups, most of them with waves that only load: one to four channel slices of a filter's tap, 3x3 and 5x5 filters, strides,
 # 1x1 whose K is one, two and several slices (fewer than the ring has stages, and more), Cout beside a tile's width, residuals, K whole and split inside and between taps.
-LOADER_TILES = {"128x64": 1, "64x64": 2, "64x32": 3, "32x32": 5, "256x64": 8, "128x128w8": 9, "128x64k128": 10, "64x64k128": 11, "128x64k128g2": 15, "64x64k128g2": 16, "64x64g2": 23}
+LOADER_TILES = {"128x64": 1, "64x64": 2, "64x32": 3, "32x32": 5, "256x64": 8, "128x128w8": 9, "128x64k128": 10, "64x64k128": 11, "128x64k128g2": 15, "64x64k128g2": 16, "128x64g2": 22, "64x64g2": 23}
+LARGE_TILES = {"256x128w8": 25, "128x256w8": 26, "256x256w8": 27, "256x128": 28}   # without
 LOADER_OPS = [
     O(T.CONV, 3, 64, 7, 7, 2, 3, 1, -1, -1),
     O(T.CONV, 64, 128, 3, 3, 1, 1, 1, -1, 0),
@@ -146,21 +147,24 @@ LOADER_OPS = [
 ]
 
 
-@pytest.mark.parametrize("name", sorted(LOADER_TILES))
-@pytest.mark.parametrize("hw,batch,split_k,dtype", [(45, 2, 1, "fp16"), (27, 1, 3, "bf16"), (4, 1, 1, "fp16")])
+@pytest.mark.parametrize("name, hw, batch, split_k, dtype", [(n, *c) for n in sorted(LOADER_TILES) for c in ((45, 2, 1, "fp16"), (27, 1, 1, "bf16"), (27, 1, 3, "bf16"), (4, 1, 1, "fp16"))] +
+                         [(n, *c) for n in sorted(LARGE_TILES) for c in ((45, 2, 1, "fp16"), (27, 1, 3, "bf16"))])
 def test_tiles_with_loading_waves(worker, name, hw, batch, split_k, dtype):
-    if split_k > 1 and name in ("256x64", "128x128w8"):
-        split_k = 1
-    run(worker, hw, dtype, batch, LOADER_TILES[name], split_k, LOADER_OPS)
+    tile = {**LOADER_TILES, **LARGE_TILES}[name]
+    own = [l for l in run(worker, hw, dtype, batch, tile, split_k, LOADER_OPS) if l["kind"] == 1 and l["conv_tile"] == tile and l["op_index"] > 0]
+    wide, basic = "k128" in name, "g2" not in name and name != "256x64" and name not in LARGE_TILES   # slices of 128; a 1x1 over 96 channels has the tile too
+    assert sorted(l["gemm_k"] for l in own) == [96] * (basic and not wide) + [576] * (not wide) + [1152, 1152, 2304, 2304, 3456, 4608, 6400]
+    assert all(l["split_k"] == (min(split_k, 2) if l["gemm_k"] == 96 else split_k) for l in own)
+    assert all((l["loaders"] > 0) == (split_k == 1 and name in LOADER_TILES) for l in own)
 
 
-# 182 x 182 pixels of 64 to 128 channels, 91 x 91 of 256 and 46 x 46 of 128 and 256: 17 to 4144 workgroups, K from half a slice to 36
+# 130 x 130 pixels, 65 x 65 and 33 x 33: 18 to 4232 workgroups, K from half a slice to 36
 BOTH_OPS = [
     O(T.CONV, 3, 64, 7, 7, 2, 3, 1, -1, -1),
-    O(T.CONV, 64, 96, 3, 3, 1, 1, 1, -1, 0),
-    O(T.CONV, 96, 64, 1, 1, 1, 0, 1, 0, 1),
-    O(T.CONV, 64, 128, 1, 1, 1, 0, 1, -1, 2),
-    O(T.CONV, 128, 128, 1, 1, 1, 0, 1, 3, 3),
+    O(T.CONV, 64, 32, 3, 3, 1, 1, 1, -1, 0),
+    O(T.CONV, 32, 64, 1, 1, 1, 0, 1, 0, 1),
+    O(T.CONV, 64, 256, 1, 1, 1, 0, 1, -1, 2),
+    O(T.CONV, 256, 128, 1, 1, 1, 0, 1, -1, 3),
     O(T.CONV, 128, 256, 1, 1, 2, 0, 0, -1, 4),
     O(T.CONV, 256, 128, 3, 3, 2, 1, 1, -1, 5),
     O(T.CONV, 128, 256, 1, 1, 1, 0, 1, -1, 6),
@@ -170,10 +174,10 @@ BOTH_OPS = [
 ]
 
 
-@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
-@pytest.mark.parametrize("tile, loaders", [(0, {1, 5, 6}), (1, {1, 2, 5, 6, 7}), (2, {1, 6, 7}), (3, {6, 7}), (4, {6, 7}), (5, {6}), (9, {5, 6, 7}),
-                                           (10, {1, 2, 6}), (11, {1, 6, 7}), (12, {6, 7}), (13, {6, 7}), (14, {6}), (15, {2, 6}), (16, {6}), (22, {2, 6, 7}), (23, {6, 7})])
-def test_layers_with_and_without_loading_waves(worker, tile, loaders, dtype):
+@pytest.mark.parametrize("tile, loaders", [(0, {1, 5, 6}), (1, {1, 2, 4, 5, 6, 7}), (2, {1, 2, 4, 5, 6, 7}), (3, {1, 6, 7}), (4, {6, 7}), (5, {6, 7}), (8, {1, 2, 5, 6}), (9, {1, 4, 5, 6, 7}),
+                                           (10, {1, 2, 6}), (11, {1, 2, 4, 5, 6, 7}), (12, {1, 6, 7}), (13, {6, 7}), (14, {6, 7}), (15, {1, 2, 6}), (16, {2, 6}),
+                                           (22, {1, 2, 5, 6, 7}), (23, {2, 6, 7})])
+def test_layers_with_and_without_loading_waves(worker, tile, loaders):
     """One network whose layers are issued both ways on every tile."""
-    plan = run(worker, 363, dtype, 1, tile, 1, BOTH_OPS)
+    plan = run(worker, 259, "bf16" if tile % 2 else "fp16", 1, tile, 1, BOTH_OPS)
     assert {l["op_index"] for l in plan if l["kind"] == 1 and l["loaders"]} == loaders
