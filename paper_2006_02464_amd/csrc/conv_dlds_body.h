@@ -68,6 +68,30 @@ static __device__ __forceinline__ int tile_div(int t, int d) {
     return __builtin_amdgcn_readfirstlane((int)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)d)));
 }
 
+// Pixel and channel tile of tile `id` under a numbering in 2^panel panels: panel after panel of tiles_n >> panel channel tiles, row by
+// row inside a panel (M pixels in whole tiles of ROUND, rows of BM).
+template <int BM, int ROUND>
+static __device__ __forceinline__ void panel_tile(int id, int tiles_n, int panel, int M, int *tile_m, int *tile_n) {
+    const int pw = tiles_n >> panel;
+    const int per = (M + ROUND - 1) / ROUND * (ROUND / BM) * pw;
+    const int p = id / per, r = id - p * per;
+    *tile_m = r / pw;
+    *tile_n = p * pw + (r - *tile_m * pw);
+}
+
+// The taps inside the image of a filter whose centre pixel is (ihc, iwc), bit r*kw+s for tap (r, s): in-range columns
+// s_lo..s_hi-1 replicated into every in-range filter row r_lo..r_hi-1 by a multiplication by the rows' unit bits (no carries:
+// cols < 2^kw).
+static __device__ __forceinline__ unsigned tap_mask(const ConvArgs &a, int pad_h, int pad_w, int ihc, int iwc) {
+    const int r_lo = max(0, pad_h - ihc), r_hi = min(a.kh, a.H + pad_h - ihc);
+    const int s_lo = max(0, pad_w - iwc), s_hi = min(a.kw, a.W + pad_w - iwc);
+    unsigned row_units = 0;  // bit r*kw for every filter row r
+    for (int r = 0; r < a.kh; ++r) row_units |= 1u << (r * a.kw);
+    const unsigned cols = ((1u << s_hi) - 1u) & ~((1u << s_lo) - 1u);
+    const unsigned rows = row_units & (unsigned)((1ull << (r_hi * a.kw)) - 1ull) & ~((1u << (r_lo * a.kw)) - 1u);
+    return cols * rows;
+}
+
 extern __shared__ __attribute__((aligned(16))) unsigned char cw_dyn_lds[];
 
 // LDS bytes of the fused second layer (see the end of the kernel): the first layer's tile, two
@@ -158,12 +182,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
         tile_m = tile_div(tile_id, tiles_n);
         tile_n = tile_id - tile_m * tiles_n;
     } else {
-        // panel after panel of tiles_n >> panel channel tiles, row by row inside a panel
-        const int pw = tiles_n >> panel;
-        const int per = (a.M + ROUND - 1) / ROUND * (ROUND / BM) * pw;
-        const int p = tile_id / per, r = tile_id - p * per;
-        tile_m = r / pw;
-        tile_n = p * pw + (r - tile_m * pw);
+        panel_tile<BM, ROUND>(tile_id, tiles_n, panel, a.M, &tile_m, &tile_n);
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     if (MT == 16 && m0 >= a.M) return;   // the lower part of the last pixels' tile
@@ -248,15 +267,7 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
                 } else {
                     const int ihc = p * a.stride, iwc = q * a.stride;
                     voff = (unsigned)((n * a.H + ihc) * a.W + iwc) * ldx * 2u;
-                    const int r_lo = max(0, pad_h - ihc), r_hi = min(a.kh, a.H + pad_h - ihc);
-                    const int s_lo = max(0, pad_w - iwc), s_hi = min(a.kw, a.W + pad_w - iwc);
-                    // in-range columns s_lo..s_hi-1 replicated into every in-range filter row r_lo..r_hi-1:
-                    // a multiplication by the rows' unit bits (no carries: cols < 2^kw)
-                    unsigned row_units = 0;  // bit r*kw for every filter row r
-                    for (int r = 0; r < a.kh; ++r) row_units |= 1u << (r * a.kw);
-                    const unsigned cols = ((1u << s_hi) - 1u) & ~((1u << s_lo) - 1u);
-                    const unsigned rows = row_units & (unsigned)((1ull << (r_hi * a.kw)) - 1ull) & ~((1u << (r_lo * a.kw)) - 1u);
-                    mask = cols * rows;
+                    mask = tap_mask(a, pad_h, pad_w, ihc, iwc);
                 }
             }
             s_row[tid] = u32x2{voff, mask};

@@ -96,7 +96,7 @@ constexpr int conv_threads() { return 64 * (WARPS_M * WARPS_N * KG + (LOADERS ? 
 // The tile on the body that is the form's.
 template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, bool SPLITK, bool FUSED, int KG, int MT, bool LOADERS>
 static __device__ __forceinline__ void conv_body(const ConvArgs &a, const int bid, const int nb, const unsigned magic) {
-    if constexpr (LOADERS) conv_loader_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, KG, MT>(a, bid, nb, magic);
+    if constexpr (LOADERS) conv_loader_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, KG>(a, bid, nb, magic);
     else conv_dlds_body<T, BM, BN, WARPS_M, WARPS_N, BK, NS, MODE, SPLITK, FUSED, KG, false, MT>(a, bid, nb);
 }
 

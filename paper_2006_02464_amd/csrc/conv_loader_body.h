@@ -33,16 +33,15 @@ static __device__ __forceinline__ V lds_read(unsigned at) {
     return *reinterpret_cast<const __attribute__((address_space(3))) V *>((size_t)at);
 }
 
-template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, int KG, int MT>
+template <typename T, int BM, int BN, int WARPS_M, int WARPS_N, int BK, int NS, int MODE, int KG>
 static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const int bid, const int nb_packed, const unsigned magic) {
-    constexpr int PARTS = MT == 16 ? (32 / BM) * (32 / BN) : 1, ROUND = MT == 16 ? 32 : BM;
-    const int nb = conv_nb_tiles(nb_packed) * PARTS, panel = conv_nb_panel(nb_packed);
+    constexpr int MT = 32;
+    const int nb = conv_nb_tiles(nb_packed), panel = conv_nb_panel(nb_packed);
     static_assert(MODE == MODE_CONV || MODE == MODE_GEMM || MODE == MODE_TAIL, "");
     typedef MfmaTile<T, MT> MF;
     typedef typename MF::acc acc_t;
     typedef typename Mfma<T>::v8 v8;
-    static_assert(MT == 32 || KG >= 4, "16x16 MFMA tiles: in wave groups");
-    static_assert((BK / MF::K) % KG == 0, "K groups: whole steps per group");
+    static_assert(KG <= 2, "one or two wave groups");
     constexpr bool GEMM = MODE != MODE_CONV;
     constexpr int CW = WARPS_M * WARPS_N * KG, NT = 64 * kLoaderWaves;
     constexpr int WM = BM / WARPS_M, WN = BN / WARPS_N, TM = WM / MT, TN = WN / MT;
@@ -62,15 +61,10 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
     if (panel == 0) {   // uniform
         tile_m = magic ? (int)__umulhi((unsigned)tile_id, magic) : tile_div(tile_id, tiles_n);
         tile_n = tile_id - tile_m * tiles_n;
-    } else {   // panel after panel of tiles_n >> panel channel tiles, row by row inside a panel
-        const int pw = tiles_n >> panel;
-        const int pp = (a.M + ROUND - 1) / ROUND * (ROUND / BM) * pw;
-        const int p = tile_id / pp, r = tile_id - p * pp;
-        tile_m = r / pw;
-        tile_n = p * pw + (r - tile_m * pw);
+    } else {
+        panel_tile<BM, BM>(tile_id, tiles_n, panel, a.M, &tile_m, &tile_n);
     }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
-    if (MT == 16 && m0 >= a.M) return;   // the lower part of the last pixels' tile
     const int nsteps = MODE == MODE_TAIL ? (a.K + BK - 1) / BK : a.K / BK;   // at least one
     // Barriers: both kinds of waves meet at (general addressing) 1 behind the rows' arithmetic, 1 + nsteps around the slices and 1 in
     // the wave groups' exchange.
@@ -117,15 +111,8 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
             auto pixel_row = [&](unsigned m) {
                 const unsigned t = fast_div(m, a.wo_div), n = fast_div(t, a.ho_div);
                 const int iwc = (int)(m - t * (unsigned)a.Wo) * a.stride, ihc = (int)(t - n * (unsigned)a.Ho) * a.stride;
-                const int r_lo = max(0, pad_h - ihc), r_hi = min(a.kh, a.H + pad_h - ihc);
-                const int s_lo = max(0, pad_w - iwc), s_hi = min(a.kw, a.W + pad_w - iwc);
-                // in-range columns s_lo..s_hi-1 replicated into every in-range filter row r_lo..r_hi-1: a multiplication by the
-                // rows' unit bits (no carries: cols < 2^kw)
-                unsigned row_units = 0;   // bit r*kw for every filter row r
-                for (int r = 0; r < a.kh; ++r) row_units |= 1u << (r * a.kw);
-                const unsigned cols = ((1u << s_hi) - 1u) & ~((1u << s_lo) - 1u);
-                const unsigned rows = row_units & (unsigned)((1ull << (r_hi * a.kw)) - 1ull) & ~((1u << (r_lo * a.kw)) - 1u);
-                return u32x2{(unsigned)((n * a.H + ihc) * a.W + iwc) * ldx2, m < (unsigned)a.M ? cols * rows : 0u};
+                const unsigned taps = tap_mask(a, pad_h, pad_w, ihc, iwc);
+                return u32x2{(unsigned)((n * a.H + ihc) * a.W + iwc) * ldx2, m < (unsigned)a.M ? taps : 0u};
             };
             if constexpr (!ROWS_SHARED) {
                 const u32x2 ri = pixel_row((unsigned)m0 + row);
@@ -268,7 +255,7 @@ static __device__ __forceinline__ void conv_loader_body(const ConvArgs &a, const
         group_exchange_write<MT, TM, TN, KG, WARPS_M * WARPS_N>(acc, xch, kg, wq, lane);
         wait_lds_and_barrier();
         typedef GroupUnits<MT, TM, TN, KG> G;
-        if (kg * G::UPG >= G::UNITS) return;   // more groups than units
+        static_assert(G::UNITS % KG == 0, "a share for every group");
         float4 sum[G::UPG];
         group_sum<MT, TM, TN, KG, WARPS_M * WARPS_N>(xch, sum, kg, wq, lane);
         group_epilogue_store<T, MT, TM, TN, KG>(sum, go, a, pos, kg);
