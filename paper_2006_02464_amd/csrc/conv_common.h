@@ -32,14 +32,19 @@ constexpr bool conv_has_loaders(int mode, bool splitk, bool fused, int bm, int b
 }
 // The launches of such a form that are issued with them: those whose workgroups are on the CUs all at once.  Loaders take workgroups' places: with them
 // two fit a CU, one of eight multiplying waves or of a larger tile, where up to five of the same tile would.  Behind that a workgroup's set-up and epilogue
-// stand alone: 1x1 64 -> 256 at 56x56 batch 16 13.2 -> 17.3 us on 64x64, 32 -> 64 at 112x112 10.7 -> 27.8 on 32x32, 128 -> 512 at 28x28 9.9 -> 11.7 on
-// 64x64 with slices of 128, 7x1 of 256 channels at 56x56 66 -> 78 on 128x64 in two groups; except that four multiplying waves gain from K = 256 on
-// (64x64 0.85-0.97 of the time, 128x64 0.93-1.0), larger tiles only with general addressing.  One slice on a CU of its own has nothing to overlap and
-// pays for the longer start: 128x128 on eight waves 4.1 -> 4.4.  Over 7900 pairs of shape and tile inside EXECs, whole K, launches under this rule take 0.74-1.0
-// times the time in the mean by tile and form and 1.08 at most (128x128 three of 1.1-1.2, 1x1 of stride 2 on less than a fifth of the CUs).
-constexpr bool conv_loads_apart(int mode, int bm, int bn, int bk, int waves, int K, long long workgroups) {
+// stand alone: 1x1 64 -> 256 at 56x56 batch 16 13.2 -> 17.3 us on 64x64, 32 -> 64 at 112x112 10.7 -> 27.8 on 32x32, 7x1 of 256 channels at 56x56 66 -> 78 on
+// 128x64 in two groups.  One slice on a CU of its own has nothing to overlap and pays for the longer start: 128x128 on eight waves 4.1 -> 4.4.
+// More of them gain on four multiplying waves, where K is long enough beside the tile's pixels: 3x3 and 5x5 0.85-0.97 of the time.  Of 1x1s, whole EXECs without
+// and with: MobileNet batch 16 at 224x224 196.2 -> 192.5 and at 208x208 190.0 -> 187.2 (128 channels at 128x64, 784 and 676 workgroups), batch 12
+// 186.7 -> 185.1 (one slice of 128 at 64x64, 1176; ResNet-50 208x208 batch 7, 592: 306.7 -> 309.0), DenseNet 193x193 batch 14 234.2 -> 233.0; Inception
+// 224x224 batch 16 410 -> 408.5 (512 channels at 128x64, 1568), but 161x161 batch 12 193.0 -> 196.5 (632) and, by its pairs, 177x177 batch 9 215.0 -> 216.8.
+// Over 7900 pairs of shape and tile inside EXECs, whole K, launches take 0.74-1.0 times the time in the mean by tile and form, without the rule 0.72-1.04.
+constexpr bool conv_loads_apart(int mode, bool pair, int bm, int bn, int bk, int waves, int K, long long workgroups) {
     const bool two = waves < 8 && bm * bn * bk <= waves * 131072;
-    return workgroups <= (two ? 512 : 256) ? two || K > bk : waves == 4 && K >= 256 && (two || mode == MODE_CONV);
+    if (workgroups <= (two ? 512 : 256)) return two || K > bk;
+    if (waves != 4 || pair) return false;
+    if (K <= bk) return two && bk == 128 && workgroups >= 1024;
+    return bm * K >= 16384 && (mode == MODE_CONV || (two && (workgroups >= 768 || K <= 256)));
 }
 
 // n / d for a divisor prepared on the host (round-up multiplier; exact for every 32-bit n).

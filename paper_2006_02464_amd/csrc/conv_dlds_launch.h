@@ -196,7 +196,7 @@ static hipError_t launch_one(dim3 grid, int block, const ConvArgs &a_in, hipStre
     if (block != 64 * WAVES) return hipErrorInvalidValue;
     if (PARTS > 1) grid = dim3(grid.x * PARTS, grid.y, 1);   // the workgroups that read ahead come behind all the parts
     if constexpr (conv_has_loaders(MODE, SPLITK, false, BM, BN, WAVES, KG)) {
-        if (conv_loads_apart(MODE, BM, BN, BK, WAVES, a.K, (long long)grid.x * grid.z))
+        if (conv_loads_apart(MODE, false, BM, BN, BK, WAVES, a.K, (long long)grid.x * grid.z))
             return launch_form<T, BM, BN, WARPS_M, WARPS_N, BK, MODE, SPLITK, KG, MT, true>(grid, a, s);
     }
     return launch_form<T, BM, BN, WARPS_M, WARPS_N, BK, MODE, SPLITK, KG, MT, false>(grid, a, s);

@@ -425,7 +425,7 @@ int conv_loader_threads(ConvTile tile, bool stem, const ConvArgs &a, const ConvA
     const int mode = a1 ? MODE_CONV : conv_mode(a, stem, conv_bk(a, stem, tile));   // a pair: general addressing
     if (!conv_has_loaders(mode, a.split_k > 1, false, d.bm, d.bn, d.threads / 64, d.kg)) return 0;
     auto tiles = [&](const ConvArgs &c) { return (long long)((c.M + d.bm - 1) / d.bm) * ((c.Cout + d.bn - 1) / d.bn) * std::max(c.nz, 1); };
-    return conv_loads_apart(mode, d.bm, d.bn, d.bk, d.threads / 64, a1 ? std::max(a.K, a1->K) : a.K, tiles(a) + (a1 ? tiles(*a1) : 0)) ? 64 * kLoaderWaves : 0;
+    return conv_loads_apart(mode, a1 != nullptr, d.bm, d.bn, d.bk, d.threads / 64, a1 ? std::max(a.K, a1->K) : a.K, tiles(a) + (a1 ? tiles(*a1) : 0)) ? 64 * kLoaderWaves : 0;
 }
 
 template <typename T, int BK, int MODE, bool SPLITK>

@@ -114,7 +114,7 @@ static hipError_t launch_pair_one(const ConvArgs &a0_in, const ConvArgs &a1_in, 
     a0.nb = conv_pack_nb((int)nb0, a0.panel_log2);
     a1.nb = conv_pack_nb((int)nb1, a1.panel_log2);
     if constexpr (conv_has_loaders(MODE_CONV, false, false, BM, BN, WAVES, KG)) {
-        if (conv_loads_apart(MODE_CONV, BM, BN, BK, WAVES, std::max(a0.K, a1.K), (long long)nb0 + nb1))
+        if (conv_loads_apart(MODE_CONV, true, BM, BN, BK, WAVES, std::max(a0.K, a1.K), (long long)nb0 + nb1))
             return launch_pair_form<T, BM, BN, WARPS_M, WARPS_N, BK, KG, MT, true>(a0, a1, nb0, nb1, s);
     }
     return launch_pair_form<T, BM, BN, WARPS_M, WARPS_N, BK, KG, MT, false>(a0, a1, nb0, nb1, s);

@@ -135,7 +135,8 @@ def test_two_wave_groups_draw_one_ticket_a_tile(ctx, name):
 # (tile, batch, image side, input channels, output channels, filter, loading threads): a tile's workgroups at 512 and above, at 256 and above, from K = 256 on, one slice
 @pytest.mark.parametrize("tile, batch, hw, cin, cout, k, loaders", [
     ("64x64", 2, 256, 64, 64, 1, 256), ("64x64", 2, 258, 64, 64, 1, 0), ("64x64", 2, 258, 192, 64, 1, 0), ("64x64", 2, 258, 256, 64, 1, 256), ("64x64", 2, 258, 64, 64, 3, 256),
-    ("64x64", 2, 258, 160, 64, 1, 0), ("64x64", 2, 258, 288, 64, 1, 256), ("32x32", 1, 256, 64, 32, 3, 256), ("32x32", 1, 258, 64, 32, 3, 0), ("64x32", 2, 256, 64, 32, 1, 256),
+    ("64x64", 2, 258, 160, 64, 1, 0), ("64x64", 2, 258, 288, 64, 1, 0), ("64x64", 2, 258, 288, 128, 1, 256), ("64x64k128", 2, 258, 128, 64, 1, 0), ("64x64k128", 2, 258, 128, 128, 1, 256), ("64x64k128", 2, 258, 128, 96, 1, 256),
+    ("64x64k128", 1, 258, 128, 192, 1, 0), ("128x64", 2, 258, 128, 192, 1, 256), ("128x64", 2, 258, 64, 192, 1, 0), ("128x64", 2, 258, 320, 128, 1, 0), ("128x64", 2, 258, 320, 192, 1, 256), ("32x32", 1, 256, 64, 32, 3, 256), ("32x32", 1, 258, 64, 32, 3, 0), ("64x32", 2, 256, 64, 32, 1, 256),
     ("64x32", 2, 258, 256, 32, 1, 0), ("32x64k128", 1, 256, 128, 64, 3, 256), ("32x64k128", 1, 258, 128, 64, 3, 0), ("128x64k128", 2, 256, 128, 64, 1, 0),
     ("128x64k128", 2, 256, 256, 64, 1, 256), ("128x64k128", 2, 258, 256, 64, 1, 0), ("128x64k128", 2, 258, 128, 64, 3, 256), ("128x64g2", 2, 256, 256, 64, 3, 256),
     ("128x64g2", 2, 258, 256, 64, 3, 0), ("64x64g2", 1, 256, 128, 64, 1, 256), ("64x64g2", 1, 258, 128, 64, 1, 0), ("128x128w8", 2, 256, 64, 128, 1, 0), ("128x128w8", 2, 256, 128, 128, 1, 256),
