@@ -15,6 +15,9 @@ constexpr unsigned kOob = 0x80000000u;  // byte offset beyond any buffer (buffer
 // MODE_TAIL: MODE_GEMM whose K ends in part of a slice (a form of its own: the masks cost the plain one 1.5 %)
 enum ConvMode : int { MODE_CONV = 0, MODE_GEMM = 1, MODE_STEM = 2, MODE_TAIL = 3 };
 
+// LDS stages of a tile's ring: 4 where that still lets two workgroups share a CU's 160 KiB, else 3.
+constexpr int conv_ring_stages(int stage_bytes) { return stage_bytes * 4 <= 80 * 1024 ? 4 : stage_bytes * 3 <= 160 * 1024 ? 3 : 2; }
+
 // Waves of a workgroup that only load (conv_loader_body.h).
 constexpr int kLoaderWaves = 4;
 // Forms that have them: tiles of one or two wave groups whose waves' registers fit beside the loaders'.  Four groups put a multiplying wave of every
@@ -34,17 +37,20 @@ constexpr bool conv_has_loaders(int mode, bool splitk, bool fused, int bm, int b
 // two fit a CU, one of eight multiplying waves or of a larger tile, where up to five of the same tile would.  Behind that a workgroup's set-up and epilogue
 // stand alone: 1x1 64 -> 256 at 56x56 batch 16 13.2 -> 17.3 us on 64x64, 32 -> 64 at 112x112 10.7 -> 27.8 on 32x32, 7x1 of 256 channels at 56x56 66 -> 78 on
 // 128x64 in two groups.  One slice on a CU of its own has nothing to overlap and pays for the longer start: 128x128 on eight waves 4.1 -> 4.4.
-// More of them gain on four multiplying waves, where K is long enough beside the tile's pixels: 3x3 and 5x5 0.85-0.97 of the time.  Of 1x1s, whole EXECs without
-// and with: MobileNet batch 16 at 224x224 196.2 -> 192.5 and at 208x208 190.0 -> 187.2 (128 channels at 128x64, 784 and 676 workgroups), batch 12
-// 186.7 -> 185.1 (one slice of 128 at 64x64, 1176; ResNet-50 208x208 batch 7, 592: 306.7 -> 309.0), DenseNet 193x193 batch 14 234.2 -> 233.0; Inception
-// 224x224 batch 16 410 -> 408.5 (512 channels at 128x64, 1568), but 161x161 batch 12 193.0 -> 196.5 (632) and, by its pairs, 177x177 batch 9 215.0 -> 216.8.
+// More of them gain with general addressing where the ring leaves a CU no room for more workgroups either: 0.85-1.0 of the time, 3x3 of 512 channels at 56x56 batch
+// 16 388 -> 352 us on 64x64 with slices of 128 and 276 -> 251 on 128x128 on eight waves, both with rings of 96 KB.  1x1s gain on four multiplying waves where K is long
+// enough beside the tile's pixels.  Whole EXECs without and with: MobileNet batch 16 at 224x224 196.2 -> 192.5 and at 208x208 190.0 -> 187.2 (128 channels at
+// 128x64, 784 and 676 workgroups), batch 12 186.7 -> 185.1 (one slice of 128 at 64x64, 1176; ResNet-50 208x208 batch 7, 592: 306.7 -> 309.0), DenseNet 193x193
+// batch 14 234.2 -> 233.0; Inception 224x224 batch 16 410 -> 408.5 (512 channels at 128x64, 1568), but 161x161 batch 12 193.0 -> 196.5 (632) and, by its
+// pairs, 177x177 batch 9 215.0 -> 216.8; 2048 channels at 56x56, 12544 workgroups of 128x64, 606 -> 641 a launch.
 // Over 7900 pairs of shape and tile inside EXECs, whole K, launches take 0.74-1.0 times the time in the mean by tile and form, without the rule 0.72-1.04.
 constexpr bool conv_loads_apart(int mode, bool pair, int bm, int bn, int bk, int waves, int K, long long workgroups) {
-    const bool two = waves < 8 && bm * bn * bk <= waves * 131072;
-    if (workgroups <= (two ? 512 : 256)) return two || K > bk;
-    if (waves != 4 || pair) return false;
-    if (K <= bk) return two && bk == 128 && workgroups >= 1024;
-    return bm * K >= 16384 && (mode == MODE_CONV || (two && (workgroups >= 768 || K <= 256)));
+    const int fit = waves < 8 && bm * bn * bk <= waves * 131072 ? 2 : 1, slices = (K + bk - 1) / bk, stage = (bm + bn) * bk * 2;
+    if (workgroups <= 256 * fit) return fit == 2 || slices > 1;
+    if (pair || waves < 4) return false;
+    if (mode == MODE_CONV) return (slices < conv_ring_stages(stage) ? slices : conv_ring_stages(stage)) * stage * (fit + 1) > 160 * 1024;
+    if (waves > 4 || fit == 1) return false;
+    return slices == 1 ? bk == 128 && workgroups >= 1024 : bm * K >= 16384 && K <= 512 && (workgroups >= 768 || K <= 256);
 }
 
 // n / d for a divisor prepared on the host (round-up multiplier; exact for every 32-bit n).

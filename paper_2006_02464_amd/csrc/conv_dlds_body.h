@@ -761,11 +761,9 @@ static __device__ __forceinline__ void conv_dlds_body(const ConvArgs &a, const i
     }
 }
 
-// LDS stages per tile: 4 where that still lets two workgroups share a CU's 160 KiB, else 3.
 template <int BM, int BN, int BK>
 struct RingDepth {
-    static constexpr int stage = (BM + BN) * BK * 2;
-    static constexpr int value = stage * 4 <= 80 * 1024 ? 4 : (stage * 3 <= 160 * 1024 ? 3 : 2);
+    static constexpr int value = conv_ring_stages((BM + BN) * BK * 2);
 };
 
 }  // namespace cw

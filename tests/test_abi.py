@@ -136,11 +136,12 @@ def test_two_wave_groups_draw_one_ticket_a_tile(ctx, name):
 @pytest.mark.parametrize("tile, batch, hw, cin, cout, k, loaders", [
     ("64x64", 2, 256, 64, 64, 1, 256), ("64x64", 2, 258, 64, 64, 1, 0), ("64x64", 2, 258, 192, 64, 1, 0), ("64x64", 2, 258, 256, 64, 1, 256), ("64x64", 2, 258, 64, 64, 3, 256),
     ("64x64", 2, 258, 160, 64, 1, 0), ("64x64", 2, 258, 288, 64, 1, 0), ("64x64", 2, 258, 288, 128, 1, 256), ("64x64k128", 2, 258, 128, 64, 1, 0), ("64x64k128", 2, 258, 128, 128, 1, 256), ("64x64k128", 2, 258, 128, 96, 1, 256),
-    ("64x64k128", 1, 258, 128, 192, 1, 0), ("128x64", 2, 258, 128, 192, 1, 256), ("128x64", 2, 258, 64, 192, 1, 0), ("128x64", 2, 258, 320, 128, 1, 0), ("128x64", 2, 258, 320, 192, 1, 256), ("32x32", 1, 256, 64, 32, 3, 256), ("32x32", 1, 258, 64, 32, 3, 0), ("64x32", 2, 256, 64, 32, 1, 256),
+    ("64x64k128", 1, 258, 128, 192, 1, 0), ("128x64", 2, 258, 128, 192, 1, 256), ("128x64", 2, 258, 64, 192, 1, 0), ("128x64", 2, 258, 320, 128, 1, 0), ("128x64", 2, 258, 320, 192, 1, 256),
+    ("128x64", 2, 258, 512, 192, 1, 256), ("128x64", 2, 258, 576, 192, 1, 0), ("32x32", 1, 256, 64, 32, 3, 256), ("32x32", 1, 258, 64, 32, 3, 0), ("64x32", 2, 256, 64, 32, 1, 256),
     ("64x32", 2, 258, 256, 32, 1, 0), ("32x64k128", 1, 256, 128, 64, 3, 256), ("32x64k128", 1, 258, 128, 64, 3, 0), ("128x64k128", 2, 256, 128, 64, 1, 0),
     ("128x64k128", 2, 256, 256, 64, 1, 256), ("128x64k128", 2, 258, 256, 64, 1, 0), ("128x64k128", 2, 258, 128, 64, 3, 256), ("128x64g2", 2, 256, 256, 64, 3, 256),
     ("128x64g2", 2, 258, 256, 64, 3, 0), ("64x64g2", 1, 256, 128, 64, 1, 256), ("64x64g2", 1, 258, 128, 64, 1, 0), ("128x128w8", 2, 256, 64, 128, 1, 0), ("128x128w8", 2, 256, 128, 128, 1, 256),
-    ("128x128w8", 2, 258, 128, 128, 1, 0), ("128x128", 1, 128, 64, 128, 3, 256), ("128x128", 1, 128, 256, 128, 1, 0), ("128x128", 1, 128, 96, 128, 1, 256),
+    ("128x128w8", 2, 258, 128, 128, 1, 0), ("128x128w8", 2, 258, 64, 128, 3, 256), ("64x64k128g2", 1, 258, 128, 64, 3, 256), ("64x64g2", 1, 258, 128, 64, 3, 0), ("128x128", 1, 128, 64, 128, 3, 256), ("128x128", 1, 128, 256, 128, 1, 0), ("128x128", 1, 128, 96, 128, 1, 256),
     ("256x128w8", 1, 128, 128, 128, 3, 0), ("128x256w8", 1, 128, 128, 256, 3, 0), ("256x128", 1, 128, 128, 128, 3, 0), ("32x32k128g4", 1, 128, 128, 32, 3, 0)])
 def test_launches_that_have_loading_waves(ctx, tile, batch, hw, cin, cout, k, loaders):
     ops = [T.Op(T.CONV, 3, cin, 7, 7, 2, 3, 1, -1, -1), T.Op(T.CONV, cin, cout, k, k, 1, k // 2, 1, -1, 0), T.Op(T.CONV, cout, 256, 1, 1, 2, 0, 1, -1, 1),
