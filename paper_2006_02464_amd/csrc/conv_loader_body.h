@@ -1,23 +1,26 @@
-// The direct-to-LDS convolution with waves that only load: the per-tile body of the per-layer launches (conv_dlds_launch.h) and of
-// the pair launches (kernels_conv_dlds.hip).
+// The direct-to-LDS convolution with waves that only load: the per-tile body of those per-layer launches (conv_dlds_launch.h) and
+// pair launches (kernels_conv_dlds.hip) that conv_loads_apart (conv_common.h) gives them to.
 //
 // Same GEMM view, weight layout, LDS stages and swizzle, MFMA roles, K order and epilogues as conv_dlds_body.h, and the same sums
-// bit for bit.  What differs is who does what.  A wave issues its instructions in order, and one that both multiplies and loads pays
-// for each in turn: per 16-k step of a 64x64 tile on four waves 32 clocks of matrix core, about 13 for each operand read and 35-40 for
-// a load to LDS, whose issue waits for the CU's address path (16 clocks a load, shared by the four SIMDs), 890 clocks a slice of 128
-// where the load path needs 512 and the matrix cores 256.  Here kLoaderWaves further waves, one a SIMD, issue all of them, and the
-// others only read and multiply:
+// bit for bit (of a hard swish's results the compiler may round a product to fp16 in one instruction here and in two there).  What differs
+// is who does what.  A wave issues its instructions in order, and one that both multiplies and loads pays for each in turn: per 16-k step
+// of a 64x64 tile on four waves 32 clocks of matrix core, about 13 for each operand read and 35-40 for a load to LDS, whose issue
+// waits for the CU's address path (16 clocks a load, shared by the four SIMDs), 890 clocks a slice of 128 where the load path needs 512
+// and the matrix cores 256.  Here kLoaderWaves further waves, one a SIMD, issue all of them, and the others only read and multiply:
 // - a slice costs what is longer of the two, not the sum;
 // - the set-up of the addresses (0.25 us, 0.5 with general addressing) is the loaders' alone; beside it the others request bias
 //   and residual, which used to be requested before the last slice;
 // - with no loads of their own to count, the multiplying waves read a slice's first operands while they multiply the last ones of
 //   the slice before: one barrier a slice, behind its last operand read, says both that the next slice has arrived and that this one's
 //   stage may be loaded again.
-// Single launches, back to back, weights of 24 layers in turn, before -> now: 3x3 of 256 channels at 14x14 batch 16 10.1 -> 9.0 us (64x64,
+// Without -> with them.  Single launches, back to back, weights of 24 layers in turn: 3x3 of 256 channels at 14x14 batch 16 10.1 -> 9.0 us (64x64,
 // slices of 128), 1x1 1024 -> 256 there 6.1 -> 5.4, 3x3 of 128 channels at 28x28 batch 8 6.7 -> 5.9, 1x1 128 -> 512 there at batch 1
-// 3.15 -> 2.81.  Whole EXECs: ResNet-152 batch 16 1161 -> 1120 us, ResNet-18 batch 8 132.2 -> 126.9, ResNet-50 batch 16 397.2 -> 391.4,
-// Inception 127x127 batch 5 114.2 -> 109.9.  Two loaders are as fast for 1x1 and 0.1-0.9 us slower for 3x3, one is slower everywhere; a
-// higher wave priority for them, or operands requested behind the first slice, cost 1-2 %.
+// 3.15 -> 2.81.  Whole EXECs: ResNet-152 batch 16 1162 -> 1121 us, ResNet-18 batch 8 132.5 -> 127.4, ResNet-50 batch 16 402.3 -> 397.6,
+// Inception 127x127 batch 5 115.7 -> 107.9.  Inside EXECs, by a kernel trace of ResNet, MobileNet and Inception: general addressing on 64x64 and 128x64 with
+// slices of 128 10.4-12.1 -> 9.2-10.6, 1x1 on 64x64 5.37-5.71 -> 5.36-5.61, on 128x128 on eight waves 6.63 -> 6.49, on 128x64 with slices of 128
+// 6.19-6.24 -> 6.35-6.39, though whole EXECs are 0.1-0.3 % faster with them there too (ResNet-50 and ResNet-152, batch 16; MobileNet the same).
+// Two loaders are as fast for 1x1 and 0.1-0.9 us slower for 3x3, one is slower everywhere; a higher wave priority for them, or operands
+// requested behind the first slice, cost 1-2 %.
 #pragma once
 #include "conv_dlds_body.h"
 

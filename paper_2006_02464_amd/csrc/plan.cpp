@@ -301,7 +301,7 @@ static int pick_res_variant(int64_t M, int64_t N, int64_t K, int32_t cin) {
 // Every tile shape's launch time as a linear function of the quantities below, fitted offline to measured
 // launches (tune.py); the plan takes the tile and split-K with the least predicted time.  A launch's time runs from its first
 // workgroup to the next launch's, by time stamps.  Over 641 GEMM shapes (five networks, 38 combinations with image
-// and batch sizes) the choice costs 1.9 % over the fastest tile of each, 3.4 % since tiles of one or two wave groups have loading waves (conv_loader_body.h).  Fitted to pairs of events, which see nothing below
+// and batch sizes) the choice costs 1.9 % over the fastest tile of each, 3.1 % since some launches have loading waves (conv_loader_body.h).  Fitted to pairs of events, which see nothing below
 // 4.2 us, whole EXECs of the 38 combinations took 5.1 % longer in the mean on the tiles there were before the 16-wide
 // ones (with these, chosen by spans without the time to the next launch, 0.6 % longer).
 enum { COST_PLAIN, COST_STAGED, COST_STEM };   // the main kernel; the register-staged one; the first convolution's form
